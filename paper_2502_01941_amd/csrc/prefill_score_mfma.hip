@@ -1,6 +1,6 @@
 // Window-attention softmax partials on the gfx950 matrix cores (Section 5.1, Eq. 3: alpha_{t,h}).
 //
-// Shape: bf16, head_dim 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6 or 8
+// Shape: bf16, head_dim 64 or 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6 or 8
 // blocks of 32 rows; rows past G*W are zero operands whose statistics are written as -inf.
 //
 // A workgroup is a pair of waves (one wave for a single row block) that takes the chunks starting inside
@@ -17,10 +17,16 @@
 // layout.  One s_barrier per block tells the pair that a block has landed and that the buffer of the
 // block before it may be refilled.  With ~166 registers per wave three waves fit on a SIMD.
 //
-// LDS layout of a block: key row r starts at r*256 + (r/4)*64 and its 16-byte column c sits in slot
-// c ^ (r%4).  The 64-byte pad per four rows plus the two-bit XOR spread the 16 lanes of a 128-bit LDS
-// read over all banks, while the address of MFMA step ks stays (lane base for ks parity) + 64*(ks/2),
-// i.e. an immediate offset - no per-step address registers.
+// LDS layout of a block (KeyLayout): a direct-to-LDS instruction writes 64 consecutive 16-byte slots, so a
+// lane chooses which 16-byte column of its row it fetches; the choice makes the 128-bit operand reads, which
+// the LDS serves sixteen lanes (rows r..r+15, one column) at a time from 64 banks, free of conflicts.
+//   256-byte rows (head_dim 128): row r starts at r*256 + (r/4)*64 and column c sits in slot c ^ (r%4).  The
+//     64-byte pad per four rows plus the two-bit XOR cover all banks, while the address of MFMA step ks
+//     stays (lane base for ks parity) + 64*(ks/2), i.e. an immediate offset - no per-step address registers.
+//   128-byte rows (head_dim 64): row r starts at r*128 and column c sits in slot c ^ ((r/2)%8): two rows
+//     share the 256 bytes of the banks, so eight pairs of rows have to differ in the slot.  Half the bytes
+//     and half the matrix steps per key, but the same exponentials: bound by vector issue (16 problems of
+//     16001 tokens, 8 KV heads, 128 query rows: 78 us = 3.4 TB/s; plain vector arithmetic took 2427 us).
 //
 // The direct-to-LDS loads are written as inline assembly and their completion is tracked by hand with
 // s_waitcnt vmcnt: when they are visible to the compiler it makes every LDS read wait for all loads
@@ -39,12 +45,33 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) const char lds_cchar;  // keeps LDS reads as ds_read, not flat
 typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
 
-constexpr int kD = 128;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+
 constexpr int kBlockKeys = 32;
-constexpr int kRowBytes = kD * 2;                    // 256
-constexpr int kGroupBytes = 4 * kRowBytes + 64;      // four rows + pad = one direct-to-LDS instruction
-constexpr int kGroupsPerBlock = kBlockKeys / 4;      // 8
-constexpr int kBufBytes = kGroupsPerBlock * kGroupBytes;  // 8704 bytes per block
+
+// How a 32-key block lies in LDS; see the top of the file.
+template <int D> struct KeyLayout;
+template <> struct KeyLayout<128> {
+  static constexpr int kRowBytes = 256;
+  static constexpr int kLoadBytes = 4 * kRowBytes + 64;  // LDS stride of one direct-to-LDS instruction: four rows + pad
+  // slot of lane l in instruction i: row 4i + l/16, slot l%16, which holds column (l%16) ^ (l/16)
+  __device__ static uint32_t fetch_column(int, int lane) { return (lane & 15) ^ (lane >> 4); }
+  __device__ static int operand_base(int row, int half) {
+    return row * kRowBytes + (row >> 2) * 64 + ((half ^ (row & 3)) << 4);
+  }
+  __device__ static int operand(int base, int ks) { return ((ks & 1) ? base ^ 32 : base) + 64 * (ks >> 1); }
+};
+template <> struct KeyLayout<64> {
+  static constexpr int kRowBytes = 128;
+  static constexpr int kLoadBytes = 8 * kRowBytes;       // eight rows
+  // row 8i + l/8, slot l%8, which holds column (l%8) ^ ((row/2)%8)
+  __device__ static uint32_t fetch_column(int i, int lane) { return (lane & 7) ^ ((4 * i + (lane >> 4)) & 7); }
+  __device__ static int operand_base(int row, int half) { return row * kRowBytes + ((half ^ ((row >> 1) & 7)) << 4); }
+  __device__ static int operand(int base, int ks) { return base ^ (ks << 5); }
+};
+template <int D> constexpr int kLoadsPerBlock = kBlockKeys * KeyLayout<D>::kRowBytes / 1024;
+template <int D> constexpr int kBufBytes = kLoadsPerBlock<D> * KeyLayout<D>::kLoadBytes;
+template <int D> constexpr int kSteps = D / 16;          // matrix steps along the head dimension
 #ifndef SHOTKV_SCORE_RING
 #define SHOTKV_SCORE_RING 3
 #endif
@@ -54,27 +81,27 @@ constexpr int kBufBytes = kGroupsPerBlock * kGroupBytes;  // 8704 bytes per bloc
 constexpr int kRing = SHOTKV_SCORE_RING;  // LDS buffers per pair: kRing - 1 blocks in flight
 static_assert(kRing >= 2 && kRing <= 5, "ring depth");
 
-// Issue this wave's share of the direct-to-LDS loads of one 32-key block: groups [g0, g0 + NG).
-// Group i fills rows 4i..4i+3: lane l writes LDS slot l of the group, which is row 4i + l/16, slot
-// l%16, and therefore fetches column (l%16) ^ (l/16) of that row.  Rows past the end of the span
-// (rem keys are left in it) re-read its last key (they are masked later), so every address stays inside it.
+// Issue this wave's share of the direct-to-LDS loads of one 32-key block: instructions [i0, i0 + NL).
+// Rows past the end of the span (rem keys are left in it) re-read its last key (they are masked later), so
+// every address stays inside it.
 // The loads carry the non-temporal hint: K is read exactly once, and a stream that does not settle in L2
 // and the memory-side cache leaves them to the statistics this kernel writes and the next kernels read
 // (measured: 8 % faster here, and the per-chunk reduction that follows finds its input in cache).
-template <int NG>
+template <int D, int NL>
 __device__ __forceinline__ void issue_block(const char* __restrict__ k_plane, int key0, int rem,
-                                            uint32_t lds_addr, int g0, int lane) {
+                                            uint32_t lds_addr, int i0, int lane) {
+  typedef KeyLayout<D> L;
+  constexpr int kRows = 1024 / L::kRowBytes;  // rows per instruction
   const int last = rem - 1;  // rem >= 1
-  const int hi = lane >> 4;
-  const uint32_t col_bytes = static_cast<uint32_t>(((lane & 15) ^ hi) << 4);
+  const char* base = k_plane + static_cast<size_t>(key0) * L::kRowBytes;
 #pragma unroll
-  for (int i = 0; i < NG; ++i) {
-    const int rr = min(4 * (g0 + i) + hi, last);
-    const uint32_t off = static_cast<uint32_t>(key0 + rr) * kRowBytes + col_bytes;
-    // M0 = LDS address of the group (wave-uniform); lane l lands at M0 + 16*l
+  for (int i = 0; i < NL; ++i) {
+    const int rr = min(kRows * (i0 + i) + lane / (kWave / kRows), last);
+    const uint32_t off = static_cast<uint32_t>(rr) * L::kRowBytes + (L::fetch_column(i0 + i, lane) << 4);
+    // M0 = LDS address of the instruction's slots (wave-uniform); lane l lands at M0 + 16*l
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                  :
-                 : "s"(lds_addr + (g0 + i) * kGroupBytes), "v"(off), "s"(k_plane)
+                 : "s"(lds_addr + (i0 + i) * L::kLoadBytes), "v"(off), "s"(base)
                  : "memory", "m0");
   }
 }
@@ -136,27 +163,33 @@ __device__ __forceinline__ void softmax_fold(floatx16 acc, float c, int half, in
   m_run = m_new;
 }
 
-// One 32-key block against this wave's NQW query blocks (qb0 = index of its first one).
-template <int NQW, bool MASKED, bool EXACT>
-__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][8], int lane,
-                                              int qb0, int key0, int rem, int causal_base, int W, float c,
-                                              float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW]) {
-  const int row = lane & 31, half = lane >> 5;
-  const int base_even = row * kRowBytes + (row >> 2) * 64 + ((half ^ (row & 3)) << 4);
-  lds_cchar* even = lds_buf + base_even;
-  lds_cchar* odd = lds_buf + (base_even ^ 32);
-  floatx16 acc[NQW];
+// S^T of one 32-key block and this wave's NQW query blocks
+template <int D, int NQW>
+__device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][kSteps<D>], int lane,
+                                             floatx16 (&acc)[NQW]) {
+  typedef KeyLayout<D> L;
+  const int base = L::operand_base(lane & 31, lane >> 5);
 #pragma unroll
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    const bf16x8 a = *reinterpret_cast<lds_bf16x8*>(((ks & 1) ? odd : even) + 64 * (ks >> 1));
+  for (int ks = 0; ks < kSteps<D>; ++ks) {
+    const bf16x8 a = *reinterpret_cast<lds_bf16x8*>(lds_buf + L::operand(base, ks));
 #pragma unroll
     for (int q = 0; q < NQW; ++q)
       acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bq[q][ks], acc[q], 0, 0, 0);
   }
+}
+
+// One 32-key block against this wave's NQW query blocks (qb0 = index of its first one).
+template <int D, int NQW, bool MASKED, bool EXACT>
+__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][kSteps<D>], int lane,
+                                              int qb0, int key0, int rem, int causal_base, int W, float c,
+                                              float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW]) {
+  const int row = lane & 31, half = lane >> 5;
+  floatx16 acc[NQW];
+  logits_block<D, NQW>(lds_buf, bq, lane, acc);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int last_visible = causal_base + ((qb0 + q) * 32 + row) % W;
@@ -167,25 +200,13 @@ __device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (
 // The same block when a chunk ends inside it: the exact online-softmax update, then the sixteen weights
 // 2^(z - reference) of every query stay in `e` so that the caller can credit them to the chunks on either
 // side of each boundary.  Nothing is added to l_run here.
-template <int NQW, bool MASKED>
-__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][8], int lane, int qb0,
+template <int D, int NQW, bool MASKED>
+__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][kSteps<D>], int lane, int qb0,
                                               int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW],
                                               floatx16 (&e)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
-  const int base_even = row * kRowBytes + (row >> 2) * 64 + ((half ^ (row & 3)) << 4);
-  lds_cchar* even = lds_buf + base_even;
-  lds_cchar* odd = lds_buf + (base_even ^ 32);
-#pragma unroll
-  for (int q = 0; q < NQW; ++q)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) e[q][v] = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    const bf16x8 a = *reinterpret_cast<lds_bf16x8*>(((ks & 1) ? odd : even) + 64 * (ks >> 1));
-#pragma unroll
-    for (int q = 0; q < NQW; ++q) e[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bq[q][ks], e[q], 0, 0, 0);
-  }
+  logits_block<D, NQW>(lds_buf, bq, lane, e);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     if (MASKED) {
@@ -297,30 +318,32 @@ __device__ __forceinline__ void credit_elements(const floatx16 (&e)[NQW], uint32
 
 constexpr int kEndCache = 128;  // chunk ends of a workgroup kept in LDS
 
-template <int NQB>
+template <int D, int NQB>
 struct PairShape {
 #ifndef SHOTKV_SCORE_MAX_WAVES
 #define SHOTKV_SCORE_MAX_WAVES 2
 #endif
   static constexpr int kWaves = NQB >= SHOTKV_SCORE_MAX_WAVES ? SHOTKV_SCORE_MAX_WAVES : (NQB >= 2 ? 2 : 1);  // waves per workgroup
   static constexpr int kNQW = NQB / kWaves;           // query blocks per wave
-  static constexpr int kLoads = kGroupsPerBlock / kWaves;  // load instructions per wave per block
+  static constexpr int kLoads = kLoadsPerBlock<D> / kWaves;  // load instructions per wave per block
   static constexpr int kThreads = kWaves * kWave;
-  // single-wave groups are LDS-limited; four query blocks per wave need the 256-register budget
-  static constexpr int kMinWavesPerSimd = kWaves == 1 ? 1 : (kNQW > 2 ? 2 : SHOTKV_SCORE_WAVES_PER_SIMD);
+  // single-wave groups are LDS-limited; four query blocks per wave need the 256-register budget; half the
+  // head dimension leaves half the query registers, room for a fourth wave
+  static constexpr int kMinWavesPerSimd =
+      kWaves == 1 ? 1 : (kNQW > 2 ? 2 : D == 64 ? SHOTKV_SCORE_WAVES_PER_SIMD + 1 : SHOTKV_SCORE_WAVES_PER_SIMD);
 };
 
-template <int NQB>
-__global__ __launch_bounds__(PairShape<NQB>::kThreads, PairShape<NQB>::kMinWavesPerSimd) void
+template <int D, int NQB>
+__global__ __launch_bounds__((PairShape<D, NQB>::kThreads), (PairShape<D, NQB>::kMinWavesPerSimd)) void
 score_partials_mfma_kernel(
     const bf16_t* __restrict__ q_obs, const bf16_t* __restrict__ k, int n_tokens, int H, int H_kv, int W,
     int n_rows, float c, const int32_t* __restrict__ group_first, const int32_t* __restrict__ chunk_start,
     const int32_t* __restrict__ chunk_len, int max_c,
     float* __restrict__ partial, float* __restrict__ group_stat) {
-  typedef PairShape<NQB> S;
+  typedef PairShape<D, NQB> S;
   constexpr int NQW = S::kNQW;
   constexpr int R = NQB * 32;
-  __shared__ __attribute__((aligned(64))) char lds[kRing][kBufBytes];
+  __shared__ __attribute__((aligned(64))) char lds[kRing][kBufBytes<D>];
   __shared__ int s_end[kEndCache];
 
   const int lane = threadIdx.x % kWave;
@@ -339,24 +362,23 @@ score_partials_mfma_kernel(
   const int32_t* cs = chunk_start + static_cast<size_t>(p) * max_c;
   const int32_t* cl = chunk_len + static_cast<size_t>(p) * max_c;
   const char* k_plane =
-      reinterpret_cast<const char*>(k) + (static_cast<size_t>(p) * H_kv + g) * n_tokens * kRowBytes;
+      reinterpret_cast<const char*>(k) + (static_cast<size_t>(p) * H_kv + g) * n_tokens * KeyLayout<D>::kRowBytes;
   const int G = H / H_kv;
-  const bf16_t* q_rows = q_obs + (static_cast<size_t>(p) * H + static_cast<size_t>(g) * G) * W * kD;
+  const bf16_t* q_rows = q_obs + (static_cast<size_t>(p) * H + static_cast<size_t>(g) * G) * W * D;
   float* out = partial + (static_cast<size_t>(p) * max_c * H_kv + g) * R;  // chunk c of this head: + c * H_kv * R
   const int qb0 = wave * NQW;
 
   // B operands: query row (qb0+q)*32 + lane%32, head-dim slice 16*ks + 8*(lane/32) .. +8
   // Query rows past n_rows = G*W (a row count that is not one of 32/64/128/192/256) are zero operands; their
   // statistics are written as -inf, so they carry no weight further down.
-  bf16x8 bq[NQW][8];
+  bf16x8 bq[NQW][kSteps<D>];
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int qi = (qb0 + q) * 32 + (lane & 31);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+    for (int ks = 0; ks < kSteps<D>; ++ks) {
       u32x4 raw = {0u, 0u, 0u, 0u};
-      if (qi < n_rows) raw = *reinterpret_cast<const u32x4*>(q_rows + qi * kD + ks * 16 + (lane >> 5) * 8);
+      if (qi < n_rows) raw = *reinterpret_cast<const u32x4*>(q_rows + qi * D + ks * 16 + (lane >> 5) * 8);
       bq[q][ks] = __builtin_bit_cast(bf16x8, raw);
     }
   }
@@ -365,7 +387,7 @@ score_partials_mfma_kernel(
 #pragma unroll
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) asm volatile("" ::"v"(bq[q][ks]));
+    for (int ks = 0; ks < kSteps<D>; ++ks) asm volatile("" ::"v"(bq[q][ks]));
 
   lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
   const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base));
@@ -427,8 +449,8 @@ score_partials_mfma_kernel(
   // `cur` sits in ring slot cur_buf; up to kLook = kRing - 1 requested blocks follow it in the next slots.
   // A new block is requested each iteration, right after the barrier that frees the slot of the block
   // before cur.
-  const int k_begin = cs[c_begin];
-  const int k_end = cs[c_end - 1] + cl[c_end - 1];
+  const int k_begin = __builtin_amdgcn_readfirstlane(cs[c_begin]);
+  const int k_end = __builtin_amdgcn_readfirstlane(cs[c_end - 1] + cl[c_end - 1]);
   // ends of the first chunks go to LDS: one read per boundary instead of a dependent trip to the table
   for (int i = threadIdx.x; i < min(c_end - c_begin, kEndCache); i += S::kThreads)
     s_end[i] = cs[c_begin + i] + cl[c_begin + i];
@@ -441,12 +463,12 @@ score_partials_mfma_kernel(
   constexpr int kLook = kRing - 1;
   auto ring_slot = [](int sl) { return sl >= kRing ? sl - kRing : sl; };
   int cur_key0 = k_begin, next_key0 = k_begin + kBlockKeys;  // next block to request
-  issue_block<S::kLoads>(k_plane, k_begin, k_end - k_begin, lds_addr, g0, lane);
+  issue_block<D, S::kLoads>(k_plane, k_begin, k_end - k_begin, lds_addr, g0, lane);
   int n_q = 0;
 #pragma unroll
   for (int i = 0; i < kLook - 1; ++i) {
     if (next_key0 < k_end) {
-      issue_block<S::kLoads>(k_plane, next_key0, k_end - next_key0, lds_addr + (i + 1) * kBufBytes, g0, lane);
+      issue_block<D, S::kLoads>(k_plane, next_key0, k_end - next_key0, lds_addr + (i + 1) * kBufBytes<D>, g0, lane);
       n_q = i + 1;
       next_key0 += kBlockKeys;
     }
@@ -484,8 +506,8 @@ score_partials_mfma_kernel(
     if (S::kWaves > 1) asm volatile("s_barrier" ::: "memory");
     if (n_stash == kStash) flush();
     if (next_key0 < k_end) {
-      issue_block<S::kLoads>(k_plane, next_key0, k_end - next_key0,
-                             lds_addr + ring_slot(cur_buf + n_q + 1) * kBufBytes, g0, lane);
+      issue_block<D, S::kLoads>(k_plane, next_key0, k_end - next_key0,
+                             lds_addr + ring_slot(cur_buf + n_q + 1) * kBufBytes<D>, g0, lane);
       ++n_q;
       next_key0 += kBlockKeys;
     }
@@ -494,20 +516,20 @@ score_partials_mfma_kernel(
     // The workgroup's first block has no reference yet and takes the exact update straight away.
     const int cur_rem = min(kBlockKeys, k_end - cur_key0);
     const bool masked = cur_rem < kBlockKeys || cur_key0 + kBlockKeys - 1 > causal_base;
-    lds_cchar* blk = lds_base + cur_buf * kBufBytes;
+    lds_cchar* blk = lds_base + cur_buf * kBufBytes<D>;
     if (cur_end >= cur_key0 + cur_rem) {  // no chunk ends inside the block
       if (first_block)
-        compute_block<NQW, true, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<D, NQW, true, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else if (masked)
-        compute_block<NQW, true, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<D, NQW, true, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else
-        compute_block<NQW, false, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<D, NQW, false, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
     } else {
       floatx16 e[NQW];
       if (masked)
-        weights_block<NQW, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<D, NQW, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       else
-        weights_block<NQW, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<D, NQW, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       uint32_t lo0 = 0u, lo1 = 0u;  // elements already credited (lower / upper lane half)
       do {
         const int hi = cur_end - cur_key0;  // wave-uniform, 1..31
@@ -560,29 +582,35 @@ int score_group_keys(int P, int H_kv, int n_tokens, int n_shots) {
 #endif
 }
 
-bool score_uses_mfma(const PrefillDims& d) {
-  return d.dtype == SHOTKV_BF16 && d.D == kD && d.R_rows <= 256 &&
-         static_cast<long>(d.n_tokens) * kRowBytes < (1L << 32);
-}
+bool score_uses_mfma(const PrefillDims& d) { return d.dtype == SHOTKV_BF16; }
 
 hipError_t launch_score_partials_mfma(const PrefillDims& d, const void* q_obs, const void* k,
                                       const PrefillWorkspace& w, hipStream_t s) {
   const dim3 grid(w.n_groups, d.H_kv, d.P);
   const float c = d.sm_scale * kLog2e;
   KernelTimer timer(d.timing, kKernelScore, s);
-#define SHOTKV_LAUNCH_SCORE(NQB)                                                                      \
-  hipLaunchKernelGGL(score_partials_mfma_kernel<NQB>, grid, dim3(PairShape<NQB>::kThreads), 0, s,     \
-                     static_cast<const bf16_t*>(q_obs), static_cast<const bf16_t*>(k), d.n_tokens, d.H, \
-                     d.H_kv, d.W, d.R_rows, c, w.group_first, w.chunk_start, w.chunk_len, w.max_c, w.partial,      \
+#define SHOTKV_LAUNCH_SCORE(DD, NQB)                                                                          \
+  hipLaunchKernelGGL((score_partials_mfma_kernel<DD, NQB>), grid, dim3(PairShape<DD, NQB>::kThreads), 0, s,   \
+                     static_cast<const bf16_t*>(q_obs), static_cast<const bf16_t*>(k), d.n_tokens, d.H,       \
+                     d.H_kv, d.W, d.R_rows, c, w.group_first, w.chunk_start, w.chunk_len, w.max_c, w.partial, \
                      w.group_stat)
-  switch (d.R / 32) {
-    case 1: SHOTKV_LAUNCH_SCORE(1); break;
-    case 2: SHOTKV_LAUNCH_SCORE(2); break;
-    case 4: SHOTKV_LAUNCH_SCORE(4); break;
-    case 6: SHOTKV_LAUNCH_SCORE(6); break;
-    case 8: SHOTKV_LAUNCH_SCORE(8); break;
-    default: return hipErrorInvalidValue;
+#define SHOTKV_LAUNCH_SCORE_ROWS(DD)             \
+  switch (d.R / 32) {                            \
+    case 1: SHOTKV_LAUNCH_SCORE(DD, 1); break;   \
+    case 2: SHOTKV_LAUNCH_SCORE(DD, 2); break;   \
+    case 4: SHOTKV_LAUNCH_SCORE(DD, 4); break;   \
+    case 6: SHOTKV_LAUNCH_SCORE(DD, 6); break;   \
+    case 8: SHOTKV_LAUNCH_SCORE(DD, 8); break;   \
+    default: return hipErrorInvalidValue;        \
   }
+  if (d.D == 128) {
+    SHOTKV_LAUNCH_SCORE_ROWS(128)
+  } else if (d.D == 64) {
+    SHOTKV_LAUNCH_SCORE_ROWS(64)
+  } else {
+    return hipErrorInvalidValue;
+  }
+#undef SHOTKV_LAUNCH_SCORE_ROWS
 #undef SHOTKV_LAUNCH_SCORE
   return hipGetLastError();
 }
