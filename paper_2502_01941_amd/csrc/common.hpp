@@ -13,8 +13,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // Keys per scoring chunk.  A chunk never straddles a shot boundary, so a chunk's softmax partial can
 // be credited to exactly one shot (or to the always-kept region).
-constexpr int kChunkKeys = 256;       // MFMA path: one wave walks a chunk in 32-key blocks
-constexpr int kChunkKeysGeneric = 64; // generic path: one 64-key block per workgroup
+constexpr int kChunkKeys = 256;
 
 typedef uint16_t bf16_t;  // raw bf16 bits
 
@@ -99,11 +98,10 @@ struct PrefillWorkspace {
   // softmax partial per (problem, chunk, kv head, row): log2 of the chunk's sum of exponentials
   // (-inf for a row that sees none of the chunk's keys)
   float*   partial;       // [P][maxC][H_kv][R]
-  // matrix-core score path: a score workgroup ("group") takes the chunks that start inside one slice
-  // of group_keys keys; group g of a problem owns chunks [group_first[g], group_first[g + 1])
+  // a score workgroup ("group") takes the chunks that start inside one slice of group_keys keys; group g of
+  // a problem owns chunks [group_first[g], group_first[g + 1])
   int32_t* group_first;   // [P][n_groups + 1]
-  // the same statistic over all chunks of a group, which is what the row denominators are built
-  // from; on the generic path (one chunk per workgroup) it is the partial array itself
+  // the same statistic over all chunks of a group, which is what the row denominators are built from
   float*   group_stat;    // [P][H_kv][n_groups][R]
   float*   row_stat;      // [P][H_kv][R]  log2 of the row's sum of exponentials over all chunks
   float*   chunk_mass;    // [P][maxC]
@@ -111,23 +109,21 @@ struct PrefillWorkspace {
   void*    vt;            // fused attention path only: V packed into 32-key blocks [P][H_kv][blocks][D][32], fp16
   uint32_t* v_absmax;     // fused attention path only: [P][H_kv] largest finite |v| of the plane, as bf16 bits
   int32_t  max_c;
-  int32_t  chunk_keys;
-  int32_t  group_keys;    // keys per slice of the key axis, 0 on the generic path
-  int32_t  n_groups;      // ceil(n_tokens / group_keys); max_c on the generic path
+  int32_t  group_keys;    // keys per slice of the key axis
+  int32_t  n_groups;      // ceil(n_tokens / group_keys)
   size_t   bytes;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-int score_group_keys(int P, int H_kv, int n_tokens, int n_shots);  // keys per workgroup of the matrix-core score kernel
+int score_group_keys(int P, int H_kv, int n_tokens, int n_shots);  // keys per workgroup of the score kernel
 
 inline PrefillWorkspace carve_prefill(void* base, int P, int H_kv, int R, int n_tokens, int n_shots,
-                                      bool mfma_score, size_t vt_bytes = 0) {
+                                      size_t vt_bytes = 0) {
   PrefillWorkspace w{};
-  w.chunk_keys = mfma_score ? kChunkKeys : kChunkKeysGeneric;
-  w.max_c = max_chunks(n_tokens, n_shots, w.chunk_keys);
-  w.group_keys = mfma_score ? score_group_keys(P, H_kv, n_tokens, n_shots) : 0;
-  w.n_groups = mfma_score ? ceil_div(n_tokens, w.group_keys) : w.max_c;
+  w.max_c = max_chunks(n_tokens, n_shots, kChunkKeys);
+  w.group_keys = score_group_keys(P, H_kv, n_tokens, n_shots);
+  w.n_groups = ceil_div(n_tokens, w.group_keys);
   size_t off = 0;
   char* b = static_cast<char*>(base);
   auto take = [&](size_t bytes) {
@@ -140,9 +136,9 @@ inline PrefillWorkspace carve_prefill(void* base, int P, int H_kv, int R, int n_
   w.chunk_start = reinterpret_cast<int32_t*>(take(P_ * C * 4));
   w.chunk_len = reinterpret_cast<int32_t*>(take(P_ * C * 4));
   w.seg_first = reinterpret_cast<int32_t*>(take(P_ * (S + 3) * 4));
-  w.group_first = mfma_score ? reinterpret_cast<int32_t*>(take(P_ * (w.n_groups + 1) * 4)) : nullptr;
+  w.group_first = reinterpret_cast<int32_t*>(take(P_ * (w.n_groups + 1) * 4));
   w.partial = reinterpret_cast<float*>(take(P_ * H_kv * C * R * 4));
-  w.group_stat = mfma_score ? reinterpret_cast<float*>(take(P_ * H_kv * w.n_groups * R * 4)) : w.partial;
+  w.group_stat = reinterpret_cast<float*>(take(P_ * H_kv * w.n_groups * R * 4));
   w.row_stat = reinterpret_cast<float*>(take(P_ * H_kv * R * 4));
   w.chunk_mass = reinterpret_cast<float*>(take(P_ * C * 4));
   w.scores = reinterpret_cast<float*>(take(P_ * S * 4 + 4));
@@ -156,7 +152,7 @@ inline PrefillWorkspace carve_prefill(void* base, int P, int H_kv, int R, int n_
 
 struct PrefillDims {
   int P, n_tokens, n_shots, H, H_kv, G, D, W;
-  int R;       // row stride of the per-row workspace arrays: G * W, padded to 32/64/128/192/256 on the matrix-core score path
+  int R;       // row stride of the per-row workspace arrays: G * W, padded to the score kernel's blocks of 32 rows
   int R_rows;  // G * W query rows per KV head that really exist
   int dtype;
   float sm_scale;
@@ -181,7 +177,7 @@ hipError_t launch_compact(const PrefillDims& d, const void* k, const void* v, vo
                           int cap, const int32_t* kept_positions, const int32_t* kept_count,
                           hipStream_t s);
 
-bool score_uses_mfma(const PrefillDims& d);
+int score_row_blocks(int dtype, int rows);  // blocks of 32 query rows the score kernel is instantiated for
 
 // causal attention forward that also writes the window rows' softmax partials and row denominators
 bool attention_supported(const PrefillDims& d);

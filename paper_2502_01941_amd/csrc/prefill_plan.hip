@@ -61,12 +61,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_chunks_kernel(
   }
   if (local_bad) atomicOr(&bad, 1);
   __syncthreads();
-  int32_t* g_first = group_first ? group_first + static_cast<size_t>(p) * (n_groups + 1) : nullptr;
+  int32_t* g_first = group_first + static_cast<size_t>(p) * (n_groups + 1);
   if (bad) {
     if (tid == 0) { status[p] = SHOTKV_ST_BAD_OFFSETS; n_chunks[p] = 0; }
     for (int s = tid; s < n_shots + 3; s += kPlanThreads) s_first[s] = 0;
-    if (g_first)
-      for (int gi = tid; gi <= n_groups; gi += kPlanThreads) g_first[gi] = 0;
+    for (int gi = tid; gi <= n_groups; gi += kPlanThreads) g_first[gi] = 0;
     return;
   }
   if (tid == 0) status[p] = SHOTKV_ST_OK;
@@ -115,16 +114,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_chunks_kernel(
     s_first[n_seg] = carry;
     n_chunks[p] = carry;
   }
-  if (g_first) {
-    // Group g of the score pass owns the chunks that start in key slice [g * group_keys, (g + 1) *
-    // group_keys): group_first[g] = first chunk starting at or after the slice's first key.  Chunk
-    // starts increase, so chunk c opens every group after its predecessor's up to its own.
-    const int nc = carry;  // final since the barrier that ended the loop above
-    for (int c = tid; c <= nc; c += kPlanThreads) {
-      const int g_hi = (c < nc) ? c_start[c] / group_keys : n_groups;
-      const int g_lo = (c == 0) ? 0 : c_start[c - 1] / group_keys + 1;
-      for (int gi = g_lo; gi <= g_hi; ++gi) g_first[gi] = c;
-    }
+  // Group g of the score pass owns the chunks that start in key slice [g * group_keys, (g + 1) *
+  // group_keys): group_first[g] = first chunk starting at or after the slice's first key.  Chunk
+  // starts increase, so chunk c opens every group after its predecessor's up to its own.
+  const int nc = carry;  // final since the barrier that ended the loop above
+  for (int c = tid; c <= nc; c += kPlanThreads) {
+    const int g_hi = (c < nc) ? c_start[c] / group_keys : n_groups;
+    const int g_lo = (c == 0) ? 0 : c_start[c - 1] / group_keys + 1;
+    for (int gi = g_lo; gi <= g_hi; ++gi) g_first[gi] = c;
   }
 }
 
@@ -134,7 +131,7 @@ hipError_t launch_plan_chunks(const PrefillDims& d, const int32_t* shot_offsets,
                               const PrefillWorkspace& w, hipStream_t s) {
   KernelTimer timer(d.timing, kKernelPlan, s);
   hipLaunchKernelGGL(plan_chunks_kernel, dim3(d.P), dim3(kPlanThreads), 0, s, shot_offsets, d.share, d.n_shots,
-                     d.n_tokens, w.chunk_keys, w.max_c, status, w.n_chunks, w.chunk_start, w.chunk_len,
+                     d.n_tokens, kChunkKeys, w.max_c, status, w.n_chunks, w.chunk_start, w.chunk_len,
                      w.seg_first, w.group_keys, w.n_groups, w.group_first, w.v_absmax, d.H_kv);
   return hipGetLastError();
 }

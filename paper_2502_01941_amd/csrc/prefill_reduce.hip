@@ -14,26 +14,23 @@ constexpr int kStatThreads = 1024;
 
 __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const float* __restrict__ group_stat,
                                                                  const int32_t* __restrict__ n_chunks,
-                                                                 int H_kv, int R, size_t problem_stride,
-                                                                 size_t head_stride, size_t group_stride,
-                                                                 int n_groups,
+                                                                 int H_kv, int R, int n_groups,
                                                                  float* __restrict__ row_stat) {
   const int g = blockIdx.x, p = blockIdx.y;
   const int nl = kStatThreads / R;  // group lanes
   const int tid = threadIdx.x;
   const int r = tid % R, gl = tid / R;
-  // entries to combine: every score workgroup's statistic (-inf from one without chunks), or on the
-  // generic path the partial of every chunk
-  const int ng = n_groups > 0 ? (n_chunks[p] > 0 ? n_groups : 0) : n_chunks[p];
-  const float* base = group_stat + p * problem_stride + g * head_stride;
+  // entries to combine: every score workgroup's statistic (-inf from one without chunks)
+  const int ng = n_chunks[p] > 0 ? n_groups : 0;
+  const float* base = group_stat + (static_cast<size_t>(p) * H_kv + g) * n_groups * R;
   // two passes over the lane's share (second one out of cache): the maximum first, then the sum of
   // 2^(x - max) with independent loads
   float M = -INFINITY;
   if (gl < nl)
-    for (int c = gl; c < ng; c += nl) M = fmaxf(M, base[c * group_stride + r]);
+    for (int c = gl; c < ng; c += nl) M = fmaxf(M, base[static_cast<size_t>(c) * R + r]);
   float L = 0.f;
   if (gl < nl && M > -INFINITY)
-    for (int c = gl; c < ng; c += nl) L += exp2f(base[c * group_stride + r] - M);  // 2^-inf = 0
+    for (int c = gl; c < ng; c += nl) L += exp2f(base[static_cast<size_t>(c) * R + r] - M);  // 2^-inf = 0
   __shared__ float sM[kStatThreads];
   __shared__ float sL[kStatThreads];
   sM[tid] = M;
@@ -101,15 +98,8 @@ hipError_t launch_chunk_mass(const PrefillDims& d, const PrefillWorkspace& w, hi
 
 hipError_t launch_row_stats(const PrefillDims& d, const PrefillWorkspace& w, hipStream_t s) {
   KernelTimer timer(d.timing, kKernelRowStats, s);
-  // per-workgroup statistics are [P][H_kv][n_groups][R]; without them (one chunk per score workgroup)
-  // the per-chunk partials [P][max_c][H_kv][R] are read in their place
-  const bool own = w.group_stat != w.partial;
-  const size_t R = d.R, heads = d.H_kv;
-  const size_t problem_stride = own ? heads * w.n_groups * R : static_cast<size_t>(w.max_c) * heads * R;
-  const size_t head_stride = own ? w.n_groups * R : R;
-  const size_t group_stride = own ? R : heads * R;
   hipLaunchKernelGGL(row_stats_kernel, dim3(d.H_kv, d.P), dim3(kStatThreads), 0, s, w.group_stat, w.n_chunks,
-                     d.H_kv, d.R, problem_stride, head_stride, group_stride, own ? w.n_groups : 0, w.row_stat);
+                     d.H_kv, d.R, w.n_groups, w.row_stat);
   return hipGetLastError();
 }
 

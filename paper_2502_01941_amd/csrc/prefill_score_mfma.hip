@@ -1,13 +1,13 @@
 // Window-attention softmax partials on the gfx950 matrix cores (Section 5.1, Eq. 3: alpha_{t,h}).
 //
-// Shape: bf16, head_dim 64 or 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6 or 8
-// blocks of 32 rows; rows past G*W are zero operands whose statistics are written as -inf.
+// Shape: bf16 or fp32, head_dim 64 or 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6
+// (bf16) or 8 blocks of 32 rows; rows past G*W are zero operands whose statistics are written as -inf.
 //
 // A workgroup is a pair of waves (one wave for a single row block) that takes the chunks starting inside
 // one slice of a KV head's key axis and walks that contiguous span in blocks of 32 keys.  Each wave keeps
 // its share of the window queries in registers as MFMA B operands and computes
-// S^T[32 keys x 32 queries] = K_blk * Q^T per row block with v_mfma_f32_32x32x16_bf16.  Keys run along the
-// accumulator registers and queries along the lanes, so the row-softmax statistics (max and sum over
+// S^T[32 keys x 32 queries] = K_blk * Q^T per row block with v_mfma_f32_32x32x16_bf16 (fp32 inputs:
+// v_mfma_f32_32x32x2_f32, full single precision).  Keys run along the accumulator registers and queries along the lanes, so the row-softmax statistics (max and sum over
 // keys) are in-lane reductions; only the two lane halves are merged, once per chunk.  A block that
 // contains a chunk boundary credits its weights to the chunks on either side with masked in-lane sums.
 //
@@ -27,6 +27,13 @@
 //     share the 256 bytes of the banks, so eight pairs of rows have to differ in the slot.  Half the bytes
 //     and half the matrix steps per key, but the same exponentials: bound by vector issue (16 problems of
 //     16001 tokens, 8 KV heads, 128 query rows: 78 us = 3.4 TB/s; plain vector arithmetic took 2427 us).
+//   512-byte rows (fp32, head_dim 128): row r starts at r*512 + (r/2)*32 and column c sits in slot c ^ (r%2);
+//     sixteen rows then cover the banks and every step is an immediate offset from one lane base.
+//
+// fp32: the matrix unit takes 16 times as long per product as in bf16, so the operand reads weigh little: one
+// query block per wave (up to four waves per workgroup, all reading the same block) keeps the query operands
+// at 64 registers.  Bound by the matrix unit: 4 problems of 4001 tokens, 8 KV heads, 128 query rows, head_dim
+// 128 in 62 us = 68 TFLOP/s (two workgroups per CU; plain vector arithmetic took 394 us).
 //
 // The direct-to-LDS loads are written as inline assembly and their completion is tracked by hand with
 // s_waitcnt vmcnt: when they are visible to the compiler it makes every LDS read wait for all loads
@@ -43,35 +50,62 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) const char lds_cchar;  // keeps LDS reads as ds_read, not flat
-typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
 
 constexpr int kBlockKeys = 32;
 
 // How a 32-key block lies in LDS; see the top of the file.
-template <int D> struct KeyLayout;
-template <> struct KeyLayout<128> {
-  static constexpr int kRowBytes = 256;
-  static constexpr int kLoadBytes = 4 * kRowBytes + 64;  // LDS stride of one direct-to-LDS instruction: four rows + pad
-  // slot of lane l in instruction i: row 4i + l/16, slot l%16, which holds column (l%16) ^ (l/16)
+template <int ROW_BYTES> struct KeyLayout;
+template <> struct KeyLayout<512> {
+  static constexpr int kLoadBytes = 2 * 512 + 32;    // LDS stride of one direct-to-LDS instruction: two rows + pad
+  // slot of lane l in instruction i: row 2i + l/32, slot l%32, which holds column (l%32) ^ (l/32)
+  __device__ static uint32_t fetch_column(int, int lane) { return (lane & 31) ^ (lane >> 5); }
+  __device__ static int operand_base(int row, int half) {
+    return row * 512 + (row >> 1) * 32 + ((half ^ (row & 1)) << 4);
+  }
+  __device__ static int operand(int base, int ks) { return base + 32 * ks; }
+};
+template <> struct KeyLayout<256> {
+  static constexpr int kLoadBytes = 4 * 256 + 64;    // four rows + pad
+  // row 4i + l/16, slot l%16, which holds column (l%16) ^ (l/16)
   __device__ static uint32_t fetch_column(int, int lane) { return (lane & 15) ^ (lane >> 4); }
   __device__ static int operand_base(int row, int half) {
-    return row * kRowBytes + (row >> 2) * 64 + ((half ^ (row & 3)) << 4);
+    return row * 256 + (row >> 2) * 64 + ((half ^ (row & 3)) << 4);
   }
   __device__ static int operand(int base, int ks) { return ((ks & 1) ? base ^ 32 : base) + 64 * (ks >> 1); }
 };
-template <> struct KeyLayout<64> {
-  static constexpr int kRowBytes = 128;
-  static constexpr int kLoadBytes = 8 * kRowBytes;       // eight rows
+template <> struct KeyLayout<128> {
+  static constexpr int kLoadBytes = 8 * 128;         // eight rows
   // row 8i + l/8, slot l%8, which holds column (l%8) ^ ((row/2)%8)
   __device__ static uint32_t fetch_column(int i, int lane) { return (lane & 7) ^ ((4 * i + (lane >> 4)) & 7); }
-  __device__ static int operand_base(int row, int half) { return row * kRowBytes + ((half ^ ((row >> 1) & 7)) << 4); }
+  __device__ static int operand_base(int row, int half) { return row * 128 + ((half ^ ((row >> 1) & 7)) << 4); }
   __device__ static int operand(int base, int ks) { return base ^ (ks << 5); }
 };
-template <int D> constexpr int kLoadsPerBlock = kBlockKeys * KeyLayout<D>::kRowBytes / 1024;
-template <int D> constexpr int kBufBytes = kLoadsPerBlock<D> * KeyLayout<D>::kLoadBytes;
-template <int D> constexpr int kSteps = D / 16;          // matrix steps along the head dimension
+
+// Element type of Q and K with the head dimension: row sizes, operand registers and the matrix instruction.
+// Step ks of a row is its 32 bytes at 32*ks; the lanes of half h hold the 16 bytes at 32*ks + 16*h of it.
+template <typename T> struct Operand;                       // 16 bytes of a row as one lane holds them
+template <> struct Operand<bf16_t> { typedef bf16x8 Vec; };
+template <> struct Operand<float> { typedef floatx4 Vec; };
+template <typename T, int D> struct Element {
+  typedef typename Operand<T>::Vec Vec;
+  static constexpr int kRowBytes = D * static_cast<int>(sizeof(T));
+  static constexpr int kSteps = kRowBytes / 32;
+  static constexpr int kLoadsPerBlock = kBlockKeys * kRowBytes / 1024;  // 1 KB direct-to-LDS instructions
+  static constexpr int kBufBytes = kLoadsPerBlock * KeyLayout<kRowBytes>::kLoadBytes;
+  typedef KeyLayout<kRowBytes> Layout;
+};
+__device__ __forceinline__ floatx16 multiply_step(bf16x8 a, bf16x8 b, floatx16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ floatx16 multiply_step(floatx4 a, floatx4 b, floatx16 acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e)  // lanes of half h supply element 4h + e of the step on both sides
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
+  return acc;
+}
 #ifndef SHOTKV_SCORE_RING
 #define SHOTKV_SCORE_RING 3
 #endif
@@ -87,17 +121,17 @@ static_assert(kRing >= 2 && kRing <= 5, "ring depth");
 // The loads carry the non-temporal hint: K is read exactly once, and a stream that does not settle in L2
 // and the memory-side cache leaves them to the statistics this kernel writes and the next kernels read
 // (measured: 8 % faster here, and the per-chunk reduction that follows finds its input in cache).
-template <int D, int NL>
+template <typename E, int NL>
 __device__ __forceinline__ void issue_block(const char* __restrict__ k_plane, int key0, int rem,
                                             uint32_t lds_addr, int i0, int lane) {
-  typedef KeyLayout<D> L;
-  constexpr int kRows = 1024 / L::kRowBytes;  // rows per instruction
+  typedef typename E::Layout L;
+  constexpr int kRows = 1024 / E::kRowBytes;  // rows per instruction
   const int last = rem - 1;  // rem >= 1
-  const char* base = k_plane + static_cast<size_t>(key0) * L::kRowBytes;
+  const char* base = k_plane + static_cast<size_t>(key0) * E::kRowBytes;
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
     const int rr = min(kRows * (i0 + i) + lane / (kWave / kRows), last);
-    const uint32_t off = static_cast<uint32_t>(rr) * L::kRowBytes + (L::fetch_column(i0 + i, lane) << 4);
+    const uint32_t off = static_cast<uint32_t>(rr) * E::kRowBytes + (L::fetch_column(i0 + i, lane) << 4);
     // M0 = LDS address of the instruction's slots (wave-uniform); lane l lands at M0 + 16*l
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                  :
@@ -164,32 +198,33 @@ __device__ __forceinline__ void softmax_fold(floatx16 acc, float c, int half, in
 }
 
 // S^T of one 32-key block and this wave's NQW query blocks
-template <int D, int NQW>
-__device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][kSteps<D>], int lane,
-                                             floatx16 (&acc)[NQW]) {
-  typedef KeyLayout<D> L;
+template <typename T, int D, int NQW>
+__device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const typename Element<T, D>::Vec (&bq)[NQW][Element<T, D>::kSteps],
+                                             int lane, floatx16 (&acc)[NQW]) {
+  typedef typename Element<T, D>::Layout L;
+  typedef typename Element<T, D>::Vec Vec;
+  typedef __attribute__((address_space(3))) const Vec lds_vec;
   const int base = L::operand_base(lane & 31, lane >> 5);
 #pragma unroll
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
 #pragma unroll
-  for (int ks = 0; ks < kSteps<D>; ++ks) {
-    const bf16x8 a = *reinterpret_cast<lds_bf16x8*>(lds_buf + L::operand(base, ks));
+  for (int ks = 0; ks < Element<T, D>::kSteps; ++ks) {
+    const Vec a = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, ks));
 #pragma unroll
-    for (int q = 0; q < NQW; ++q)
-      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bq[q][ks], acc[q], 0, 0, 0);
+    for (int q = 0; q < NQW; ++q) acc[q] = multiply_step(a, bq[q][ks], acc[q]);
   }
 }
 
 // One 32-key block against this wave's NQW query blocks (qb0 = index of its first one).
-template <int D, int NQW, bool MASKED, bool EXACT>
-__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][kSteps<D>], int lane,
+template <typename T, int D, int NQW, bool MASKED, bool EXACT>
+__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const typename Element<T, D>::Vec (&bq)[NQW][Element<T, D>::kSteps], int lane,
                                               int qb0, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
   floatx16 acc[NQW];
-  logits_block<D, NQW>(lds_buf, bq, lane, acc);
+  logits_block<T, D, NQW>(lds_buf, bq, lane, acc);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int last_visible = causal_base + ((qb0 + q) * 32 + row) % W;
@@ -200,13 +235,13 @@ __device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (
 // The same block when a chunk ends inside it: the exact online-softmax update, then the sixteen weights
 // 2^(z - reference) of every query stay in `e` so that the caller can credit them to the chunks on either
 // side of each boundary.  Nothing is added to l_run here.
-template <int D, int NQW, bool MASKED>
-__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][kSteps<D>], int lane, int qb0,
+template <typename T, int D, int NQW, bool MASKED>
+__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const typename Element<T, D>::Vec (&bq)[NQW][Element<T, D>::kSteps], int lane, int qb0,
                                               int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW],
                                               floatx16 (&e)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
-  logits_block<D, NQW>(lds_buf, bq, lane, e);
+  logits_block<T, D, NQW>(lds_buf, bq, lane, e);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     if (MASKED) {
@@ -318,32 +353,40 @@ __device__ __forceinline__ void credit_elements(const floatx16 (&e)[NQW], uint32
 
 constexpr int kEndCache = 128;  // chunk ends of a workgroup kept in LDS
 
-template <int D, int NQB>
-struct PairShape {
+template <typename T, int D, int NQB>
+struct GroupShape {
 #ifndef SHOTKV_SCORE_MAX_WAVES
 #define SHOTKV_SCORE_MAX_WAVES 2
 #endif
-  static constexpr int kWaves = NQB >= SHOTKV_SCORE_MAX_WAVES ? SHOTKV_SCORE_MAX_WAVES : (NQB >= 2 ? 2 : 1);  // waves per workgroup
-  static constexpr int kNQW = NQB / kWaves;           // query blocks per wave
-  static constexpr int kLoads = kLoadsPerBlock<D> / kWaves;  // load instructions per wave per block
+  static constexpr bool kF32 = sizeof(T) == 4;
+  // waves per workgroup: a pair in bf16, up to four in fp32 (one or two query blocks each)
+  static constexpr int kMaxWaves = kF32 ? 4 : SHOTKV_SCORE_MAX_WAVES;
+  static constexpr int kWaves = NQB < kMaxWaves ? NQB : kMaxWaves;
+  static constexpr int kNQW = NQB / kWaves;                                 // query blocks per wave
+  static constexpr int kLoads = Element<T, D>::kLoadsPerBlock / kWaves;     // load instructions per wave per block
+  static_assert(NQB % kWaves == 0 && Element<T, D>::kLoadsPerBlock % kWaves == 0, "even shares");
   static constexpr int kThreads = kWaves * kWave;
-  // single-wave groups are LDS-limited; four query blocks per wave need the 256-register budget; half the
-  // head dimension leaves half the query registers, room for a fourth wave
-  static constexpr int kMinWavesPerSimd =
-      kWaves == 1 ? 1 : (kNQW > 2 ? 2 : D == 64 ? SHOTKV_SCORE_WAVES_PER_SIMD + 1 : SHOTKV_SCORE_WAVES_PER_SIMD);
+  // Waves per SIMD the registers are budgeted for: what the query operands leave room for (bf16, head_dim 128:
+  // three waves with up to two query blocks per wave, two with more), and no more than the LDS admits.
+  static constexpr int kQueryRegs = kNQW * Element<T, D>::kSteps * 4;
+  static constexpr int kRegWaves =
+      (kQueryRegs > 64 || kNQW > 2) ? 2 : kQueryRegs > 32 ? SHOTKV_SCORE_WAVES_PER_SIMD : SHOTKV_SCORE_WAVES_PER_SIMD + 1;
+  static constexpr int kLdsWaves = 160 * 1024 / (kRing * Element<T, D>::kBufBytes + 1024) * kWaves / 4;
+  static constexpr int kMinWavesPerSimd = kLdsWaves < 1 ? 1 : kLdsWaves < kRegWaves ? kLdsWaves : kRegWaves;
 };
 
-template <int D, int NQB>
-__global__ __launch_bounds__((PairShape<D, NQB>::kThreads), (PairShape<D, NQB>::kMinWavesPerSimd)) void
+template <typename T, int D, int NQB>
+__global__ __launch_bounds__((GroupShape<T, D, NQB>::kThreads), (GroupShape<T, D, NQB>::kMinWavesPerSimd)) void
 score_partials_mfma_kernel(
-    const bf16_t* __restrict__ q_obs, const bf16_t* __restrict__ k, int n_tokens, int H, int H_kv, int W,
+    const T* __restrict__ q_obs, const T* __restrict__ k, int n_tokens, int H, int H_kv, int W,
     int n_rows, float c, const int32_t* __restrict__ group_first, const int32_t* __restrict__ chunk_start,
     const int32_t* __restrict__ chunk_len, int max_c,
     float* __restrict__ partial, float* __restrict__ group_stat) {
-  typedef PairShape<D, NQB> S;
+  typedef GroupShape<T, D, NQB> S;
+  typedef Element<T, D> E;
   constexpr int NQW = S::kNQW;
   constexpr int R = NQB * 32;
-  __shared__ __attribute__((aligned(64))) char lds[kRing][kBufBytes<D>];
+  __shared__ __attribute__((aligned(64))) char lds[kRing][E::kBufBytes];
   __shared__ int s_end[kEndCache];
 
   const int lane = threadIdx.x % kWave;
@@ -362,24 +405,25 @@ score_partials_mfma_kernel(
   const int32_t* cs = chunk_start + static_cast<size_t>(p) * max_c;
   const int32_t* cl = chunk_len + static_cast<size_t>(p) * max_c;
   const char* k_plane =
-      reinterpret_cast<const char*>(k) + (static_cast<size_t>(p) * H_kv + g) * n_tokens * KeyLayout<D>::kRowBytes;
+      reinterpret_cast<const char*>(k) + (static_cast<size_t>(p) * H_kv + g) * n_tokens * E::kRowBytes;
   const int G = H / H_kv;
-  const bf16_t* q_rows = q_obs + (static_cast<size_t>(p) * H + static_cast<size_t>(g) * G) * W * D;
+  const T* q_rows = q_obs + (static_cast<size_t>(p) * H + static_cast<size_t>(g) * G) * W * D;
   float* out = partial + (static_cast<size_t>(p) * max_c * H_kv + g) * R;  // chunk c of this head: + c * H_kv * R
   const int qb0 = wave * NQW;
 
-  // B operands: query row (qb0+q)*32 + lane%32, head-dim slice 16*ks + 8*(lane/32) .. +8
-  // Query rows past n_rows = G*W (a row count that is not one of 32/64/128/192/256) are zero operands; their
+  // B operands: query row (qb0+q)*32 + lane%32, the lane half's 16 bytes of every step
+  // Query rows past n_rows = G*W (a row count that is not one of the instantiated ones) are zero operands; their
   // statistics are written as -inf, so they carry no weight further down.
-  bf16x8 bq[NQW][kSteps<D>];
+  constexpr int kVec = 16 / sizeof(T);
+  typename E::Vec bq[NQW][E::kSteps];
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int qi = (qb0 + q) * 32 + (lane & 31);
 #pragma unroll
-    for (int ks = 0; ks < kSteps<D>; ++ks) {
+    for (int ks = 0; ks < E::kSteps; ++ks) {
       u32x4 raw = {0u, 0u, 0u, 0u};
-      if (qi < n_rows) raw = *reinterpret_cast<const u32x4*>(q_rows + qi * D + ks * 16 + (lane >> 5) * 8);
-      bq[q][ks] = __builtin_bit_cast(bf16x8, raw);
+      if (qi < n_rows) raw = *reinterpret_cast<const u32x4*>(q_rows + qi * D + ks * (2 * kVec) + (lane >> 5) * kVec);
+      bq[q][ks] = __builtin_bit_cast(typename E::Vec, raw);
     }
   }
   // the query loads must have landed before the streaming loop starts: inside the loop the only
@@ -387,7 +431,7 @@ score_partials_mfma_kernel(
 #pragma unroll
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
-    for (int ks = 0; ks < kSteps<D>; ++ks) asm volatile("" ::"v"(bq[q][ks]));
+    for (int ks = 0; ks < E::kSteps; ++ks) asm volatile("" ::"v"(bq[q][ks]));
 
   lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
   const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base));
@@ -463,12 +507,12 @@ score_partials_mfma_kernel(
   constexpr int kLook = kRing - 1;
   auto ring_slot = [](int sl) { return sl >= kRing ? sl - kRing : sl; };
   int cur_key0 = k_begin, next_key0 = k_begin + kBlockKeys;  // next block to request
-  issue_block<D, S::kLoads>(k_plane, k_begin, k_end - k_begin, lds_addr, g0, lane);
+  issue_block<E, S::kLoads>(k_plane, k_begin, k_end - k_begin, lds_addr, g0, lane);
   int n_q = 0;
 #pragma unroll
   for (int i = 0; i < kLook - 1; ++i) {
     if (next_key0 < k_end) {
-      issue_block<D, S::kLoads>(k_plane, next_key0, k_end - next_key0, lds_addr + (i + 1) * kBufBytes<D>, g0, lane);
+      issue_block<E, S::kLoads>(k_plane, next_key0, k_end - next_key0, lds_addr + (i + 1) * E::kBufBytes, g0, lane);
       n_q = i + 1;
       next_key0 += kBlockKeys;
     }
@@ -495,6 +539,7 @@ score_partials_mfma_kernel(
     cur_end = cur_c < c_end ? chunk_end(cur_c) : INT32_MAX;
   };
 
+#pragma clang loop unroll(disable)
   while (true) {
     // this wave's share of `cur` has landed once only the loads of the queued blocks are outstanding
     // (stores of statistics issued meanwhile are younger than those loads and only make the wait stricter)
@@ -506,8 +551,8 @@ score_partials_mfma_kernel(
     if (S::kWaves > 1) asm volatile("s_barrier" ::: "memory");
     if (n_stash == kStash) flush();
     if (next_key0 < k_end) {
-      issue_block<D, S::kLoads>(k_plane, next_key0, k_end - next_key0,
-                             lds_addr + ring_slot(cur_buf + n_q + 1) * kBufBytes<D>, g0, lane);
+      issue_block<E, S::kLoads>(k_plane, next_key0, k_end - next_key0,
+                             lds_addr + ring_slot(cur_buf + n_q + 1) * E::kBufBytes, g0, lane);
       ++n_q;
       next_key0 += kBlockKeys;
     }
@@ -516,20 +561,20 @@ score_partials_mfma_kernel(
     // The workgroup's first block has no reference yet and takes the exact update straight away.
     const int cur_rem = min(kBlockKeys, k_end - cur_key0);
     const bool masked = cur_rem < kBlockKeys || cur_key0 + kBlockKeys - 1 > causal_base;
-    lds_cchar* blk = lds_base + cur_buf * kBufBytes<D>;
+    lds_cchar* blk = lds_base + cur_buf * E::kBufBytes;
     if (cur_end >= cur_key0 + cur_rem) {  // no chunk ends inside the block
       if (first_block)
-        compute_block<D, NQW, true, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, true, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else if (masked)
-        compute_block<D, NQW, true, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, true, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else
-        compute_block<D, NQW, false, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, false, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
     } else {
       floatx16 e[NQW];
       if (masked)
-        weights_block<D, NQW, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       else
-        weights_block<D, NQW, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       uint32_t lo0 = 0u, lo1 = 0u;  // elements already credited (lower / upper lane half)
       do {
         const int hi = cur_end - cur_key0;  // wave-uniform, 1..31
@@ -582,37 +627,48 @@ int score_group_keys(int P, int H_kv, int n_tokens, int n_shots) {
 #endif
 }
 
-bool score_uses_mfma(const PrefillDims& d) { return d.dtype == SHOTKV_BF16; }
+int score_row_blocks(int dtype, int rows) {
+  // what the kernel is instantiated for; fp32 has no six-block form (its four waves share the rows evenly)
+  const int need = ceil_div(rows, 32);
+  return need <= 2 ? need : need <= 4 ? 4 : (need <= 6 && dtype == SHOTKV_BF16) ? 6 : 8;
+}
 
-hipError_t launch_score_partials_mfma(const PrefillDims& d, const void* q_obs, const void* k,
-                                      const PrefillWorkspace& w, hipStream_t s) {
-  const dim3 grid(w.n_groups, d.H_kv, d.P);
-  const float c = d.sm_scale * kLog2e;
-  KernelTimer timer(d.timing, kKernelScore, s);
-#define SHOTKV_LAUNCH_SCORE(DD, NQB)                                                                          \
-  hipLaunchKernelGGL((score_partials_mfma_kernel<DD, NQB>), grid, dim3(PairShape<DD, NQB>::kThreads), 0, s,   \
-                     static_cast<const bf16_t*>(q_obs), static_cast<const bf16_t*>(k), d.n_tokens, d.H,       \
-                     d.H_kv, d.W, d.R_rows, c, w.group_first, w.chunk_start, w.chunk_len, w.max_c, w.partial, \
-                     w.group_stat)
-#define SHOTKV_LAUNCH_SCORE_ROWS(DD)             \
-  switch (d.R / 32) {                            \
-    case 1: SHOTKV_LAUNCH_SCORE(DD, 1); break;   \
-    case 2: SHOTKV_LAUNCH_SCORE(DD, 2); break;   \
-    case 4: SHOTKV_LAUNCH_SCORE(DD, 4); break;   \
-    case 6: SHOTKV_LAUNCH_SCORE(DD, 6); break;   \
-    case 8: SHOTKV_LAUNCH_SCORE(DD, 8); break;   \
-    default: return hipErrorInvalidValue;        \
+template <typename T, int D, int NQB>
+static void launch_score(const PrefillDims& d, const void* q_obs, const void* k, const PrefillWorkspace& w,
+                         hipStream_t s) {
+  hipLaunchKernelGGL((score_partials_mfma_kernel<T, D, NQB>), dim3(w.n_groups, d.H_kv, d.P),
+                     dim3(GroupShape<T, D, NQB>::kThreads), 0, s, static_cast<const T*>(q_obs),
+                     static_cast<const T*>(k), d.n_tokens, d.H, d.H_kv, d.W, d.R_rows, d.sm_scale * kLog2e,
+                     w.group_first, w.chunk_start, w.chunk_len, w.max_c, w.partial, w.group_stat);
+}
+
+template <typename T, int D>
+static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, const void* k, const PrefillWorkspace& w,
+                                    hipStream_t s) {
+  switch (d.R / 32) {
+    case 1: launch_score<T, D, 1>(d, q_obs, k, w, s); break;
+    case 2: launch_score<T, D, 2>(d, q_obs, k, w, s); break;
+    case 4: launch_score<T, D, 4>(d, q_obs, k, w, s); break;
+    case 6:
+      if constexpr (sizeof(T) == 2) { launch_score<T, D, 6>(d, q_obs, k, w, s); break; }
+      return hipErrorInvalidValue;
+    case 8: launch_score<T, D, 8>(d, q_obs, k, w, s); break;
+    default: return hipErrorInvalidValue;
   }
-  if (d.D == 128) {
-    SHOTKV_LAUNCH_SCORE_ROWS(128)
-  } else if (d.D == 64) {
-    SHOTKV_LAUNCH_SCORE_ROWS(64)
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef SHOTKV_LAUNCH_SCORE_ROWS
-#undef SHOTKV_LAUNCH_SCORE
   return hipGetLastError();
+}
+
+hipError_t launch_score_partials(const PrefillDims& d, const void* q_obs, const void* k, const PrefillWorkspace& w,
+                                 hipStream_t s) {
+  KernelTimer timer(d.timing, kKernelScore, s);
+  if (d.dtype == SHOTKV_BF16) {
+    if (d.D == 128) return launch_score_rows<bf16_t, 128>(d, q_obs, k, w, s);
+    if (d.D == 64) return launch_score_rows<bf16_t, 64>(d, q_obs, k, w, s);
+  } else {
+    if (d.D == 128) return launch_score_rows<float, 128>(d, q_obs, k, w, s);
+    if (d.D == 64) return launch_score_rows<float, 64>(d, q_obs, k, w, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace shotkv

@@ -28,17 +28,6 @@ int static_scratch(void** out) {
 }
 }  // namespace
 
-hipError_t launch_score_partials_generic(const PrefillDims& d, const void* q_obs, const void* k,
-                                         const PrefillWorkspace& w, hipStream_t s);
-hipError_t launch_score_partials_mfma(const PrefillDims& d, const void* q_obs, const void* k,
-                                      const PrefillWorkspace& w, hipStream_t s);
-
-hipError_t launch_score_partials(const PrefillDims& d, const void* q_obs, const void* k,
-                                 const PrefillWorkspace& w, hipStream_t s) {
-  return score_uses_mfma(d) ? launch_score_partials_mfma(d, q_obs, k, w, s)
-                            : launch_score_partials_generic(d, q_obs, k, w, s);
-}
-
 namespace {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -68,13 +57,9 @@ int make_prefill_dims(const shotkv_config* cfg, int P, int n_tokens, int n_shots
   if (P < 1 || n_tokens < cfg->window || n_shots < 0 || n_shots > SHOTKV_MAX_SHOTS) return SHOTKV_E_SHAPE;
   d->P = P; d->n_tokens = n_tokens; d->n_shots = n_shots;
   d->H = cfg->n_q_heads; d->H_kv = cfg->n_kv_heads; d->G = G; d->D = cfg->head_dim;
-  d->W = cfg->window; d->R_rows = G * cfg->window; d->R = d->R_rows; d->dtype = cfg->dtype;
+  d->W = cfg->window; d->R_rows = G * cfg->window; d->dtype = cfg->dtype;
+  d->R = 32 * score_row_blocks(d->dtype, d->R_rows);
   d->sm_scale = cfg->sm_scale;
-  if (score_uses_mfma(*d)) {  // the matrix-core kernel works on 1, 2, 4, 6 or 8 blocks of 32 query rows
-    const int need = ceil_div(d->R_rows, 32);
-    const int blocks = need <= 2 ? need : need <= 4 ? 4 : need <= 6 ? 6 : 8;
-    d->R = blocks * 32;
-  }
   d->select_mode = cfg->select_mode;
   d->timing = cfg->timing_events;
   d->share = 1;
@@ -92,7 +77,7 @@ int make_prefill_dims(const shotkv_config* cfg, int P, int n_tokens, int n_shots
 }
 
 PrefillWorkspace carve(const PrefillDims& d, void* base) {
-  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots, score_uses_mfma(d));
+  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots);
 }
 
 int from_hip(hipError_t e) { return e == hipSuccess ? SHOTKV_OK : SHOTKV_E_LAUNCH; }
@@ -216,7 +201,7 @@ static int make_attention_dims(const shotkv_config* cfg, int P, int n_tokens, in
 
 static PrefillWorkspace carve_attention(const PrefillDims& d, void* base) {
   const size_t vt_bytes = static_cast<size_t>(d.P) * d.H_kv * attention_key_blocks(d.n_tokens) * 32 * d.D * 2;
-  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots, true, vt_bytes);
+  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots, vt_bytes);
 }
 
 size_t shotkv_prefill_attention_workspace_bytes(const shotkv_config* cfg, int32_t P, int32_t n_tokens,

@@ -12,9 +12,9 @@ from oracle import shotkv_oracle as orc
 
 pytestmark = pytest.mark.gpu
 
-# Products of bf16 values are exact in float32, so a logit is off by the rounding of its sum alone: head_dim
-# additions of 2^-24 each, and its absolute error is the weight's relative error.  2e-5 covers that for the
-# |logit| < 20 drawn here with the exponential's and the log's own few units in the last place.
+# A logit is a sum of head_dim products in float32 (those of bf16 values are exact): at most 2 * head_dim
+# roundings of 2^-24 of its terms, and its absolute error is the weight's relative error.  2e-5 covers that for
+# the |logit| < 20 drawn here with the exponential's and the log's own few units in the last place.
 SCORE_RTOL = 2e-5
 
 LENGTHS = (33, 255, 256, 257, 511, 2049)
@@ -38,7 +38,7 @@ def _offsets(rng, N, n):
 
 
 @pytest.mark.parametrize("G,W", ROWS)
-@pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16)])
+@pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
 def test_tile_edges(kv, D, dtype, G, W):
     Hkv, P = 2, 2
     rng = np.random.default_rng(17 * G + W + D)
