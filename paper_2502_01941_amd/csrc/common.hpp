@@ -219,7 +219,7 @@ inline DecodeWorkspace carve_decode(void* base, int S, int H, int H_kv, int D, i
   return w;
 }
 
-// Tokens per workgroup the matrix-core decode kernel can hold logits for in LDS.
+// Tokens a decode workgroup can hold logits for in LDS at a time.
 #ifndef SHOTKV_DEC_MAX_RANGE
 #define SHOTKV_DEC_MAX_RANGE 1024
 #endif
@@ -230,11 +230,6 @@ constexpr int kDecodeMaxSplits = 1024;  // token ranges per (sequence, KV head) 
 inline int padded_group(int G) { return G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : G <= 8 ? 8 : 0; }
 
 int decode_splits(int S, int H_kv, int total_tokens);
-bool decode_uses_mfma(const DecodeDims& d);
-hipError_t launch_decode_partial_mfma(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
-                                      const void* k_new, const void* v_new, const DecodeWorkspace& w,
-                                      hipStream_t s);
-
 hipError_t launch_decode_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
                                  const void* k_new, const void* v_new, const DecodeWorkspace& w,
                                  hipStream_t s);

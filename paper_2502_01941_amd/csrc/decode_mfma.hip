@@ -1,32 +1,44 @@
-// Split-KV decode attention for bf16, head_dim 128, with the logits on the matrix cores
+// Split-KV decode attention with the logits on the matrix cores
 // (Section 5.1, Eq. 7 and 9: attention of the current query over prefill rows and decode slots).
 //
-// A workgroup owns one token range of one (sequence, KV head) and makes two passes over it:
-//   1. K pass: the logits of four tokens per v_mfma_f32_16x16x32_bf16, with the head dimension cut into
-//      four pieces that sit in different operand rows/columns, so that the A operands are whole
-//      256-byte K rows fetched straight from global memory with coalesced 16-byte loads (see the
-//      kernel).  The scaled logits go to LDS.
-//   between: validity mask (free slots), per-head maximum, weights 2^(z - max) and their sums, all on
-//      the logits in LDS; decode-slot logits are also written out for the retention score (Eq. 7).
-//   2. V pass: 16 lanes stream one V row each (16 bytes per lane) and accumulate weight * V with the
-//      weights read from LDS.  No rescaling is needed because the maximum is already known.
+// A workgroup owns one token range of one (sequence, KV head) and makes two passes over it, in pieces of at
+// most kMaxRange tokens:
+//   1. K pass: the logits of 4 or 8 tokens per matrix step, with the head dimension cut into pieces that
+//      sit in different operand rows/columns, so that the A operands are whole K rows fetched straight
+//      from global memory with coalesced 16-byte loads (RowShape).  The scaled logits go to LDS, their
+//      maximum stays in registers.
+//   between: weights 2^(z - max) by all threads, tokens along the lanes; decode-slot logits are also written
+//      out for the retention score (Eq. 7).  The first V rows are already on their way: they are requested
+//      between the loads of a wave's last K block and its use.
+//   2. V pass: RowShape::kLanes lanes stream one V row each (16 bytes per lane) and accumulate weight * V with
+//      the weights read from LDS, the next batch of rows in flight while one is used.  No rescaling is
+//      needed because the maximum is already known.
+// Bound by the stream of K and V rows: 32 query / 8 KV heads, head_dim 128 bf16, 512 caches of ~5000 rows 1.79 ms
+// = 5.9 TB/s, 16 caches 60 us.  Before the rows of 64-dimensional heads and of fp32 caches took this form they
+// were scored and summed by one-pass vector arithmetic: 32 caches of 2001 + 512 rows, head_dim 64, 57 us then,
+// 36 us now; 8 caches of 2000 + 500 fp32 rows 57 -> 39 us a step.  Requesting the first V rows ahead of the
+// weights is worth 4 us of 74 at 16 caches.
 // Compared with a one-pass online softmax this moves the dot products off the vector ALU, removes the
 // cross-lane reductions per token and the per-token rescale of the output accumulators.
 #include "common.hpp"
+
+#include <type_traits>
 
 namespace shotkv {
 
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
 
 // 16 bytes of a K or V row with the non-temporal hint.  A step reads every live row once; once the caches
 // of a batch outgrow L2 and the memory-side cache, rows that do not settle there stream faster (4-7 %
 // at 16 and more sequences of 5K tokens, no change for one to four sequences).
-__device__ __forceinline__ u32x4 stream_load(const u32x4* p) { return __builtin_nontemporal_load(p); }
+template <typename V>
+__device__ __forceinline__ V stream_load(const char* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+}
 
 // value of the lane N places away inside each row of 16 lanes (rotation, so every lane gets one)
 template <int N>
@@ -36,298 +48,462 @@ __device__ __forceinline__ float row_rotate(float x) {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kD = 128;
-constexpr int kMaxRange = kDecodeMaxRange;  // tokens per workgroup the LDS logit buffer can hold
+constexpr int kMaxRange = kDecodeMaxRange;  // tokens whose logits the LDS buffer holds at a time
 #ifndef SHOTKV_DEC_V_UNROLL
 #define SHOTKV_DEC_V_UNROLL 4
 #endif
 constexpr int kVUnroll = SHOTKV_DEC_V_UNROLL;  // V rows a lane group has in flight
 
-// lowest free slot of a sequence, -1 if none; every thread of the block gets the answer
-__device__ int lowest_free_slot(const int32_t* __restrict__ slot_pos, int n_slots, int* s_red) {
-  int best = INT32_MAX;
-  for (int i = threadIdx.x; i < n_slots; i += blockDim.x)
-    if (slot_pos[i] < 0) { best = i; break; }
-  for (int o = kWave / 2; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o, kWave));
-  if (threadIdx.x % kWave == 0) s_red[threadIdx.x / kWave] = best;
-  __syncthreads();
-  int r = INT32_MAX;
-  for (int w = 0; w < kWaves; ++w) r = min(r, s_red[w]);
-  __syncthreads();
-  return r == INT32_MAX ? -1 : r;
+// How a row lies across the lanes of the K pass.  A matrix step has 16 operand rows and 16 columns and four
+// k-slices of 16 bytes (lane / 16).  A's row holds piece `i % kPieces` of token `i / kPieces`, B's column
+// j = kCols * piece + h the same piece of query head h, so C[kPieces * tau + piece][kCols * piece + h] is that
+// piece's share of the logit and the shares of one logit sit in lanes kCols apart.  Laid out like this the
+// lanes that hold one token read its whole row (256 bytes of it per load) with one 16-byte load each.
+template <int ROW_BYTES> struct RowShape {
+  static constexpr int kPieces = ROW_BYTES == 128 ? 2 : 4;
+  static constexpr int kCols = 16 / kPieces;                        // query heads per matrix step
+  static constexpr int kTokens = 16 / kPieces;                      // tokens per matrix step
+  static constexpr int kLoads = ROW_BYTES * kTokens / (kWave * 16); // 1 KB loads per matrix step
+  static constexpr int kBlock = 8 * 1024 / ROW_BYTES;               // tokens a wave takes at a time (8 loads)
+  static constexpr int kLanes = ROW_BYTES / 16;                     // lanes per row in the V pass
+};
+
+template <typename T> struct Operand;  // 16 bytes of a row as one lane holds them
+template <> struct Operand<bf16_t> { typedef bf16x8 Vec; };
+template <> struct Operand<float> { typedef floatx4 Vec; };
+__device__ __forceinline__ floatx4 multiply_step(bf16x8 a, bf16x8 b, floatx4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 multiply_step(floatx4 a, floatx4 b, floatx4 acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
+  return acc;
 }
 
-template <int G>
-__global__ __launch_bounds__(kThreads) void decode_partial_mfma_kernel(
-    const bf16_t* __restrict__ k_prefill, const bf16_t* __restrict__ v_prefill,
-    const int32_t* __restrict__ prefill_count, bf16_t* __restrict__ k_dec, bf16_t* __restrict__ v_dec,
-    const int32_t* __restrict__ slot_pos, int cap, int n_slots, int H, int H_kv, int n_group,
-    int n_splits, int split_tokens, float scale_log2e, const bf16_t* __restrict__ q_new,
-    const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new, float2* __restrict__ part_ml,
-    float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out) {
-  const int split = blockIdx.x, g = blockIdx.y, s = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+template <typename T> struct Widen;   // the elements of 16 bytes as floats
+template <> struct Widen<bf16_t> {
+  static constexpr int kElems = 8;
+  __device__ static void get(const u32x4& raw, float* f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f[2 * i] = __uint_as_float(raw[i] << 16);
+      f[2 * i + 1] = __uint_as_float(raw[i] & 0xffff0000u);
+    }
+  }
+};
+template <> struct Widen<float> {
+  static constexpr int kElems = 4;
+  __device__ static void get(const u32x4& raw, float* f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = __uint_as_float(raw[i]);
+  }
+};
 
-  __shared__ __attribute__((aligned(16))) float zbuf[kMaxRange][G];  // logits, then weights
-  __shared__ float s_M[G];
-  __shared__ float s_L[G];
-  __shared__ float s_o[kWaves][G][kD];
-  __shared__ int s_red[kWaves];
-  __shared__ int s_sp[kMaxRange];  // slot map of the decode slots inside this workgroup's range
+template <typename T, int D, int G, bool PIECES>
+__global__ __launch_bounds__(kThreads, G == 8 ? 3 : 4) void decode_partial_kernel(
+    const char* __restrict__ k_prefill, const char* __restrict__ v_prefill,
+    const int32_t* __restrict__ prefill_count, char* __restrict__ k_dec, char* __restrict__ v_dec,
+    const int32_t* __restrict__ slot_pos, int cap, int n_slots, int H, int H_kv, int n_group,
+    int n_splits, int split_tokens, float scale_log2e, const char* __restrict__ q_new,
+    const char* __restrict__ k_new, const char* __restrict__ v_new, float2* __restrict__ part_ml,
+    float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out) {
+  constexpr int kRow = D * static_cast<int>(sizeof(T));  // bytes per row
+  typedef RowShape<kRow> S;
+  constexpr int E = Widen<T>::kElems;
+  const int split = blockIdx.x, g = blockIdx.y, s = blockIdx.z;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+  constexpr int kGroups = kThreads / S::kLanes;  // V rows the workgroup takes at a time
+  constexpr int kBatchRows = kGroups * kVUnroll;
+  static_assert(kBatchRows % S::kBlock == 0, "row counts padded to V batches are whole K blocks");
+  // logits, then weights: the live prefill rows of a piece, then its slots, each padded to whole V batches
+  __shared__ __attribute__((aligned(16))) float zbuf[kMaxRange + 2 * kBatchRows][G];
+  __shared__ float s_max[kWaves][G];
+  __shared__ float s_sum[kWaves][G];
+  float (*s_o)[G][D] = reinterpret_cast<float (*)[G][D]>(&zbuf[0][0]);  // the waves' output sums, after the weights
+  static_assert(kWaves * D <= kMaxRange, "output sums fit");
+  __shared__ int s_red[2][kWaves];
+  __shared__ int s_sp[kMaxRange];  // slot map of the decode slots of the piece
 
   // G is the group size rounded up to a power of two; heads past the real n_group are zero queries
   // whose results are never written
   const size_t head0 = static_cast<size_t>(s) * H + static_cast<size_t>(g) * n_group;
-  // Query operands first: these loads and the one of the row count below are in flight together.
-  const int i16 = lane & 15, ksl = lane >> 4;  // A row / B column, and k-slice (8 elements) of the lane
-  const int tau = i16 >> 2, piece = i16 & 3;   // as A row; as B/C column: piece i16 >> 2, head i16 & 3
-  const int elem_off = 32 * piece + 8 * ksl;
-  constexpr int kHeadSets = (G + 3) / 4;
-  bf16x8 bq[kHeadSets];
+  const int i16 = lane & 15, ksl = lane >> 4;          // A row / B column, and k-slice of the lane
+  const int tau = i16 / S::kPieces;                    // as A row: token of the step
+  const int col_piece = i16 / S::kCols, col_head = i16 % S::kCols;  // as B/C column
+  const int a_off = 64 * (i16 % S::kPieces) + 16 * ksl;             // byte offset inside (each 256 bytes of) a row
+  constexpr int kHeadSets = (G + S::kCols - 1) / S::kCols;
+  typedef typename Operand<T>::Vec Vec;
+  Vec bq[kHeadSets][S::kLoads];
 #pragma unroll
-  for (int m = 0; m < kHeadSets; ++m) {
-    u32x4 raw = {0u, 0u, 0u, 0u};
-    const int hq = (i16 & 3) + 4 * m;
-    if (hq < n_group) raw = *reinterpret_cast<const u32x4*>(q_new + (head0 + hq) * kD + 32 * (i16 >> 2) + 8 * ksl);
-    bq[m] = __builtin_bit_cast(bf16x8, raw);
-  }
+  for (int m = 0; m < kHeadSets; ++m)
+#pragma unroll
+    for (int j = 0; j < S::kLoads; ++j) {
+      u32x4 raw = {0u, 0u, 0u, 0u};
+      const int hq = col_head + S::kCols * m;
+      if (hq < n_group)
+        raw = *reinterpret_cast<const u32x4*>(q_new + (head0 + hq) * kRow + 256 * j + 64 * col_piece + 16 * ksl);
+      bq[m][j] = __builtin_bit_cast(Vec, raw);
+    }
+  // Token axis of a sequence: t < cap is row t of the prefill cache (live while t < prefill_count), t >= cap is
+  // decode slot t - cap.  A range is a part of the one followed by a part of the other; every block of rows lies
+  // in one part, so its address is a wave-uniform base plus a small lane offset.
   const int32_t* sp = slot_pos + static_cast<size_t>(s) * n_slots;
-  // Token axis of a sequence: t < cap is row t of the prefill cache (live while t < prefill_count), t >= cap
-  // is decode slot t - cap.  Nothing about the ranges or the addresses depends on prefill_count, so the
-  // first rows are requested while that count is still on its way; it only masks.
   const int pc = min(prefill_count[s], cap);
-  const int t_begin = split * split_tokens;
-  const int t_end = min(t_begin + split_tokens, cap + n_slots);
-  const int T = max(t_end - t_begin, 0);
-  // Only a range that reaches into the decode slots needs the slot map: its part of it goes to LDS
-  // (so that the row fetches below do not wait on a second, dependent load), and the slot that takes
-  // the new token is found in the same round trip.
-  const int d_lo = max(t_begin - cap, 0);  // decode slots [d_lo, d_lo + n_range_slots) lie in the range
-  const int n_range_slots = max(t_end - cap, 0) - d_lo;
-  if (t_end > cap)
-    for (int i = tid; i < n_range_slots; i += kThreads) s_sp[i] = sp[d_lo + i];
-  const int new_slot = (t_end > cap) ? lowest_free_slot(sp, n_slots, s_red) : n_slots;  // has barriers
-  if (t_end == cap + n_slots && g == 0 && tid == 0) new_slot_out[s] = new_slot;
+  const int range_begin = split * split_tokens;
+  const int range_end = min(range_begin + split_tokens, cap + n_slots);
+  const size_t plane = static_cast<size_t>(s) * H_kv + g;
+  const char* kp = k_prefill + plane * cap * kRow;
+  const char* vp = v_prefill + plane * cap * kRow;
+  char* kd = k_dec + plane * n_slots * kRow;
+  char* vd = v_dec + plane * n_slots * kRow;
+  const char* kn = k_new + plane * kRow;
+  const char* vn = v_new + plane * kRow;
 
-  const size_t plane_p = (static_cast<size_t>(s) * H_kv + g) * cap;
-  const size_t plane_d = (static_cast<size_t>(s) * H_kv + g) * n_slots;
-  const size_t new_off = (static_cast<size_t>(s) * H_kv + g) * kD;
-
-  // token t of the sequence: live prefill row, occupied slot, the slot taking the new token, or nothing
-  auto token_valid = [&](int t) {
-    if (t < cap) return t < pc;
-    const int slot = t - cap;
-    return slot < n_slots && (slot == new_slot || s_sp[slot - d_lo] >= 0);
+  // ---- K rows: block [row0, row0 + kBlock) of the `rows` rows that start at `base`.  Rows past the end re-read
+  // the last one, so every address stays inside the plane; their logits are not used. --------------------------
+  constexpr int kStepsPerBlock = 8 / S::kLoads;
+  Vec kraw[8];
+  auto load_block = [&](const char* base, int row0, int rows) __attribute__((always_inline)) {
+    const char* at = base + static_cast<size_t>(row0) * kRow;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t r = min((i / S::kLoads) * S::kTokens + tau, rows - 1 - row0);
+      kraw[i] = stream_load<Vec>(at + (r * kRow + (i % S::kLoads) * 256 + a_off));
+    }
   };
+  // A wave's first block is requested before the count of live rows has arrived (dead rows may hold anything).
+  const int early_rows = min(range_end, cap) - range_begin;
+  if (wave * S::kBlock < early_rows) load_block(kp + static_cast<size_t>(range_begin) * kRow, wave * S::kBlock, early_rows);
 
-  if (new_slot >= 0 && T > 0) {
-    // ---- pass 1: logits ------------------------------------------------------------------------
-    // One v_mfma_f32_16x16x32_bf16 scores four tokens.  Row i = 4*tau + piece of its A operand holds
-    // the 32-element piece `piece` of token `tau`, column j = 4*piece + h of its B operand the same
-    // piece of query head h, so C[4*tau + piece][4*piece + h] is that piece's share of the logit and
-    // the four shares sit in lanes 4 apart.  Laid out like this the 16 lanes that hold one token
-    // read its whole 256-byte row with one 16-byte load each: every load instruction fetches four
-    // complete rows, already in operand order.
-    for (int blk = wave; blk * 32 < T; blk += kWaves) {
-      // a block of dead prefill rows only (count below cap) is skipped: its logits are masked between the
-      // passes whatever zbuf holds.  A wave's first block is fetched regardless, before the count is known.
-      if (blk != wave && t_begin + blk * 32 >= pc && t_begin + blk * 32 + 31 < cap) continue;
-      // so is a block of decode slots none of which holds a token (a pool that is still filling up)
-      if (t_begin + blk * 32 >= cap) {
-        const int tt = blk * 32 + (lane & 31);
-        const bool holds = tt < T && token_valid(t_begin + tt);
-        if (__builtin_amdgcn_ballot_w64(holds) == 0) continue;
+  // Only a range that reaches into the decode slots needs the slot that takes the new token, the lowest free
+  // one, and the slot map of its (first) piece with the last occupied slot of it (a pool that is still filling
+  // up is empty behind that); all come out of one round of loads.
+  int new_slot = n_slots, last_used = -1;
+  if (range_end > cap) {
+    constexpr int kBatch = 8;  // loads in flight per thread
+    const int d_lo = max(range_begin - cap, 0), d_hi = min(range_begin + kMaxRange, range_end) - cap;
+    int best = INT32_MAX;
+#pragma clang loop unroll(disable)
+    for (int i0 = tid; i0 < n_slots && (best == INT32_MAX || i0 < d_hi); i0 += kBatch * kThreads) {
+      int pos[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) pos[j] = sp[min(i0 + j * kThreads, n_slots - 1)];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const int i = min(i0 + j * kThreads, n_slots - 1);
+        if (pos[j] < 0) best = min(best, i);
+        if (i >= d_lo && i < d_hi) {
+          s_sp[i - d_lo] = pos[j];
+          if (pos[j] >= 0) last_used = max(last_used, i);
+        }
       }
-      u32x4 raw[8];
-      const int tt0 = blk * 32 + tau;
-      if (t_begin + blk * 32 + 31 < cap && blk * 32 + 31 < T) {  // the whole block lies in the prefill cache
-        const bf16_t* kr = k_prefill + (plane_p + t_begin + tt0) * kD + elem_off;
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      best = min(best, __shfl_xor(best, o, kWave));
+      last_used = max(last_used, __shfl_xor(last_used, o, kWave));
+    }
+    if (lane == 0) { s_red[0][wave] = best; s_red[1][wave] = last_used; }
+    __syncthreads();
 #pragma unroll
-        for (int gi = 0; gi < 8; ++gi) raw[gi] = stream_load(reinterpret_cast<const u32x4*>(kr + gi * 4 * kD));
-      } else {
+    for (int w = 0; w < kWaves; ++w) {
+      best = min(best, s_red[0][w]);
+      last_used = max(last_used, s_red[1][w]);
+    }
+    new_slot = __builtin_amdgcn_readfirstlane(best == INT32_MAX ? -1 : best);
+    if (new_slot < d_hi) last_used = max(last_used, new_slot);
+    last_used = __builtin_amdgcn_readfirstlane(last_used);
+  }
+  if (range_end == cap + n_slots && g == 0 && tid == 0) new_slot_out[s] = new_slot;
+
+  const int grp = tid / S::kLanes, v_off = 16 * (tid % S::kLanes);
+  float o[G][E], M[G], L[G];  // L: this thread's share of the sum of weights
 #pragma unroll
-        for (int gi = 0; gi < 8; ++gi) {
-          const int tt = tt0 + 4 * gi;
-          const int t = t_begin + tt;
-          // rows past the range and free slots read the new token's key instead (always valid
-          // memory); their logits are masked between the passes
-          const bf16_t* kr = k_new + new_off;
-          bool is_new = false;
-          if (tt < T) {
-            if (t < cap) {
-              kr = k_prefill + (plane_p + t) * kD;
-            } else {
-              const int slot = t - cap;
-              is_new = slot == new_slot;
-              if (!is_new && s_sp[slot - d_lo] >= 0) kr = k_dec + (plane_d + slot) * kD;
+  for (int h = 0; h < G; ++h) {
+    M[h] = -INFINITY;
+    L[h] = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[h][e] = 0.f;
+  }
+
+  // The range is taken in pieces that the logit buffer holds.  Only contexts of over a million tokens have more
+  // than one (PIECES); a loop around the body costs the others registers for what the compiler moves out of it.
+  const int n_pieces = PIECES ? ceil_div(range_end - range_begin, kMaxRange) : range_end > range_begin;
+  if (new_slot >= 0)
+#pragma clang loop unroll(disable)
+    for (int piece = 0; piece < n_pieces; ++piece) {
+      const bool first = !PIECES || piece == 0;
+      const int t_begin = PIECES ? range_begin + piece * kMaxRange : range_begin;
+      const int t_end = PIECES ? min(range_end, t_begin + kMaxRange) : range_end;
+      const int n_p = max(min(t_end, pc) - t_begin, 0);         // live prefill rows of the piece
+      const int d_lo = max(t_begin - cap, 0);                   // its decode slots: [d_lo, d_lo + n_d)
+      const int n_d = max((first ? min(t_end - cap, last_used + 1) : t_end - cap) - d_lo, 0);
+      const int new_row = new_slot >= d_lo && new_slot < d_lo + n_d ? new_slot - d_lo : -1;  // the new token's, if inside
+      if (!first) {
+        __syncthreads();  // the previous piece's weights and slot map are done with
+        for (int i = tid; i < n_d; i += kThreads) s_sp[i] = sp[d_lo + i];
+        __syncthreads();
+      }
+      const char* kp0 = kp + static_cast<size_t>(t_begin) * kRow;
+      const char* vp0 = vp + static_cast<size_t>(t_begin) * kRow;
+      char* kd0 = kd + static_cast<size_t>(d_lo) * kRow;
+      char* vd0 = vd + static_cast<size_t>(d_lo) * kRow;
+      auto slot_used = [&](int i) __attribute__((always_inline)) {
+        return (i == new_row || s_sp[min(i, kMaxRange - 1)] >= 0) && i < n_d;
+      };
+
+      // ---- pass 1: logits --------------------------------------------------------------------------------
+      const int z_d = ceil_div(n_p, kBatchRows) * kBatchRows;  // first entry of the slots in zbuf
+      const int nb_p = ceil_div(n_p, S::kBlock), n_blk = nb_p + ceil_div(n_d, S::kBlock);
+      float mx[kHeadSets];  // largest logit this lane has seen, of head col_head + kCols * m
+#pragma unroll
+      for (int m = 0; m < kHeadSets; ++m) mx[m] = -INFINITY;
+      auto fetch = [&](int blk) __attribute__((always_inline)) {
+        if (blk < nb_p) {
+          load_block(kp0, blk * S::kBlock, n_p);
+          return;
+        }
+        const int row0 = (blk - nb_p) * S::kBlock;
+        load_block(kd0, row0, n_d);
+        if (new_row >= row0 && new_row < row0 + S::kBlock) {  // append: only this workgroup reads the slot this step
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (row0 + (i / S::kLoads) * S::kTokens + tau == new_row) {
+              kraw[i] = stream_load<Vec>(kn + (i % S::kLoads) * 256 + a_off);
+              *reinterpret_cast<Vec*>(kd0 + static_cast<size_t>(new_row) * kRow + (i % S::kLoads) * 256 + a_off) =
+                  kraw[i];
+            }
+        }
+      };
+      // Logits of the block in kraw to zbuf[z0..]; counts(row, z): what the row at z0 + row adds to the maximum.
+      auto multiply_block = [&](int z0, auto counts) __attribute__((always_inline)) {
+#pragma unroll
+        for (int st = 0; st < kStepsPerBlock; ++st) {
+#pragma unroll
+          for (int m = 0; m < kHeadSets; ++m) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < S::kLoads; ++j) acc = multiply_step(kraw[st * S::kLoads + j], bq[m][j], acc);
+            const int hq = col_head + S::kCols * m;
+            // this lane's column holds piece col_piece; rows 4*ksl + v are (token, piece) pairs
+            constexpr int kOwn = 4 / S::kPieces;  // tokens among a lane's four rows
+#pragma unroll
+            for (int i = 0; i < kOwn; ++i) {
+              float z;
+              if constexpr (S::kPieces == 4) {
+                z = col_piece == 0 ? acc[0] : col_piece == 1 ? acc[1] : col_piece == 2 ? acc[2] : acc[3];
+                z += row_rotate<4>(z);
+              } else {
+                z = col_piece ? acc[2 * i + 1] : acc[2 * i];
+              }
+              z += row_rotate<8>(z);  // now every lane of the column set that shares a head has the logit
+              z *= scale_log2e;
+              const int row = st * S::kTokens + kOwn * ksl + i;
+              mx[m] = fmaxf(mx[m], counts(row, z));
+              if (i16 < S::kCols && hq < G) zbuf[z0 + row][hq] = z;
             }
           }
-          raw[gi] = stream_load(reinterpret_cast<const u32x4*>(kr + elem_off));
-          // append: only this workgroup reads the slot this step
-          if (is_new) *reinterpret_cast<u32x4*>(k_dec + (plane_d + new_slot) * kD + elem_off) = raw[gi];
         }
-      }
-#pragma unroll
-      for (int gi = 0; gi < 8; ++gi) {
-#pragma unroll
-        for (int m = 0; m < kHeadSets; ++m) {
-          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw[gi]), bq[m], acc, 0, 0, 0);
-          // lane (column 4*piece + h, row group ksl) holds rows 4*ksl + v: token ksl of the group, piece v
-          const int pb = i16 >> 2;
-          float z = pb == 0 ? acc[0] : pb == 1 ? acc[1] : pb == 2 ? acc[2] : acc[3];
-          z += row_rotate<4>(z);
-          z += row_rotate<8>(z);  // now every lane of the column set {h, h+4, h+8, h+12} has the logit
-          const int hq = i16 + 4 * m;
-          const int ttc = blk * 32 + 4 * gi + ksl;
-          if (i16 < 4 && hq < G && ttc < T) zbuf[ttc][hq] = z * scale_log2e;
+      };
+      auto use_block = [&](int blk) __attribute__((always_inline)) {
+        if (blk < nb_p) {
+          // (a first block that was requested early holds dead rows behind the live ones)
+          const int live = n_p - blk * S::kBlock;
+          multiply_block(blk * S::kBlock, [&](int row, float z) { return row < live ? z : -INFINITY; });
+        } else {
+          const int row0 = (blk - nb_p) * S::kBlock;
+          multiply_block(z_d + row0, [&](int row, float z) { return slot_used(row0 + row) ? z : -INFINITY; });
         }
+      };
+      int blk = wave;
+      // the wave's first block: of the first piece it is there already if it lies among the live rows
+      if (blk < n_blk && !(first && blk < nb_p)) fetch(blk);
+#pragma clang loop unroll(disable)
+      for (; blk + kWaves < n_blk; blk += kWaves) {
+        use_block(blk);
+        fetch(blk + kWaves);
       }
-    }
-    __syncthreads();
 
-    // ---- between the passes: mask, maximum, weights and their sum; one wave per query head, so
-    //      only wave-level reductions and no workgroup barrier in between ----------------------------
-    for (int h = wave; h < n_group; h += kWaves) {
-      float mx = -INFINITY;
-      for (int tt = lane; tt < T; tt += kWave) {
-        float z = zbuf[tt][h];
-        if (!token_valid(t_begin + tt)) { z = -INFINITY; zbuf[tt][h] = z; }
-        mx = fmaxf(mx, z);
-      }
-      mx = wave_max(mx);
-      float sum = 0.f;
-      for (int tt = lane; tt < T; tt += kWave) {  // every lane re-reads what it wrote itself
-        const float z = zbuf[tt][h];
-        const int t = t_begin + tt;
-        if (t >= cap && z != -INFINITY) z_dec[(head0 + h) * n_slots + (t - cap)] = z;
-        const float p = (z == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(z - mx);
-        zbuf[tt][h] = p;
-        sum += p;
-      }
-      sum = wave_sum(sum);
-      if (lane == 0) { s_M[h] = mx; s_L[h] = sum; }
-    }
-    __syncthreads();
-  } else {
-    if (tid < G) { s_M[tid] = -INFINITY; s_L[tid] = 0.f; }
-    __syncthreads();
-  }
+      // V rows b * kBatchRows + u * kGroups + grp of the piece's live prefill rows (b < nv_p) or slots; rows past
+      // the end re-read the last one and have no weight
+      const int nv_p = ceil_div(n_p, kBatchRows), n_v = nv_p + ceil_div(n_d, kBatchRows);
+      u32x4 vraw[2][kVUnroll];
+      auto load_rows = [&](int b, u32x4 (&raw)[kVUnroll]) __attribute__((always_inline)) {
+        const bool in_p = b < nv_p;
+        const int row0 = (in_p ? b : b - nv_p) * kBatchRows, last_row = (in_p ? n_p : n_d) - 1 - row0;
+        const char* at = (in_p ? vp0 : vd0) + static_cast<size_t>(row0) * kRow;
+#pragma unroll
+        for (int u = 0; u < kVUnroll; ++u) {
+          const uint32_t r = min(u * kGroups + grp, last_row);
+          raw[u] = stream_load<u32x4>(at + (r * kRow + v_off));
+        }
+      };
+      if (n_v > 0) load_rows(0, vraw[0]);  // in flight while the last logits and the weights are computed
+      if (blk < n_blk) use_block(blk);
 
-  // ---- pass 2: weighted values -------------------------------------------------------------------
-  constexpr int kGroups = kThreads / 16;  // 16 lanes per V row
-  const int grp = tid >> 4, lir = tid & 15;
-  float o[G][8];
+      // ---- between the passes: maximum, weights and their sum -----------------------------------------
 #pragma unroll
-  for (int hh = 0; hh < G; ++hh)
+      for (int m = 0; m < kHeadSets; ++m) {
+        // lanes 16, 32 and 48 away hold other tokens of the same head (and so do, redundantly, the other pieces)
+        const float w = max_across_halves(mx[m]);
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w), __float_as_uint(w), false, false);
+        const float wm = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        const int hq = col_head + S::kCols * m;
+        if (lane < S::kCols && hq < G) s_max[wave][hq] = wm;
+      }
+      __syncthreads();
+      float ref[G];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[hh][e] = 0.f;
-  if (new_slot >= 0) {
-    // kVUnroll rows per lane group are requested before any of them is used.  A token without weight
-    // (masked, or underflowed to exactly zero) reads the new token's value row instead - always valid
-    // memory - and contributes zero times that.
-    for (int tt0 = grp; tt0 < T; tt0 += kGroups * kVUnroll) {
-      float p[kVUnroll][G];
-      u32x4 raw[kVUnroll];
-      bool any[kVUnroll], is_new[kVUnroll];
-      bool work = false;
+      for (int h = 0; h < G; ++h) {
+        float m_new = M[h];
 #pragma unroll
-      for (int u = 0; u < kVUnroll; ++u) {
-        const int tt = tt0 + u * kGroups;
-        const bool inside = tt < T;
-        const int ttc = inside ? tt : 0;
-        any[u] = false;
+        for (int w = 0; w < kWaves; ++w) m_new = fmaxf(m_new, s_max[w][h]);
+        if (!first) {  // a later piece: what the earlier ones gave moves to the new maximum
+          const float alpha = M[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M[h] - m_new);
+          L[h] *= alpha;
 #pragma unroll
-        for (int hh = 0; hh < G; ++hh) {
-          p[u][hh] = (inside && hh < n_group) ? zbuf[ttc][hh] : 0.f;  // padding heads carry no weight
-          any[u] = any[u] || p[u][hh] != 0.f;
+          for (int e = 0; e < E; ++e) o[h][e] *= alpha;
         }
-        // the slot taking the new token: its value row is appended whatever weight the token got
-        // (a weight that underflows to zero must not leave a stale row behind for later steps)
-        is_new[u] = inside && t_begin + ttc >= cap && (t_begin + ttc - cap) == new_slot;
-        work = work || any[u] || is_new[u];
+        M[h] = m_new;
+        ref[h] = m_new == -INFINITY ? 0.f : m_new;
       }
-      // dead prefill rows and empty decode slots: nothing to fetch, nothing to add
-      if (__builtin_amdgcn_ballot_w64(work) == 0) continue;
+#pragma clang loop unroll(disable)
+      for (int tt = tid; tt < n_v * kBatchRows; tt += kThreads) {
+        const int slot = tt - z_d;
+        const bool valid = slot < 0 ? tt < n_p : slot_used(slot);
+        float z[G];
 #pragma unroll
-      for (int u = 0; u < kVUnroll; ++u) {
-        const int tt = tt0 + u * kGroups;
-        const int t = t_begin + (tt < T ? tt : 0);
-        const bf16_t* vr = v_new + new_off;
-        if (any[u] && !is_new[u])
-          vr = (t < cap) ? v_prefill + (plane_p + t) * kD : v_dec + (plane_d + (t - cap)) * kD;
-        raw[u] = stream_load(reinterpret_cast<const u32x4*>(vr + lir * 8));
-        if (is_new[u]) *reinterpret_cast<u32x4*>(v_dec + (plane_d + new_slot) * kD + lir * 8) = raw[u];
-      }
+        for (int h = 0; h < G; ++h) z[h] = zbuf[tt][h];
+        if (slot >= 0 && valid) {
 #pragma unroll
-      for (int u = 0; u < kVUnroll; ++u) {
-        float vf[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          vf[2 * i] = __uint_as_float(raw[u][i] << 16);
-          vf[2 * i + 1] = __uint_as_float(raw[u][i] & 0xffff0000u);
+          for (int h = 0; h < G; ++h)
+            if (h < n_group) z_dec[(head0 + h) * n_slots + (d_lo + slot)] = z[h];
         }
 #pragma unroll
-        for (int hh = 0; hh < G; ++hh)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[hh][e] = fmaf(p[u][hh], vf[e], o[hh][e]);
+        for (int h = 0; h < G; ++h) {
+          const float p = valid ? __builtin_amdgcn_exp2f(z[h] - ref[h]) : 0.f;
+          zbuf[tt][h] = p;
+          L[h] += p;
+        }
       }
+      __syncthreads();
+
+      // ---- pass 2: weighted values -----------------------------------------------------------------------
+      auto use_rows = [&](int b, u32x4 (&raw)[kVUnroll]) __attribute__((always_inline)) {
+        if (b >= nv_p) {
+#pragma unroll
+          for (int u = 0; u < kVUnroll; ++u) {
+            const int row = (b - nv_p) * kBatchRows + u * kGroups + grp;
+            // a free slot's stale values must not meet its weight of zero; the slot taking the new token: its value
+            // row is appended whatever weight the token got
+            if (!slot_used(row)) raw[u] = u32x4{0u, 0u, 0u, 0u};
+            if (row == new_row) {
+              raw[u] = stream_load<u32x4>(vn + v_off);
+              *reinterpret_cast<u32x4*>(vd0 + static_cast<size_t>(row) * kRow + v_off) = raw[u];
+            }
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kVUnroll; ++u) {
+          float vf[E];
+          Widen<T>::get(raw[u], vf);
+#pragma unroll
+          for (int h = 0; h < G; ++h) {
+            const float p = zbuf[b * kBatchRows + u * kGroups + grp][h];
+#pragma unroll
+            for (int e = 0; e < E; ++e) o[h][e] = fmaf(p, vf[e], o[h][e]);
+          }
+        }
+      };
+#pragma clang loop unroll(disable)
+      for (int b = 0; b < n_v; b += 2) {
+        if (b + 1 < n_v) load_rows(b + 1, vraw[1]);
+        use_rows(b, vraw[0]);
+        if (b + 1 >= n_v) break;
+        if (b + 2 < n_v) load_rows(b + 2, vraw[0]);
+        use_rows(b + 1, vraw[1]);
+      }
+      if (!PIECES) break;
     }
+
+  // sum over the row groups of a wave, then over the waves
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      if constexpr (S::kLanes == 8) o[h][e] += row_rotate<8>(o[h][e]);
+      if constexpr (S::kLanes <= 16) o[h][e] = sum_across_row_pairs(o[h][e]);
+      o[h][e] = sum_across_halves(o[h][e]);
+    }
+    const float l = wave_sum(L[h]);
+    if (lane == 0) s_sum[wave][h] = l;
   }
-  // sum over the four row groups of a wave, then over the waves
+  __syncthreads();  // every wave is done with the weights
+  if (lane < S::kLanes) {
 #pragma unroll
-  for (int hh = 0; hh < G; ++hh)
+    for (int h = 0; h < G; ++h)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      o[hh][e] = sum_across_halves(sum_across_row_pairs(o[hh][e]));
-    }
-  if (lane < 16) {
-#pragma unroll
-    for (int hh = 0; hh < G; ++hh)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s_o[wave][hh][lir * 8 + e] = o[hh][e];
+      for (int e = 0; e < E; ++e) s_o[wave][h][lane * E + e] = o[h][e];
   }
   __syncthreads();
-  for (int idx = tid; idx < G * kD; idx += kThreads) {
-    const int hh = idx / kD, dd = idx % kD;
-    if (hh >= n_group) continue;
-    float acc = 0.f;
+  for (int idx = tid; idx < G * D; idx += kThreads) {
+    const int h = idx / D, dd = idx % D;
+    if (h >= n_group) continue;
+    float acc = 0.f, l = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) acc += s_o[w][hh][dd];
-    const size_t r = (head0 + hh) * n_splits + split;
-    part_o[r * kD + dd] = acc;
-    if (dd == 0) part_ml[r] = make_float2(s_M[hh], s_L[hh]);
+    for (int w = 0; w < kWaves; ++w) {
+      acc += s_o[w][h][dd];
+      l += s_sum[w][h];
+    }
+    const size_t r = (head0 + h) * n_splits + split;
+    part_o[r * D + dd] = acc;
+    float m = M[0];
+#pragma unroll
+    for (int i = 1; i < G; ++i) m = i == h ? M[i] : m;
+    if (dd == 0) part_ml[r] = make_float2(m, l);
   }
 }
 
 }  // namespace
 
-bool decode_uses_mfma(const DecodeDims& d) {
-  return d.dtype == SHOTKV_BF16 && d.D == kD && d.split_tokens <= kMaxRange;
-}
-
-hipError_t launch_decode_partial_mfma(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
-                                      const void* k_new, const void* v_new, const DecodeWorkspace& w,
-                                      hipStream_t s) {
+template <typename T, int D>
+static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
+                                 const void* k_new, const void* v_new, const DecodeWorkspace& w, hipStream_t s) {
   const dim3 grid(d.n_splits, d.H_kv, d.S), block(kThreads);
   const float c = d.sm_scale * kLog2e;
   KernelTimer timer(d.timing, kKernelDecodePartial, s);
 #define SHOTKV_LAUNCH_DEC(GG)                                                                           \
-  hipLaunchKernelGGL(decode_partial_mfma_kernel<GG>, grid, block, 0, s,                                 \
-                     static_cast<const bf16_t*>(st.k_prefill), static_cast<const bf16_t*>(st.v_prefill), \
-                     st.prefill_count, static_cast<bf16_t*>(st.k_dec), static_cast<bf16_t*>(st.v_dec),   \
-                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, d.n_splits, d.split_tokens, c,     \
-                     static_cast<const bf16_t*>(q_new), static_cast<const bf16_t*>(k_new),               \
-                     static_cast<const bf16_t*>(v_new), w.part_ml, w.part_o, w.z_dec, w.new_slot)
-  switch (padded_group(d.G)) {
-    case 1: SHOTKV_LAUNCH_DEC(1); break;
-    case 2: SHOTKV_LAUNCH_DEC(2); break;
-    case 4: SHOTKV_LAUNCH_DEC(4); break;
-    case 8: SHOTKV_LAUNCH_DEC(8); break;
+  auto* kernel = d.split_tokens > kMaxRange ? decode_partial_kernel<T, D, GG, true>                     \
+                                            : decode_partial_kernel<T, D, GG, false>;                   \
+  hipLaunchKernelGGL(kernel, grid, block, 0, s,                                                         \
+                     static_cast<const char*>(st.k_prefill), static_cast<const char*>(st.v_prefill),    \
+                     st.prefill_count, static_cast<char*>(st.k_dec), static_cast<char*>(st.v_dec),      \
+                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, d.n_splits, d.split_tokens, c,    \
+                     static_cast<const char*>(q_new), static_cast<const char*>(k_new),                  \
+                     static_cast<const char*>(v_new), w.part_ml, w.part_o, w.z_dec, w.new_slot)
+  switch (padded_group(d.G)) {  // the kernel is instantiated for power-of-two groups and skips the padding
+    case 1: { SHOTKV_LAUNCH_DEC(1); break; }
+    case 2: { SHOTKV_LAUNCH_DEC(2); break; }
+    case 4: { SHOTKV_LAUNCH_DEC(4); break; }
+    case 8: { SHOTKV_LAUNCH_DEC(8); break; }
     default: return hipErrorInvalidValue;
   }
 #undef SHOTKV_LAUNCH_DEC
   return hipGetLastError();
+}
+
+hipError_t launch_decode_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
+                                 const void* k_new, const void* v_new, const DecodeWorkspace& w,
+                                 hipStream_t s) {
+  if (d.dtype == SHOTKV_BF16) {
+    if (d.D == 128) return launch_partial<bf16_t, 128>(d, st, q_new, k_new, v_new, w, s);
+    if (d.D == 64) return launch_partial<bf16_t, 64>(d, st, q_new, k_new, v_new, w, s);
+  } else {
+    if (d.D == 128) return launch_partial<float, 128>(d, st, q_new, k_new, v_new, w, s);
+    if (d.D == 64) return launch_partial<float, 64>(d, st, q_new, k_new, v_new, w, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace shotkv

@@ -1,0 +1,93 @@
+"""GPU parity of the decode step where its blocks end: every row size (dtype, head dimension), group size and cache
+length around the blocks of rows a wave takes, with dead prefill rows and free slots holding values that would
+show (huge, infinite, NaN), pools with holes, and a context long enough for a range to be taken in pieces."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import to_np
+from oracle import shotkv_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+# float32 logits, weights and sums over up to a few hundred rows against float64: a logit is off by at most
+# 2 * head_dim roundings of 2^-24 of its terms (|logit| < 30 here), which is the weight's relative error
+RTOL = 2e-5
+
+
+@pytest.fixture(scope="module")
+def kv():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_01941_amd import shotkv
+    shotkv.load_library()
+    return shotkv
+
+
+def _state(kv, rng, S, H, Hkv, D, dtype, cap, counts, n_slots, used, budget, scale):
+    """Random caches; rows past a sequence's count and slots that are not in `used` hold poison."""
+    def normal(*shape):
+        return torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)).to(dtype).cuda()
+    kp, vp = normal(S, Hkv, cap, D), normal(S, Hkv, cap, D)
+    kd, vd = normal(S, Hkv, n_slots, D), normal(S, Hkv, n_slots, D)
+    slot_pos = torch.full((S, n_slots), -1, dtype=torch.int32, device="cuda")
+    poison_k, poison_v = [3e30, float("nan"), float("-inf")], [float("nan"), float("inf"), -3e30]
+    for s in range(S):
+        kp[s, :, counts[s]:] = poison_k[s % 3]
+        vp[s, :, counts[s]:] = poison_v[s % 3]
+        free = np.setdiff1d(np.arange(n_slots), used[s])
+        kd[s, :, free], vd[s, :, free] = poison_k[(s + 1) % 3], poison_v[(s + 1) % 3]
+        slot_pos[s, used[s]] = torch.arange(len(used[s]), dtype=torch.int32, device="cuda")
+    count = torch.tensor(counts, dtype=torch.int32, device="cuda")
+    return kv.DecodeState(kp, vp, count, kd, vd, slot_pos, budget, H, scale)
+
+
+def _check_steps(kv, rng, state, budget, n_steps, scale):
+    S, H, Hkv, D, dtype = state.S, state.H, state.H_kv, state.D, state.dtype
+    host = []
+    for s in range(S):
+        c = int(state.prefill_count[s].item())
+        host.append([to_np(state.k_prefill[s, :, :c]), to_np(state.v_prefill[s, :, :c]), c, to_np(state.k_dec[s]).copy(),
+                     to_np(state.v_dec[s]).copy(), state.slot_pos[s].cpu().numpy().copy()])
+    for step in range(1000, 1000 + n_steps):
+        new = [torch.from_numpy(rng.standard_normal((S, h, D), dtype=np.float32)).to(dtype).cuda() for h in (H, Hkv, Hkv)]
+        kv.decode_step(state, step, *new)
+        torch.cuda.synchronize()
+        for s in range(S):
+            kp, vp, c, kd, vd, sp = host[s]
+            with np.errstate(invalid="ignore", over="ignore"):
+                r = orc.decode_step(kp, vp, c, kd, vd, sp, budget, step, *[to_np(t[s]) for t in new], scale)
+            assert int(state.status[s]) == r["status"]
+            got = state.out[s].cpu().numpy()
+            assert np.all(np.abs(got - r["out"]) <= RTOL * np.abs(r["out"]).max(axis=1, keepdims=True)), (step, s)
+            np.testing.assert_allclose(state.token_scores[s].cpu().numpy(), r["token_scores"], rtol=RTOL, atol=1e-30)
+            assert r["margin"] > 1e-6 and int(state.evicted_pos[s]) == r["evicted_pos"]
+            np.testing.assert_array_equal(state.slot_pos[s].cpu().numpy(), sp)
+            np.testing.assert_array_equal(to_np(state.k_dec[s]), kd)
+            np.testing.assert_array_equal(to_np(state.v_dec[s]), vd)
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 8])
+@pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
+def test_row_counts_around_the_blocks(kv, D, dtype, G):
+    rng = np.random.default_rng(100 * G + D + (dtype == torch.float32))
+    S, Hkv = 3, 2
+    for cap, n_slots in [(0, 5), (1, 1), (16, 17), (17, 33), (32, 130), (33, 9), (64, 64), (65, 257), (127, 128), (129, 40),
+                         (300, 300)]:
+        counts = [cap, int(rng.integers(0, cap + 1)), max(cap - 1, 0)]
+        used = [np.arange(n_slots - 1),                                       # full but for the last slot
+                np.sort(rng.choice(n_slots, size=n_slots // 2, replace=False)),  # holes
+                np.arange(min(3, n_slots - 1))]                               # still filling up
+        budget = max(1, n_slots - 1)
+        scale = 1.0 / np.sqrt(D)
+        state = _state(kv, rng, S, Hkv * G, Hkv, D, dtype, cap, counts, n_slots, used, budget, scale)
+        _check_steps(kv, rng, state, budget, 2 if n_slots > 1 else 1, scale)
+
+
+@pytest.mark.parametrize("D,dtype,cap", [(64, torch.bfloat16, 1_049_000), (128, torch.float32, 1_100_003)])
+def test_ranges_longer_than_the_logit_buffer(kv, D, dtype, cap):
+    """More than 2^20 tokens: a range is taken in pieces of 1024 rows, the pool's slots in the last one."""
+    rng = np.random.default_rng(cap)
+    n_slots, scale = 700, 1.0 / np.sqrt(D)
+    state = _state(kv, rng, 1, 4, 1, D, dtype, cap, [cap - 5], n_slots, [np.arange(n_slots - 1)], n_slots - 1, scale)
+    _check_steps(kv, rng, state, n_slots - 1, 2, scale)
