@@ -34,7 +34,7 @@ SCORE_KERNEL_SOURCE = os.path.join(ROOT, "paper_2502_01941_amd", "csrc", "prefil
 MEASURED_TRAFFIC = {"model32k": {"sha256": "864e57a17e23b5707280de8a5e16578af9d20837ac6324b9182bbe9136777c50",
                                  "bytes": 8.96e9}}
 
-PREFILL_KINDS = ("plan", "score", "row_stats", "chunk_mass", "reduce_select", "compact")
+PREFILL_KINDS = ("score", "chunk_mass", "reduce_select", "compact")
 
 
 def _measured_traffic(workload):
@@ -327,7 +327,6 @@ def main():
         del qa, attn, q2, k2, v2, out2
         torch.cuda.empty_cache()
         result["other_workloads"] = others
-        result["generic_paths"] = "fp32 / head_dim 64 inputs take untuned vector-ALU kernels (tests only; not measured here)"
 
     # What a plain streaming kernel reaches on this machine: torch's elementwise int32 x + 1 over 1 GiB (reads
     # 1 GiB, writes 1 GiB).  Context for the roofline fractions, and with --calibrate-copy the kernel of

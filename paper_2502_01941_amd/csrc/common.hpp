@@ -11,10 +11,6 @@ namespace shotkv {
 constexpr int kWave = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Keys per scoring chunk.  A chunk never straddles a shot boundary, so a chunk's softmax partial can
-// be credited to exactly one shot (or to the always-kept region).
-constexpr int kChunkKeys = 256;
-
 typedef uint16_t bf16_t;  // raw bf16 bits
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t x) {
@@ -54,11 +50,13 @@ __device__ __forceinline__ float sum_across_row_pairs(float x) {
 
 __host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Upper bound on the number of chunks one problem can be cut into: every segment (n_shots shots plus
-// the prefix and tail regions) adds at most one partially filled chunk.
-__host__ __device__ __forceinline__ int max_chunks(int n_tokens, int n_shots, int chunk_keys) {
-  return ceil_div(n_tokens, chunk_keys) + n_shots + 2;
-}
+// Segments and chunks.  A problem's key axis is cut into segments - 0 the tokens before the first shot, s = 1..n
+// shot s - 1, n + 1 the tokens after the last shot - and into slices of group_keys keys.  A chunk is the part of
+// one segment that lies in one slice, so a chunk's softmax statistic belongs to one shot (or to the always-kept
+// region) and to one score workgroup.  Its number is slice + segment: along the key axis every cut raises one of
+// the two, so the numbers grow, no table of chunks is needed, and the chunks of one segment are consecutive
+// (from first key / group_keys + s to last key / group_keys + s).  Numbers that no chunk has hold garbage.
+__host__ __device__ __forceinline__ int max_chunks(int n_groups, int n_shots) { return n_groups + n_shots + 1; }
 
 // ---- optional per-kernel timing (host) -----------------------------------------------------------
 
@@ -89,41 +87,36 @@ class KernelTimer {
 // ---- workspace carving (host) -------------------------------------------------------------------
 
 struct PrefillWorkspace {
-  // chunk table, one row per problem
-  int32_t* n_chunks;      // [P]
-  int32_t* chunk_start;   // [P][maxC] first key of the chunk
-  int32_t* chunk_len;     // [P][maxC] keys in the chunk (<= chunk_keys)
-  int32_t* seg_first;     // [P][n_shots+3] first chunk of segment s; segment 0 = prefix, 1..n = shots,
-                          //                n+1 = tail, entry n+2 = n_chunks
   // softmax partial per (problem, chunk, kv head, row): log2 of the chunk's sum of exponentials
   // (-inf for a row that sees none of the chunk's keys)
-  float*   partial;       // [P][maxC][H_kv][R]
-  // a score workgroup ("group") takes the chunks that start inside one slice of group_keys keys; group g of
-  // a problem owns chunks [group_first[g], group_first[g + 1])
-  int32_t* group_first;   // [P][n_groups + 1]
-  // the same statistic over all chunks of a group, which is what the row denominators are built from
+  float*   partial;       // [P][H_kv][maxC][R]
+  // the same statistic over all chunks of a slice, which is what the row denominators are built from; the fused
+  // attention kernel writes the denominator itself, as the statistic of a single slice
   float*   group_stat;    // [P][H_kv][n_groups][R]
-  float*   row_stat;      // [P][H_kv][R]  log2 of the row's sum of exponentials over all chunks
-  float*   chunk_mass;    // [P][maxC]
+  float*   chunk_mass;    // [P][maxC][H_kv]
   float*   scores;        // [P][n_shots]
   void*    vt;            // fused attention path only: V packed into 32-key blocks [P][H_kv][blocks][D][32], fp16
   uint32_t* v_absmax;     // fused attention path only: [P][H_kv] largest finite |v| of the plane, as bf16 bits
+  uint32_t* v_share_max;  // fused attention path only: [P][H_kv][kVShares] the same of every share of the plane
   int32_t  max_c;
-  int32_t  group_keys;    // keys per slice of the key axis
+  int32_t  group_keys;    // keys per slice of the key axis, a power of two
   int32_t  n_groups;      // ceil(n_tokens / group_keys)
   size_t   bytes;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+constexpr int kVShares = 128;        // shares of a V plane whose maxima are taken separately (fused attention path)
+constexpr int kOneSlice = 1 << 30;   // group_keys where the whole key axis is one slice
+
 int score_group_keys(int P, int H_kv, int n_tokens, int n_shots);  // keys per workgroup of the score kernel
 
 inline PrefillWorkspace carve_prefill(void* base, int P, int H_kv, int R, int n_tokens, int n_shots,
-                                      size_t vt_bytes = 0) {
+                                      int group_keys, size_t vt_bytes = 0) {
   PrefillWorkspace w{};
-  w.max_c = max_chunks(n_tokens, n_shots, kChunkKeys);
-  w.group_keys = score_group_keys(P, H_kv, n_tokens, n_shots);
-  w.n_groups = ceil_div(n_tokens, w.group_keys);
+  w.group_keys = group_keys;
+  w.n_groups = (n_tokens - 1) / group_keys + 1;
+  w.max_c = max_chunks(w.n_groups, n_shots);
   size_t off = 0;
   char* b = static_cast<char*>(base);
   auto take = [&](size_t bytes) {
@@ -132,18 +125,13 @@ inline PrefillWorkspace carve_prefill(void* base, int P, int H_kv, int R, int n_
     return p;
   };
   const size_t P_ = P, C = w.max_c, S = n_shots;
-  w.n_chunks = reinterpret_cast<int32_t*>(take(P_ * 4));
-  w.chunk_start = reinterpret_cast<int32_t*>(take(P_ * C * 4));
-  w.chunk_len = reinterpret_cast<int32_t*>(take(P_ * C * 4));
-  w.seg_first = reinterpret_cast<int32_t*>(take(P_ * (S + 3) * 4));
-  w.group_first = reinterpret_cast<int32_t*>(take(P_ * (w.n_groups + 1) * 4));
   w.partial = reinterpret_cast<float*>(take(P_ * H_kv * C * R * 4));
   w.group_stat = reinterpret_cast<float*>(take(P_ * H_kv * w.n_groups * R * 4));
-  w.row_stat = reinterpret_cast<float*>(take(P_ * H_kv * R * 4));
-  w.chunk_mass = reinterpret_cast<float*>(take(P_ * C * 4));
+  w.chunk_mass = reinterpret_cast<float*>(take(P_ * C * H_kv * 4));
   w.scores = reinterpret_cast<float*>(take(P_ * S * 4 + 4));
   w.vt = vt_bytes ? take(vt_bytes) : nullptr;
   w.v_absmax = vt_bytes ? reinterpret_cast<uint32_t*>(take(P_ * H_kv * 4)) : nullptr;
+  w.v_share_max = vt_bytes ? reinterpret_cast<uint32_t*>(take(P_ * H_kv * kVShares * 4)) : nullptr;
   w.bytes = off;
   return w;
 }
@@ -161,12 +149,11 @@ struct PrefillDims {
   void* const* timing;  // the caller's timing events, or null
 };
 
-hipError_t launch_plan_chunks(const PrefillDims& d, const int32_t* shot_offsets, int32_t* status,
-                              const PrefillWorkspace& w, hipStream_t s);
 hipError_t launch_score_partials(const PrefillDims& d, const void* q_obs, const void* k,
-                                 const PrefillWorkspace& w, hipStream_t s);
-hipError_t launch_row_stats(const PrefillDims& d, const PrefillWorkspace& w, hipStream_t s);
-hipError_t launch_chunk_mass(const PrefillDims& d, const PrefillWorkspace& w, hipStream_t s);
+                                 const int32_t* shot_offsets, const PrefillWorkspace& w, hipStream_t s);
+// Row denominators from the slices' statistics and, with them, every chunk's attention mass.  n_valid: rows of
+// the R-row arrays that are written (the rest carries no weight).
+hipError_t launch_chunk_mass(const PrefillDims& d, int n_valid, const PrefillWorkspace& w, hipStream_t s);
 // Shot scores from the chunk masses (with_mass), the selection and copy plan (with_select), or both in
 // one launch.  with_mass writes shot_scores; otherwise shot_scores is read.
 hipError_t launch_reduce_select(const PrefillDims& d, bool with_mass, bool with_select, float* shot_scores,
@@ -184,7 +171,7 @@ bool attention_supported(const PrefillDims& d);
 int attention_key_blocks(int n_tokens);
 hipError_t launch_pack_vt(const PrefillDims& d, const void* v, const PrefillWorkspace& w, hipStream_t s);
 hipError_t launch_attention_scores(const PrefillDims& d, const void* q, const void* k, const void* vt,
-                                   float* attn_out, const PrefillWorkspace& w, hipStream_t s);
+                                   const int32_t* shot_offsets, float* attn_out, const PrefillWorkspace& w, hipStream_t s);
 
 struct DecodeDims {
   int S, H, H_kv, G, D, dtype, cap, n_slots, budget, step, n_splits, split_tokens;

@@ -62,10 +62,10 @@ constexpr int kThreadsQ = kWavesQ * kWave;
 constexpr int kLoadsPerWave = 4;                      // 2 K groups + 2 V^T slabs per wave per block
 
 // ---- V packing -----------------------------------------------------------------------------------
-// Largest finite |v| of every KV-head plane, as bf16 bits (their order is the order of the magnitudes),
-// collected with atomic maxima into v_absmax, which the planning kernel has set to zero.
+// Largest finite |v| of every share of every KV-head plane, as bf16 bits (their order is the order of the
+// magnitudes); the packing kernel takes the maximum over a plane's shares.
 __global__ __launch_bounds__(256) void v_absmax_kernel(const bf16_t* __restrict__ v, int n_tokens,
-                                                       uint32_t* __restrict__ v_absmax) {
+                                                       uint32_t* __restrict__ v_share_max) {
   const size_t plane = blockIdx.y;
   const size_t n16 = static_cast<size_t>(n_tokens) * kD / 8;  // 16-byte pieces of the plane
   const size_t per = (n16 + gridDim.x - 1) / gridDim.x;       // a contiguous share per workgroup
@@ -86,7 +86,6 @@ __global__ __launch_bounds__(256) void v_absmax_kernel(const bf16_t* __restrict_
     fold(r0); fold(r1); fold(r2); fold(r3);
   }
   for (; i < hi; i += 256) fold(src[i]);
-  // one atomic per workgroup: a few dozen per plane, not thousands on one address
   __shared__ uint32_t wave_best[256 / kWave];
   best = wave_max(best);
   if (threadIdx.x % kWave == 0) wave_best[threadIdx.x / kWave] = best;
@@ -94,7 +93,7 @@ __global__ __launch_bounds__(256) void v_absmax_kernel(const bf16_t* __restrict_
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int w = 1; w < 256 / kWave; ++w) best = max(best, wave_best[w]);
-    if (best != 0u) atomicMax(v_absmax + plane, best);
+    v_share_max[plane * kVShares + blockIdx.x] = best;
   }
 }
 
@@ -110,12 +109,17 @@ __device__ __forceinline__ float plane_scale(uint32_t absmax_bits, bool inverse)
 // c = 2*s + half holds, in order, the eight keys whose weights a lane of half `half` feeds to matrix step s.
 // Keys past n_tokens are zero.
 __global__ __launch_bounds__(256) void pack_vt_kernel(const bf16_t* __restrict__ v, int n_tokens, int n_blocks,
-                                                      const uint32_t* __restrict__ v_absmax,
+                                                      const uint32_t* __restrict__ v_share_max, int n_shares,
+                                                      uint32_t* __restrict__ v_absmax,
                                                       uint16_t* __restrict__ vt) {
   const int blk = blockIdx.x;
   const size_t plane = blockIdx.y;  // p * H_kv + g
+  uint32_t absmax = 0u;
+  for (int i = threadIdx.x % kWave; i < n_shares; i += kWave) absmax = max(absmax, v_share_max[plane * kVShares + i]);
+  absmax = wave_max(absmax);
+  if (blk == 0 && threadIdx.x == 0) v_absmax[plane] = absmax;  // for the attention kernel
   __shared__ uint16_t tile[kBlockKeys][kD + 2];
-  const float scale = plane_scale(v_absmax[plane], false);
+  const float scale = plane_scale(absmax, false);
   const bf16_t* src = v + plane * n_tokens * kD;
   for (int i = threadIdx.x; i < kBlockKeys * kD / 8; i += 256) {
     const int key = i / (kD / 8), d8 = i % (kD / 8);
@@ -196,9 +200,8 @@ __device__ __forceinline__ f16x8 to_f16x8(const float* x) {
 __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const uint16_t* __restrict__ vt,
     const uint32_t* __restrict__ v_absmax, int n_tokens, int n_blocks_total, int H, int H_kv, int W, float c, float* __restrict__ o_out,
-    const int32_t* __restrict__ n_chunks, const int32_t* __restrict__ chunk_start,
-    const int32_t* __restrict__ chunk_len, int max_c, int R, float* __restrict__ partial,
-    float* __restrict__ row_stat) {
+    const int32_t* __restrict__ shot_offsets, int share, int n_shots, int max_c, int R,
+    float* __restrict__ partial, float* __restrict__ row_stat) {
   __shared__ __attribute__((aligned(64))) char lds[kRing][kStageBytes];
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -245,23 +248,22 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
 #pragma unroll
     for (int v = 0; v < 16; ++v) ot[t][v] = 0.f;
 
-  // Eq. 3 bookkeeping (emitting waves only): the chunk whose sum is being collected
-  const int nc = wave_emits ? n_chunks[p] : 0;
-  const int32_t* cs = chunk_start + static_cast<size_t>(p) * max_c;
-  const int32_t* cl = chunk_len + static_cast<size_t>(p) * max_c;
-  int cur_c = 0, cur_s = 0, cur_e = 0;
-  if (nc > 0) { cur_s = cs[0]; cur_e = cur_s + cl[0]; }
+  // Eq. 3 bookkeeping (emitting waves only): the segment whose sum is being collected, see max_chunks().  (Offsets
+  // that are out of order give wrong statistics in range; the problem's scores are discarded.)
+  const int32_t* off = shot_offsets + static_cast<size_t>(p / share) * (n_shots + 1);
+  const int n_seg = wave_emits ? n_shots + 2 : 0;
+  auto segment_end = [&](int sg) { return sg <= n_shots ? off[sg] : n_tokens; };
+  int cur_c = 0, cur_s = 0, cur_e = wave_emits ? segment_end(0) : 0;
   float l_chunk = 0.f;
   const int h_local = h - g * G;
-  float* part_row = partial + static_cast<size_t>(p) * max_c * H_kv * R + static_cast<size_t>(g) * R +
-                    h_local * W + win_j;  // + chunk * H_kv * R
+  float* part_row = partial + (static_cast<size_t>(p) * H_kv + g) * max_c * R + h_local * W + win_j;  // + segment * R
   auto finish_chunk = [&]() {
     const float tot = sum_across_halves(l_chunk);
     if (lane_emits)
-      part_row[static_cast<size_t>(cur_c) * H_kv * R] = tot > 0.f ? m_run + __builtin_amdgcn_logf(tot) : -INFINITY;
+      part_row[static_cast<size_t>(cur_c) * R] = tot > 0.f ? m_run + __builtin_amdgcn_logf(tot) : -INFINITY;
     l_chunk = 0.f;
     ++cur_c;
-    if (cur_c < nc) { cur_s = cs[cur_c]; cur_e = cur_s + cl[cur_c]; }
+    if (cur_c < n_seg) { cur_s = cur_e; cur_e = segment_end(cur_c); }
   };
 
   issue(0, 0);
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
     }
     // ---- Eq. 3: this block's weights credited to the chunks it overlaps --------------------------
     if (wave_emits) {
-      while (cur_c < nc && cur_s < key0 + kBlockKeys) {
+      while (cur_c < n_seg && cur_s < key0 + kBlockKeys) {
         const int lo = max(cur_s, key0) - key0 - 4 * half, hi = min(cur_e, key0 + kBlockKeys) - key0 - 4 * half;
         float sum = 0.f;
 #pragma unroll
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
   const float l_tot = sum_across_halves(l_run);
   if (wave_emits) {
     // chunks that reach past this tile's keys hold what their visible part gave; later ones nothing
-    while (cur_c < nc) finish_chunk();
+    while (cur_c < n_seg) finish_chunk();
     if (lane_emits)
       row_stat[(static_cast<size_t>(p) * H_kv + g) * R + h_local * W + win_j] = m_run + __builtin_amdgcn_logf(l_tot);
   }
@@ -398,24 +400,25 @@ hipError_t launch_pack_vt(const PrefillDims& d, const void* v, const PrefillWork
   KernelTimer timer(d.timing, kKernelPackVt, s);
   // enough workgroups to fill the chip a few times over, each with at least 128 rows of a plane
   const int planes = d.P * d.H_kv;
-  const int shares = max(1, min(ceil_div(d.n_tokens, 128), ceil_div(1024, planes)));
+  const int shares = max(1, min(min(ceil_div(d.n_tokens, 128), ceil_div(1024, planes)), kVShares));
   hipLaunchKernelGGL(v_absmax_kernel, dim3(shares, planes), dim3(256), 0, s, static_cast<const bf16_t*>(v),
-                     d.n_tokens, w.v_absmax);
+                     d.n_tokens, w.v_share_max);
   hipLaunchKernelGGL(pack_vt_kernel, dim3(nb, d.P * d.H_kv), dim3(256), 0, s, static_cast<const bf16_t*>(v),
-                     d.n_tokens, nb, w.v_absmax, static_cast<uint16_t*>(w.vt));
+                     d.n_tokens, nb, w.v_share_max, shares, w.v_absmax, static_cast<uint16_t*>(w.vt));
   return hipGetLastError();
 }
 
 hipError_t launch_attention_scores(const PrefillDims& d, const void* q, const void* k, const void* vt,
-                                   float* attn_out, const PrefillWorkspace& w, hipStream_t s) {
+                                   const int32_t* shot_offsets, float* attn_out, const PrefillWorkspace& w,
+                                   hipStream_t s) {
   const int nb = attention_key_blocks(d.n_tokens);
   const dim3 grid(d.H, d.P, ceil_div(d.n_tokens, kTileQ));
   KernelTimer timer(d.timing, kKernelAttention, s);
   hipLaunchKernelGGL(attention_scores_kernel, grid, dim3(kThreadsQ), 0, s, static_cast<const bf16_t*>(q),
                      static_cast<const bf16_t*>(k), static_cast<const uint16_t*>(vt), w.v_absmax, d.n_tokens, nb, d.H,
                      d.H_kv,
-                     d.W, d.sm_scale * kLog2e, attn_out, w.n_chunks, w.chunk_start, w.chunk_len, w.max_c, d.R,
-                     w.partial, w.row_stat);
+                     d.W, d.sm_scale * kLog2e, attn_out, shot_offsets, d.share, d.n_shots, w.max_c, d.R, w.partial,
+                     w.group_stat);
   return hipGetLastError();
 }
 

@@ -1,105 +1,125 @@
-// Normalisation of the window-softmax partials (Section 5.1, Eq. 3).
+// Normalisation of the window-softmax partials (Section 5.1, Eq. 3): per (problem, chunk, KV head) the attention
+// mass sum over the head's query rows of 2^(lse_chunk - lse_row), where lse_row is the log2 of the row's softmax
+// denominator over all of its keys.
 //
-//   row_stats  : per (problem, KV head, query row) the log2 of the softmax denominator over all of the
-//                row's keys, combined from the per-workgroup statistics the score kernel wrote
-//   chunk_mass : per (problem, chunk) the attention mass sum_{heads, rows} 2^(lse_chunk - lse_row)
-// All sums are in fixed order (no atomics), so results are reproducible run to run.
+// A workgroup takes a tile of the chunks of one KV head.  It first combines the head's row denominators from the
+// slices' statistics - a few KB that every tile of the head reads again, out of cache, which costs less than a
+// launch of its own (a dependent kernel ends no earlier than 4-5 us after its predecessor) - and then sums its
+// chunks, a group of lanes per chunk with 16-byte loads.  All sums are in fixed order (no atomics), so results
+// are reproducible run to run.
 #include "common.hpp"
 
 namespace shotkv {
 
 namespace {
 
-constexpr int kStatThreads = 1024;
-
-__global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const float* __restrict__ group_stat,
-                                                                 const int32_t* __restrict__ n_chunks,
-                                                                 int H_kv, int R, int n_groups,
-                                                                 float* __restrict__ row_stat) {
-  const int g = blockIdx.x, p = blockIdx.y;
-  const int nl = kStatThreads / R;  // group lanes
-  const int tid = threadIdx.x;
-  const int r = tid % R, gl = tid / R;
-  // entries to combine: every score workgroup's statistic (-inf from one without chunks)
-  const int ng = n_chunks[p] > 0 ? n_groups : 0;
-  const float* base = group_stat + (static_cast<size_t>(p) * H_kv + g) * n_groups * R;
-  // two passes over the lane's share (second one out of cache): the maximum first, then the sum of
-  // 2^(x - max) with independent loads
-  float M = -INFINITY;
-  if (gl < nl)
-    for (int c = gl; c < ng; c += nl) M = fmaxf(M, base[static_cast<size_t>(c) * R + r]);
-  float L = 0.f;
-  if (gl < nl && M > -INFINITY)
-    for (int c = gl; c < ng; c += nl) L += exp2f(base[static_cast<size_t>(c) * R + r] - M);  // 2^-inf = 0
-  __shared__ float sM[kStatThreads];
-  __shared__ float sL[kStatThreads];
-  sM[tid] = M;
-  sL[tid] = L;
-  __syncthreads();
-  if (tid < R) {
-    float Mt = -INFINITY;
-    for (int i = 0; i < nl; ++i) Mt = fmaxf(Mt, sM[i * R + tid]);
-    float Lt = 0.f;
-    if (Mt > -INFINITY)
-      for (int i = 0; i < nl; ++i) Lt += sL[i * R + tid] * exp2f(sM[i * R + tid] - Mt);
-    // log2 of the row's softmax denominator; +inf for a row without keys so that its weights vanish
-    row_stat[(static_cast<size_t>(p) * H_kv + g) * R + tid] = Lt > 0.f ? Mt + log2f(Lt) : INFINITY;
-  }
-}
-
 constexpr int kMassThreads = 256;
-constexpr int kMassWaves = kMassThreads / kWave;
-constexpr int kMassPerWave = 4;  // chunks a wave has in flight
-constexpr int kMassPerBlock = kMassWaves * kMassPerWave;
+constexpr int kMaxRows = 256;
 
+// LANES: lanes per chunk, R / 4 rounded up to a power of two
+template <int LANES>
 __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* __restrict__ partial,
-                                                                  const float* __restrict__ row_stat,
-                                                                  const int32_t* __restrict__ n_chunks,
-                                                                  int H_kv, int R, int max_c,
-                                                                  float* __restrict__ chunk_mass) {
-  const int p = blockIdx.y;
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int c0 = blockIdx.x * kMassPerBlock + wave;  // this wave's chunks: c0, c0 + kMassWaves, ...
-  const int nc = n_chunks[p];
-  if (blockIdx.x * kMassPerBlock >= nc) return;
-  // a chunk's statistics of all KV heads are contiguous and line up with the row denominators
-  const float* stat = row_stat + static_cast<size_t>(p) * H_kv * R;
-  const int E = H_kv * R;
-  float acc[kMassPerWave];
+                                                                  const float* __restrict__ group_stat, int H_kv,
+                                                                  int R, int n_valid, int n_groups, int max_c,
+                                                                  int tile, float* __restrict__ chunk_mass) {
+  const int g = blockIdx.y, p = blockIdx.z, tid = threadIdx.x;
+  const size_t head = static_cast<size_t>(p) * H_kv + g;
+  constexpr int kTeams = kMassThreads / LANES;  // lane groups: one slice, later one chunk each
+  const int team = tid / LANES, row0 = 4 * (tid % LANES);
+  const bool has_rows = row0 < R;
+
+  // ---- row denominators: every team combines its share of the slices, then the teams are combined ------
+  __shared__ float s_max[kTeams][4 * LANES];
+  __shared__ float s_sum[kTeams][4 * LANES];
+  __shared__ __attribute__((aligned(16))) float s_lse[4 * LANES];
+  {
+    float M[4], L[4];
 #pragma unroll
-  for (int j = 0; j < kMassPerWave; ++j) acc[j] = 0.f;
-  for (int e = lane; e < E; e += kWave) {
-    const float st = stat[e];
-    float x[kMassPerWave];
+    for (int e = 0; e < 4; ++e) { M[e] = -INFINITY; L[e] = 0.f; }
+    const float* stat = group_stat + head * n_groups * R + row0;
+    constexpr int kBatch = 4;  // loads in flight
+    for (int s0 = team; s0 < n_groups; s0 += kTeams * kBatch) {
+      float4 x[kBatch];
 #pragma unroll
-    for (int j = 0; j < kMassPerWave; ++j) {  // independent loads first
-      const int c = min(c0 + j * kMassWaves, nc - 1);
-      x[j] = partial[(static_cast<size_t>(p) * max_c + c) * E + e];
+      for (int j = 0; j < kBatch; ++j) {
+        x[j] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        const int sl = s0 + j * kTeams;
+        if (has_rows && sl < n_groups) x[j] = *reinterpret_cast<const float4*>(stat + static_cast<size_t>(sl) * R);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float m = M[e];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) m = fmaxf(m, reinterpret_cast<const float*>(&x[j])[e]);
+        if (m > -INFINITY) {
+          L[e] *= exp2f(M[e] - m);
+#pragma unroll
+          for (int j = 0; j < kBatch; ++j) L[e] += exp2f(reinterpret_cast<const float*>(&x[j])[e] - m);  // 2^-inf = 0
+          M[e] = m;
+        }
+      }
     }
 #pragma unroll
-    for (int j = 0; j < kMassPerWave; ++j) acc[j] += exp2f(x[j] - st);  // 2^-inf = 0
+    for (int e = 0; e < 4; ++e) { s_max[team][row0 + e] = M[e]; s_sum[team][row0 + e] = L[e]; }
   }
+  __syncthreads();
+  if (tid < 4 * LANES) {
+    float M = -INFINITY, L = 0.f;
 #pragma unroll
-  for (int j = 0; j < kMassPerWave; ++j) {
-    const float total = wave_sum(acc[j]);
-    const int c = c0 + j * kMassWaves;
-    if (lane == 0 && c < nc) chunk_mass[static_cast<size_t>(p) * max_c + c] = total;
+    for (int t = 0; t < kTeams; ++t) M = fmaxf(M, s_max[t][tid]);
+    if (M > -INFINITY)
+#pragma unroll
+      for (int t = 0; t < kTeams; ++t) L += s_sum[t][tid] * exp2f(s_max[t][tid] - M);
+    // log2 of the row's softmax denominator; +inf for a row without keys so that its weights vanish
+    s_lse[tid] = L > 0.f && tid < n_valid ? M + log2f(L) : INFINITY;
+  }
+  __syncthreads();
+
+  // ---- masses -------------------------------------------------------------------------------------------
+  const float4 lse = *reinterpret_cast<const float4*>(&s_lse[row0]);
+  const float* rows = partial + head * max_c * R + row0;
+  const int c_end = min((static_cast<int>(blockIdx.x) + 1) * tile, max_c);
+  constexpr int kBatch = 4;  // chunks a team has in flight
+  for (int c0 = blockIdx.x * tile + team; c0 < c_end; c0 += kTeams * kBatch) {
+    float4 x[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int c = min(c0 + j * kTeams, c_end - 1);
+      x[j] = has_rows ? *reinterpret_cast<const float4*>(rows + static_cast<size_t>(c) * R) : lse;
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      float m = row0 + 0 < n_valid ? exp2f(x[j].x - lse.x) : 0.f;  // 2^-inf = 0
+      m += row0 + 1 < n_valid ? exp2f(x[j].y - lse.y) : 0.f;
+      m += row0 + 2 < n_valid ? exp2f(x[j].z - lse.z) : 0.f;
+      m += row0 + 3 < n_valid ? exp2f(x[j].w - lse.w) : 0.f;
+#pragma unroll
+      for (int o = LANES / 2; o > 0; o >>= 1) m += __shfl_xor(m, o, kWave);
+      const int c = c0 + j * kTeams;
+      if (row0 == 0 && c < c_end) chunk_mass[(static_cast<size_t>(p) * max_c + c) * H_kv + g] = m;
+    }
   }
 }
 
 }  // namespace
 
-hipError_t launch_chunk_mass(const PrefillDims& d, const PrefillWorkspace& w, hipStream_t s) {
+hipError_t launch_chunk_mass(const PrefillDims& d, int n_valid, const PrefillWorkspace& w, hipStream_t s) {
+  KernelTimer stat_timer(d.timing, kKernelRowStats, s);  // the row denominators are part of the same kernel
   KernelTimer timer(d.timing, kKernelChunkMass, s);
-  hipLaunchKernelGGL(chunk_mass_kernel, dim3(ceil_div(w.max_c, kMassPerBlock), d.P), dim3(kMassThreads), 0, s,
-                     w.partial, w.row_stat, w.n_chunks, d.H_kv, d.R, w.max_c, w.chunk_mass);
-  return hipGetLastError();
-}
-
-hipError_t launch_row_stats(const PrefillDims& d, const PrefillWorkspace& w, hipStream_t s) {
-  KernelTimer timer(d.timing, kKernelRowStats, s);
-  hipLaunchKernelGGL(row_stats_kernel, dim3(d.H_kv, d.P), dim3(kStatThreads), 0, s, w.group_stat, w.n_chunks,
-                     d.H_kv, d.R, w.n_groups, w.row_stat);
+  if (d.R % 4 || d.R > kMaxRows) return hipErrorInvalidValue;
+  // small tiles spread few problems over the chip, large ones share the row denominators of many
+  const int heads = d.P * d.H_kv;
+  const int tiles = max(1, min(ceil_div(w.max_c, 32), ceil_div(2048, heads)));
+  const int tile = ceil_div(w.max_c, tiles);
+  const dim3 grid(ceil_div(w.max_c, tile), d.H_kv, d.P);
+#define SHOTKV_LAUNCH_MASS(LL)                                                                               \
+  hipLaunchKernelGGL(chunk_mass_kernel<LL>, grid, dim3(kMassThreads), 0, s, w.partial, w.group_stat, d.H_kv, d.R, \
+                     n_valid, w.n_groups, w.max_c, tile, w.chunk_mass)
+  if (d.R <= 32) SHOTKV_LAUNCH_MASS(8);
+  else if (d.R <= 64) SHOTKV_LAUNCH_MASS(16);
+  else if (d.R <= 128) SHOTKV_LAUNCH_MASS(32);
+  else SHOTKV_LAUNCH_MASS(64);
+#undef SHOTKV_LAUNCH_MASS
   return hipGetLastError();
 }
 

@@ -3,8 +3,9 @@
 // Shape: bf16 or fp32, head_dim 64 or 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6
 // (bf16) or 8 blocks of 32 rows; rows past G*W are zero operands whose statistics are written as -inf.
 //
-// A workgroup is a pair of waves (one wave for a single row block) that takes the chunks starting inside
-// one slice of a KV head's key axis and walks that contiguous span in blocks of 32 keys.  Each wave keeps
+// A workgroup is a pair of waves (one wave for a single row block) that takes one slice of a KV head's key axis
+// and walks it in blocks of 32 keys.  It finds the shot boundaries inside its slice itself (one pass over the
+// offsets, in flight together with the queries and the first blocks).  Each wave keeps
 // its share of the window queries in registers as MFMA B operands and computes
 // S^T[32 keys x 32 queries] = K_blk * Q^T per row block with v_mfma_f32_32x32x16_bf16 (fp32 inputs:
 // v_mfma_f32_32x32x2_f32, full single precision).  Keys run along the accumulator registers and queries along the lanes, so the row-softmax statistics (max and sum over
@@ -351,7 +352,7 @@ __device__ __forceinline__ void credit_elements(const floatx16 (&e)[NQW], uint32
   for (int q = 0; q < NQW; ++q) l_run[q] += se[q] + so[q];
 }
 
-constexpr int kEndCache = 128;  // chunk ends of a workgroup kept in LDS
+constexpr int kEndCache = 128;  // shot boundaries of a slice kept in LDS
 
 template <typename T, int D, int NQB>
 struct GroupShape {
@@ -379,36 +380,26 @@ template <typename T, int D, int NQB>
 __global__ __launch_bounds__((GroupShape<T, D, NQB>::kThreads), (GroupShape<T, D, NQB>::kMinWavesPerSimd)) void
 score_partials_mfma_kernel(
     const T* __restrict__ q_obs, const T* __restrict__ k, int n_tokens, int H, int H_kv, int W,
-    int n_rows, float c, const int32_t* __restrict__ group_first, const int32_t* __restrict__ chunk_start,
-    const int32_t* __restrict__ chunk_len, int max_c,
-    float* __restrict__ partial, float* __restrict__ group_stat) {
+    int n_rows, float c, const int32_t* __restrict__ shot_offsets, int share, int n_shots, int group_keys,
+    int max_c, float* __restrict__ partial, float* __restrict__ group_stat) {
   typedef GroupShape<T, D, NQB> S;
   typedef Element<T, D> E;
   constexpr int NQW = S::kNQW;
   constexpr int R = NQB * 32;
   __shared__ __attribute__((aligned(64))) char lds[kRing][E::kBufBytes];
   __shared__ int s_end[kEndCache];
+  __shared__ int s_count[S::kWaves][2];
 
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int g = blockIdx.y, p = blockIdx.z;
-  // this workgroup's chunks: those that start inside its slice of the key axis
-  const int32_t* gf = group_first + static_cast<size_t>(p) * (gridDim.x + 1) + blockIdx.x;
-  const int c_begin = gf[0], c_end = gf[1];
-  if (c_begin >= c_end) {  // no chunk starts here (or the problem's offsets are bad): the whole
-                           // workgroup leaves together, before any barrier
-    for (int r = threadIdx.x; r < R; r += S::kThreads)
-      group_stat[((static_cast<size_t>(p) * H_kv + g) * gridDim.x + blockIdx.x) * R + r] = -INFINITY;
-    return;
-  }
-
-  const int32_t* cs = chunk_start + static_cast<size_t>(p) * max_c;
-  const int32_t* cl = chunk_len + static_cast<size_t>(p) * max_c;
+  const int32_t* off = shot_offsets + static_cast<size_t>(p / share) * (n_shots + 1);
+  const int k_begin = blockIdx.x * group_keys, k_end = min(k_begin + group_keys, n_tokens);
   const char* k_plane =
       reinterpret_cast<const char*>(k) + (static_cast<size_t>(p) * H_kv + g) * n_tokens * E::kRowBytes;
   const int G = H / H_kv;
   const T* q_rows = q_obs + (static_cast<size_t>(p) * H + static_cast<size_t>(g) * G) * W * D;
-  float* out = partial + (static_cast<size_t>(p) * max_c * H_kv + g) * R;  // chunk c of this head: + c * H_kv * R
+  float* out = partial + (static_cast<size_t>(p) * H_kv + g) * max_c * R;  // chunk c of this head: + c * R
   const int qb0 = wave * NQW;
 
   // B operands: query row (qb0+q)*32 + lane%32, the lane half's 16 bytes of every step
@@ -426,17 +417,71 @@ score_partials_mfma_kernel(
       bq[q][ks] = __builtin_bit_cast(typename E::Vec, raw);
     }
   }
+  lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
+  const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base));
+  const int causal_base = n_tokens - W;
+  const int g0 = wave * S::kLoads;
+
+  // The slice is walked in blocks of 32 keys that take no notice of chunk boundaries: a block that contains a
+  // boundary credits its weights to the chunks on either side with masked in-lane sums (sentence-sized units end
+  // inside most blocks, shots of hundreds of tokens inside few), and no block carries padding except the last.
+  // `cur` sits in ring slot cur_buf; up to kLook = kRing - 1 requested blocks follow it in the next slots.
+  // A new block is requested each iteration, right after the barrier that frees the slot of the block
+  // before cur.
+  constexpr int kLook = kRing - 1;
+  auto ring_slot = [](int sl) { return sl >= kRing ? sl - kRing : sl; };
+  int cur_key0 = k_begin, next_key0 = k_begin + kBlockKeys;  // next block to request
+  issue_block<E, S::kLoads>(k_plane, k_begin, k_end - k_begin, lds_addr, g0, lane);
+  int n_q = 0;
+#pragma unroll
+  for (int i = 0; i < kLook - 1; ++i) {
+    if (next_key0 < k_end) {
+      issue_block<E, S::kLoads>(k_plane, next_key0, k_end - next_key0, lds_addr + (i + 1) * E::kBufBytes, g0, lane);
+      n_q = i + 1;
+      next_key0 += kBlockKeys;
+    }
+  }
+
+  // Shot boundaries: segment of a key = offsets that are not above it.  The ends inside the slice go to LDS, one
+  // read per boundary instead of a dependent trip to memory.  (Offsets that are out of order give a wrong but
+  // harmless set of chunk numbers in range; the problem's scores are discarded.)
+  int seg0 = 0, seg1 = 0;
+  constexpr int kOffBatch = 8;  // loads in flight
+#pragma clang loop unroll(disable)
+  for (int i0 = wave * kWave; i0 <= n_shots; i0 += S::kThreads * kOffBatch) {
+    int o[kOffBatch];
+#pragma unroll
+    for (int j = 0; j < kOffBatch; ++j) o[j] = off[min(i0 + j * S::kThreads + lane, n_shots)];
+#pragma unroll
+    for (int j = 0; j < kOffBatch; ++j) {
+      const int i = i0 + j * S::kThreads + lane;
+      if (i > n_shots) o[j] = INT32_MAX;
+      seg0 += __popcll(__builtin_amdgcn_ballot_w64(o[j] <= k_begin));
+      seg1 += __popcll(__builtin_amdgcn_ballot_w64(o[j] < k_end));
+      if (o[j] > k_begin && o[j] < k_end) s_end[i % kEndCache] = o[j];
+    }
+  }
+  if (lane == 0) { s_count[wave][0] = seg0; s_count[wave][1] = seg1; }
   // the query loads must have landed before the streaming loop starts: inside the loop the only
   // vector-memory loads are the block loads, whose completion is tracked by hand
 #pragma unroll
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
     for (int ks = 0; ks < E::kSteps; ++ks) asm volatile("" ::"v"(bq[q][ks]));
-
-  lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
-  const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base));
-  const int causal_base = n_tokens - W;
-  const int g0 = wave * S::kLoads;
+  __syncthreads();
+  seg0 = seg1 = 0;
+#pragma unroll
+  for (int w = 0; w < S::kWaves; ++w) {
+    seg0 += s_count[w][0];
+    seg1 += s_count[w][1];
+  }
+  seg0 = __builtin_amdgcn_readfirstlane(seg0);
+  seg1 = __builtin_amdgcn_readfirstlane(seg1);
+  const bool ends_in_lds = seg1 - seg0 <= kEndCache;
+  auto segment_end = [&](int sg) {
+    if (sg >= seg1) return k_end;
+    return __builtin_amdgcn_readfirstlane(ends_in_lds ? s_end[sg % kEndCache] : off[sg]);
+  };
 
   float m_run[NQW], l_run[NQW], l_grp[NQW];
 #pragma unroll
@@ -471,7 +516,7 @@ score_partials_mfma_kernel(
     for (int sl = 0; sl < 4; ++sl) {
       const int j = sl + 4 * my_half;
       if (j < n_stash) {
-        float* dst = out + static_cast<size_t>(stash_c0 + j) * H_kv * R + (lane & 31) * NQB + qb0;
+        float* dst = out + static_cast<size_t>(stash_c0 + j) * R + (lane & 31) * NQB + qb0;
         if (NQW == 4) {
           *reinterpret_cast<float4*>(dst) =
               make_float4(stash[sl][0], stash[sl][1 % NQW], stash[sl][2 % NQW], stash[sl][3 % NQW]);
@@ -486,40 +531,9 @@ score_partials_mfma_kernel(
     n_stash = 0;
   };
 
-  // The workgroup's chunks tile one contiguous span of the key axis, which is walked in blocks of 32
-  // keys that take no notice of chunk boundaries: a block that contains a boundary credits its weights
-  // to the chunks on either side with masked in-lane sums (sentence-sized units end inside most blocks,
-  // shots of hundreds of tokens inside few), and no block carries padding except the span's last.
-  // `cur` sits in ring slot cur_buf; up to kLook = kRing - 1 requested blocks follow it in the next slots.
-  // A new block is requested each iteration, right after the barrier that frees the slot of the block
-  // before cur.
-  const int k_begin = __builtin_amdgcn_readfirstlane(cs[c_begin]);
-  const int k_end = __builtin_amdgcn_readfirstlane(cs[c_end - 1] + cl[c_end - 1]);
-  // ends of the first chunks go to LDS: one read per boundary instead of a dependent trip to the table
-  for (int i = threadIdx.x; i < min(c_end - c_begin, kEndCache); i += S::kThreads)
-    s_end[i] = cs[c_begin + i] + cl[c_begin + i];
-  __syncthreads();
-  auto chunk_end = [&](int ci) {
-    const int i = ci - c_begin;
-    const int e = i < kEndCache ? s_end[i] : cs[ci] + cl[ci];
-    return __builtin_amdgcn_readfirstlane(e);
-  };
-  constexpr int kLook = kRing - 1;
-  auto ring_slot = [](int sl) { return sl >= kRing ? sl - kRing : sl; };
-  int cur_key0 = k_begin, next_key0 = k_begin + kBlockKeys;  // next block to request
-  issue_block<E, S::kLoads>(k_plane, k_begin, k_end - k_begin, lds_addr, g0, lane);
-  int n_q = 0;
-#pragma unroll
-  for (int i = 0; i < kLook - 1; ++i) {
-    if (next_key0 < k_end) {
-      issue_block<E, S::kLoads>(k_plane, next_key0, k_end - next_key0, lds_addr + (i + 1) * E::kBufBytes, g0, lane);
-      n_q = i + 1;
-      next_key0 += kBlockKeys;
-    }
-  }
   int cur_buf = 0;
   bool first_block = true;
-  int cur_c = c_begin, cur_end = chunk_end(c_begin);
+  int cur_seg = seg0, cur_end = segment_end(seg0);
 
   // the current chunk is complete: add up the lane halves (same reference), keep its statistic
   auto finish_chunk = [&]() {
@@ -534,9 +548,9 @@ score_partials_mfma_kernel(
       l_run[q] = 0.f;  // the reference carries over to the next chunk
     }
     if (n_stash == kStash) flush();  // several chunks can end inside one block
-    stash_put(val, cur_c);
-    ++cur_c;
-    cur_end = cur_c < c_end ? chunk_end(cur_c) : INT32_MAX;
+    stash_put(val, blockIdx.x + cur_seg);
+    ++cur_seg;
+    cur_end = cur_seg <= seg1 ? segment_end(cur_seg) : INT32_MAX;
   };
 
 #pragma clang loop unroll(disable)
@@ -611,7 +625,7 @@ int score_group_keys(int P, int H_kv, int n_tokens, int n_shots) {
 #ifdef SHOTKV_SCORE_GROUP_KEYS
   return SHOTKV_SCORE_GROUP_KEYS;
 #else
-  // A workgroup takes the chunks that start inside a slice of the key axis.  Long slices amortise its
+  // A workgroup takes one slice of the key axis.  Long slices amortise its
   // query registers and its start-up, but the chip wants a thousand workgroups or more: measured on
   // batches of 1 to 128 problems of 32K tokens, 2048-key slices win from about four thousand workgroups
   // on, 1024-key slices from about one thousand on, and below that the count matters more than the length.
@@ -634,39 +648,40 @@ int score_row_blocks(int dtype, int rows) {
 }
 
 template <typename T, int D, int NQB>
-static void launch_score(const PrefillDims& d, const void* q_obs, const void* k, const PrefillWorkspace& w,
-                         hipStream_t s) {
+static void launch_score(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
+                         const PrefillWorkspace& w, hipStream_t s) {
   hipLaunchKernelGGL((score_partials_mfma_kernel<T, D, NQB>), dim3(w.n_groups, d.H_kv, d.P),
                      dim3(GroupShape<T, D, NQB>::kThreads), 0, s, static_cast<const T*>(q_obs),
                      static_cast<const T*>(k), d.n_tokens, d.H, d.H_kv, d.W, d.R_rows, d.sm_scale * kLog2e,
-                     w.group_first, w.chunk_start, w.chunk_len, w.max_c, w.partial, w.group_stat);
+                     off, d.share, d.n_shots, w.group_keys, w.max_c, w.partial, w.group_stat);
 }
 
 template <typename T, int D>
-static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, const void* k, const PrefillWorkspace& w,
-                                    hipStream_t s) {
+static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
+                                    const PrefillWorkspace& w, hipStream_t s) {
   switch (d.R / 32) {
-    case 1: launch_score<T, D, 1>(d, q_obs, k, w, s); break;
-    case 2: launch_score<T, D, 2>(d, q_obs, k, w, s); break;
-    case 4: launch_score<T, D, 4>(d, q_obs, k, w, s); break;
+    case 1: launch_score<T, D, 1>(d, q_obs, k, off, w, s); break;
+    case 2: launch_score<T, D, 2>(d, q_obs, k, off, w, s); break;
+    case 4: launch_score<T, D, 4>(d, q_obs, k, off, w, s); break;
     case 6:
-      if constexpr (sizeof(T) == 2) { launch_score<T, D, 6>(d, q_obs, k, w, s); break; }
+      if constexpr (sizeof(T) == 2) { launch_score<T, D, 6>(d, q_obs, k, off, w, s); break; }
       return hipErrorInvalidValue;
-    case 8: launch_score<T, D, 8>(d, q_obs, k, w, s); break;
+    case 8: launch_score<T, D, 8>(d, q_obs, k, off, w, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_score_partials(const PrefillDims& d, const void* q_obs, const void* k, const PrefillWorkspace& w,
-                                 hipStream_t s) {
+hipError_t launch_score_partials(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
+                                 const PrefillWorkspace& w, hipStream_t s) {
+  KernelTimer plan_timer(d.timing, kKernelPlan, s);  // the kernel finds the shot boundaries of its slices itself
   KernelTimer timer(d.timing, kKernelScore, s);
   if (d.dtype == SHOTKV_BF16) {
-    if (d.D == 128) return launch_score_rows<bf16_t, 128>(d, q_obs, k, w, s);
-    if (d.D == 64) return launch_score_rows<bf16_t, 64>(d, q_obs, k, w, s);
+    if (d.D == 128) return launch_score_rows<bf16_t, 128>(d, q_obs, k, off, w, s);
+    if (d.D == 64) return launch_score_rows<bf16_t, 64>(d, q_obs, k, off, w, s);
   } else {
-    if (d.D == 128) return launch_score_rows<float, 128>(d, q_obs, k, w, s);
-    if (d.D == 64) return launch_score_rows<float, 64>(d, q_obs, k, w, s);
+    if (d.D == 128) return launch_score_rows<float, 128>(d, q_obs, k, off, w, s);
+    if (d.D == 64) return launch_score_rows<float, 64>(d, q_obs, k, off, w, s);
   }
   return hipErrorInvalidValue;
 }

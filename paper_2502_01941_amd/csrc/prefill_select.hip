@@ -175,7 +175,7 @@ __device__ void sort_keys_descending(uint64_t (&k)[E], int n_pad, uint64_t* keys
 
 template <bool MASS, bool SELECT>
 __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
-    const int32_t* __restrict__ seg_first, const float* __restrict__ chunk_mass, int max_c,
+    const float* __restrict__ chunk_mass, int max_c, int group_shift, int H_kv,
     float* __restrict__ shot_scores,
     const int32_t* __restrict__ shot_offsets, const int32_t* __restrict__ budget_tokens, int share,
     int n_shots, int n_tokens, int cap, int select_mode, int32_t* __restrict__ kept_count,
@@ -219,18 +219,23 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     if (i >= n_shots) continue;
     if (MASS) {
       if (!bad) {
-        const float* mass = chunk_mass + static_cast<size_t>(p) * max_c;
-        const int32_t* sf = seg_first + static_cast<size_t>(p) * (n_shots + 3);
+        // shot i is segment i + 1: its chunks' masses are consecutive, one word per KV head each
+        const int lo = s_off[i], hi = s_off[i + 1];
+        const int c0 = (lo >> group_shift) + i + 1, c1 = ((hi - 1) >> group_shift) + i + 1;
+        const float* mass = chunk_mass + (static_cast<size_t>(p) * max_c + c0) * H_kv;
         float sum = 0.f;
-        for (int c = sf[i + 1]; c < sf[i + 2]; ++c) sum += mass[c];
-        my_score[j] = sum / static_cast<float>(s_off[i + 1] - s_off[i]);
+        for (int e = 0; e < (c1 - c0 + 1) * H_kv; ++e) sum += mass[e];
+        my_score[j] = sum / static_cast<float>(hi - lo);
       }
       scores[i] = my_score[j];
     } else if (!bad) {
       my_score[j] = scores[i];
     }
   }
-  if (!SELECT) return;
+  if (!SELECT) {
+    if (tid == 0) status[p] = bad ? SHOTKV_ST_BAD_OFFSETS : SHOTKV_ST_OK;
+    return;
+  }
 
   uint8_t* sel = shot_selected ? shot_selected + static_cast<size_t>(p) * n_shots : nullptr;
   int32_t* kept_pos = kept_positions + static_cast<size_t>(p) * cap;
@@ -354,9 +359,10 @@ hipError_t launch_reduce_select(const PrefillDims& d, bool with_mass, bool with_
                                 int32_t* kept_count, uint8_t* shot_selected, int32_t* status,
                                 int32_t* kept_positions, const PrefillWorkspace& w, hipStream_t s) {
   KernelTimer timer(d.timing, kKernelReduceSelect, s);
+  const int group_shift = 31 - __builtin_clz(static_cast<unsigned>(w.group_keys));
 #define SHOTKV_LAUNCH_RS(M, S)                                                                          \
-  hipLaunchKernelGGL((reduce_select_kernel<M, S>), dim3(d.P), dim3(kSelThreads), 0, s, w.seg_first,     \
-                     w.chunk_mass, w.max_c, shot_scores,                                                \
+  hipLaunchKernelGGL((reduce_select_kernel<M, S>), dim3(d.P), dim3(kSelThreads), 0, s, w.chunk_mass,    \
+                     w.max_c, group_shift, d.H_kv, shot_scores,                                         \
                      shot_offsets, budget_tokens, d.share, d.n_shots, d.n_tokens, cap, d.select_mode,   \
                      kept_count, shot_selected, status, kept_positions)
   if (with_mass && with_select) SHOTKV_LAUNCH_RS(true, true);

@@ -77,7 +77,8 @@ int make_prefill_dims(const shotkv_config* cfg, int P, int n_tokens, int n_shots
 }
 
 PrefillWorkspace carve(const PrefillDims& d, void* base) {
-  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots);
+  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots,
+                       score_group_keys(d.P, d.H_kv, d.n_tokens, d.n_shots));
 }
 
 int from_hip(hipError_t e) { return e == hipSuccess ? SHOTKV_OK : SHOTKV_E_LAUNCH; }
@@ -123,10 +124,8 @@ int shotkv_prefill_scores(const shotkv_config* cfg, int32_t P, int32_t n_tokens,
   const PrefillWorkspace w = carve(d, workspace);
   if (workspace_bytes < w.bytes) return SHOTKV_E_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_plan_chunks(d, shot_offsets, status, w, s);
-  if (e == hipSuccess) e = launch_score_partials(d, q_obs, k, w, s);
-  if (e == hipSuccess) e = launch_row_stats(d, w, s);
-  if (e == hipSuccess) e = launch_chunk_mass(d, w, s);
+  hipError_t e = launch_score_partials(d, q_obs, k, shot_offsets, w, s);
+  if (e == hipSuccess) e = launch_chunk_mass(d, d.R, w, s);
   if (e == hipSuccess)
     e = launch_reduce_select(d, true, false, shot_scores, shot_offsets, nullptr, 0, nullptr, nullptr, status,
                              nullptr, w, s);
@@ -178,10 +177,8 @@ int shotkv_prefill_compress(const shotkv_config* cfg, int32_t P, int32_t n_token
   if (workspace_bytes < w.bytes) return SHOTKV_E_WORKSPACE;
   float* scores = shot_scores ? shot_scores : w.scores;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_plan_chunks(d, shot_offsets, status, w, s);
-  if (e == hipSuccess) e = launch_score_partials(d, q_obs, k, w, s);
-  if (e == hipSuccess) e = launch_row_stats(d, w, s);
-  if (e == hipSuccess) e = launch_chunk_mass(d, w, s);
+  hipError_t e = launch_score_partials(d, q_obs, k, shot_offsets, w, s);
+  if (e == hipSuccess) e = launch_chunk_mass(d, d.R, w, s);
   if (e == hipSuccess)
     e = launch_reduce_select(d, true, true, scores, shot_offsets, budget_tokens, cap, kept_count,
                              shot_selected, status, kept_positions, w, s);
@@ -189,19 +186,19 @@ int shotkv_prefill_compress(const shotkv_config* cfg, int32_t P, int32_t n_token
   return from_hip(e);
 }
 
-// dims and workspace of the fused attention entry point: the row stride is exactly G * W (no matrix-core
-// row padding: the attention kernel writes every row that exists), chunks as on the matrix-core path
+// dims and workspace of the fused attention entry point: window rows in their own order (the attention kernel
+// writes every row that exists), one slice, so that every segment is one chunk
 static int make_attention_dims(const shotkv_config* cfg, int P, int n_tokens, int n_shots, PrefillDims* d) {
   const int rc = make_prefill_dims(cfg, P, n_tokens, n_shots, d);
   if (rc != SHOTKV_OK) return rc;
   if (!attention_supported(*d)) return SHOTKV_E_SHAPE;
-  d->R = d->R_rows;
+  d->R = ceil_div(d->R_rows, 32) * 32;
   return SHOTKV_OK;
 }
 
 static PrefillWorkspace carve_attention(const PrefillDims& d, void* base) {
   const size_t vt_bytes = static_cast<size_t>(d.P) * d.H_kv * attention_key_blocks(d.n_tokens) * 32 * d.D * 2;
-  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots, vt_bytes);
+  return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots, kOneSlice, vt_bytes);
 }
 
 size_t shotkv_prefill_attention_workspace_bytes(const shotkv_config* cfg, int32_t P, int32_t n_tokens,
@@ -232,10 +229,9 @@ int shotkv_prefill_attention_compress(const shotkv_config* cfg, int32_t P, int32
   if (workspace_bytes < w.bytes) return SHOTKV_E_WORKSPACE;
   float* scores = shot_scores ? shot_scores : w.scores;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_plan_chunks(d, shot_offsets, status, w, s);
-  if (e == hipSuccess) e = launch_pack_vt(d, v, w, s);
-  if (e == hipSuccess) e = launch_attention_scores(d, q, k, w.vt, attn_out, w, s);
-  if (e == hipSuccess) e = launch_chunk_mass(d, w, s);
+  hipError_t e = launch_pack_vt(d, v, w, s);
+  if (e == hipSuccess) e = launch_attention_scores(d, q, k, w.vt, shot_offsets, attn_out, w, s);
+  if (e == hipSuccess) e = launch_chunk_mass(d, d.R_rows, w, s);
   if (e == hipSuccess)
     e = launch_reduce_select(d, true, true, scores, shot_offsets, budget_tokens, cap, kept_count,
                              shot_selected, status, kept_positions, w, s);

@@ -58,3 +58,41 @@ def test_tile_edges(kv, D, dtype, G, W):
             np.testing.assert_allclose(res.shot_scores[p].cpu().numpy(), ref["scores"], rtol=SCORE_RTOL, atol=0,
                                        err_msg=f"N={N} p={p}")
             check_prefill_problem(res, p, q[p], k[p], v[p], offs[p], budget, N, scale, orc.SELECT_PREFIX, ref=ref)
+
+
+@pytest.mark.parametrize("attention", [False, True])
+def test_offsets_out_of_order_stay_harmless(kv, attention):
+    """Problems whose offsets are unsorted or out of range, between healthy ones: status BAD_OFFSETS, nothing kept,
+    zero scores, and the healthy problems' results are those of a batch without them."""
+    Hkv, G, W, D, N, n = 2, 4, 32, 128, 900, 6
+    H, scale = Hkv * G, 1.0 / math.sqrt(128)
+    good = np.array([10, 150, 290, 300, 555, 556, 850], dtype=np.int32)
+    bad = [[10, 290, 150, 300, 555, 556, 850], [-5, 150, 290, 300, 555, 556, 850], [10, 150, 290, 300, 555, 556, 2**31 - 1],
+           [899, 800, 700, 500, 300, 100, 5], [10, 10, 10, 10, 10, 10, 10], [-2**31, 2**31 - 1, 0, -1, 901, 450, 900]]
+    offs = np.stack([good] + [np.array(b, dtype=np.int64).astype(np.int32) for b in bad] + [good])
+    P = len(offs)
+    rng = np.random.default_rng(5)
+    q = torch.from_numpy(rng.standard_normal((P, H, N, D), dtype=np.float32)).to(torch.bfloat16).cuda()
+    k = torch.from_numpy(rng.standard_normal((P, Hkv, N, D), dtype=np.float32)).to(torch.bfloat16).cuda()
+    v = torch.from_numpy(rng.standard_normal((P, Hkv, N, D), dtype=np.float32)).to(torch.bfloat16).cuda()
+    bud = torch.full((P,), 500, dtype=torch.int32, device="cuda")
+
+    def call(rows):
+        a = [t[rows].contiguous() for t in (q, k, v)]
+        o, b = torch.from_numpy(offs).cuda()[rows].contiguous(), bud[rows].contiguous()
+        if attention:
+            return kv.prefill_attention_compress(*a, o, b, 600, W, scale)[1]
+        return kv.prefill_compress(a[0][:, :, -W:].contiguous(), a[1], a[2], o, b, 600, scale)
+
+    res, ref = call(list(range(P))), call([0, P - 1])
+    scores, status = kv.prefill_scores(q[:, :, -W:].contiguous(), k, torch.from_numpy(offs).cuda(), scale)
+    torch.cuda.synchronize()
+    want = [0] + [kv.ST_BAD_OFFSETS] * len(bad) + [0]
+    assert res.status.cpu().tolist() == want and status.cpu().tolist() == want
+    for p in range(1, P - 1):
+        assert int(res.kept_count[p]) == 0 and not res.shot_selected[p].any()
+        assert not res.shot_scores[p].any() and not scores[p].any()
+    for i, p in enumerate((0, P - 1)):
+        assert torch.equal(res.shot_scores[p], ref.shot_scores[i]) and torch.equal(res.shot_selected[p], ref.shot_selected[i])
+        kept = int(ref.kept_count[i])
+        assert int(res.kept_count[p]) == kept and torch.equal(res.k_out[p, :, :kept], ref.k_out[i, :, :kept])
