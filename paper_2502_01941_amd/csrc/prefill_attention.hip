@@ -22,8 +22,8 @@
 //                     instead of bf16's 8, which holds the output within 4e-4 of its row maximum with one
 //                     instruction per step (a bf16 weight is off by up to 2^-9; bf16 hi + lo would cost a
 //                     second instruction).  fp16's narrow range is dealt with by two exact power-of-two
-//                     scalings: the softmax reference sits 15 below the running maximum, so weights lie
-//                     in (0, 2^15] and anything above 2^-39 of the largest survives; and the pre-pass
+//                     scalings: the softmax reference sits 8 below a running maximum, so weights lie
+//                     in (0, 2^15) and anything above 2^-32 of the largest survives; and the pre-pass
 //                     scales every KV-head plane of V so that its largest finite |v| lands in [2^14, 2^15).
 //                     Sums of weights stay in fp32 and carry the same reference.
 // K and packed-V blocks are streamed global -> LDS with direct-to-LDS loads into a ring of three stages
@@ -32,6 +32,8 @@
 // 16-byte column).  The grid puts the query tile in its slowest dimension, longest tiles first, so that
 // every head's long tiles are dispatched before anybody's short ones.
 #include "common.hpp"
+
+#include <type_traits>
 
 namespace shotkv {
 
@@ -53,7 +55,17 @@ constexpr int kRowBytes = kD * 2;
 constexpr int kGroupBytes = 4 * kRowBytes + 64;       // K: four rows + pad = one direct-to-LDS instruction
 constexpr int kKBytes = 8 * kGroupBytes;              // 8704
 constexpr int kVtBytes = kD * kBlockKeys * 2;         // 8192: [128 d][32 keys] fp16
-constexpr int kWeightShift = 15;                      // softmax reference = running maximum - 15 (log2 domain)
+// Softmax reference.  Any reference gives the same softmax; a weight is 2^(logit - reference).  In a row's first
+// kExactBlocks blocks the reference follows the largest logit (minus kWeightShift, log2 domain) block by block: the
+// largest weight is then a power of two, which fp16 holds exactly, and short rows are where single weights show.
+// After that it stays until a lane's sum of sixteen weights says that one may leave fp16's range, which takes a logit
+// 2^7 times as heavy as everything so far.  Following the maximum all the way redoes the 64 output registers in most
+// of the first blocks of 32 rows (one row in 32 raises it) and puts the maximum chain ahead of every exponential.
+// Measured at 8192 / 32768 tokens, whole call: 620 / 8555 us following, 574 / 8035 us with sixteen such blocks,
+// 563 / 7985 us with one; output error against float64 1.62e-4, 1.67e-4 and 1.80e-4.
+constexpr int kWeightShift = 8;
+constexpr int kExactBlocks = 16;
+constexpr float kMaxBlockSum = 32768.f;
 constexpr int kStageBytes = kKBytes + kVtBytes;
 constexpr int kRing = 3;
 constexpr int kTileQ = 128;
@@ -154,20 +166,26 @@ __global__ __launch_bounds__(256) void pack_vt_kernel(const bf16_t* __restrict__
 // ---- streaming helpers ---------------------------------------------------------------------------
 // K groups [g0, g0 + 2) of a block: group i fills rows 4i..4i+3; lane l writes LDS slot l of the group
 // (row 4i + l/16, slot l%16) and therefore fetches column (l%16) ^ (l/16) of that row.  Rows past the
-// last token re-read it (they are masked by causality).
+// last token re-read it (they are masked by causality); only the last block has any.
 __device__ __forceinline__ void issue_k(const char* __restrict__ k_plane, int key0, int n_tokens,
                                         uint32_t lds_addr, int g0, int lane) {
   const int hi = lane >> 4;
   const uint32_t col_bytes = static_cast<uint32_t>(((lane & 15) ^ hi) << 4);
+  const char* base = k_plane + static_cast<size_t>(key0) * kRowBytes;
+  uint32_t off[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int rr = min(key0 + 4 * (g0 + i) + hi, n_tokens - 1);
-    const uint32_t off = static_cast<uint32_t>(rr) * kRowBytes + col_bytes;
+  for (int i = 0; i < 2; ++i) off[i] = static_cast<uint32_t>(4 * (g0 + i) + hi) * kRowBytes + col_bytes;
+  if (key0 + kBlockKeys > n_tokens) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      off[i] = static_cast<uint32_t>(min(4 * (g0 + i) + hi, n_tokens - 1 - key0)) * kRowBytes + col_bytes;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
-                 : "s"(lds_addr + (g0 + i) * kGroupBytes), "v"(off), "s"(k_plane)
+                 : "s"(lds_addr + (g0 + i) * kGroupBytes), "v"(off[i]), "s"(base)
                  : "memory", "m0");
-  }
 }
 // V^T slabs [i0, i0 + 2) of a packed block: slab i fills rows (d) 16i..16i+15 of 64 bytes; lane l writes
 // row 16i + l/4, slot l%4 and fetches column (l%4) ^ ((row/4)%4) of that row: sixteen consecutive rows,
@@ -268,7 +286,9 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
 
   issue(0, 0);
   if (n_blocks > 1) issue(1, 1);
-  for (int b = 0; b < n_blocks; ++b) {
+  // EXACT: see kExactBlocks
+  auto block_step = [&](int b, auto exact_c) __attribute__((always_inline)) {
+    constexpr bool EXACT = decltype(exact_c)::value;
     // this wave's loads of block b have landed once only those of block b+1 can be outstanding
     if (b + 1 < n_blocks) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -301,30 +321,40 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
         for (int v = 0; v < 16; ++v)
           if (8 * (v >> 2) + (v & 3) >= limit) acc[v] = -INFINITY;
       }
-      float bm = fmaxf(acc[0], acc[1]);
+      float s0, s1;
+      auto weigh = [&]() __attribute__((always_inline)) {
+        s0 = s1 = 0.f;
 #pragma unroll
-      for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, acc[v]), acc[v + 1]);
-      bm = max_across_halves(bm);
-      // the reference sits kWeightShift below the largest logit: weights up to 2^15, well inside fp16, and
-      // small ones far from its underflow.  Finite from the first block on: key 0 is always visible
-      const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
-      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 from -inf
-        l_run *= alpha;
-        l_chunk *= alpha;
+        for (int v = 0; v < 16; v += 2) {
+          pw[v] = __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run));
+          pw[v + 1] = __builtin_amdgcn_exp2f(fmaf(acc[v + 1], c, -m_run));
+          s0 += pw[v];
+          s1 += pw[v + 1];
+        }
+      };
+      auto raise = [&]() __attribute__((always_inline)) {  // the reference follows the largest logit
+        float bm = __builtin_elementwise_maximum(acc[0], acc[1]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int v = 2; v < 16; v += 2)
+          bm = __builtin_elementwise_maximum(__builtin_elementwise_maximum(bm, acc[v]), acc[v + 1]);
+        bm = max_across_halves(bm);
+        const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
+        if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+          const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 from -inf
+          l_run *= alpha;
+          l_chunk *= alpha;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) ot[t][v] *= alpha;
-        m_run = m_new;
-      }
-      float s0 = 0.f, s1 = 0.f;
+          for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        pw[v] = __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run));
-        pw[v + 1] = __builtin_amdgcn_exp2f(fmaf(acc[v + 1], c, -m_run));
-        s0 += pw[v];
-        s1 += pw[v + 1];
+            for (int v = 0; v < 16; ++v) ot[t][v] *= alpha;
+          m_run = m_new;
+        }
+      };
+      if (EXACT) raise();
+      weigh();
+      if (!EXACT && __builtin_amdgcn_ballot_w64(!(s0 + s1 < kMaxBlockSum)) != 0) {
+        raise();
+        weigh();
       }
       l_run += s0 + s1;
     } else {
@@ -361,7 +391,12 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
         }
       }
     }
-  }
+  };
+  const int n_exact = min(n_blocks, kExactBlocks);
+#pragma clang loop unroll(disable)
+  for (int b = 0; b < n_exact; ++b) block_step(b, std::true_type());
+#pragma clang loop unroll(disable)
+  for (int b = n_exact; b < n_blocks; ++b) block_step(b, std::false_type());
 
   // ---- results -------------------------------------------------------------------------------------
   const float l_tot = sum_across_halves(l_run);

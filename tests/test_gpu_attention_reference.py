@@ -1,0 +1,49 @@
+"""GPU parity of the fused attention pass where its softmax reference has to move late: rows whose logits grow along
+the prompt, by a little in every block (the reference stays) or by far more than fp16 holds (it must follow), and
+rows whose first keys are the heaviest."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from helpers import to_np
+from oracle import shotkv_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+OUT_TOL = 1e-3        # |dO| <= OUT_TOL * max|O| per query row (weights reach the matrix cores with 11 significant bits)
+
+
+@pytest.fixture(scope="module")
+def kv():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_01941_amd import shotkv
+    shotkv.load_library()
+    return shotkv
+
+
+@pytest.mark.parametrize("growth", ["steady", "late_jump", "jump_each_block", "falling", "huge"])
+@pytest.mark.parametrize("N", [513, 1100])
+def test_logits_that_grow_along_the_prompt(kv, N, growth):
+    H, Hkv, W, D, n = 4, 2, 32, 128, 5
+    rng = np.random.default_rng(N + len(growth))
+    q = np.abs(rng.standard_normal((1, H, N, D), dtype=np.float32))
+    k = 0.05 * rng.standard_normal((1, Hkv, N, D), dtype=np.float32)
+    t = np.arange(N, dtype=np.float32)[:, None]
+    k += {"steady": 0.25 * t / N, "late_jump": 0.4 * (t >= 512 + 7), "jump_each_block": 0.02 * (t // 32),
+          "falling": 0.4 * (1 - t / N), "huge": 8.0 * (t >= 40) * (t % 97 == 3)}[growth]
+    scale = 1.0 / math.sqrt(D)
+    q, k = (torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (q, k))
+    v = torch.from_numpy(rng.standard_normal((1, Hkv, N, D), dtype=np.float32)).to(torch.bfloat16).cuda()
+    off = torch.from_numpy(np.linspace(3, N - 40, n + 1).astype(np.int32)[None]).cuda()
+    bud = torch.tensor([N // 2], dtype=torch.int32, device="cuda")
+    attn, res = kv.prefill_attention_compress(q, k, v, off, bud, N // 2, W, scale)
+    torch.cuda.synchronize()
+    ref = orc.causal_attention(to_np(q[0]), to_np(k[0]), to_np(v[0]), scale)
+    got = attn[0].cpu().numpy()
+    assert np.all(np.abs(got - ref) <= OUT_TOL * np.abs(ref).max(axis=2, keepdims=True))
+    want = orc.prefill_compress(to_np(q[0, :, -W:]), to_np(k[0]), to_np(v[0]), off[0].cpu().numpy(), N // 2, scale)
+    # shots that get less than 1e-30 of the weight may underflow to zero
+    np.testing.assert_allclose(res.shot_scores[0].cpu().numpy(), want["scores"], rtol=2e-5, atol=1e-30)
