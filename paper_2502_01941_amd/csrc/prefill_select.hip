@@ -173,6 +173,35 @@ __device__ void sort_keys_descending(uint64_t (&k)[E], int n_pad, uint64_t* keys
   }
 }
 
+// First fit over the ranking by one wave, 64 ranks at a time: len[r] and shot[r] of rank r, keep[shot] = 1 where it
+// still fits.  A shot longer than what is left can never fit again, so only the others are candidates; the ones
+// ahead of the first candidate that overflows the running sum are kept together, that one is skipped, and the
+// rest go on with what is left.  A walk by one thread reads two words of LDS per rank one
+// after the other: this kernel took 43 us for 8 problems of 400 shots with it, 23 us with this one.
+__device__ void first_fit_walk(const int* len, const uint16_t* shot, int n, int left, uint8_t* keep) {
+  const int lane = threadIdx.x;
+  for (int r0 = 0; r0 < n; r0 += kWave) {
+    const int r = r0 + lane;
+    const int my_len = r < n ? len[r] : 0;
+    bool open = r < n && my_len <= left, taken = false;
+    while (__builtin_amdgcn_ballot_w64(open) != 0) {
+      int incl = open ? my_len : 0;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += up;
+      }
+      const uint64_t over = __builtin_amdgcn_ballot_w64(open && incl > left);
+      const int first = over ? __builtin_ctzll(over) : kWave;  // the first candidate that does not fit
+      if (open && lane < first) taken = true;
+      const int used = first > 0 ? __builtin_amdgcn_readlane(incl, first - 1) : 0;
+      left -= used;
+      open = open && lane > first && my_len <= left;
+    }
+    if (taken) keep[shot[r]] = 1;
+  }
+}
+
 template <bool MASS, bool SELECT>
 __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     const float* __restrict__ chunk_mass, int max_c, int group_shift, int H_kv,
@@ -299,13 +328,8 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
       const int inclusive = s_a[r] + (s_off[shot + 1] - s_off[shot]);
       if (inclusive <= shot_budget) s_keep[shot] = 1;
     }
-  } else if (tid == 0) {  // first-fit: inherently sequential over the ranking
-    int used = 0;
-    for (int r = 0; r < n_shots; ++r) {
-      const int shot = s_idx[r];
-      const int len = s_a[r];
-      if (used + len <= shot_budget) { used += len; s_keep[shot] = 1; }
-    }
+  } else if (tid < kWave) {
+    first_fit_walk(s_a, s_idx, n_shots, shot_budget, s_keep);
   }
   __syncthreads();
 
