@@ -210,21 +210,22 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
 
 }  // namespace
 
-#ifndef SHOTKV_DEC_TARGET_GROUPS
-#define SHOTKV_DEC_TARGET_GROUPS 1024
-#endif
-int decode_splits(int S, int H_kv, int total_tokens) {
-  // enough workgroups to fill 256 CUs several times over, but no split shorter than 128 tokens and
-  // no more splits than the finish kernel takes
+int decode_splits(int S, int H_kv, int G, int total_tokens) {
+  // Token ranges per (sequence, KV head).  The workgroups of a launch should all be resident at once, so a count is
+  // rounded down: 1056 workgroups of which 1024 fit take nearly twice as long as 960.  With more than two query
+  // heads per KV head three workgroups per CU are better than four (and with more than four that is what fits):
+  // 16 sequences of 4500 rows and 8 heads 73 us at 768 workgroups, 85 at 1024; 12 sequences of 5120 rows and 4
+  // heads 55 and 58 (62 at 1056); 16 of 5120 rows 69.8 and 70.8.  One or two heads: 54.1 and 52.8 us at 16
+  // sequences.  768 is passed over where it cannot be met within a sixth (64 sequences of 364 rows: 34.5 us with
+  // 512 workgroups, 33.8 with 1024).
   const int pairs = S * H_kv;
-  int splits = ceil_div(SHOTKV_DEC_TARGET_GROUPS, pairs);
-  const int max_by_tokens = total_tokens / 128 > 0 ? total_tokens / 128 : 1;
-  if (splits > max_by_tokens) splits = max_by_tokens;
-  const int min_by_range = ceil_div(total_tokens, kDecodeMaxRange);  // one piece of logits per workgroup
-  if (splits < min_by_range) splits = min_by_range;
-  if (splits > kDecodeMaxSplits) splits = kDecodeMaxSplits;
-  if (splits < 1) splits = 1;
-  return splits;
+  const int many = max(1, 1024 / pairs), few = max(1, 768 / pairs);
+  int splits = G > 2 && few * pairs >= 640 ? few : many;
+  // no range shorter than 96 tokens (one sequence of 3800 rows: 20.5 us, 21.6 with 128, 25 with 32) ...
+  splits = min(splits, max(1, total_tokens / 96));
+  // ... none longer than one piece of logits per workgroup, and no more than the finish kernel takes
+  splits = max(splits, ceil_div(total_tokens, kDecodeMaxRange));
+  return max(1, min(splits, kDecodeMaxSplits));
 }
 
 hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& st, float* out,

@@ -255,7 +255,7 @@ static int make_decode_dims(const shotkv_config* cfg, int S, int cap, int n_slot
   d->sm_scale = cfg->sm_scale;
   d->timing = cfg->timing_events;
   const int total = cap + n_slots;
-  d->n_splits = decode_splits(d->S, d->H_kv, total);  // pairs after the per-KV-head rewrite
+  d->n_splits = decode_splits(d->S, d->H_kv, d->G, total);  // pairs after the per-KV-head rewrite
   d->split_tokens = ceil_div(total, d->n_splits);
   return SHOTKV_OK;
 }
