@@ -28,13 +28,19 @@ __device__ __forceinline__ bool evict_before(float sa, int pa, float sb, int pb)
 // Score(t) = sum over heads of the attention weight (Eq. 7) and retains under the budget (Eq. 8: the
 // new token is exempt, the lowest score goes, the newest among equals); workgroups 1.. each merge the
 // split partials of kFinHeadsPerGroup query heads into the attention output (Eq. 9).  Every workgroup
-// first derives the softmax statistics of the heads it needs from the split partials; after that all
-// of its loads are independent of one another, so the kernel costs two memory round trips.
+// first derives the softmax statistics of the heads it needs from the split partials.  The kernel is bound by
+// its trips to memory, so what the second phase needs - the logits of the first round of slots, the first
+// partials - is requested ahead of the statistics and all of it is one trip: 7.8 us for one sequence of 3800 rows
+// and 32 heads (8.6 one after the other), 10.4 us for 16 sequences of 5121 (10.8).
+// kAhead: heads whose logits of a thread's first slot are requested that way.  32 cost 100 registers, one workgroup
+// per CU, which is dear where heads are few and sequences many (per-KV-head mode: 256 pairs of 4 heads 12.1 us),
+// so up to 8 heads take the small form.
 constexpr int kFinHeadsPerGroup = 4;
+template <int D, int kAhead>
 __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     const float2* __restrict__ part_ml, const float* __restrict__ part_o,
     const float* __restrict__ z_dec, int32_t* __restrict__ slot_pos,
-    const int32_t* __restrict__ new_slot_in, int n_slots, int H, int D, int n_splits, int budget,
+    const int32_t* __restrict__ new_slot_in, int n_slots, int H, int n_splits, int budget,
     int step_index, float* __restrict__ out, float* __restrict__ token_scores,
     int32_t* __restrict__ evicted_pos, int32_t* __restrict__ status) {
   const int s = blockIdx.y, tid = threadIdx.x;
@@ -42,6 +48,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   __shared__ float s_M[kFinMaxHeads];
   __shared__ float s_invL[kFinMaxHeads];
   __shared__ float s_w[kFinHeadsPerGroup][kDecodeMaxSplits];  // merge workgroups only
+  __shared__ __attribute__((aligned(16))) float s_o[kFinThreads * 4];  // merge workgroups only
   __shared__ float s_best_score[kFinWaves];
   __shared__ int s_best_pos[kFinWaves];
   __shared__ int s_best_slot[kFinWaves];
@@ -54,8 +61,51 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   // heads whose statistics this workgroup needs: all of them for the scores, its own for the merge
   const int h_lo = retain ? 0 : (static_cast<int>(blockIdx.x) - 1) * kFinHeadsPerGroup;
   const int h_hi = retain ? H : min(h_lo + kFinHeadsPerGroup, H);
-  // (requested before the slot index above is looked at, so that the two loads travel together)
-  // global softmax statistics per head: one wave per head, lanes over the splits; each split's weight
+
+  // A pool of budget + 1 slots is one more than a round of threads: the few slots past the last full
+  // round are scored by one wave each, lanes over the heads.
+  constexpr int kMaxExtra = 4;  // per wave
+  int n_extra = n_slots > kFinThreads ? n_slots % kFinThreads : 0;
+  if (n_extra > kMaxExtra * kFinWaves) n_extra = 0;
+  const int n_main = n_slots - n_extra;
+
+  // ---- what the second phase reads first -------------------------------------------------------------
+  float z_first[kAhead];  // (a slot of no token may hold anything)
+  int pos_first = -1;
+  float ez[kMaxExtra];
+  int epos[kMaxExtra];
+  // merge: a thread takes four columns of one head and every kTeams-th split
+  constexpr int kColumns = D / 4;
+  constexpr int kTeams = kFinThreads / (kFinHeadsPerGroup * kColumns);
+  const int mh = h_lo + tid / kColumns % kFinHeadsPerGroup, column = tid % kColumns;
+  const int team = tid / (kColumns * kFinHeadsPerGroup);
+  const float4* po = reinterpret_cast<const float4*>(part_o) + (head0 + min(mh, H - 1)) * n_splits * kColumns + column;
+  constexpr int kPartsAhead = 4;
+  float4 part_first[kPartsAhead];
+  if (retain) {
+#pragma unroll
+    for (int h = 0; h < kAhead; ++h)
+      z_first[h] = (h < H && tid < n_main) ? z_dec[(head0 + h) * n_slots + tid] : 0.f;
+    if (tid < n_main) pos_first = sp[tid];
+#pragma unroll
+    for (int k = 0; k < kMaxExtra; ++k) {
+      const int slot = n_main + wave + k * kFinWaves;
+      ez[k] = -INFINITY;
+      epos[k] = -1;
+      if (slot < n_slots) {
+        epos[k] = sp[slot];
+        if (lane < H) ez[k] = z_dec[(head0 + lane) * n_slots + slot];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kPartsAhead; ++j) {
+      const int i = team + j * kTeams;
+      part_first[j] = i < n_splits ? po[static_cast<size_t>(i) * kColumns] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+
+  // ---- global softmax statistics per head: one wave per head, lanes over the splits; each split's weight
   // 2^(m - M) is kept so that the merge below is a plain weighted sum
   // (a wave's heads are taken two at a time so that their first loads travel together)
   for (int h = h_lo + wave; h < h_hi; h += 2 * kFinWaves) {
@@ -63,17 +113,19 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     const bool two = h2 < h_hi;
     const float2* ml = part_ml + (head0 + h) * n_splits;
     const float2* ml2 = part_ml + (head0 + (two ? h2 : h)) * n_splits;
-    float M = -INFINITY, M2 = -INFINITY;
-    for (int i = lane; i < n_splits; i += kWave) {
-      const float a = ml[i].x, b = ml2[i].x;
-      M = fmaxf(M, a);
-      M2 = fmaxf(M2, b);
+    // the first 64 splits stay in registers, any others are looked at twice (out of cache)
+    const float2 none = make_float2(-INFINITY, 0.f);
+    const float2 a = lane < n_splits ? ml[lane] : none, b = lane < n_splits ? ml2[lane] : none;
+    float M = a.x, M2 = b.x;
+    for (int i = lane + kWave; i < n_splits; i += kWave) {
+      M = fmaxf(M, ml[i].x);
+      M2 = fmaxf(M2, ml2[i].x);
     }
     M = wave_max(M);
     M2 = wave_max(M2);
     float L = 0.f, L2 = 0.f;
-    for (int i = lane; i < n_splits; i += kWave) {  // second look at the same few bytes: out of cache
-      const float2 x = ml[i], y = ml2[i];
+    for (int i = lane; i < n_splits; i += kWave) {
+      const float2 x = i == lane ? a : ml[i], y = i == lane ? b : ml2[i];
       const float wgt = x.y > 0.f ? __builtin_amdgcn_exp2f(x.x - M) : 0.f;
       const float wgt2 = y.y > 0.f ? __builtin_amdgcn_exp2f(y.x - M2) : 0.f;
       L += x.y * wgt;
@@ -107,12 +159,30 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   __syncthreads();
 
   if (!retain) {  // attention output of this workgroup's heads
-    for (int idx = h_lo * D + tid; idx < h_hi * D; idx += kFinThreads) {
-      const int h = idx / D, dd = idx - h * D;
-      const float* po = part_o + (head0 + h) * n_splits * D + dd;
-      float acc = 0.f;
-      for (int i = 0; i < n_splits; ++i) acc = fmaf(po[static_cast<size_t>(i) * D], s_w[h - h_lo][i], acc);
-      out[(head0 + h) * D + dd] = acc * s_invL[h];
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](const float4& x, float w) {
+      acc.x = fmaf(x.x, w, acc.x);
+      acc.y = fmaf(x.y, w, acc.y);
+      acc.z = fmaf(x.z, w, acc.z);
+      acc.w = fmaf(x.w, w, acc.w);
+    };
+    if (mh < h_hi) {
+#pragma unroll
+      for (int j = 0; j < kPartsAhead; ++j) {
+        const int i = team + j * kTeams;
+        if (i < n_splits) add(part_first[j], s_w[mh - h_lo][i]);
+      }
+      for (int i = team + kPartsAhead * kTeams; i < n_splits; i += kTeams)
+        add(po[static_cast<size_t>(i) * kColumns], s_w[mh - h_lo][i]);
+    }
+    *reinterpret_cast<float4*>(&s_o[4 * tid]) = acc;
+    __syncthreads();
+    const int idx = h_lo * D + tid;  // team t's sums of these heads start at t * kFinHeadsPerGroup * D
+    if (tid < kFinHeadsPerGroup * D && idx < h_hi * D) {
+      float sum = 0.f;
+#pragma unroll
+      for (int t = 0; t < kTeams; ++t) sum += s_o[t * kFinHeadsPerGroup * D + tid];
+      out[head0 * D + idx] = sum * s_invL[idx / D];
     }
     return;
   }
@@ -120,33 +190,27 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   // retention scores and the eviction candidate
   float best_score = INFINITY;
   int best_pos = -1, best_slot = -1, count = 0;
-  // A pool of budget + 1 slots is one more than a round of threads: the few slots past the last full
-  // round are scored by one wave each, lanes over the heads, and their logits are requested here, ahead
-  // of the main loop, so that they do not cost a dependent trip to memory of their own.
-  constexpr int kMaxExtra = 4;  // per wave
-  int n_extra = n_slots > kFinThreads ? n_slots % kFinThreads : 0;
-  if (n_extra > kMaxExtra * kFinWaves) n_extra = 0;
-  const int n_main = n_slots - n_extra;
-  float ez[kMaxExtra];
-  int epos[kMaxExtra];
-#pragma unroll
-  for (int k = 0; k < kMaxExtra; ++k) {
-    const int slot = n_main + wave + k * kFinWaves;
-    ez[k] = -INFINITY;
-    epos[k] = -1;
-    if (slot < n_slots) {
-      epos[k] = (slot == new_slot) ? step_index : sp[slot];
-      if (lane < H) ez[k] = z_dec[(head0 + lane) * n_slots + slot];
-    }
-  }
+  constexpr int kHeadBatch = 16;  // loads in flight
   for (int slot = tid; slot < n_main; slot += kFinThreads) {
-    const int pos = (slot == new_slot) ? step_index : sp[slot];
+    const bool first = slot == tid;
+    const int pos = (slot == new_slot) ? step_index : first ? pos_first : sp[slot];
     float score = 0.f;
     if (pos >= 0) {
       ++count;
       const float* z = z_dec + head0 * n_slots + slot;
-      for (int h = 0; h < H; ++h)
-        score += __builtin_amdgcn_exp2f(z[static_cast<size_t>(h) * n_slots] - s_M[h]) * s_invL[h];
+      if (first) {
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h)
+          if (h < H) score += __builtin_amdgcn_exp2f(z_first[h] - s_M[h]) * s_invL[h];
+      }
+      for (int h0 = first ? kAhead : 0; h0 < H; h0 += kHeadBatch) {
+        float zz[kHeadBatch];
+#pragma unroll
+        for (int j = 0; j < kHeadBatch; ++j) zz[j] = z[static_cast<size_t>(min(h0 + j, H - 1)) * n_slots];
+#pragma unroll
+        for (int j = 0; j < kHeadBatch; ++j)
+          if (h0 + j < H) score += __builtin_amdgcn_exp2f(zz[j] - s_M[h0 + j]) * s_invL[h0 + j];
+      }
       if (slot != new_slot && (best_slot < 0 || evict_before(score, pos, best_score, best_pos))) {
         best_score = score; best_pos = pos; best_slot = slot;
       }
@@ -157,7 +221,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   for (int k = 0; k < kMaxExtra; ++k) {
     const int slot = n_main + wave + k * kFinWaves;
     if (slot < n_slots) {  // wave-uniform
-      const int pos = epos[k];
+      const int pos = slot == new_slot ? step_index : epos[k];
       float part = 0.f;
       if (pos >= 0 && lane < H) part = __builtin_amdgcn_exp2f(ez[k] - s_M[lane]) * s_invL[lane];
       // same order of the head sum as in the main loop would need a serial add; a tree sum over the
@@ -188,23 +252,32 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     s_best_slot[wave] = best_slot; s_count[wave] = count;
   }
   __syncthreads();  // also: every thread has read its slot_pos entries before thread 0 rewrites two
-  if (tid == 0) {
-    int total = s_count[0];  // this thread already holds wave 0's candidate
-    for (int w = 1; w < kFinWaves; ++w) {
-      total += s_count[w];
-      if (s_best_slot[w] >= 0 &&
-          (best_slot < 0 || evict_before(s_best_score[w], s_best_pos[w], best_score, best_pos))) {
-        best_score = s_best_score[w]; best_pos = s_best_pos[w]; best_slot = s_best_slot[w];
+  if (wave == 0) {
+    const bool has = lane < kFinWaves;
+    best_score = has ? s_best_score[lane] : INFINITY;
+    best_pos = has ? s_best_pos[lane] : -1;
+    best_slot = has ? s_best_slot[lane] : -1;
+    int total = has ? s_count[lane] : 0;
+#pragma unroll
+    for (int o = kFinWaves / 2; o > 0; o >>= 1) {
+      const float os = __shfl_xor(best_score, o, kWave);
+      const int op = __shfl_xor(best_pos, o, kWave);
+      const int ol = __shfl_xor(best_slot, o, kWave);
+      total += __shfl_xor(total, o, kWave);
+      if (ol >= 0 && (best_slot < 0 || evict_before(os, op, best_score, best_pos))) {
+        best_score = os; best_pos = op; best_slot = ol;
       }
     }
-    sp[new_slot] = step_index;
-    int ev = -1;
-    if (total > budget && best_slot >= 0) {
-      ev = best_pos;
-      sp[best_slot] = -1;
+    if (lane == 0) {
+      sp[new_slot] = step_index;
+      int ev = -1;
+      if (total > budget && best_slot >= 0) {
+        ev = best_pos;
+        sp[best_slot] = -1;
+      }
+      if (evicted_pos) evicted_pos[s] = ev;
+      status[s] = SHOTKV_ST_OK;
     }
-    if (evicted_pos) evicted_pos[s] = ev;
-    status[s] = SHOTKV_ST_OK;
   }
 }
 
@@ -233,9 +306,11 @@ hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& 
                                 const DecodeWorkspace& w, hipStream_t s) {
   if (d.H > kFinMaxHeads || d.n_splits > kDecodeMaxSplits) return hipErrorInvalidValue;
   KernelTimer timer(d.timing, kKernelDecodeFinish, s);
-  hipLaunchKernelGGL(decode_finish_kernel, dim3(1 + ceil_div(d.H, kFinHeadsPerGroup), d.S), dim3(kFinThreads), 0, s, w.part_ml, w.part_o, w.z_dec,
-                     st.slot_pos, w.new_slot, d.n_slots, d.H, d.D, d.n_splits, d.budget, d.step, out,
-                     token_scores, evicted_pos, status);
+  const dim3 grid(1 + ceil_div(d.H, kFinHeadsPerGroup), d.S);
+  auto* kernel = d.D == 128 ? (d.H <= 8 ? decode_finish_kernel<128, 8> : decode_finish_kernel<128, 32>)
+                            : (d.H <= 8 ? decode_finish_kernel<64, 8> : decode_finish_kernel<64, 32>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kFinThreads), 0, s, w.part_ml, w.part_o, w.z_dec, st.slot_pos, w.new_slot,
+                     d.n_slots, d.H, d.n_splits, d.budget, d.step, out, token_scores, evicted_pos, status);
   return hipGetLastError();
 }
 
