@@ -109,7 +109,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr int kVShares = 128;        // shares of a V plane whose maxima are taken separately (fused attention path)
 constexpr int kOneSlice = 1 << 30;   // group_keys where the whole key axis is one slice
 
-int score_group_keys(int P, int H_kv, int n_tokens, int n_shots);  // keys per workgroup of the score kernel
+int score_group_keys(int P, int H_kv, int row_blocks, int n_tokens, int n_shots);  // keys per workgroup of the score kernel
 
 inline PrefillWorkspace carve_prefill(void* base, int P, int H_kv, int R, int n_tokens, int n_shots,
                                       int group_keys, size_t vt_bytes = 0) {

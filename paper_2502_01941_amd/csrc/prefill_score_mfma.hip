@@ -3,7 +3,7 @@
 // Shape: bf16 or fp32, head_dim 64 or 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6
 // (bf16) or 8 blocks of 32 rows; rows past G*W are zero operands whose statistics are written as -inf.
 //
-// A workgroup is a pair of waves (one wave for a single row block) that takes one slice of a KV head's key axis
+// A workgroup is a pair of waves (one wave for a single row block, four for small launches and for 256 rows) that takes one slice of a KV head's key axis
 // and walks it in blocks of 32 keys.  It finds the shot boundaries inside its slice itself (one pass over the
 // offsets, in flight together with the queries and the first blocks).  Each wave keeps
 // its share of the window queries in registers as MFMA B operands and computes
@@ -13,9 +13,9 @@
 // contains a chunk boundary credits its weights to the chunks on either side with masked in-lane sums.
 //
 // K blocks are streamed global -> LDS with 16-byte direct-to-LDS loads (whole 256-byte rows, fully
-// coalesced; each wave fetches half of every block) into a ring of three buffers, so two blocks are
-// in flight while one is being consumed; both waves read the whole block back in MFMA A-operand
-// layout.  One s_barrier per block tells the pair that a block has landed and that the buffer of the
+// coalesced; each wave fetches its share of every block) into a ring of three buffers, so two blocks are
+// in flight while one is being consumed; all waves read the whole block back in MFMA A-operand
+// layout.  One s_barrier per block tells the waves that a block has landed and that the buffer of the
 // block before it may be refilled.  With ~166 registers per wave three waves fit on a SIMD.
 //
 // LDS layout of a block (KeyLayout): a direct-to-LDS instruction writes 64 consecutive 16-byte slots, so a
@@ -354,15 +354,9 @@ __device__ __forceinline__ void credit_elements(const floatx16 (&e)[NQW], uint32
 
 constexpr int kEndCache = 128;  // shot boundaries of a slice kept in LDS
 
-template <typename T, int D, int NQB>
+template <typename T, int D, int NQB, int WAVES>
 struct GroupShape {
-#ifndef SHOTKV_SCORE_MAX_WAVES
-#define SHOTKV_SCORE_MAX_WAVES 2
-#endif
-  static constexpr bool kF32 = sizeof(T) == 4;
-  // waves per workgroup: a pair in bf16, up to four in fp32 (one or two query blocks each)
-  static constexpr int kMaxWaves = kF32 ? 4 : SHOTKV_SCORE_MAX_WAVES;
-  static constexpr int kWaves = NQB < kMaxWaves ? NQB : kMaxWaves;
+  static constexpr int kWaves = WAVES;                                      // waves per workgroup
   static constexpr int kNQW = NQB / kWaves;                                 // query blocks per wave
   static constexpr int kLoads = Element<T, D>::kLoadsPerBlock / kWaves;     // load instructions per wave per block
   static_assert(NQB % kWaves == 0 && Element<T, D>::kLoadsPerBlock % kWaves == 0, "even shares");
@@ -376,13 +370,13 @@ struct GroupShape {
   static constexpr int kMinWavesPerSimd = kLdsWaves < 1 ? 1 : kLdsWaves < kRegWaves ? kLdsWaves : kRegWaves;
 };
 
-template <typename T, int D, int NQB>
-__global__ __launch_bounds__((GroupShape<T, D, NQB>::kThreads), (GroupShape<T, D, NQB>::kMinWavesPerSimd)) void
+template <typename T, int D, int NQB, int WAVES>
+__global__ __launch_bounds__((GroupShape<T, D, NQB, WAVES>::kThreads), (GroupShape<T, D, NQB, WAVES>::kMinWavesPerSimd)) void
 score_partials_mfma_kernel(
     const T* __restrict__ q_obs, const T* __restrict__ k, int n_tokens, int H, int H_kv, int W,
     int n_rows, float c, const int32_t* __restrict__ shot_offsets, int share, int n_shots, int group_keys,
     int max_c, float* __restrict__ partial, float* __restrict__ group_stat) {
-  typedef GroupShape<T, D, NQB> S;
+  typedef GroupShape<T, D, NQB, WAVES> S;
   typedef Element<T, D> E;
   constexpr int NQW = S::kNQW;
   constexpr int R = NQB * 32;
@@ -621,7 +615,7 @@ score_partials_mfma_kernel(
 
 }  // namespace
 
-int score_group_keys(int P, int H_kv, int n_tokens, int n_shots) {
+int score_group_keys(int P, int H_kv, int row_blocks, int n_tokens, int n_shots) {
 #ifdef SHOTKV_SCORE_GROUP_KEYS
   return SHOTKV_SCORE_GROUP_KEYS;
 #else
@@ -630,12 +624,13 @@ int score_group_keys(int P, int H_kv, int n_tokens, int n_shots) {
   // batches of 1 to 128 problems of 32K tokens, 2048-key slices win from about four thousand workgroups
   // on, 1024-key slices from about one thousand on, and below that the count matters more than the length: one
   // problem of 2000 / 4000 tokens (8 KV heads) takes 24.3 / 26.0 us with 128-key slices, 27.2 / 28.5 us with 256;
-  // from 8192 tokens on 256 is faster (31.7 against 32.5 us).
+  // from 8192 tokens on 256 is faster (31.7 against 32.5 us), 16384 tokens 36.1 with 256 and 37.6 with 512,
+  // 32768 tokens 47.4 and 43.6 (128 query rows on four waves; 32 or 160 rows on fewer: 38.6 and 40.3, 59.1 and 60.5).
   const long total_keys = static_cast<long>(n_tokens) * H_kv * P;
   long keys = total_keys < 48L * 1024L ? 128 : 256;
   if (total_keys >= 2048L * 4096L) keys = 2048;
   else if (total_keys >= 1024L * 1024L) keys = 1024;
-  else if (total_keys >= 512L * 1024L) keys = 512;
+  else if (total_keys >= ((row_blocks & 3) ? 512L : 256L) * 1024L) keys = 512;
   // sentence-sized units: most blocks hold a boundary and cost twice a plain block, so the workgroups'
   // run times differ more and shorter ones balance better (3 % at 1240 units per 32K tokens)
   if (n_shots > 0 && n_tokens / n_shots < 64 && keys > 512) keys = 512;
@@ -649,26 +644,46 @@ int score_row_blocks(int dtype, int rows) {
   return need <= 2 ? need : need <= 4 ? 4 : (need <= 6 && dtype == SHOTKV_BF16) ? 6 : 8;
 }
 
-template <typename T, int D, int NQB>
+template <typename T, int D, int NQB, int WAVES>
 static void launch_score(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
                          const PrefillWorkspace& w, hipStream_t s) {
-  hipLaunchKernelGGL((score_partials_mfma_kernel<T, D, NQB>), dim3(w.n_groups, d.H_kv, d.P),
-                     dim3(GroupShape<T, D, NQB>::kThreads), 0, s, static_cast<const T*>(q_obs),
+  hipLaunchKernelGGL((score_partials_mfma_kernel<T, D, NQB, WAVES>), dim3(w.n_groups, d.H_kv, d.P),
+                     dim3(GroupShape<T, D, NQB, WAVES>::kThreads), 0, s, static_cast<const T*>(q_obs),
                      static_cast<const T*>(k), d.n_tokens, d.H, d.H_kv, d.W, d.R_rows, d.sm_scale * kLog2e,
                      off, d.share, d.n_shots, w.group_keys, w.max_c, w.partial, w.group_stat);
+}
+
+// Waves that share the query blocks of a workgroup.  With four (one block each at 128 rows) a launch of few
+// workgroups reaches all SIMDs and a block of keys takes half as long; with two every block of keys is read from LDS
+// half as often, which is what counts once the chip is full.  Whole compression, four against two waves, 8 KV heads,
+// 128 rows, head_dim 128: 8192 tokens 29.6 / 31.5 us, 4 x 32768 93 / 99, 32 x 32768 545 / 550, 64 x 32768 1074 / 1071,
+// 128 x 32768 2080 / 2049; units of 25 tokens 4 x 32768 173 / 177, 32 x 32768 986 / 946; head_dim 64: 8 x 16384
+// 75 / 81, 16 x 16001 122 / 118.  256 rows always take four (two blocks each instead of four, which spills):
+// 32 x 32768 805 / 924 us.
+static bool four_waves(const PrefillDims& d) {
+  const long total_keys = static_cast<long>(d.n_tokens) * d.H_kv * d.P;
+  const bool short_units = d.n_shots > 0 && d.n_tokens / d.n_shots < 64;
+  return total_keys < (d.D == 64 ? 3L << 19 : short_units ? 2L << 20 : 12L << 20);
 }
 
 template <typename T, int D>
 static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
                                     const PrefillWorkspace& w, hipStream_t s) {
+  constexpr bool kF32 = sizeof(T) == 4;
   switch (d.R / 32) {
-    case 1: launch_score<T, D, 1>(d, q_obs, k, off, w, s); break;
-    case 2: launch_score<T, D, 2>(d, q_obs, k, off, w, s); break;
-    case 4: launch_score<T, D, 4>(d, q_obs, k, off, w, s); break;
+    case 1: launch_score<T, D, 1, 1>(d, q_obs, k, off, w, s); break;
+    case 2: launch_score<T, D, 2, 2>(d, q_obs, k, off, w, s); break;
+    case 4:
+      if constexpr (!kF32)
+        if (!four_waves(d)) { launch_score<T, D, 4, 2>(d, q_obs, k, off, w, s); break; }
+      launch_score<T, D, 4, 4>(d, q_obs, k, off, w, s);
+      break;
     case 6:
-      if constexpr (sizeof(T) == 2) { launch_score<T, D, 6>(d, q_obs, k, off, w, s); break; }
+      if constexpr (!kF32) { launch_score<T, D, 6, 2>(d, q_obs, k, off, w, s); break; }
       return hipErrorInvalidValue;
-    case 8: launch_score<T, D, 8>(d, q_obs, k, off, w, s); break;
+    case 8:
+      launch_score<T, D, 8, 4>(d, q_obs, k, off, w, s);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -78,7 +78,7 @@ int make_prefill_dims(const shotkv_config* cfg, int P, int n_tokens, int n_shots
 
 PrefillWorkspace carve(const PrefillDims& d, void* base) {
   return carve_prefill(base, d.P, d.H_kv, d.R, d.n_tokens, d.n_shots,
-                       score_group_keys(d.P, d.H_kv, d.n_tokens, d.n_shots));
+                       score_group_keys(d.P, d.H_kv, d.R / 32, d.n_tokens, d.n_shots));
 }
 
 int from_hip(hipError_t e) { return e == hipSuccess ? SHOTKV_OK : SHOTKV_E_LAUNCH; }
