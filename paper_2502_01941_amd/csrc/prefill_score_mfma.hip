@@ -3,13 +3,14 @@
 // Shape: bf16 or fp32, head_dim 64 or 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6
 // (bf16) or 8 blocks of 32 rows; rows past G*W are zero operands whose statistics are written as -inf.
 //
-// A workgroup is a pair of waves (one wave for a single row block, four for small launches and for 256 rows) that takes one slice of a KV head's key axis
-// and walks it in blocks of 32 keys.  It finds the shot boundaries inside its slice itself (one pass over the
+// A workgroup is a pair of waves (one wave for a single row block, four for small launches and for 256 rows) that
+// takes one slice of a KV head's key axis and walks it in blocks of 32 keys.  It finds the shot boundaries inside
+// its slice itself (one pass over the
 // offsets, in flight together with the queries and the first blocks).  Each wave keeps
 // its share of the window queries in registers as MFMA B operands and computes
-// S^T[32 keys x 32 queries] = K_blk * Q^T per row block with v_mfma_f32_32x32x16_bf16 (fp32 inputs:
-// v_mfma_f32_32x32x2_f32, full single precision).  Keys run along the accumulator registers and queries along the lanes, so the row-softmax statistics (max and sum over
-// keys) are in-lane reductions; only the two lane halves are merged, once per chunk.  A block that
+// S^T[32 keys x 32 queries] = K_blk * Q^T per row block with v_mfma_f32_32x32x16_bf16 (fp32
+// inputs: six of them per step, see below).  Keys run along the accumulator registers and queries along the
+// lanes, so the row-softmax statistics (max and sum over keys) are in-lane reductions; only the two lane halves are merged, once per chunk.  A block that
 // contains a chunk boundary credits its weights to the chunks on either side with masked in-lane sums.
 //
 // K blocks are streamed global -> LDS with 16-byte direct-to-LDS loads (whole 256-byte rows, fully
@@ -31,10 +32,13 @@
 //   512-byte rows (fp32, head_dim 128): row r starts at r*512 + (r/2)*32 and column c sits in slot c ^ (r%2);
 //     sixteen rows then cover the banks and every step is an immediate offset from one lane base.
 //
-// fp32: the matrix unit takes 16 times as long per product as in bf16, so the operand reads weigh little: one
-// query block per wave (up to four waves per workgroup, all reading the same block) keeps the query operands
-// at 64 registers.  Bound by the matrix unit: 4 problems of 4001 tokens, 8 KV heads, 128 query rows, head_dim
-// 128 in 62 us = 68 TFLOP/s (two workgroups per CU; plain vector arithmetic took 394 us).
+// fp32: the matrix unit's own fp32 form takes 16 times as long per product as bf16, so both operands are split
+// exactly into three bf16 parts (split_f32) and six products of parts are summed in fp32, 0.37 of that time.  Error
+// of the scores against float64 over head layouts, windows and 1001 .. 65000 tokens: 0.8 - 2.6e-7 of the norm,
+// with the fp32 form 0.9 - 2.7e-7.  One query block per wave (96 operand registers at head_dim 128), up to eight
+// waves per workgroup, all reading the same block.  4 problems of 4001 tokens, 8 KV heads, 128 query rows,
+// head_dim 128: 36 us, with the fp32 form 48, with plain vector arithmetic 394; 16 of 8192 tokens (whole call)
+// 338 us, with the fp32 form 420.
 //
 // The direct-to-LDS loads are written as inline assembly and their completion is tracked by hand with
 // s_waitcnt vmcnt: when they are visible to the compiler it makes every LDS read wait for all loads
@@ -94,6 +98,8 @@ template <typename T, int D> struct Element {
   typedef typename Operand<T>::Vec Vec;
   static constexpr int kRowBytes = D * static_cast<int>(sizeof(T));
   static constexpr int kSteps = kRowBytes / 32;
+  // query operand registers (vectors of 8 bf16): one per step in bf16, three parts per pair of steps in fp32
+  static constexpr int kQueryVecs = sizeof(T) == 2 ? kSteps : 3 * kSteps / 2;
   static constexpr int kLoadsPerBlock = kBlockKeys * kRowBytes / 1024;  // 1 KB direct-to-LDS instructions
   static constexpr int kBufBytes = kLoadsPerBlock * KeyLayout<kRowBytes>::kLoadBytes;
   typedef KeyLayout<kRowBytes> Layout;
@@ -101,11 +107,37 @@ template <typename T, int D> struct Element {
 __device__ __forceinline__ floatx16 multiply_step(bf16x8 a, bf16x8 b, floatx16 acc) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
 }
-__device__ __forceinline__ floatx16 multiply_step(floatx4 a, floatx4 b, floatx16 acc) {
+// fp32 as three bf16 parts, exactly: each part is the truncation of what the ones before leave (8 + 8 + 8 bits).
+// Every product of two parts is exact in fp32, and of the nine the six down to 2^-16 of the first are taken: what is
+// left out is below 2^-23 of |q||k| per element, an fp32 multiply-add's own rounding.
+struct Split { bf16x8 hi, mid, lo; };
+__device__ __forceinline__ Split split_f32(floatx4 a, floatx4 b) {
+  u32x4 h, m, l;
+  auto parts = [](float x, uint32_t& hi, uint32_t& mid, uint32_t& lo) __attribute__((always_inline)) {
+    hi = __float_as_uint(x);
+    const float r = x - __uint_as_float(hi & 0xffff0000u);
+    mid = __float_as_uint(r);
+    lo = __float_as_uint(r - __uint_as_float(mid & 0xffff0000u));
+  };
 #pragma unroll
-  for (int e = 0; e < 4; ++e)  // lanes of half h supply element 4h + e of the step on both sides
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
-  return acc;
+  for (int e = 0; e < 4; ++e) {
+    const float x0 = e < 2 ? a[2 * e] : b[2 * e - 4], x1 = e < 2 ? a[2 * e + 1] : b[2 * e - 3];
+    uint32_t h0, m0, l0, h1, m1, l1;
+    parts(x0, h0, m0, l0);
+    parts(x1, h1, m1, l1);
+    h[e] = __builtin_amdgcn_perm(h1, h0, 0x07060302u);  // the upper halves of both
+    m[e] = __builtin_amdgcn_perm(m1, m0, 0x07060302u);
+    l[e] = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
+  }
+  return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+__device__ __forceinline__ floatx16 multiply_split(const Split& a, bf16x8 bh, bf16x8 bm, bf16x8 bl, floatx16 acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo, bh, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid, bm, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, bl, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid, bh, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, bm, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, bh, acc, 0, 0, 0);
 }
 #ifndef SHOTKV_SCORE_RING
 #define SHOTKV_SCORE_RING 3
@@ -200,7 +232,7 @@ __device__ __forceinline__ void softmax_fold(floatx16 acc, float c, int half, in
 
 // S^T of one 32-key block and this wave's NQW query blocks
 template <typename T, int D, int NQW>
-__device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const typename Element<T, D>::Vec (&bq)[NQW][Element<T, D>::kSteps],
+__device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
                                              int lane, floatx16 (&acc)[NQW]) {
   typedef typename Element<T, D>::Layout L;
   typedef typename Element<T, D>::Vec Vec;
@@ -210,17 +242,29 @@ __device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const typename 
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
+  if constexpr (sizeof(T) == 2) {
 #pragma unroll
-  for (int ks = 0; ks < Element<T, D>::kSteps; ++ks) {
-    const Vec a = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, ks));
+    for (int ks = 0; ks < Element<T, D>::kSteps; ++ks) {
+      const Vec a = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, ks));
 #pragma unroll
-    for (int q = 0; q < NQW; ++q) acc[q] = multiply_step(a, bq[q][ks], acc[q]);
+      for (int q = 0; q < NQW; ++q) acc[q] = multiply_step(a, bq[q][ks], acc[q]);
+    }
+  } else {
+#pragma unroll
+    for (int kp = 0; kp < Element<T, D>::kSteps / 2; ++kp) {
+      const Vec a0 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp));
+      const Vec a1 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp + 1));
+      const Split a = split_f32(a0, a1);
+#pragma unroll
+      for (int q = 0; q < NQW; ++q)
+        acc[q] = multiply_split(a, bq[q][3 * kp], bq[q][3 * kp + 1], bq[q][3 * kp + 2], acc[q]);
+    }
   }
 }
 
 // One 32-key block against this wave's NQW query blocks (qb0 = index of its first one).
 template <typename T, int D, int NQW, bool MASKED, bool EXACT>
-__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const typename Element<T, D>::Vec (&bq)[NQW][Element<T, D>::kSteps], int lane,
+__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs], int lane,
                                               int qb0, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
@@ -237,7 +281,7 @@ __device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const typename
 // 2^(z - reference) of every query stay in `e` so that the caller can credit them to the chunks on either
 // side of each boundary.  Nothing is added to l_run here.
 template <typename T, int D, int NQW, bool MASKED>
-__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const typename Element<T, D>::Vec (&bq)[NQW][Element<T, D>::kSteps], int lane, int qb0,
+__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs], int lane, int qb0,
                                               int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW],
                                               floatx16 (&e)[NQW]) {
@@ -363,7 +407,7 @@ struct GroupShape {
   static constexpr int kThreads = kWaves * kWave;
   // Waves per SIMD the registers are budgeted for: what the query operands leave room for (bf16, head_dim 128:
   // three waves with up to two query blocks per wave, two with more), and no more than the LDS admits.
-  static constexpr int kQueryRegs = kNQW * Element<T, D>::kSteps * 4;
+  static constexpr int kQueryRegs = kNQW * Element<T, D>::kQueryVecs * 4;
   static constexpr int kRegWaves =
       (kQueryRegs > 64 || kNQW > 2) ? 2 : kQueryRegs > 32 ? SHOTKV_SCORE_WAVES_PER_SIMD : SHOTKV_SCORE_WAVES_PER_SIMD + 1;
   static constexpr int kLdsWaves = 160 * 1024 / (kRing * Element<T, D>::kBufBytes + 1024) * kWaves / 4;
@@ -400,15 +444,26 @@ score_partials_mfma_kernel(
   // Query rows past n_rows = G*W (a row count that is not one of the instantiated ones) are zero operands; their
   // statistics are written as -inf, so they carry no weight further down.
   constexpr int kVec = 16 / sizeof(T);
-  typename E::Vec bq[NQW][E::kSteps];
+  bf16x8 bq[NQW][E::kQueryVecs];
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int qi = (qb0 + q) * 32 + (lane & 31);
-#pragma unroll
-    for (int ks = 0; ks < E::kSteps; ++ks) {
+    auto query = [&](int ks) __attribute__((always_inline)) {
       u32x4 raw = {0u, 0u, 0u, 0u};
       if (qi < n_rows) raw = *reinterpret_cast<const u32x4*>(q_rows + qi * D + ks * (2 * kVec) + (lane >> 5) * kVec);
-      bq[q][ks] = __builtin_bit_cast(typename E::Vec, raw);
+      return __builtin_bit_cast(typename E::Vec, raw);
+    };
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+      for (int ks = 0; ks < E::kSteps; ++ks) bq[q][ks] = query(ks);
+    } else {
+#pragma unroll
+      for (int kp = 0; kp < E::kSteps / 2; ++kp) {
+        const Split b = split_f32(query(2 * kp), query(2 * kp + 1));
+        bq[q][3 * kp] = b.hi;
+        bq[q][3 * kp + 1] = b.mid;
+        bq[q][3 * kp + 2] = b.lo;
+      }
     }
   }
   lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
@@ -461,7 +516,7 @@ score_partials_mfma_kernel(
 #pragma unroll
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
-    for (int ks = 0; ks < E::kSteps; ++ks) asm volatile("" ::"v"(bq[q][ks]));
+    for (int ks = 0; ks < E::kQueryVecs; ++ks) asm volatile("" ::"v"(bq[q][ks]));
   __syncthreads();
   seg0 = seg1 = 0;
 #pragma unroll
@@ -682,7 +737,7 @@ static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, con
       if constexpr (!kF32) { launch_score<T, D, 6, 2>(d, q_obs, k, off, w, s); break; }
       return hipErrorInvalidValue;
     case 8:
-      launch_score<T, D, 8, 4>(d, q_obs, k, off, w, s);
+      launch_score<T, D, 8, kF32 ? 8 : 4>(d, q_obs, k, off, w, s);  // fp32 operands: one block per wave
       break;
     default: return hipErrorInvalidValue;
   }
