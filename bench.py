@@ -1,7 +1,7 @@
 """Benchmark of the ShotKV hot path on one MI355X.
 
-A step = one pass of the whole hot path over one batch of synthetic input: prefill compression (chunk
-plan, window-attention scores, per-shot reduction, selection, K/V compaction) of all 128 (layer, batch)
+A step = one pass of the whole hot path over one batch of synthetic input: prefill compression
+(window-attention scores, per-shot reduction, selection, K/V compaction) of all 128 (layer, batch)
 problems of the 32-layer x batch-4 x 32K-token Llama-3-8B-shaped workload, followed by one decode step
 (attention over the compressed caches + token retention) for the same 128 (layer, sequence) caches.
 Inputs are resident in HBM before the timed region.  The timed region carries no instrumentation; kernel

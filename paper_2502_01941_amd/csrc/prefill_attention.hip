@@ -19,7 +19,7 @@
 //                     contiguous; a small pre-pass packs V once into 32-key blocks [d][key] in exactly the
 //                     key order the accumulator registers have.
 //   precision         this product runs in fp16 (v_mfma_f32_32x32x16_f16): a weight keeps 11 significant bits
-//                     instead of bf16's 8, which holds the output within 4e-4 of its row maximum with one
+//                     instead of bf16's 8, which holds the output within 5.1e-4 of its row maximum with one
 //                     instruction per step (a bf16 weight is off by up to 2^-9; bf16 hi + lo would cost a
 //                     second instruction).  fp16's narrow range is dealt with by two exact power-of-two
 //                     scalings: the softmax reference sits 8 below a running maximum, so weights lie
