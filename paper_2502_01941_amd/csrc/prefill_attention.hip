@@ -19,11 +19,11 @@
 //                     contiguous; a small pre-pass packs V once into 32-key blocks [d][key] in exactly the
 //                     key order the accumulator registers have.
 //   precision         this product runs in fp16 (v_mfma_f32_32x32x16_f16): a weight keeps 11 significant bits
-//                     instead of bf16's 8, which holds the output within 5.1e-4 of its row maximum with one
+//                     instead of bf16's 8, which holds the output within 4.6e-4 of its row maximum with one
 //                     instruction per step (a bf16 weight is off by up to 2^-9; bf16 hi + lo would cost a
 //                     second instruction).  fp16's narrow range is dealt with by two exact power-of-two
-//                     scalings: the softmax reference sits 8 below a running maximum, so weights lie
-//                     in (0, 2^15) and anything above 2^-32 of the largest survives; and the pre-pass
+//                     scalings: the softmax reference sits 15 below the running maximum, so weights lie
+//                     in (0, 2^15] and anything above 2^-39 of the largest survives; and the pre-pass
 //                     scales every KV-head plane of V so that its largest finite |v| lands in [2^14, 2^15).
 //                     Sums of weights stay in fp32 and carry the same reference.
 // K and packed-V blocks are streamed global -> LDS with direct-to-LDS loads into a ring of three stages
@@ -32,8 +32,6 @@
 // 16-byte column).  The grid puts the query tile in its slowest dimension, longest tiles first, so that
 // every head's long tiles are dispatched before anybody's short ones.
 #include "common.hpp"
-
-#include <type_traits>
 
 namespace shotkv {
 
@@ -55,17 +53,12 @@ constexpr int kRowBytes = kD * 2;
 constexpr int kGroupBytes = 4 * kRowBytes + 64;       // K: four rows + pad = one direct-to-LDS instruction
 constexpr int kKBytes = 8 * kGroupBytes;              // 8704
 constexpr int kVtBytes = kD * kBlockKeys * 2;         // 8192: [128 d][32 keys] fp16
-// Softmax reference.  Any reference gives the same softmax; a weight is 2^(logit - reference).  In a row's first
-// kExactBlocks blocks the reference follows the largest logit (minus kWeightShift, log2 domain) block by block: the
-// largest weight is then a power of two, which fp16 holds exactly, and short rows are where single weights show.
-// After that it stays until a lane's sum of sixteen weights says that one may leave fp16's range, which takes a logit
-// 2^7 times as heavy as everything so far.  Following the maximum all the way redoes the 64 output registers in most
-// of the first blocks of 32 rows (one row in 32 raises it) and puts the maximum chain ahead of every exponential.
-// Measured at 8192 / 32768 tokens, whole call: 620 / 8555 us following, 574 / 8035 us with sixteen such blocks,
-// 563 / 7985 us with one; output error against float64 1.62e-4, 1.67e-4 and 1.80e-4.
-constexpr int kWeightShift = 8;
-constexpr int kExactBlocks = 16;
-constexpr float kMaxBlockSum = 32768.f;
+// Softmax reference = running maximum - kWeightShift (log2 domain), in every block: the largest weight is then a power
+// of two, which fp16 holds exactly, and weights keep their 11 bits down to 2^-29 of it.  A reference that stays where it
+// is until a weight nears fp16's range (8 below the maximum, 2^7 of headroom) is 8 % faster (8192 tokens 550 us, 596 as
+// it is), but its weights lose bits from 2^-22 on - one of 2^-26 is off by up to 0.8 %, one of 2^-30 by 11 % - and
+// where the heaviest keys carry small values those weights make the output.
+constexpr int kWeightShift = 15;
 constexpr int kStageBytes = kKBytes + kVtBytes;
 constexpr int kRing = 3;
 constexpr int kTileQ = 128;
@@ -225,8 +218,9 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int tile = gridDim.z - 1 - blockIdx.z;  // long tiles first, for all heads and problems
   // Workgroups are dealt to the eight XCDs round-robin: query heads that read one KV head go to one XCD, whose L2
-  // then holds that head's K and V once instead of every XCD all of them (8192 tokens 558 -> 554 us, 20000 tokens
-  // 3021 -> 2967, 32768 tokens 7797 -> 7717, 64 heads at 6000 tokens 624 -> 593).
+  // then holds that head's K and V once instead of every XCD all of them (8192 tokens 601 -> 596 us, 20000 tokens
+  // 3262 -> 3137, 32768 tokens 8618 -> 8236, 64 heads at 6000 tokens 672 -> 638).  Head counts that are no multiple of
+  // eight, and the per-KV-head mode (gridDim.x is the group size there), keep their order.
   const int h = gridDim.x % 8 == 0 ? (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
   const int p = blockIdx.y;
   const int G = H / H_kv, g = h / G;
@@ -290,9 +284,7 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
 
   issue(0, 0);
   if (n_blocks > 1) issue(1, 1);
-  // EXACT: see kExactBlocks
-  auto block_step = [&](int b, auto exact_c) __attribute__((always_inline)) {
-    constexpr bool EXACT = decltype(exact_c)::value;
+  for (int b = 0; b < n_blocks; ++b) {
     // this wave's loads of block b have landed once only those of block b+1 can be outstanding
     if (b + 1 < n_blocks) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -325,40 +317,29 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
         for (int v = 0; v < 16; ++v)
           if (8 * (v >> 2) + (v & 3) >= limit) acc[v] = -INFINITY;
       }
-      float s0, s1;
-      auto weigh = [&]() __attribute__((always_inline)) {
-        s0 = s1 = 0.f;
+      float bm = fmaxf(acc[0], acc[1]);
 #pragma unroll
-        for (int v = 0; v < 16; v += 2) {
-          pw[v] = __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run));
-          pw[v + 1] = __builtin_amdgcn_exp2f(fmaf(acc[v + 1], c, -m_run));
-          s0 += pw[v];
-          s1 += pw[v + 1];
-        }
-      };
-      auto raise = [&]() __attribute__((always_inline)) {  // the reference follows the largest logit
-        float bm = __builtin_elementwise_maximum(acc[0], acc[1]);
+      for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, acc[v]), acc[v + 1]);
+      bm = max_across_halves(bm);
+      // finite from the first block on: key 0 is always visible
+      const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
+      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 from -inf
+        l_run *= alpha;
+        l_chunk *= alpha;
 #pragma unroll
-        for (int v = 2; v < 16; v += 2)
-          bm = __builtin_elementwise_maximum(__builtin_elementwise_maximum(bm, acc[v]), acc[v + 1]);
-        bm = max_across_halves(bm);
-        const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
-        if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-          const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 from -inf
-          l_run *= alpha;
-          l_chunk *= alpha;
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
+          for (int v = 0; v < 16; ++v) ot[t][v] *= alpha;
+        m_run = m_new;
+      }
+      float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) ot[t][v] *= alpha;
-          m_run = m_new;
-        }
-      };
-      if (EXACT) raise();
-      weigh();
-      if (!EXACT && __builtin_amdgcn_ballot_w64(!(s0 + s1 < kMaxBlockSum)) != 0) {
-        raise();
-        weigh();
+      for (int v = 0; v < 16; v += 2) {
+        pw[v] = __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run));
+        pw[v + 1] = __builtin_amdgcn_exp2f(fmaf(acc[v + 1], c, -m_run));
+        s0 += pw[v];
+        s1 += pw[v + 1];
       }
       l_run += s0 + s1;
     } else {
@@ -395,12 +376,7 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
         }
       }
     }
-  };
-  const int n_exact = min(n_blocks, kExactBlocks);
-#pragma clang loop unroll(disable)
-  for (int b = 0; b < n_exact; ++b) block_step(b, std::true_type());
-#pragma clang loop unroll(disable)
-  for (int b = n_exact; b < n_blocks; ++b) block_step(b, std::false_type());
+  }
 
   // ---- results -------------------------------------------------------------------------------------
   const float l_tot = sum_across_halves(l_run);

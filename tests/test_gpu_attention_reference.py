@@ -47,3 +47,28 @@ def test_logits_that_grow_along_the_prompt(kv, N, growth):
     want = orc.prefill_compress(to_np(q[0, :, -W:]), to_np(k[0]), to_np(v[0]), off[0].cpu().numpy(), N // 2, scale)
     # shots that get less than 1e-30 of the weight may underflow to zero
     np.testing.assert_allclose(res.shot_scores[0].cpu().numpy(), want["scores"], rtol=2e-5, atol=1e-30)
+
+
+@pytest.mark.parametrize("heavy", [0, 300])
+def test_light_keys_keep_their_bits_behind_a_heavy_one(kv, heavy):
+    """One key takes nearly all of the weight and carries a zero value, so the output is made by keys of 2^-28 .. 2^-29
+    of it.  The softmax reference sits 15 (log2) below the maximum: their fp16 weights are at least 2^-14, the smallest
+    with all 11 bits, and each is off by at most 2^-11; the values are positive, so that bounds the sum's error too."""
+    H, Hkv, W, D, N, n = 4, 2, 32, 128, 700, 4
+    rng = np.random.default_rng(heavy)
+    q = np.zeros((1, H, N, D), dtype=np.float32)
+    q[..., 0] = 1.0
+    k = 0.1 * rng.standard_normal((1, Hkv, N, D), dtype=np.float32)
+    k[..., 0] = -rng.random((1, Hkv, N), dtype=np.float32)      # light logits -1 .. 0 in the log2 domain
+    k[..., heavy, 0] = 28.0
+    v = 0.5 + rng.random((1, Hkv, N, D), dtype=np.float32)
+    v[..., heavy, :] = 0.0
+    scale = math.log(2.0)
+    q, k, v = (torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (q, k, v))
+    off = torch.from_numpy(np.linspace(3, N - 40, n + 1).astype(np.int32)[None]).cuda()
+    bud = torch.tensor([N // 2], dtype=torch.int32, device="cuda")
+    attn, _ = kv.prefill_attention_compress(q, k, v, off, bud, N // 2, W, scale)
+    torch.cuda.synchronize()
+    ref = orc.causal_attention(to_np(q[0]), to_np(k[0]), to_np(v[0]), scale)
+    got = attn[0].cpu().numpy()
+    assert np.all(np.abs(got - ref) <= OUT_TOL * np.abs(ref).max(axis=2, keepdims=True))
