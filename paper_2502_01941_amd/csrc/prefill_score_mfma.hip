@@ -33,8 +33,8 @@
 //     sixteen rows then cover the banks and every step is an immediate offset from one lane base.
 //
 // fp32: the matrix unit's own fp32 form takes 16 times as long per product as bf16, so both operands are split
-// exactly into three bf16 parts (split_f32) and six products of parts are summed in fp32, 0.37 of that time.  Error
-// of the scores against float64 over head layouts, windows and 1001 .. 65000 tokens: 0.8 - 2.6e-7 of the norm,
+// into three bf16 parts (split_f32) and six products of parts are summed in fp32, 0.37 of that time; the few values
+// that bf16 parts cannot hold take the fp32 form (logits_block).  Error of the scores against float64 over head layouts, windows and 1001 .. 65000 tokens: 0.9 - 2.7e-7 of the norm,
 // with the fp32 form 0.9 - 2.7e-7.  One query block per wave (96 operand registers at head_dim 128), up to eight
 // waves per workgroup, all reading the same block.  4 problems of 4001 tokens, 8 KV heads, 128 query rows,
 // head_dim 128: 36 us, with the fp32 form 48, with plain vector arithmetic 394; 16 of 8192 tokens (whole call)
@@ -52,6 +52,8 @@ namespace shotkv {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float floatx2;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) const char lds_cchar;  // keeps LDS reads as ds_read, not flat
@@ -107,27 +109,27 @@ template <typename T, int D> struct Element {
 __device__ __forceinline__ floatx16 multiply_step(bf16x8 a, bf16x8 b, floatx16 acc) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
 }
-// fp32 as three bf16 parts, exactly: each part is the truncation of what the ones before leave (8 + 8 + 8 bits).
-// Every product of two parts is exact in fp32, and of the nine the six down to 2^-16 of the first are taken: what is
-// left out is below 2^-23 of |q||k| per element, an fp32 multiply-add's own rounding.
+// fp32 as three bf16 parts, each what the ones before leave rounded to nearest: |mid| <= 2^-8 and |lo| <= 2^-17 of the
+// element's leading power of two, both of either sign, and nothing is left.  Every product of two parts is exact in
+// fp32.  Of the nine the six largest are taken; the dropped mid * lo, lo * mid and lo * lo together stay below 2^-23.9
+// of |q||k| per element with no preferred sign - the rounding of one fp32 multiply-add.  (Truncated parts cost the same
+// instructions, but there the dropped products reach 2^-21 and all have the sign of q * k.)
+// Two things a bf16 part cannot hold: infinities, as well as elements above 2^128 - 2^119, which round up to one (the
+// parts behind them are NaN), and the last bits of elements below 2^-100 (logits_block).
 struct Split { bf16x8 hi, mid, lo; };
 __device__ __forceinline__ Split split_f32(floatx4 a, floatx4 b) {
   u32x4 h, m, l;
-  auto parts = [](float x, uint32_t& hi, uint32_t& mid, uint32_t& lo) __attribute__((always_inline)) {
-    hi = __float_as_uint(x);
-    const float r = x - __uint_as_float(hi & 0xffff0000u);
-    mid = __float_as_uint(r);
-    lo = __float_as_uint(r - __uint_as_float(mid & 0xffff0000u));
+  auto round2 = [](float x0, float x1) __attribute__((always_inline)) {
+    const floatx2 f = {x0, x1};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
   };
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float x0 = e < 2 ? a[2 * e] : b[2 * e - 4], x1 = e < 2 ? a[2 * e + 1] : b[2 * e - 3];
-    uint32_t h0, m0, l0, h1, m1, l1;
-    parts(x0, h0, m0, l0);
-    parts(x1, h1, m1, l1);
-    h[e] = __builtin_amdgcn_perm(h1, h0, 0x07060302u);  // the upper halves of both
-    m[e] = __builtin_amdgcn_perm(m1, m0, 0x07060302u);
-    l[e] = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
+    h[e] = round2(x0, x1);
+    const float r0 = x0 - __uint_as_float(h[e] << 16), r1 = x1 - __uint_as_float(h[e] & 0xffff0000u);
+    m[e] = round2(r0, r1);
+    l[e] = round2(r0 - __uint_as_float(m[e] << 16), r1 - __uint_as_float(m[e] & 0xffff0000u));
   }
   return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
 }
@@ -230,18 +232,32 @@ __device__ __forceinline__ void softmax_fold(floatx16 acc, float c, int half, in
   m_run = m_new;
 }
 
-// S^T of one 32-key block and this wave's NQW query blocks
+// Where the wave's queries lie in memory, and whether their logits may be taken from bf16 parts (fp32 only): every
+// query element is zero or between 2^-100 and 2^50, so that its parts are exact and that what a tiny key element's
+// parts lose (below 2^-126) cannot show, and the scale is below 2^30.
+template <typename T> struct Queries {
+  const T* rows;
+  int qb0, n_rows;
+  bool plain;
+};
+
+// S^T of one 32-key block and this wave's NQW query blocks.  fp32: from the bf16 parts; an infinite key element, or one
+// that rounds up to infinity, makes its logits NaN, and the block is then taken again in the matrix unit's fp32 form,
+// as every block is for queries that are not plain.
 template <typename T, int D, int NQW>
 __device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
-                                             int lane, floatx16 (&acc)[NQW]) {
+                                             const Queries<T>& src, int lane, floatx16 (&acc)[NQW]) {
   typedef typename Element<T, D>::Layout L;
   typedef typename Element<T, D>::Vec Vec;
   typedef __attribute__((address_space(3))) const Vec lds_vec;
   const int base = L::operand_base(lane & 31, lane >> 5);
+  auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int q = 0; q < NQW; ++q)
+    for (int q = 0; q < NQW; ++q)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
+  };
+  clear();
   if constexpr (sizeof(T) == 2) {
 #pragma unroll
     for (int ks = 0; ks < Element<T, D>::kSteps; ++ks) {
@@ -250,29 +266,51 @@ __device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&
       for (int q = 0; q < NQW; ++q) acc[q] = multiply_step(a, bq[q][ks], acc[q]);
     }
   } else {
+    if (src.plain) {
 #pragma unroll
-    for (int kp = 0; kp < Element<T, D>::kSteps / 2; ++kp) {
-      const Vec a0 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp));
-      const Vec a1 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp + 1));
-      const Split a = split_f32(a0, a1);
+      for (int kp = 0; kp < Element<T, D>::kSteps / 2; ++kp) {
+        const Vec a0 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp));
+        const Vec a1 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp + 1));
+        const Split a = split_f32(a0, a1);
+#pragma unroll
+        for (int q = 0; q < NQW; ++q)
+          acc[q] = multiply_split(a, bq[q][3 * kp], bq[q][3 * kp + 1], bq[q][3 * kp + 2], acc[q]);
+      }
+      float any = acc[0][0];  // NaN if one of the logits is
 #pragma unroll
       for (int q = 0; q < NQW; ++q)
-        acc[q] = multiply_split(a, bq[q][3 * kp], bq[q][3 * kp + 1], bq[q][3 * kp + 2], acc[q]);
+#pragma unroll
+        for (int v = 0; v < 16; v += 2)
+          any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(any, acc[q][v]), acc[q][v + 1]);
+      if (__builtin_amdgcn_ballot_w64(any != any) == 0) return;
+      clear();
+    }
+#pragma clang loop unroll(disable)
+    for (int ks = 0; ks < Element<T, D>::kSteps; ++ks) {
+      const Vec a = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, ks));
+#pragma unroll
+      for (int q = 0; q < NQW; ++q) {
+        const int qi = (src.qb0 + q) * 32 + (lane & 31);
+        Vec b = {0.f, 0.f, 0.f, 0.f};
+        if (qi < src.n_rows) b = *reinterpret_cast<const Vec*>(src.rows + qi * D + ks * 8 + (lane >> 5) * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc[q], 0, 0, 0);
+      }
     }
   }
 }
 
-// One 32-key block against this wave's NQW query blocks (qb0 = index of its first one).
+// One 32-key block against this wave's NQW query blocks.
 template <typename T, int D, int NQW, bool MASKED, bool EXACT>
-__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs], int lane,
-                                              int qb0, int key0, int rem, int causal_base, int W, float c,
+__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
+                                              const Queries<T>& src, int lane, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
   floatx16 acc[NQW];
-  logits_block<T, D, NQW>(lds_buf, bq, lane, acc);
+  logits_block<T, D, NQW>(lds_buf, bq, src, lane, acc);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
-    const int last_visible = causal_base + ((qb0 + q) * 32 + row) % W;
+    const int last_visible = causal_base + ((src.qb0 + q) * 32 + row) % W;
     softmax_fold<MASKED, EXACT>(acc[q], c, half, rem, key0, last_visible, m_run[q], l_run[q], l_grp[q]);
   }
 }
@@ -281,16 +319,16 @@ __device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (
 // 2^(z - reference) of every query stay in `e` so that the caller can credit them to the chunks on either
 // side of each boundary.  Nothing is added to l_run here.
 template <typename T, int D, int NQW, bool MASKED>
-__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs], int lane, int qb0,
-                                              int key0, int rem, int causal_base, int W, float c,
+__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
+                                              const Queries<T>& src, int lane, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW],
                                               floatx16 (&e)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
-  logits_block<T, D, NQW>(lds_buf, bq, lane, e);
+  logits_block<T, D, NQW>(lds_buf, bq, src, lane, e);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     if (MASKED) {
-      const int last_visible = causal_base + ((qb0 + q) * 32 + row) % W;
+      const int last_visible = causal_base + ((src.qb0 + q) * 32 + row) % W;
       const int limit = min(rem, last_visible - key0 + 1) - 4 * half;
 #pragma unroll
       for (int v = 0; v < 16; ++v)
@@ -445,12 +483,21 @@ score_partials_mfma_kernel(
   // statistics are written as -inf, so they carry no weight further down.
   constexpr int kVec = 16 / sizeof(T);
   bf16x8 bq[NQW][E::kQueryVecs];
+  uint32_t largest = 0u, smallest = UINT32_MAX;  // of the query elements' magnitudes, zeros left out; fp32 only
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int qi = (qb0 + q) * 32 + (lane & 31);
     auto query = [&](int ks) __attribute__((always_inline)) {
       u32x4 raw = {0u, 0u, 0u, 0u};
       if (qi < n_rows) raw = *reinterpret_cast<const u32x4*>(q_rows + qi * D + ks * (2 * kVec) + (lane >> 5) * kVec);
+      if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t mag = raw[e] & 0x7fffffffu;
+          largest = max(largest, mag);
+          smallest = min(smallest, mag - 1u);  // a zero wraps to the top
+        }
+      }
       return __builtin_bit_cast(typename E::Vec, raw);
     };
     if constexpr (sizeof(T) == 2) {
@@ -466,6 +513,10 @@ score_partials_mfma_kernel(
       }
     }
   }
+  Queries<T> src{q_rows, qb0, n_rows, true};
+  if constexpr (sizeof(T) == 4)
+    src.plain = __builtin_amdgcn_ballot_w64(largest > __float_as_uint(0x1p50f) ||
+                                            smallest < __float_as_uint(0x1p-100f) - 1u) == 0 && c < 0x1p30f;
   lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
   const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base));
   const int causal_base = n_tokens - W;
@@ -627,17 +678,17 @@ score_partials_mfma_kernel(
     lds_cchar* blk = lds_base + cur_buf * E::kBufBytes;
     if (cur_end >= cur_key0 + cur_rem) {  // no chunk ends inside the block
       if (first_block)
-        compute_block<T, D, NQW, true, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, true, true>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else if (masked)
-        compute_block<T, D, NQW, true, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, true, false>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else
-        compute_block<T, D, NQW, false, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, false, false>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
     } else {
       floatx16 e[NQW];
       if (masked)
-        weights_block<T, D, NQW, true>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, true>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       else
-        weights_block<T, D, NQW, false>(blk, bq, lane, qb0, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, false>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       uint32_t lo0 = 0u, lo1 = 0u;  // elements already credited (lower / upper lane half)
       do {
         const int hi = cur_end - cur_key0;  // wave-uniform, 1..31

@@ -13,7 +13,8 @@ from oracle import shotkv_oracle as orc
 pytestmark = pytest.mark.gpu
 
 # A logit is a sum of head_dim products in float32 (those of bf16 values are exact): at most 2 * head_dim
-# roundings of 2^-24 of its terms, and its absolute error is the weight's relative error.  2e-5 covers that for
+# roundings of 2^-24 of its terms (what the split of float32 elements drops is below one more per element), and its
+# absolute error is the weight's relative error.  2e-5 covers that for
 # the |logit| < 20 drawn here with the exponential's and the log's own few units in the last place.
 SCORE_RTOL = 2e-5
 
@@ -96,3 +97,53 @@ def test_offsets_out_of_order_stay_harmless(kv, attention):
         assert torch.equal(res.shot_scores[p], ref.shot_scores[i]) and torch.equal(res.shot_selected[p], ref.shot_selected[i])
         kept = int(ref.kept_count[i])
         assert int(res.kept_count[p]) == kept and torch.equal(res.k_out[p, :, :kept], ref.k_out[i, :, :kept])
+
+
+def _scores_and_oracle(kv, q, k, off, scale):
+    q, k = (torch.from_numpy(x.astype(np.float32)).cuda() for x in (q, k))
+    scores, status = kv.prefill_scores(q, k, torch.from_numpy(off[None]).cuda(), scale)
+    torch.cuda.synchronize()
+    assert status.cpu().tolist() == [0]
+    with np.errstate(invalid="ignore"):
+        ref = oracle_prefill(q[0], k[0], k[0], off, k.shape[2], scale)
+    return scores[0].cpu().numpy(), ref["scores"]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_float32_products_are_rounded_not_truncated(kv, D):
+    """Mantissas whose low parts are as large and of one sign as they get, 1 + 2^-7 - 2^-23 on both sides, in a product
+    of 65 that an exact -65 takes away again.  A float32 multiply-add rounds such a term by 65 * 2^-24; the logit is a
+    handful of roundings, here at most four, and its error is the weight's relative error.  A truncated low part would
+    be worth 65 * 2^-21, eight times the unit."""
+    N, W, x = 600, 8, 8 * (1 + 2.0**-7 - 2.0**-23)
+    q, k = np.zeros((1, 2, W, D)), np.zeros((1, 2, N, D))
+    q[..., 0], q[..., 33] = x, 65.0
+    k[:, :, 100:110, 0], k[:, :, 100:110, 33] = x, -1.0
+    off = np.array([0, 100, 110, N], dtype=np.int32)
+    got, want = _scores_and_oracle(kv, q, k, off, 1.0)
+    np.testing.assert_allclose(got, want, rtol=4 * 65 * 2.0**-24, atol=0)
+
+
+@pytest.mark.parametrize("G,W", [(1, 8), (2, 32), (4, 32), (8, 32)])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("case", ["minus_infinity", "largest_keys", "huge_queries"])
+def test_float32_values_over_the_whole_range(kv, D, G, W, case):
+    """Keys at minus infinity get no weight; keys near the largest float32 and queries far from one, whose product is
+    an ordinary number, count like any others."""
+    N, Hkv = 700, 2
+    rng = np.random.default_rng(G + D)
+    q = rng.standard_normal((1, Hkv * G, W, D), dtype=np.float32)
+    k = rng.standard_normal((1, Hkv, N, D), dtype=np.float32)
+    if case == "minus_infinity":
+        q[..., 5] = np.abs(q[..., 5]) + 0.1
+        k[:, :, 97:130, 5] = -np.inf
+        k[:, :, 400, 5] = -np.inf
+    elif case == "largest_keys":
+        q[..., 5] = 2.0**-126 * (1 + rng.random(q.shape[:3], dtype=np.float32))
+        k[..., 5] = 3.4e38 * rng.choice([-1, 1], size=k.shape[:3])
+    else:
+        q[..., 5] = 2.0**120 * rng.standard_normal(q.shape[:3], dtype=np.float32)
+        k[..., 5] = 2.0**-120 * rng.standard_normal(k.shape[:3], dtype=np.float32)
+    off = np.array([0, 50, 97, 130, 131, 400, 401, 690], dtype=np.int32)
+    got, want = _scores_and_oracle(kv, q, k, off, 1.0 / math.sqrt(D))
+    np.testing.assert_allclose(got, want, rtol=SCORE_RTOL, atol=0)
