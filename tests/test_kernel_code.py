@@ -1,0 +1,39 @@
+"""What the compiler makes of kernels whose speed hangs on it: loads that would wait for a whole stream in flight, and
+values that would pass through scratch memory.  Compiles the kernel file to assembly; needs no GPU."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2502_01941_amd import build
+
+
+def _kernels(source):
+    """{kernel name: its instructions} of one kernel file, with the flags that the library is built with."""
+    cmd = [build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, source), "-o", "-"]
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    assert proc.returncode == 0, proc.stderr
+    names = set(re.findall(r"^\s*\.amdhsa_kernel\s+(\S+)", proc.stdout, re.M))
+    kernels, current = {}, None
+    for line in proc.stdout.splitlines():
+        label = re.match(r"(_Z\w+):", line)
+        if label:
+            current = label.group(1) if label.group(1) in names else None
+            kernels.setdefault(current, [])
+        elif line.startswith("\t.section") or line.startswith(".Lfunc_end"):
+            current = None
+        elif current and re.match(r"\t[a-z]", line):
+            kernels[current].append(line.strip())
+    kernels.pop(None, None)
+    assert kernels and set(kernels) == names and all(kernels.values())
+    return kernels
+
+
+@pytest.mark.parametrize("source", ["prefill_score_mfma.hip"])
+def test_no_generic_or_scratch_access(source):
+    """A load through a generic pointer (global memory or LDS, decided at run time) waits for all vector memory, the
+    blocks in flight included; scratch is memory too."""
+    for name, code in _kernels(source).items():
+        found = [i for i in code if i.startswith(("flat_load", "flat_store", "scratch_load", "scratch_store"))]
+        assert not found, (name, found)
