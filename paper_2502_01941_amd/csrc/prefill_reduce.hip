@@ -85,7 +85,8 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int c = min(c0 + j * kTeams, c_end - 1);
-      x[j] = has_rows ? *reinterpret_cast<const float4*>(rows + static_cast<size_t>(c) * R) : lse;
+      x[j] = lse;  // (as one conditional expression it became a choice of pointers, and lse went through scratch)
+      if (has_rows) x[j] = *reinterpret_cast<const float4*>(rows + static_cast<size_t>(c) * R);
     }
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
