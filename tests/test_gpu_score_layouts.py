@@ -147,3 +147,17 @@ def test_float32_values_over_the_whole_range(kv, D, G, W, case):
     off = np.array([0, 50, 97, 130, 131, 400, 401, 690], dtype=np.int32)
     got, want = _scores_and_oracle(kv, q, k, off, 1.0 / math.sqrt(D))
     np.testing.assert_allclose(got, want, rtol=SCORE_RTOL, atol=0)
+
+
+def test_a_unit_of_many_slices(kv):
+    """One unit over 128 slices of the key axis and 8 KV heads: its first key takes nearly all of the mass, 8, and the
+    other thousand (slice, head) parts 2.2e-7 each, just under half a unit in the last place below 8, 2.8e-5 of it
+    together.  Added one after the other in float32 they would all be lost; in 64 sums side by side each addition is off
+    by at most half a unit below 1, 16 of them by 5e-7."""
+    H, W, D, N = 8, 1, 64, 32768
+    q, k = np.zeros((1, H, W, D)), np.zeros((1, H, N, D))
+    q[..., 0] = 1.0
+    k[:, :, 0, 0] = 30.125
+    off = np.array([0, N - 8], dtype=np.int32)
+    got, want = _scores_and_oracle(kv, q, k, off, math.log(2.0))
+    np.testing.assert_allclose(got, want, rtol=1e-5, atol=0)
