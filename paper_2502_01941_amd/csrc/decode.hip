@@ -283,17 +283,21 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
 
 }  // namespace
 
-int decode_splits(int S, int H_kv, int G, int total_tokens) {
+int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
   // Token ranges per (sequence, KV head).  The workgroups of a launch should all be resident at once, so a count is
   // rounded down: 1056 workgroups of which 1024 fit take nearly twice as long as 960.  With more than two query
-  // heads per KV head three workgroups per CU are better than four (and with more than four that is what fits):
+  // heads per KV head three workgroups per CU are better than four:
   // 16 sequences of 4500 rows and 8 heads 73 us at 768 workgroups, 85 at 1024; 12 sequences of 5120 rows and 4
   // heads 55 and 58 (62 at 1056); 16 of 5120 rows 69.8 and 70.8.  One or two heads: 54.1 and 52.8 us at 16
   // sequences.  768 is passed over where it cannot be met within a sixth (64 sequences of 364 rows: 34.5 us with
-  // 512 workgroups, 33.8 with 1024).
+  // 512 workgroups, 33.8 with 1024) - but not where three per CU is all that fits (more than four heads and rows of up to
+  // 256 bytes, by registers and LDS; 512-byte rows fit four): 33 sequences of 1800 rows, 8 heads per KV head, 73.4 us
+  // with 528 workgroups, 80.7 with 792; 50 of 900 rows 63.8 with 400, 75.0 with 800; 7 heads 51.3 and 57.9; 512-byte
+  // rows 120 and 112.5.
   const int pairs = S * H_kv;
   const int many = max(1, 1024 / pairs), few = max(1, 768 / pairs);
-  int splits = G > 2 && few * pairs >= 640 ? few : many;
+  const bool three_fit = G > 4 && row_bytes <= 256;
+  int splits = three_fit || (G > 2 && few * pairs >= 640) ? few : many;
   // no range shorter than 96 tokens (one sequence of 3800 rows: 20.5 us, 21.6 with 128, 25 with 32) ...
   splits = min(splits, max(1, total_tokens / 96));
   // ... none longer than one piece of logits per workgroup, and no more than the finish kernel takes

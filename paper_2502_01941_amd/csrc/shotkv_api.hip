@@ -255,7 +255,8 @@ static int make_decode_dims(const shotkv_config* cfg, int S, int cap, int n_slot
   d->sm_scale = cfg->sm_scale;
   d->timing = cfg->timing_events;
   const int total = cap + n_slots;
-  d->n_splits = decode_splits(d->S, d->H_kv, d->G, total);  // pairs after the per-KV-head rewrite
+  const int row_bytes = d->D * (d->dtype == SHOTKV_BF16 ? 2 : 4);
+  d->n_splits = decode_splits(d->S, d->H_kv, d->G, row_bytes, total);  // pairs after the per-KV-head rewrite
   d->split_tokens = ceil_div(total, d->n_splits);
   return SHOTKV_OK;
 }
