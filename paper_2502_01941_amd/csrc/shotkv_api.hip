@@ -257,6 +257,10 @@ static int make_decode_dims(const shotkv_config* cfg, int S, int cap, int n_slot
   const int total = cap + n_slots;
   const int row_bytes = d->D * (d->dtype == SHOTKV_BF16 ? 2 : 4);
   d->n_splits = decode_splits(d->S, d->H_kv, d->G, row_bytes, total);  // pairs after the per-KV-head rewrite
+  // Ranges of less than 128 tokens are for speed only: a step does not outgrow the static scratch array by them.
+  while (d->n_splits > max(1, total / 128) &&
+         carve_decode(nullptr, d->S, d->H, d->H_kv, d->D, n_slots, d->n_splits).bytes > SHOTKV_STATIC_SCRATCH_BYTES)
+    --d->n_splits;
   d->split_tokens = ceil_div(total, d->n_splits);
   return SHOTKV_OK;
 }

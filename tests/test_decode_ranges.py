@@ -33,3 +33,13 @@ def test_workgroups_are_resident_at_once(D, dtype, G):
         for S in range(1, 560, 1 if G > 4 else 7):
             n = _ranges(S, 2 * G, 2, D, dtype, total - 100, 100)
             assert n >= least and (n == max(least, 1) or 2 * S * n <= fit), (S, total, n)
+
+
+@pytest.mark.parametrize("S,H,Hkv,dtype,cap,n_slots", [
+    (64, 64, 8, torch.bfloat16, 2, 253), (64, 64, 8, torch.float32, 3, 252), (51, 32, 4, torch.float32, 1, 638),
+    (51, 32, 4, torch.bfloat16, 2, 637)])
+def test_short_ranges_do_not_outgrow_the_static_scratch(S, H, Hkv, dtype, cap, n_slots):
+    """Shapes whose partial sums fit the static scratch array with ranges of at least 128 tokens but would not with
+    shorter ones: the step takes them without a workspace of its own."""
+    n = _ranges(S, H, Hkv, 128, dtype, cap, n_slots)
+    assert S * H * (n * 130 + n_slots) * 4 <= 8 << 20
