@@ -100,7 +100,7 @@ template <> struct Widen<float> {
 };
 
 template <typename T, int D, int G, bool PIECES>
-__global__ __launch_bounds__(kThreads, G == 8 ? 3 : 4) void decode_partial_kernel(
+__global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_partial_kernel(
     const char* __restrict__ k_prefill, const char* __restrict__ v_prefill,
     const int32_t* __restrict__ prefill_count, char* __restrict__ k_dec, char* __restrict__ v_dec,
     const int32_t* __restrict__ slot_pos, int cap, int n_slots, int H, int H_kv, int n_group,
@@ -228,7 +228,10 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 4) void decode_partial_kerne
   }
 
   // The range is taken in pieces that the logit buffer holds.  Only contexts of over a million tokens have more
-  // than one (PIECES); a loop around the body costs the others registers for what the compiler moves out of it.
+  // than one (PIECES); a loop around the body costs the others registers for what the compiler moves out of it, and
+  // this form has the register budget of two waves per SIMD for the same reason: 1.2 million rows, 32 query / 8 KV
+  // heads, 1288 us with four (spills), 879 with three, 809 with two; 28 / 4 heads 969, 969 and 490; 16 / 4 at
+  // head_dim 64 497, 282 and 240.
   const int n_pieces = PIECES ? ceil_div(range_end - range_begin, kMaxRange) : range_end > range_begin;
   if (new_slot >= 0)
 #pragma clang loop unroll(disable)

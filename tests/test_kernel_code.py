@@ -30,7 +30,7 @@ def _kernels(source):
     return kernels
 
 
-@pytest.mark.parametrize("source", ["prefill_score_mfma.hip", "prefill_reduce.hip"])
+@pytest.mark.parametrize("source", ["prefill_score_mfma.hip", "prefill_reduce.hip", "decode_mfma.hip"])
 def test_no_generic_or_scratch_access(source):
     """A load through a generic pointer (global memory or LDS, decided at run time) waits for all vector memory, the
     blocks in flight included; scratch is memory too."""
