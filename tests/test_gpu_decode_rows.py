@@ -91,3 +91,24 @@ def test_ranges_longer_than_the_logit_buffer(kv, D, dtype, cap):
     n_slots, scale = 700, 1.0 / np.sqrt(D)
     state = _state(kv, rng, 1, 4, 1, D, dtype, cap, [cap - 5], n_slots, [np.arange(n_slots - 1)], n_slots - 1, scale)
     _check_steps(kv, rng, state, n_slots - 1, 2, scale)
+
+
+@pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
+def test_infinite_values_stay_in_their_column(kv, D, dtype):
+    """The last live prefill row and the last occupied slot hold an infinite value each: it shows in its own output
+    column as infinity, and nowhere else (padding rows that read it again must not turn it into NaN)."""
+    rng = np.random.default_rng(D)
+    cap, n_slots, H, Hkv, scale = 200, 40, 8, 2, 1.0 / np.sqrt(D)
+    state = _state(kv, rng, 1, H, Hkv, D, dtype, cap, [77], n_slots, [np.arange(23)], 39, scale)
+    state.v_prefill[0, :, 76, 5], state.v_dec[0, :, 22, 9] = float("inf"), float("-inf")
+    kp, vp = to_np(state.k_prefill[0, :, :77]), to_np(state.v_prefill[0, :, :77])
+    kd, vd, sp = to_np(state.k_dec[0]).copy(), to_np(state.v_dec[0]).copy(), state.slot_pos[0].cpu().numpy().copy()
+    new = [torch.from_numpy(rng.standard_normal((1, h, D), dtype=np.float32)).to(dtype).cuda() for h in (H, Hkv, Hkv)]
+    kv.decode_step(state, 1000, *new)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = orc.decode_step(kp, vp, 77, kd, vd, sp, 39, 1000, *[to_np(t[0]) for t in new], scale)["out"]
+    got = state.out[0].cpu().numpy()
+    assert np.all(got[:, 5] == np.inf) and np.all(got[:, 9] == -np.inf)
+    rest = np.setdiff1d(np.arange(D), [5, 9])
+    assert np.all(np.abs(got[:, rest] - ref[:, rest]) <= RTOL * np.abs(ref[:, rest]).max(axis=1, keepdims=True))
