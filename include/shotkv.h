@@ -88,9 +88,9 @@ typedef struct {
    * events [2 * kind] and [2 * kind + 1] on its stream around each kernel of that kind it enqueues;
    * the caller synchronises and reads elapsed times.  The library creates no objects and keeps no
    * state between calls.  Kinds, in order: chunk plan, score, row statistics, chunk mass, shot scores
-   * and selection, compaction, decode partial, decode finish, V packing, fused attention.  A kernel that does
-   * the work of two kinds (scoring finds its chunks itself, chunk mass the row statistics) is recorded under
-   * both. */
+   * and selection, compaction, decode partial, decode finish, V packing, fused attention.  Chunk plan and row
+   * statistics have no kernels of their own (scoring and fused attention find their chunks themselves, chunk mass
+   * the row statistics): their events are recorded with nothing in between, so the kinds add up to the call. */
   void* const* timing_events;
 } shotkv_config;
 

@@ -66,7 +66,8 @@ enum KernelKind {
 };
 static_assert(kKernelKinds == SHOTKV_KERNEL_KINDS, "kernel kinds");
 
-// Brackets one kernel launch with the caller's HIP events for that kind, if the caller passed any.
+// Brackets one kernel launch with the caller's HIP events for that kind, if the caller passed any.  A kind whose work
+// another kernel does is bracketed around nothing, so that kernel's time is counted under one kind only.
 class KernelTimer {
  public:
   KernelTimer(void* const* events, KernelKind kind, hipStream_t stream)

@@ -428,6 +428,7 @@ hipError_t launch_attention_scores(const PrefillDims& d, const void* q, const vo
                                    hipStream_t s) {
   const int nb = attention_key_blocks(d.n_tokens);
   const dim3 grid(d.H, d.P, ceil_div(d.n_tokens, kTileQ));
+  { KernelTimer plan_timer(d.timing, kKernelPlan, s); }  // the kernel walks the shot boundaries itself
   KernelTimer timer(d.timing, kKernelAttention, s);
   hipLaunchKernelGGL(attention_scores_kernel, grid, dim3(kThreadsQ), 0, s, static_cast<const bf16_t*>(q),
                      static_cast<const bf16_t*>(k), static_cast<const uint16_t*>(vt), w.v_absmax, d.n_tokens, nb, d.H,

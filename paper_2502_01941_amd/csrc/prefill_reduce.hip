@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
 }  // namespace
 
 hipError_t launch_chunk_mass(const PrefillDims& d, int n_valid, const PrefillWorkspace& w, hipStream_t s) {
-  KernelTimer stat_timer(d.timing, kKernelRowStats, s);  // the row denominators are part of the same kernel
+  { KernelTimer stat_timer(d.timing, kKernelRowStats, s); }  // the row denominators are part of the same kernel
   KernelTimer timer(d.timing, kKernelChunkMass, s);
   if (d.R % 4 || d.R > kMaxRows) return hipErrorInvalidValue;
   // small tiles spread few problems over the chip, large ones share the row denominators of many

@@ -803,7 +803,7 @@ static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, con
 
 hipError_t launch_score_partials(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
                                  const PrefillWorkspace& w, hipStream_t s) {
-  KernelTimer plan_timer(d.timing, kKernelPlan, s);  // the kernel finds the shot boundaries of its slices itself
+  { KernelTimer plan_timer(d.timing, kKernelPlan, s); }  // the kernel finds the shot boundaries of its slices itself
   KernelTimer timer(d.timing, kKernelScore, s);
   if (d.dtype == SHOTKV_BF16) {
     if (d.D == 128) return launch_score_rows<bf16_t, 128>(d, q_obs, k, off, w, s);

@@ -115,3 +115,37 @@ def test_caller_owned_timing_events(kv):
     kv.decode_step(state, 1, qn, kn, vn)
     torch.cuda.synchronize()
     assert state.cfg.timing_events is None and int(state.status.abs().sum().item()) == 0
+
+
+def test_timing_kinds_add_up(kv):
+    """Every kernel is counted under one kind: chunk plan and row statistics, whose work other kernels do, are recorded
+    (their events can be read after every call that scores) but stay far below the kernels that do it."""
+    P, H, Hkv, D, W, N, n = 4, 32, 8, 128, 32, 32768, 160
+    q = torch.randn((P, H, W, D), device="cuda").to(torch.bfloat16)
+    k = torch.randn((P, Hkv, N, D), device="cuda").to(torch.bfloat16)
+    off = torch.linspace(0, N - W, n + 1, device="cuda").int().expand(P, n + 1).contiguous()
+    bud = torch.full((P,), 3000, dtype=torch.int32, device="cuda")
+    kinds = ("plan", "score", "row_stats", "chunk_mass", "reduce_select", "compact")
+    runs = []
+    for _ in range(8):
+        timers = kv.KernelTimers()
+        with timers:
+            kv.prefill_compress(q, k, k, off, bud, 3000, 0.1)
+        runs.append(timers.read(kinds))
+    ms = {x: min(r[x] for r in runs) for x in kinds}
+    assert ms["plan"] < 0.5 * ms["score"] and ms["score"] > 0.03, ms
+    assert ms["row_stats"] < ms["chunk_mass"], ms
+    N, n = 4096, 20
+    qa = torch.randn((1, H, N, D), device="cuda").to(torch.bfloat16)
+    off = torch.linspace(0, N - W, n + 1, device="cuda").int()[None].contiguous()
+    timers = kv.KernelTimers()
+    before = timers.events[2 * kv.KERNEL_KINDS.index("plan")]
+    first = torch.cuda.Event(enable_timing=True)
+    first.record()
+    torch.cuda.synchronize()
+    with timers:
+        kv.prefill_attention_compress(qa, k[:1, :, :N].contiguous(), k[:1, :, :N].contiguous(), off, bud[:1], 3000, W, 0.1)
+    torch.cuda.synchronize()
+    assert first.elapsed_time(before) > 0       # the plan's events were recorded by the call, after `first`
+    ms = timers.read(("plan", "pack_vt", "attention"))
+    assert ms["plan"] < 0.5 * ms["attention"], ms
