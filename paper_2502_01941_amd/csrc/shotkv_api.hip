@@ -30,6 +30,8 @@ int static_scratch(void** out) {
 
 namespace {
 
+constexpr int kMaxScoredTokens = 1 << 30;  // the score kernel's key positions stay clear of 32-bit overflow
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 int check_config(const shotkv_config* cfg) {
@@ -119,6 +121,7 @@ int shotkv_prefill_scores(const shotkv_config* cfg, int32_t P, int32_t n_tokens,
   PrefillDims d;
   const int rc = make_prefill_dims(cfg, P, n_tokens, n_shots, &d);
   if (rc != SHOTKV_OK) return rc;
+  if (n_tokens > kMaxScoredTokens) return SHOTKV_E_SHAPE;
   if (!q_obs || !k || !shot_offsets || !shot_scores || !status || !workspace) return SHOTKV_E_NULL;
   if (!aligned16(q_obs) || !aligned16(k) || !aligned16(workspace)) return SHOTKV_E_ALIGN;
   const PrefillWorkspace w = carve(d, workspace);
@@ -166,7 +169,7 @@ int shotkv_prefill_compress(const shotkv_config* cfg, int32_t P, int32_t n_token
   PrefillDims d;
   const int rc = make_prefill_dims(cfg, P, n_tokens, n_shots, &d);
   if (rc != SHOTKV_OK) return rc;
-  if (cap < 1) return SHOTKV_E_SHAPE;
+  if (cap < 1 || n_tokens > kMaxScoredTokens) return SHOTKV_E_SHAPE;
   if (!q_obs || !k || !v || !shot_offsets || !budget_tokens || !k_out || !v_out || !kept_positions ||
       !kept_count || !status || !workspace)
     return SHOTKV_E_NULL;

@@ -75,6 +75,18 @@ def test_null_arguments_are_rejected_before_any_launch(lib):
     assert rc == -1
 
 
+def test_prompts_past_the_key_range_are_rejected_before_any_launch(lib):
+    """Key positions are 32-bit and walked in blocks past the end of a slice: near 2^31 tokens they would overflow.
+    (The pointers are never read: the call ends at the shape.)"""
+    from paper_2502_01941_amd import shotkv
+    cfg, some = ctypes.byref(shotkv._config(1, 1, 64, 1, torch.bfloat16, 0.1, 0)), ctypes.c_void_p(4096)
+    for n_tokens in (2**31 - 1, 2**31 - 1024, 2**30 + 1):
+        assert lib.shotkv_prefill_scores(cfg, 1, n_tokens, 4, some, some, some, some, some, some, 2**62, None) == -2
+        assert lib.shotkv_prefill_compress(cfg, 1, n_tokens, 4, some, some, some, some, some, some, some, 8, some, some,
+                                           None, None, some, some, 2**62, None) == -2
+    assert lib.shotkv_prefill_scores(cfg, 1, 2**30, 4, some, some, some, some, some, some, 0, None) == -3   # workspace
+
+
 def test_missing_library_fails_loudly_and_package_never_imports_the_oracle():
     """There is no CPU fallback: without the built library the binding raises, in a fresh interpreter; and
     nothing in the product package refers to the oracle."""
