@@ -3,15 +3,15 @@
 // Shape: bf16 or fp32, head_dim 64 or 128, up to 256 query rows (G*W) per KV head, instantiated for 1, 2, 4, 6
 // (bf16) or 8 blocks of 32 rows; rows past G*W are zero operands whose statistics are written as -inf.
 //
-// A workgroup is a pair of waves (one wave for a single row block, four for small launches and for 256 rows) that
-// takes one slice of a KV head's key axis and walks it in blocks of 32 keys.  It finds the shot boundaries inside
-// its slice itself (one pass over the
-// offsets, in flight together with the queries and the first blocks).  Each wave keeps
-// its share of the window queries in registers as MFMA B operands and computes
-// S^T[32 keys x 32 queries] = K_blk * Q^T per row block with v_mfma_f32_32x32x16_bf16 (fp32
-// inputs: six of them per step, see below).  Keys run along the accumulator registers and queries along the
-// lanes, so the row-softmax statistics (max and sum over keys) are in-lane reductions; only the two lane halves are merged, once per chunk.  A block that
-// contains a chunk boundary credits its weights to the chunks on either side with masked in-lane sums.
+// A workgroup is one to eight waves (one per row block for one or two blocks and in fp32; two, or four in small
+// launches, for 128 rows in bf16, two for 192 and four for 256) that take one slice of a KV head's key axis and walk it
+// in blocks of 32 keys.  It finds the shot boundaries inside its slice itself (one pass over the offsets, in flight
+// together with the queries and the first blocks).  Each wave keeps its share of the window queries in registers as
+// MFMA B operands and computes S^T[32 keys x 32 queries] = K_blk * Q^T per row block with v_mfma_f32_32x32x16_bf16
+// (fp32 inputs: six of them per step, see below).  Keys run along the accumulator registers and queries along the
+// lanes, so the row-softmax statistics (max and sum over keys) are in-lane reductions; only the two lane halves are
+// merged, once per chunk.  A block that contains a chunk boundary credits its weights to the chunks on either side
+// with masked in-lane sums.
 //
 // K blocks are streamed global -> LDS with 16-byte direct-to-LDS loads (whole 256-byte rows, fully
 // coalesced; each wave fetches its share of every block) into a ring of three buffers, so two blocks are
@@ -34,8 +34,8 @@
 //
 // fp32: the matrix unit's own fp32 form takes 16 times as long per product as bf16, so both operands are split
 // into three bf16 parts (split_f32) and six products of parts are summed in fp32, 0.37 of that time; the few values
-// that bf16 parts cannot hold take the fp32 form (logits_block).  Error of the scores against float64 over head layouts, windows and 1001 .. 65000 tokens: 0.9 - 2.7e-7 of the norm,
-// with the fp32 form 0.9 - 2.7e-7.  One query block per wave (96 operand registers at head_dim 128), up to eight
+// that bf16 parts cannot hold take the fp32 form (logits_block).  Error of the scores against float64 over head
+// layouts, windows and 1001 .. 65000 tokens: 0.9 - 2.7e-7 of the norm, with the fp32 form 0.9 - 2.7e-7.  One query block per wave (96 operand registers at head_dim 128), up to eight
 // waves per workgroup, all reading the same block.  4 problems of 4001 tokens, 8 KV heads, 128 query rows,
 // head_dim 128: 36 us, with the fp32 form 48, with plain vector arithmetic 394; 16 of 8192 tokens (whole call)
 // 338 us, with the fp32 form 420.
@@ -148,7 +148,7 @@ __device__ __forceinline__ floatx16 multiply_split(const Split& a, bf16x8 bh, bf
 #ifndef SHOTKV_SCORE_WAVES_PER_SIMD
 #define SHOTKV_SCORE_WAVES_PER_SIMD 3
 #endif
-constexpr int kRing = SHOTKV_SCORE_RING;  // LDS buffers per pair: kRing - 1 blocks in flight
+constexpr int kRing = SHOTKV_SCORE_RING;  // LDS buffers per workgroup: kRing - 1 blocks in flight
 static_assert(kRing >= 2 && kRing <= 5, "ring depth");
 
 // Issue this wave's share of the direct-to-LDS loads of one 32-key block: instructions [i0, i0 + NL).
@@ -563,8 +563,8 @@ score_partials_mfma_kernel(
     }
   }
   if (lane == 0) { s_count[wave][0] = seg0; s_count[wave][1] = seg1; }
-  // the query loads must have landed before the streaming loop starts: inside the loop the only
-  // vector-memory loads are the block loads, whose completion is tracked by hand
+  // the query loads must have landed before the streaming loop starts: inside the loop the only vector-memory loads are
+  // the block loads, whose completion is tracked by hand, and the queries of the fp32 form, which wait for all of them
 #pragma unroll
   for (int q = 0; q < NQW; ++q)
 #pragma unroll
@@ -623,10 +623,7 @@ score_partials_mfma_kernel(
       const int j = sl + 4 * my_half;
       if (j < n_stash) {
         float* dst = out + static_cast<size_t>(stash_c0 + j) * R + (lane & 31) * NQB + qb0;
-        if (NQW == 4) {
-          *reinterpret_cast<float4*>(dst) =
-              make_float4(stash[sl][0], stash[sl][1 % NQW], stash[sl][2 % NQW], stash[sl][3 % NQW]);
-        } else if (NQW == 2) {
+        if (NQW == 2) {
           *reinterpret_cast<float2*>(dst) = make_float2(stash[sl][0], stash[sl][NQW - 1]);
         } else {
 #pragma unroll
@@ -667,7 +664,7 @@ score_partials_mfma_kernel(
     else if (n_q == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(S::kLoads) : "memory");
     else if (n_q == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * S::kLoads) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * S::kLoads) : "memory");
-    // ... and after the barrier so has the partner's; the pair is also done reading the block before
+    // ... and after the barrier so has the other waves'; all are also done reading the block before
     if (S::kWaves > 1) asm volatile("s_barrier" ::: "memory");
     if (n_stash == kStash) flush();
     if (next_key0 < k_end) {
@@ -751,7 +748,7 @@ int score_group_keys(int P, int H_kv, int row_blocks, int n_tokens, int n_shots)
 }
 
 int score_row_blocks(int dtype, int rows) {
-  // what the kernel is instantiated for; fp32 has no six-block form (its four waves share the rows evenly)
+  // what the kernel is instantiated for; fp32, with one block per wave, has no six-block form
   const int need = ceil_div(rows, 32);
   return need <= 2 ? need : need <= 4 ? 4 : (need <= 6 && dtype == SHOTKV_BF16) ? 6 : 8;
 }
