@@ -325,7 +325,8 @@ def test_one_million_tokens(kv):
 @pytest.mark.parametrize("H,Hkv", [(8, 2), (4, 2), (2, 2), (12, 2), (16, 2)])
 def test_units_of_one_to_three_tokens(kv, H, Hkv):
     """Units of one to three tokens: up to thirty-two chunk boundaries inside one 32-key block, at every
-    element position of both lane halves, for one to four query blocks per wave (G = 4, 2, 1, 6, 8)."""
+    element position of both lane halves, for one to three query blocks per wave (one at G = 4, 2, 1, three at 6, two
+    at 8)."""
     P, D, W, N, n = 2, 128, 32, 2100, 1000
     g = torch.Generator(device="cuda").manual_seed(4242 + H)
     q = torch.randn((P, H, W, D), generator=g, device="cuda").to(torch.bfloat16)

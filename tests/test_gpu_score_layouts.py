@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import check_prefill_problem, oracle_prefill
+from helpers import check_prefill_problem, oracle_prefill, to_np
 from oracle import shotkv_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -161,3 +161,54 @@ def test_a_unit_of_many_slices(kv):
     off = np.array([0, N - 8], dtype=np.int32)
     got, want = _scores_and_oracle(kv, q, k, off, math.log(2.0))
     np.testing.assert_allclose(got, want, rtol=1e-5, atol=0)
+
+
+def _check_scores(kv, rng, P, G, Hkv, W, D, dtype, N, offs, problems):
+    """prefill_scores of P random problems against the oracle on some of them."""
+    scale = 1.0 / math.sqrt(D)
+    gen = torch.Generator(device="cuda").manual_seed(int(rng.integers(1 << 30)))
+    q = 2 * torch.randn((P, Hkv * G, W, D), generator=gen, device="cuda")
+    k = torch.randn((P, Hkv, N, D), generator=gen, device="cuda")
+    q, k = q.to(dtype), k.to(dtype)
+    scores, status = kv.prefill_scores(q, k, torch.from_numpy(offs).cuda(), scale)
+    torch.cuda.synchronize()
+    assert not status.any()
+    for p in problems:
+        mass = orc.token_mass(orc.window_attention(to_np(q[p]), to_np(k[p]), scale))
+        np.testing.assert_allclose(scores[p].cpu().numpy(), orc.shot_scores_from_mass(mass, offs[p]), rtol=SCORE_RTOL, atol=0,
+                                   err_msg=f"p={p}")
+
+
+def test_head_dim_64_in_two_waves(kv):
+    """128 query rows of head_dim 64 take two waves per workgroup from 1.5 M keys in a launch on, with 1024-key slices."""
+    P, Hkv, N, n = 12, 8, 16411, 70
+    rng = np.random.default_rng(3)
+    assert P * Hkv * N >= 3 << 19
+    offs = np.stack([_offsets(rng, N, n) for _ in range(P)])
+    _check_scores(kv, rng, P, 4, Hkv, 32, 64, torch.bfloat16, N, offs, (0, P - 1))
+
+
+def _tiny_units(rng, P, N, n):
+    """n units of one or two tokens between a prefix of three tokens and the tail"""
+    lengths = rng.integers(1, 3, size=(P, n))
+    offs = 3 + np.concatenate([np.zeros((P, 1), dtype=np.int64), np.cumsum(lengths, axis=1)], axis=1)
+    assert offs.max() <= N
+    return offs.astype(np.int32)
+
+
+@pytest.mark.parametrize("G,D,dtype", [(4, 128, torch.bfloat16), (6, 128, torch.bfloat16), (8, 64, torch.bfloat16),
+                                       (1, 64, torch.bfloat16), (4, 128, torch.float32), (8, 64, torch.float32)])
+def test_more_ends_in_a_slice_than_are_kept(kv, G, D, dtype):
+    """256-key slices (51200 keys in the launch) with units of one or two tokens: about 170 ends in a slice, more than
+    the 128 that are kept in LDS, so the ends come from memory while blocks are in flight."""
+    P, Hkv, N, n = 1, 8, 6400, 4096
+    rng = np.random.default_rng(G + D)
+    _check_scores(kv, rng, P, G, Hkv, 32, D, dtype, N, _tiny_units(rng, P, N, n), (0,))
+
+
+def test_short_units_in_two_waves(kv):
+    """The same in the two-wave form that launches of 2 M keys take for short units, with 512-key slices."""
+    P, Hkv, N, n = 41, 8, 6400, 4096
+    rng = np.random.default_rng(11)
+    assert P * Hkv * N >= 2 << 20
+    _check_scores(kv, rng, P, 4, Hkv, 32, 128, torch.bfloat16, N, _tiny_units(rng, P, N, n), (0, P - 1))
