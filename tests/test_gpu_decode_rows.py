@@ -93,6 +93,20 @@ def test_ranges_longer_than_the_logit_buffer(kv, D, dtype, cap):
     _check_steps(kv, rng, state, n_slots - 1, 2, scale)
 
 
+@pytest.mark.parametrize("D,dtype,cap,n_slots,free", [
+    (64, torch.bfloat16, 1_049_000, 700, 597), (128, torch.float32, 1_049_000, 3000, 1613), (64, torch.bfloat16, 2_100_000, 5000, 3282)])
+def test_new_token_in_a_later_piece(kv, D, dtype, cap, n_slots, free):
+    """Ranges of 1026, 1028 and 2056 tokens in pieces of 1024; the free slot lies in the second (third) piece of its
+    range, and the pool's slots lie in several pieces of several ranges."""
+    per_range = -(-(cap + n_slots) // 1024)
+    assert (cap + free) % per_range >= per_range // 1024 * 1024 >= 1024
+    rng = np.random.default_rng(free)
+    scale = 1.0 / np.sqrt(D)
+    used = np.setdiff1d(np.arange(n_slots), [free])
+    state = _state(kv, rng, 1, 4, 1, D, dtype, cap, [cap - 5], n_slots, [used], n_slots - 1, scale)
+    _check_steps(kv, rng, state, n_slots - 1, 2, scale)
+
+
 @pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
 def test_infinite_values_stay_in_their_column(kv, D, dtype):
     """The last live prefill row and the last occupied slot hold an infinite value each: it shows in its own output
