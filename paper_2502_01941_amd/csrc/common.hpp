@@ -48,6 +48,13 @@ __device__ __forceinline__ float sum_across_row_pairs(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// reference + log2(sum), sum > 0.  The hardware logarithm errs low by a part of its result's last place, which for a sum
+// of hundreds is 2^-20: only the mantissa goes through it, the exponent is exact.
+__device__ __forceinline__ float add_log2(float reference, float sum) {
+  return reference + static_cast<float>(__builtin_amdgcn_frexp_expf(sum)) +
+         __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(sum));
+}
+
 __host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Segments and chunks.  A problem's key axis is cut into segments - 0 the tokens before the first shot, s = 1..n

@@ -276,7 +276,7 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
   auto finish_chunk = [&]() {
     const float tot = sum_across_halves(l_chunk);
     if (lane_emits)
-      part_row[static_cast<size_t>(cur_c) * R] = tot > 0.f ? m_run + __builtin_amdgcn_logf(tot) : -INFINITY;
+      part_row[static_cast<size_t>(cur_c) * R] = tot > 0.f ? add_log2(m_run, tot) : -INFINITY;
     l_chunk = 0.f;
     ++cur_c;
     if (cur_c < n_seg) { cur_s = cur_e; cur_e = segment_end(cur_c); }
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
     // chunks that reach past this tile's keys hold what their visible part gave; later ones nothing
     while (cur_c < n_seg) finish_chunk();
     if (lane_emits)
-      row_stat[(static_cast<size_t>(p) * H_kv + g) * R + h_local * W + win_j] = m_run + __builtin_amdgcn_logf(l_tot);
+      row_stat[(static_cast<size_t>(p) * H_kv + g) * R + h_local * W + win_j] = add_log2(m_run, l_tot);
   }
   if (q_row < n_tokens) {
     const float inv = 1.f / l_tot;

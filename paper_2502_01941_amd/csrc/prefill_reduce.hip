@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
 #pragma unroll
       for (int t = 0; t < kTeams; ++t) L += s_sum[t][tid] * exp2f(s_max[t][tid] - M);
     // log2 of the row's softmax denominator; +inf for a row without keys so that its weights vanish
-    s_lse[tid] = L > 0.f && tid < n_valid ? M + log2f(L) : INFINITY;
+    s_lse[tid] = L > 0.f && tid < n_valid ? add_log2(M, L) : INFINITY;
   }
   __syncthreads();
 

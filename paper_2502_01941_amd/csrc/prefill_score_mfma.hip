@@ -645,7 +645,7 @@ score_partials_mfma_kernel(
     for (int q = 0; q < NQW; ++q) {
       const float l = sum_across_halves(l_run[q]);
       // log2(0) = -inf: a query that saw none of the chunk's keys; so is a padding query row
-      val[q] = (l > 0.f && (qb0 + q) * 32 + (lane & 31) < n_rows) ? m_run[q] + __builtin_amdgcn_logf(l)
+      val[q] = (l > 0.f && (qb0 + q) * 32 + (lane & 31) < n_rows) ? add_log2(m_run[q], l)
                                                                    : -INFINITY;
       l_grp[q] += l;
       l_run[q] = 0.f;  // the reference carries over to the next chunk
@@ -717,7 +717,7 @@ score_partials_mfma_kernel(
                  (lane & 31) * NQB + qb0;
 #pragma unroll
     for (int q = 0; q < NQW; ++q)
-      dst[q] = (l_grp[q] > 0.f && (qb0 + q) * 32 + lane < n_rows) ? m_run[q] + __builtin_amdgcn_logf(l_grp[q])
+      dst[q] = (l_grp[q] > 0.f && (qb0 + q) * 32 + lane < n_rows) ? add_log2(m_run[q], l_grp[q])
                                                                  : -INFINITY;
   }
 }
