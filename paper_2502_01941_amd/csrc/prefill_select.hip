@@ -203,14 +203,14 @@ __device__ void first_fit_walk(const int* len, const uint16_t* shot, int n, int 
 }
 
 // Sum of words[first], words[first + width], ... of n words: kBatch loads in flight, added up as a tree.
-template <int kBatch>
-__device__ __forceinline__ float strided_sum(const float* words, int n, int first, int width) {
+template <int kBatch, typename Load>
+__device__ __forceinline__ float strided_sum(int n, int first, int width, Load word) {
   float sum = 0.f;
 #pragma clang loop unroll(disable)
   for (int e0 = first; e0 < n; e0 += kBatch * width) {
     float x[kBatch];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) x[j] = words[min(e0 + j * width, n - 1)];
+    for (int j = 0; j < kBatch; ++j) x[j] = word(min(e0 + j * width, n - 1));
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) x[j] = e0 + j * width < n ? x[j] : 0.f;
 #pragma unroll
@@ -262,8 +262,8 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
   // Shot i is segment i + 1: its chunks' masses are consecutive, one word per KV head each.  A unit of thousands of
   // tokens is hundreds of words, which one thread would read one after the other; a group of lanes takes it, each with
   // at least eight words to add (fewer cost more in the exchange than they save: 8192 tokens in 40 shots, 14 words
-  // each, 29.5 us with one lane and 30.3 with sixteen) and sixteen loads in flight, or eight where units are many and
-  // short (scores of 32768 tokens in 4000 units 79.6 us, 90.7 with sixteen).  Whole call, 32 query / 8 KV heads,
+  // each, 29.5 us with one lane and 30.3 with sixteen) and sixteen loads in flight, or four of 16 bytes where units are
+  // many and short (whole call, 32768 tokens in 4000 units: 132 us, 143 with eight of 4 bytes).  Whole call, 32 query / 8 KV heads,
   // one thread per shot with one load at a time against this: 4000 tokens in 2 units 32.7 / 25.6 us, 8192 in 2
   // 38.9 / 31.5, 32768 in 4 57.9 / 47.2, 131072 in one 144 / 79.  The sums are also more exact than one long one.
   auto shot_sum = [&](int i, int first, int width) {
@@ -271,7 +271,14 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     const int c0 = (lo >> group_shift) + i + 1, c1 = ((hi - 1) >> group_shift) + i + 1;
     const float* words = chunk_mass + (static_cast<size_t>(p) * max_c + c0) * H_kv;
     const int n = (c1 - c0 + 1) * H_kv;
-    return n_shots > kSelThreads / 2 ? strided_sum<8>(words, n, first, width) : strided_sum<16>(words, n, first, width);
+    if (n_shots > kSelThreads / 2 && H_kv % 4 == 0) {  // one lane per unit, which has H_kv words per chunk
+      const float4* quads = reinterpret_cast<const float4*>(words);
+      return strided_sum<4>(n / 4, first, width, [&](int e) {
+        const float4 x = quads[e];
+        return (x.x + x.y) + (x.z + x.w);
+      });
+    }
+    return strided_sum<16>(n, first, width, [&](int e) { return words[e]; });
   };
   int width = 1;
   if (MASS) {
