@@ -207,7 +207,8 @@ def test_more_ends_in_a_slice_than_are_kept(kv, G, D, dtype):
 
 
 def test_short_units_in_two_waves(kv):
-    """The same in the two-wave form that launches of 2 M keys take for short units, with 512-key slices."""
+    """The same in the two-wave form that launches of 0.5 M keys take for such units (2 M for units of 16 to 63 tokens),
+    with 512-key slices."""
     P, Hkv, N, n = 41, 8, 6400, 4096
     rng = np.random.default_rng(11)
     assert P * Hkv * N >= 2 << 20
