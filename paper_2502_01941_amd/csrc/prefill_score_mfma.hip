@@ -768,7 +768,7 @@ static void launch_score(const PrefillDims& d, const void* q_obs, const void* k,
 // 128 rows, head_dim 128: 8192 tokens 29.6 / 31.5 us, 4 x 32768 93 / 99, 32 x 32768 545 / 550, 64 x 32768 1074 / 1071,
 // 128 x 32768 2080 / 2049; units of 25 tokens 4 x 32768 173 / 177, 32 x 32768 986 / 946; head_dim 64: 8 x 16384
 // 75 / 81, 16 x 16001 122 / 118.  A unit's end costs a wave the same whatever share of the rows it has, so with several
-// ends in a block two waves are better early: units of 8 tokens, 32768 tokens 132 / 144, 4 x 32768 266 / 256, at
+// ends in a block two waves are better early: units of 8 tokens, 32768 tokens 143 / 154, 4 x 32768 266 / 256, at
 // head_dim 64 238 / 199, 16 x 8192 in units of 6 278 / 262, 2 x 32768 in units of 15 146 / 148.  256 rows always take four (two blocks each instead of four, which spills):
 // 32 x 32768 805 / 924 us.
 static bool four_waves(const PrefillDims& d) {
