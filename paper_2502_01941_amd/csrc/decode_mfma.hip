@@ -76,13 +76,25 @@ template <int ROW_BYTES> struct RowShape {
 template <typename T> struct Operand;  // 16 bytes of a row as one lane holds them
 template <> struct Operand<bf16_t> { typedef bf16x8 Vec; };
 template <> struct Operand<float> { typedef floatx4 Vec; };
-__device__ __forceinline__ floatx4 multiply_step(bf16x8 a, bf16x8 b, floatx4 acc) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-}
-__device__ __forceinline__ floatx4 multiply_step(floatx4 a, floatx4 b, floatx4 acc) {
+// The shares of a step's logits from its loads.  fp32 sums the four elements of a lane's 16 bytes apart and adds the four
+// sums at the end: a fourth of the roundings in a row, and four chains of matrix instructions instead of one.
+template <int LOADS>
+__device__ __forceinline__ floatx4 multiply_step(const bf16x8* a, const bf16x8 (&b)[LOADS]) {
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
+  for (int j = 0; j < LOADS; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], b[j], acc, 0, 0, 0);
   return acc;
+}
+template <int LOADS>
+__device__ __forceinline__ floatx4 multiply_step(const floatx4* a, const floatx4 (&b)[LOADS]) {
+  floatx4 acc[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][e], b[j][e], acc[e], 0, 0, 0);
+  }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
 template <typename T> struct Widen;   // the elements of 16 bytes as floats
@@ -300,9 +312,7 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
         for (int st = 0; st < kStepsPerBlock; ++st) {
 #pragma unroll
           for (int m = 0; m < kHeadSets; ++m) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int j = 0; j < S::kLoads; ++j) acc = multiply_step(kraw[st * S::kLoads + j], bq[m][j], acc);
+            const floatx4 acc = multiply_step<S::kLoads>(&kraw[st * S::kLoads], bq[m]);
             const int hq = col_head + S::kCols * m;
             // this lane's column holds piece col_piece; rows 4*ksl + v are (token, piece) pairs
             constexpr int kOwn = 4 / S::kPieces;  // tokens among a lane's four rows
