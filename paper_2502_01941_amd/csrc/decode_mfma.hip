@@ -14,9 +14,9 @@
 //      the weights read from LDS, the next batch of rows in flight while one is used.  No rescaling is
 //      needed because the maximum is already known.
 // Bound by the stream of K and V rows: 32 query / 8 KV heads, head_dim 128 bf16, 512 caches of ~5000 rows 1.79 ms
-// = 5.9 TB/s, 16 caches 60 us.  Before the rows of 64-dimensional heads and of fp32 caches took this form they
+// = 5.9 TB/s, 16 caches 58 us.  Before the rows of 64-dimensional heads and of fp32 caches took this form they
 // were scored and summed by one-pass vector arithmetic: 32 caches of 2001 + 512 rows, head_dim 64, 57 us then,
-// 36 us now; 8 caches of 2000 + 500 fp32 rows 57 -> 39 us a step.  Requesting the first V rows ahead of the
+// 33 us now; 8 caches of 2000 + 500 fp32 rows 57 -> 38 us a step.  Requesting the first V rows ahead of the
 // weights is worth 4 us of 74 at 16 caches.
 // Compared with a one-pass online softmax this moves the dot products off the vector ALU, removes the
 // cross-lane reductions per token and the per-token rescale of the output accumulators.

@@ -28,17 +28,17 @@
 //   128-byte rows (head_dim 64): row r starts at r*128 and column c sits in slot c ^ ((r/2)%8): two rows
 //     share the 256 bytes of the banks, so eight pairs of rows have to differ in the slot.  Half the bytes
 //     and half the matrix steps per key, but the same exponentials: bound by vector issue (16 problems of
-//     16001 tokens, 8 KV heads, 128 query rows: 78 us = 3.4 TB/s; plain vector arithmetic took 2427 us).
+//     16001 tokens, 8 KV heads, 128 query rows: 72 us = 3.6 TB/s; plain vector arithmetic took 2427 us).
 //   512-byte rows (fp32, head_dim 128): row r starts at r*512 + (r/2)*32 and column c sits in slot c ^ (r%2);
 //     sixteen rows then cover the banks and every step is an immediate offset from one lane base.
 //
 // fp32: the matrix unit's own fp32 form takes 16 times as long per product as bf16, so both operands are split
 // into three bf16 parts (split_f32) and six products of parts are summed in fp32, 0.37 of that time; the few values
 // that bf16 parts cannot hold take the fp32 form (logits_block).  Error of the scores against float64 over head
-// layouts, windows and 1001 .. 65000 tokens: 0.9 - 2.7e-7 of the norm, with the fp32 form 0.9 - 2.7e-7.  One query block per wave (96 operand registers at head_dim 128), up to eight
-// waves per workgroup, all reading the same block.  4 problems of 4001 tokens, 8 KV heads, 128 query rows,
-// head_dim 128: 36 us, with the fp32 form 48, with plain vector arithmetic 394; 16 of 8192 tokens (whole call)
-// 338 us, with the fp32 form 420.
+// layouts, windows and 1001 .. 65000 tokens: 0.3 - 0.8e-7 of the norm.  One query block per wave (96 operand
+// registers at head_dim 128), up to eight waves per workgroup, all reading the same block.  4 problems of 4001 tokens,
+// 8 KV heads, 128 query rows, head_dim 128: 37 us, with the fp32 form 48, with plain vector arithmetic 394; 16 of 8192
+// tokens (whole call) 351 us, with the fp32 form 420.
 //
 // The direct-to-LDS loads are written as inline assembly and their completion is tracked by hand with
 // s_waitcnt vmcnt: when they are visible to the compiler it makes every LDS read wait for all loads
@@ -484,7 +484,10 @@ score_partials_mfma_kernel(
   // statistics are written as -inf, so they carry no weight further down.
   constexpr int kVec = 16 / sizeof(T);
   bf16x8 bq[NQW][E::kQueryVecs];
-  uint32_t largest = 0u, smallest = UINT32_MAX;  // of the query elements' magnitudes, zeros left out; fp32 only
+  // of the query elements' magnitudes, fp32 only: the largest, and the smallest as twice its bits less one (a zero wraps
+  // to the top); an element costs two instructions
+  float largest = 0.f;
+  uint32_t smallest = UINT32_MAX;
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int qi = (qb0 + q) * 32 + (lane & 31);
@@ -494,9 +497,8 @@ score_partials_mfma_kernel(
       if constexpr (sizeof(T) == 4) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const uint32_t mag = raw[e] & 0x7fffffffu;
-          largest = max(largest, mag);
-          smallest = min(smallest, mag - 1u);  // a zero wraps to the top
+          largest = fmaxf(largest, fabsf(__uint_as_float(raw[e])));  // (NaNs are found in the logits)
+          smallest = min(smallest, (raw[e] << 1) - 1u);
         }
       }
       return __builtin_bit_cast(typename E::Vec, raw);
@@ -516,8 +518,8 @@ score_partials_mfma_kernel(
   }
   Queries<T> src{q_rows, qb0, n_rows, true};
   if constexpr (sizeof(T) == 4)
-    src.plain = __builtin_amdgcn_ballot_w64(largest > __float_as_uint(0x1p50f) ||
-                                            smallest < __float_as_uint(0x1p-100f) - 1u) == 0 && c < 0x1p30f;
+    src.plain = __builtin_amdgcn_ballot_w64(largest > 0x1p50f || smallest < 2 * __float_as_uint(0x1p-100f) - 1u) == 0 &&
+                c < 0x1p30f;
   lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
   const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base));
   const int causal_base = n_tokens - W;
