@@ -22,10 +22,12 @@
 //                     instead of bf16's 8, which holds the output within 4.6e-4 of its row maximum with one
 //                     instruction per step (a bf16 weight is off by up to 2^-9; bf16 hi + lo would cost a
 //                     second instruction).  fp16's narrow range is dealt with by two exact power-of-two
-//                     scalings: the softmax reference sits 15 below the running maximum, so weights lie
-//                     in (0, 2^15] and anything above 2^-39 of the largest survives; and the pre-pass
+//                     scalings: the softmax reference sits 15 to 16 below the running maximum, so the largest
+//                     weight lies in [2^15, 2^16) and anything above 2^-39 of it survives; and the pre-pass
 //                     scales every KV-head plane of V so that its largest finite |v| lands in [2^14, 2^15).
-//                     Sums of weights stay in fp32 and carry the same reference.
+//                     Sums of weights are taken in fp32 and carry the same reference; in tiles without window rows
+//                     they add the weights as the product takes them (fp16), so that both sides of the quotient are
+//                     off the same way.
 // K and packed-V blocks are streamed global -> LDS with direct-to-LDS loads into a ring of three stages
 // shared by the four waves (one barrier per block); the LDS layouts are bank-conflict free for the
 // 128-bit operand reads (K as in the score kernel; V^T rows of 64 bytes with a two-bit XOR of the
@@ -53,11 +55,12 @@ constexpr int kRowBytes = kD * 2;
 constexpr int kGroupBytes = 4 * kRowBytes + 64;       // K: four rows + pad = one direct-to-LDS instruction
 constexpr int kKBytes = 8 * kGroupBytes;              // 8704
 constexpr int kVtBytes = kD * kBlockKeys * 2;         // 8192: [128 d][32 keys] fp16
-// Softmax reference = running maximum - kWeightShift (log2 domain), in every block: the largest weight is then a power
-// of two, which fp16 holds exactly, and weights keep their 11 bits down to 2^-29 of it.  A reference that stays where it
-// is until a weight nears fp16's range (8 below the maximum, 2^7 of headroom) is 8 % faster (8192 tokens 550 us, 596 as
-// it is), but its weights lose bits from 2^-22 on - one of 2^-26 is off by up to 0.8 %, one of 2^-30 by 11 % - and
-// where the heaviest keys carry small values those weights make the output.
+// The softmax reference moves to the running maximum - kWeightShift (log2 domain), and then stays until a weight passes
+// fp16's largest value, 2 above: weights keep their 11 bits down to 2^-29 of the largest, or below.  Nothing but the sum of
+// the weights has to be looked at in a block where it stays (an infinite one shows it), which saves the block's maximum.
+// A reference with more headroom (8 below the maximum, 2^7) moves less often yet, but its weights lose bits from 2^-22
+// on - one of 2^-26 is off by up to 0.8 %, one of 2^-30 by 11 % - and where the heaviest keys carry small values those
+// weights make the output.
 constexpr int kWeightShift = 15;
 constexpr int kStageBytes = kKBytes + kVtBytes;
 constexpr int kRing = 3;
@@ -157,107 +160,114 @@ __global__ __launch_bounds__(256) void pack_vt_kernel(const bf16_t* __restrict__
 }
 
 // ---- streaming helpers ---------------------------------------------------------------------------
-// K groups [g0, g0 + 2) of a block: group i fills rows 4i..4i+3; lane l writes LDS slot l of the group
-// (row 4i + l/16, slot l%16) and therefore fetches column (l%16) ^ (l/16) of that row.  Rows past the
-// last token re-read it (they are masked by causality); only the last block has any.
+__device__ __forceinline__ void load_lds(const char* base, uint32_t off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds_addr), "v"(off), "s"(base)
+               : "memory", "m0");
+}
+// Where a lane fetches from, within the KB that one instruction brings, for both kinds of block: lane l fills LDS slot
+// l, and 16-byte column x of a K row (four rows to an instruction) sits in slot x ^ row, column x of a V^T row (d;
+// sixteen rows to an instruction) in slot x ^ (d / 4): sixteen consecutive V^T rows, read 16 bytes each by sixteen
+// lanes, then cover the 64 LDS banks exactly once.
+__device__ __forceinline__ uint32_t piece_offset(int lane) { return (lane << 4) ^ ((lane >> 4) << 4); }
+
+// K groups [g0, g0 + 2) of a block: group i fills rows 4i..4i+3.  Rows past the last token re-read it (they are masked
+// by causality); only the last block of the prompt has any.
+template <bool CLAMP>
 __device__ __forceinline__ void issue_k(const char* __restrict__ k_plane, int key0, int n_tokens,
-                                        uint32_t lds_addr, int g0, int lane) {
-  const int hi = lane >> 4;
-  const uint32_t col_bytes = static_cast<uint32_t>(((lane & 15) ^ hi) << 4);
-  const char* base = k_plane + static_cast<size_t>(key0) * kRowBytes;
-  uint32_t off[2];
+                                        uint32_t lds_addr, int g0, uint32_t piece, int lane) {
+  const char* base = k_plane + static_cast<size_t>(key0 + 4 * g0) * kRowBytes;
+  if (CLAMP && key0 + kBlockKeys > n_tokens) {
+    const uint32_t col_bytes = piece & (kRowBytes - 1);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) off[i] = static_cast<uint32_t>(4 * (g0 + i) + hi) * kRowBytes + col_bytes;
-  if (key0 + kBlockKeys > n_tokens) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      off[i] = static_cast<uint32_t>(min(4 * (g0 + i) + hi, n_tokens - 1 - key0)) * kRowBytes + col_bytes;
+    for (int i = 0; i < 2; ++i) {
+      const int row = min(4 * (g0 + i) + (lane >> 4), n_tokens - 1 - key0);
+      load_lds(k_plane + static_cast<size_t>(key0) * kRowBytes, static_cast<uint32_t>(row) * kRowBytes + col_bytes,
+               lds_addr + (g0 + i) * kGroupBytes);
+    }
+    return;
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_addr + (g0 + i) * kGroupBytes), "v"(off[i]), "s"(base)
-                 : "memory", "m0");
+  for (int i = 0; i < 2; ++i) load_lds(base + i * 1024, piece, lds_addr + (g0 + i) * kGroupBytes);
 }
-// V^T slabs [i0, i0 + 2) of a packed block: slab i fills rows (d) 16i..16i+15 of 64 bytes; lane l writes
-// row 16i + l/4, slot l%4 and fetches column (l%4) ^ ((row/4)%4) of that row: sixteen consecutive rows,
-// read 16 bytes each by sixteen lanes, then cover the 64 LDS banks exactly once.
-__device__ __forceinline__ void issue_vt(const char* __restrict__ vt_block, uint32_t lds_addr, int i0, int lane) {
+// V^T slabs [i0, i0 + 2) of a packed block: slab i fills rows (d) 16i..16i+15 of 64 bytes
+__device__ __forceinline__ void issue_vt(const char* __restrict__ vt_block, uint32_t lds_addr, int i0, uint32_t piece) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int d = 16 * (i0 + i) + (lane >> 2);
-    const int c = (lane & 3) ^ ((d >> 2) & 3);
-    const uint32_t off = static_cast<uint32_t>(d * 64 + c * 16);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_addr + (i0 + i) * 1024), "v"(off), "s"(vt_block)
-                 : "memory", "m0");
-  }
+  for (int i = 0; i < 2; ++i) load_lds(vt_block + (i0 + i) * 1024, piece, lds_addr + (i0 + i) * 1024);
 }
 
-__device__ __forceinline__ f16x8 to_f16x8(const float* x) {
-  f16x8 r;
-#pragma unroll
-  for (int j = 0; j < 8; j += 2) {
-    const floatx2 f = {x[j], x[j + 1]};
-    const f16x2 hh = __builtin_convertvector(f, f16x2);  // round to nearest even
-    r[j] = hh[0];
-    r[j + 1] = hh[1];
-  }
-  return r;
+__device__ __forceinline__ f16x2 to_f16x2(float x0, float x1) {
+  const floatx2 f = {x0, x1};
+  return __builtin_convertvector(f, f16x2);  // round to nearest even
 }
 
-__global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const uint16_t* __restrict__ vt,
-    const uint32_t* __restrict__ v_absmax, int n_tokens, int n_blocks_total, int H, int H_kv, int W, float c, float* __restrict__ o_out,
-    const int32_t* __restrict__ shot_offsets, int share, int n_shots, int max_c, int R,
-    float* __restrict__ partial, float* __restrict__ row_stat) {
-  __shared__ __attribute__((aligned(64))) char lds[kRing][kStageBytes];
+// The lane number made afresh: a value that is needed again after a loop need not hold a register through it.
+__device__ __forceinline__ int lane_again() {
+  uint32_t zero = 0;
+  asm volatile("" : "+s"(zero));
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero)));
+}
+
+struct AttentionArgs {
+  const bf16_t* q;
+  const bf16_t* k;
+  const uint16_t* vt;
+  const uint32_t* v_absmax;
+  int n_tokens, n_blocks_total, H, H_kv, W;
+  float c;  // softmax scale in the log2 domain
+  float* o_out;
+  const int32_t* shot_offsets;
+  int share, n_shots, max_c, R;
+  float* partial;
+  float* row_stat;
+};
+
+// One tile: 128 consecutive queries from q0 on, each wave 32 of them.  EMIT: the tile may hold window rows, or end the
+// prompt; its weights are kept in fp32 for the statistics.
+template <bool EMIT>
+__device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, int p, int q0, lds_cchar* lds_base) {
+  // Operands read from LDS ahead of the matrix instructions that take them, those of O^T ahead of the softmax: as many
+  // as three waves per SIMD have registers for.  Read two at a time where they are taken, as the compiler does by itself,
+  // 8192 tokens take 575 us instead of 568.
+  constexpr int kKAhead = 6, kVAhead = 4;
+  const int n_tokens = x.n_tokens, W = x.W, R = x.R, max_c = x.max_c;
+  const float c = x.c;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int tile = gridDim.z - 1 - blockIdx.z;  // long tiles first, for all heads and problems
-  // Workgroups are dealt to the eight XCDs round-robin: query heads that read one KV head go to one XCD, whose L2
-  // then holds that head's K and V once instead of every XCD all of them (8192 tokens 601 -> 596 us, 20000 tokens
-  // 3262 -> 3137, 32768 tokens 8618 -> 8236, 64 heads at 6000 tokens 672 -> 638).  Head counts that are no multiple of
-  // eight, and the per-KV-head mode (gridDim.x is the group size there), keep their order.
-  const int h = gridDim.x % 8 == 0 ? (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
-  const int p = blockIdx.y;
-  const int G = H / H_kv, g = h / G;
-  const int q0 = tile * kTileQ;
+  const int G = x.H / x.H_kv, g = h / G;
   const int half = lane >> 5;
-  const int q_row = q0 + 32 * wave + (lane & 31);       // this lane's query
-  const int q_eff = min(q_row, n_tokens - 1);           // rows past the prompt repeat the last one, unstored
   const int wave_min_q = q0 + 32 * wave;
   const int wave_max_q = min(wave_min_q + 31, n_tokens - 1);
   const int last_q = min(q0 + kTileQ, n_tokens) - 1;
   const int n_blocks = last_q / kBlockKeys + 1;         // keys 0..last_q
   // the window rows of this wave, if any, take part in Eq. 3
   const int win0 = n_tokens - W;
-  const bool wave_emits = wave_min_q + 31 >= win0 && wave_min_q < n_tokens;
-  const int win_j = q_row - win0;
-  const bool lane_emits = win_j >= 0 && q_row < n_tokens && half == 0;
+  const bool wave_emits = EMIT && wave_max_q >= win0 && wave_min_q < n_tokens;
+  const int q_row = wave_min_q + (lane & 31);           // this lane's query
+  const int q_eff = EMIT ? min(q_row, n_tokens - 1) : q_row;  // rows past the prompt repeat the last one, unstored
+  const bool lane_emits = EMIT && q_row >= win0 && q_row < n_tokens && half == 0;
 
-  const char* k_plane = reinterpret_cast<const char*>(k) + (static_cast<size_t>(p) * H_kv + g) * n_tokens * kRowBytes;
-  const char* vt_plane =
-      reinterpret_cast<const char*>(vt) + (static_cast<size_t>(p) * H_kv + g) * n_blocks_total * kVtBytes;
+  const size_t plane = static_cast<size_t>(p) * x.H_kv + g;
+  const char* k_plane = reinterpret_cast<const char*>(x.k) + plane * n_tokens * kRowBytes;
+  const char* vt_plane = reinterpret_cast<const char*>(x.vt) + plane * x.n_blocks_total * kVtBytes;
   // B operands of S^T: query q_eff, head-dim slice 16*ks + 8*half .. +8
-  const bf16_t* q_ptr = q + ((static_cast<size_t>(p) * H + h) * n_tokens + q_eff) * kD + half * 8;
   bf16x8 bq[8];
+  const bf16_t* q_ptr = x.q + ((static_cast<size_t>(p) * x.H + h) * n_tokens + q_eff) * kD + half * 8;
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks)
-    bq[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(q_ptr + ks * 16));
+  for (int ks = 0; ks < 8; ++ks) bq[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(q_ptr + ks * 16));
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) asm volatile("" ::"v"(bq[ks]));  // landed before the hand-tracked loads start
 
-  lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
   const uint32_t lds_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base));
+  const uint32_t piece = piece_offset(lane);
   auto issue = [&](int b, int slot) {
-    issue_k(k_plane, b * kBlockKeys, n_tokens, lds_addr + slot * kStageBytes, 2 * wave, lane);
-    issue_vt(vt_plane + static_cast<size_t>(b) * kVtBytes, lds_addr + slot * kStageBytes + kKBytes, 2 * wave, lane);
+    issue_k<EMIT>(k_plane, b * kBlockKeys, n_tokens, lds_addr + slot * kStageBytes, 2 * wave, piece, lane);
+    issue_vt(vt_plane + static_cast<size_t>(b) * kVtBytes, lds_addr + slot * kStageBytes + kKBytes, 2 * wave, piece);
   };
 
-  float m_run = -INFINITY, l_run = 0.f;
+  constexpr f16x2 kOnes = {static_cast<_Float16>(1.f), static_cast<_Float16>(1.f)};
+  float m_run = -INFINITY, l_run = 0.f, l_chunk = 0.f;
   floatx16 ot[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
@@ -266,17 +276,23 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
 
   // Eq. 3 bookkeeping (emitting waves only): the segment whose sum is being collected, see max_chunks().  (Offsets
   // that are out of order give wrong statistics in range; the problem's scores are discarded.)
-  const int32_t* off = shot_offsets + static_cast<size_t>(p / share) * (n_shots + 1);
-  const int n_seg = wave_emits ? n_shots + 2 : 0;
-  auto segment_end = [&](int sg) { return sg <= n_shots ? off[sg] : n_tokens; };
+  // The ends of 64 segments at a time sit in the lanes: a load at every end would wait for the stream as well.
+  const int32_t* off = x.shot_offsets + static_cast<size_t>(p / x.share) * (x.n_shots + 1);
+  const int n_seg = wave_emits ? x.n_shots + 2 : 0;
+  int ends = 0;
+  auto segment_end = [&](int sg) {
+    if (sg % kWave == 0) {
+      const int i = sg + lane;
+      ends = i <= x.n_shots ? off[i] : n_tokens;
+    }
+    return __builtin_amdgcn_readlane(ends, sg % kWave);
+  };
   int cur_c = 0, cur_s = 0, cur_e = wave_emits ? segment_end(0) : 0;
-  float l_chunk = 0.f;
   const int h_local = h - g * G;
-  float* part_row = partial + (static_cast<size_t>(p) * H_kv + g) * max_c * R + h_local * W + win_j;  // + segment * R
+  float* part_row = x.partial + plane * max_c * R + h_local * W + (q_row - win0);  // + segment * R
   auto finish_chunk = [&]() {
     const float tot = sum_across_halves(l_chunk);
-    if (lane_emits)
-      part_row[static_cast<size_t>(cur_c) * R] = tot > 0.f ? add_log2(m_run, tot) : -INFINITY;
+    if (lane_emits) part_row[static_cast<size_t>(cur_c) * R] = tot > 0.f ? add_log2(m_run, tot) : -INFINITY;
     l_chunk = 0.f;
     ++cur_c;
     if (cur_c < n_seg) { cur_s = cur_e; cur_e = segment_end(cur_c); }
@@ -284,32 +300,51 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
 
   issue(0, 0);
   if (n_blocks > 1) issue(1, 1);
+  // where a lane reads the first operand of S^T and of O^T in a stage: 16-byte column half of row lane % 32, XOR-swizzled
+  const uint32_t k_read = (lane & 31) * kRowBytes + ((lane & 31) >> 2) * 64 + ((half ^ (lane & 3)) << 4);
+  const uint32_t v_read = (lane & 31) * 64 + ((half ^ ((lane >> 2) & 3)) << 4);
+  int slot = 0, slot2 = 2;  // of blocks b and b + 2
   for (int b = 0; b < n_blocks; ++b) {
     // this wave's loads of block b have landed once only those of block b+1 can be outstanding
     if (b + 1 < n_blocks) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // ... and after the barrier so have the other waves'; everybody is also done with block b-1
     asm volatile("s_barrier" ::: "memory");
-    const int slot = b % kRing;
-    if (b + 2 < n_blocks) issue(b + 2, (b + 2) % kRing);
+    if (b + 2 < n_blocks) issue(b + 2, slot2);
+    const uint32_t blk = lds_addr + slot * kStageBytes;
+    slot = slot + 1 == kRing ? 0 : slot + 1;
+    slot2 = slot2 + 1 == kRing ? 0 : slot2 + 1;
     const int key0 = b * kBlockKeys;
     const bool has_work = key0 <= wave_max_q;
-    float pw[16];
+    if (!has_work && !wave_emits) continue;
+    floatx16 acc;
+    f16x8 p16[2];
+    float block_sum = 0.f;  // of the weights in fp32, where they are kept
+    f16x8 va[8];  // A operands of O^T: step i % 2 of head-dim rows 32 * (i / 2) ..
+    uint32_t v_even = blk + kKBytes + v_read;
+    asm("" : "+v"(v_even));
+    auto load_v = [&](int i) {
+      return *reinterpret_cast<lds_f16x8*>(static_cast<uintptr_t>((i & 1 ? v_even ^ 32 : v_even) + 2048 * (i >> 1)));
+    };
     if (has_work) {
-      lds_cchar* blk = lds_base + slot * kStageBytes;
       // ---- S^T: keys along registers (row 8*(v/4) + 4*half + v%4), queries along lanes -------------
-      const int row = lane & 31;
-      const int base_even = row * kRowBytes + (row >> 2) * 64 + ((half ^ (row & 3)) << 4);
-      lds_cchar* even = blk + base_even;
-      lds_cchar* odd = blk + (base_even ^ 32);
-      floatx16 acc;
+      uint32_t even = blk + k_read, odd;
+      asm("" : "+v"(even));  // one register through the loop, not one for each
+      odd = even ^ 32;
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
-        const bf16x8 a = *reinterpret_cast<lds_bf16x8*>(((ks & 1) ? odd : even) + 64 * (ks >> 1));
+        const bf16x8 a = *reinterpret_cast<lds_bf16x8*>(static_cast<uintptr_t>(((ks & 1) ? odd : even) + 64 * (ks >> 1)));
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bq[ks], acc, 0, 0, 0);
       }
+      __builtin_amdgcn_sched_group_barrier(0x100, kKAhead, 0);
+#pragma unroll
+      for (int i = 0; i < 8 - kKAhead; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, kKAhead, 0);
       // ---- causal mask, online softmax ---------------------------------------------------------
       if (key0 + kBlockKeys - 1 > wave_min_q) {
         const int limit = q_eff - key0 + 1 - 4 * half;  // rows below this are visible
@@ -317,44 +352,82 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
         for (int v = 0; v < 16; ++v)
           if (8 * (v >> 2) + (v & 3) >= limit) acc[v] = -INFINITY;
       }
-      float bm = fmaxf(acc[0], acc[1]);
 #pragma unroll
-      for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, acc[v]), acc[v + 1]);
-      bm = max_across_halves(bm);
-      // finite from the first block on: key 0 is always visible
-      const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
-      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+      for (int i = 0; i < kVAhead; ++i) va[i] = load_v(i);
+      __builtin_amdgcn_sched_barrier(0);
+      // the reference goes to kWeightShift below the row's maximum, in all rows of a wave where one has a new maximum
+      auto follow = [&]() __attribute__((always_inline)) {
+        float bm = fmaxf(acc[0], acc[1]);
+#pragma unroll
+        for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, acc[v]), acc[v + 1]);
+        bm = max_across_halves(bm);
+        // finite from the first block on: key 0 is always visible
+        const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
+        if (__builtin_amdgcn_ballot_w64(m_new > m_run) == 0) return;
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 from -inf
         l_run *= alpha;
-        l_chunk *= alpha;
+        if (EMIT) l_chunk *= alpha;
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
           for (int v = 0; v < 16; ++v) ot[t][v] *= alpha;
         m_run = m_new;
-      }
-      float s0 = 0.f, s1 = 0.f;
+      };
+      auto weight = [&](int v) { return __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run)); };
+      auto pack = [&](int v, float w0, float w1) {
+        const f16x2 w = to_f16x2(w0, w1);
+        p16[v / 8][v % 8] = w[0];
+        p16[v / 8][v % 8 + 1] = w[1];
+        return w;
+      };
+      // the weights against the reference as it stands, and their sum as the product will see them
+      auto weigh = [&]() __attribute__((always_inline)) {
+        float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        pw[v] = __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run));
-        pw[v + 1] = __builtin_amdgcn_exp2f(fmaf(acc[v + 1], c, -m_run));
-        s0 += pw[v];
-        s1 += pw[v + 1];
+        for (int v = 0; v < 16; v += 4) {
+          s0 = __builtin_amdgcn_fdot2(pack(v, weight(v), weight(v + 1)), kOnes, s0, false);
+          s1 = __builtin_amdgcn_fdot2(pack(v + 2, weight(v + 2), weight(v + 3)), kOnes, s1, false);
+        }
+        return s0 + s1;
+      };
+      float sum;
+      if (EMIT) {  // the statistics take the weights in fp32
+        follow();
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+          acc[v] = weight(v);
+          acc[v + 1] = weight(v + 1);
+          pack(v, acc[v], acc[v + 1]);
+          s0 += acc[v];
+          s1 += acc[v + 1];
+        }
+        sum = block_sum = s0 + s1;
+      } else {
+        sum = weigh();
+        // a weight past fp16's range is infinite and so is the sum
+        if (__builtin_amdgcn_ballot_w64(!(sum < 0x1p30f)) != 0) {
+          follow();
+          sum = weigh();
+        }
       }
-      l_run += s0 + s1;
+      l_run += sum;
     } else {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) pw[v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
     }
     // ---- Eq. 3: this block's weights credited to the chunks it overlaps --------------------------
     if (wave_emits) {
       while (cur_c < n_seg && cur_s < key0 + kBlockKeys) {
         const int lo = max(cur_s, key0) - key0 - 4 * half, hi = min(cur_e, key0 + kBlockKeys) - key0 - 4 * half;
-        float sum = 0.f;
+        float sum = block_sum;
+        if (cur_s > key0 || cur_e < key0 + kBlockKeys) {
+          sum = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = 8 * (v >> 2) + (v & 3);
-          sum += (r >= lo && r < hi) ? pw[v] : 0.f;
+          for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + (v & 3);
+            sum += (r >= lo && r < hi) ? acc[v] : 0.f;
+          }
         }
         l_chunk += sum;
         if (cur_e <= key0 + kBlockKeys) finish_chunk();
@@ -363,34 +436,34 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
     }
     // ---- O^T += V_blk^T P^T in fp16 -------------------------------------------------------------------
     if (has_work) {
-      lds_cchar* vblk = lds_base + slot * kStageBytes + kKBytes;
-      const f16x8 p16[2] = {to_f16x8(pw), to_f16x8(pw + 8)};
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int d = 32 * t + (lane & 31);
+      for (int i = kVAhead; i < 8; ++i) va[i] = load_v(i);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          const int col = (2 * s + half) ^ ((d >> 2) & 3);
-          const f16x8 a = *reinterpret_cast<lds_f16x8*>(vblk + d * 64 + col * 16);
-          ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, p16[s], ot[t], 0, 0, 0);
-        }
+      for (int i = 0; i < 8; ++i)
+        ot[i >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[i], p16[i & 1], ot[i >> 1], 0, 0, 0);
+#pragma unroll
+      for (int i = kVAhead; i < 8; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
       }
+      __builtin_amdgcn_sched_group_barrier(0x008, kVAhead, 1);
     }
   }
 
   // ---- results -------------------------------------------------------------------------------------
-  const float l_tot = sum_across_halves(l_run);
   if (wave_emits) {
     // chunks that reach past this tile's keys hold what their visible part gave; later ones nothing
     while (cur_c < n_seg) finish_chunk();
-    if (lane_emits)
-      row_stat[(static_cast<size_t>(p) * H_kv + g) * R + h_local * W + win_j] = add_log2(m_run, l_tot);
+    const float l_row = sum_across_halves(l_run);
+    if (lane_emits) x.row_stat[plane * R + h_local * W + (q_row - win0)] = add_log2(m_run, l_row);
   }
-  if (q_row < n_tokens) {
+  // undoes V's scale; applied after the normalisation, because up / l_tot can fall below the normal range
+  const float up = plane_scale(x.v_absmax[plane], true);
+  const float l_tot = sum_across_halves(l_run);
+  const int row_out = wave_min_q + (lane_again() & 31);
+  if (!EMIT || row_out < n_tokens) {
     const float inv = 1.f / l_tot;
-    // undoes V's scale; applied after the normalisation, because up / l_tot can fall below the normal range
-    const float up = plane_scale(v_absmax[static_cast<size_t>(p) * H_kv + g], true);
-    float* dst = o_out + ((static_cast<size_t>(p) * H + h) * n_tokens + q_row) * kD + 4 * half;
+    float* dst = x.o_out + ((static_cast<size_t>(p) * x.H + h) * n_tokens + row_out) * kD + 4 * (lane_again() >> 5);
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -399,6 +472,29 @@ __global__ __launch_bounds__(kThreadsQ, 2) void attention_scores_kernel(
             make_float4(ot[t][4 * a] * inv * up, ot[t][4 * a + 1] * inv * up, ot[t][4 * a + 2] * inv * up,
                         ot[t][4 * a + 3] * inv * up);
   }
+}
+
+// n_plain tiles of queries that are not in the window, then the rest; the longest first.
+//
+// Bound by power: with the matrix pipe busy 66 % of the time the clock is 1.56 GHz at 32768 tokens (60 % and 1.65 GHz
+// before the reference stayed).  Whole call, 32 query / 8 KV heads, before and after the reference stays, operands are
+// read ahead and the segment ends sit in the lanes: 1500 tokens 88 and 80 us, 3000 tokens 161 and 145, 8192 603 and 573,
+// 32768 8385 and 7920.  Waves of 64 queries, which read LDS half as often, have registers for two per SIMD: 7400 - 7700
+// us at 32768 tokens, but 372 instead of 350 at 6000 and slower in most calls below, so there is one kernel.
+__global__ __launch_bounds__(kThreadsQ, 3) void attention_scores_kernel(AttentionArgs x, int n_plain) {
+  __shared__ __attribute__((aligned(64))) char lds[kRing][kStageBytes];
+  lds_cchar* lds_base = (lds_cchar*)&lds[0][0];
+  // Workgroups are dealt to the eight XCDs round-robin: query heads that read one KV head go to one XCD, whose L2
+  // then holds that head's K and V once instead of every XCD all of them (8192 tokens 601 -> 596 us, 20000 tokens
+  // 3262 -> 3137, 32768 tokens 8618 -> 8236, 64 heads at 6000 tokens 672 -> 638).  Where the heads of all problems
+  // together are no multiple of eight they keep their order.
+  const int total = gridDim.x * gridDim.y;
+  int head = blockIdx.x + gridDim.x * blockIdx.y;
+  if (total % 8 == 0) head = (head % 8) * (total / 8) + head / 8;
+  const int p = head / gridDim.x, h = head - p * gridDim.x;
+  const int tile = gridDim.z - 1 - blockIdx.z;  // long tiles first, for all heads and problems
+  if (tile < n_plain) attention_tile<false>(x, h, p, tile * kTileQ, lds_base);
+  else attention_tile<true>(x, h, p, tile * kTileQ, lds_base);
 }
 
 }  // namespace
@@ -427,14 +523,14 @@ hipError_t launch_attention_scores(const PrefillDims& d, const void* q, const vo
                                    const int32_t* shot_offsets, float* attn_out, const PrefillWorkspace& w,
                                    hipStream_t s) {
   const int nb = attention_key_blocks(d.n_tokens);
-  const dim3 grid(d.H, d.P, ceil_div(d.n_tokens, kTileQ));
   { KernelTimer plan_timer(d.timing, kKernelPlan, s); }  // the kernel walks the shot boundaries itself
   KernelTimer timer(d.timing, kKernelAttention, s);
-  hipLaunchKernelGGL(attention_scores_kernel, grid, dim3(kThreadsQ), 0, s, static_cast<const bf16_t*>(q),
-                     static_cast<const bf16_t*>(k), static_cast<const uint16_t*>(vt), w.v_absmax, d.n_tokens, nb, d.H,
-                     d.H_kv,
-                     d.W, d.sm_scale * kLog2e, attn_out, shot_offsets, d.share, d.n_shots, w.max_c, d.R, w.partial,
-                     w.group_stat);
+  const AttentionArgs args = {static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
+                              static_cast<const uint16_t*>(vt), w.v_absmax, d.n_tokens, nb, d.H, d.H_kv, d.W,
+                              d.sm_scale * kLog2e, attn_out, shot_offsets, d.share, d.n_shots, w.max_c, d.R, w.partial,
+                              w.group_stat};
+  const dim3 grid(d.H, d.P, ceil_div(d.n_tokens, kTileQ));
+  hipLaunchKernelGGL(attention_scores_kernel, grid, dim3(kThreadsQ), 0, s, args, (d.n_tokens - d.W) / kTileQ);
   return hipGetLastError();
 }
 

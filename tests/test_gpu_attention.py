@@ -76,6 +76,27 @@ def test_attention_and_compression_match_the_oracle(kv, H, H_kv, W, N, n_shots, 
     assert torch.equal(res.shot_selected, res2.shot_selected) and torch.equal(res.kept_count, res2.kept_count)
 
 
+@pytest.mark.parametrize("N,W,n_shots", [
+    (480, 16, 61), (480, 16, 62), (480, 16, 63), (512, 32, 64), (600, 32, 127),  # 64 segments, the ends a wave holds
+    (416, 32, 3), (417, 32, 3), (415, 32, 3),       # the window ends, or does not end, a tile of 128 queries (384 + 32)
+    (64, 64, 2), (65, 64, 2), (191, 64, 2), (40, 32, 1),    # nothing but window rows in most or all tiles
+])
+def test_segment_ends_and_tiles_at_the_window(kv, N, W, n_shots):
+    H, H_kv, budget = 2, 1, N
+    gen = torch.Generator().manual_seed(N + n_shots)
+    q, k, v = (torch.randn((1, h, N, 128), generator=gen).to(torch.bfloat16).cuda() for h in (H, H_kv, H_kv))
+    inner = 2 + torch.randperm(N - 4, generator=gen)[: n_shots + 1].sort().values     # back to back, some of one token
+    off = inner.to(torch.int32)[None].cuda()
+    bud = torch.tensor([budget], dtype=torch.int32, device="cuda")
+    scale = 128 ** -0.5
+    attn, res = kv.prefill_attention_compress(q, k, v, off, bud, budget, W, scale)
+    torch.cuda.synchronize()
+    ref = orc.causal_attention(to_np(q[0]), to_np(k[0]), to_np(v[0]), scale)
+    got = attn[0].cpu().numpy()
+    assert np.all(np.abs(got - ref) <= OUT_TOL * np.abs(ref).max(axis=2, keepdims=True))
+    check_prefill_problem(res, 0, q[0, :, N - W:], k[0], v[0], off[0].cpu().numpy(), budget, budget, scale)
+
+
 @pytest.mark.parametrize("factors", [(1e-30, 1.0), (3e4, 1e30), (2.0 ** -120, 2.0 ** 100), (0.0, 1.0)])
 def test_value_magnitudes(kv, factors):
     """The weighted-value product runs in fp16 behind an exact per-plane power-of-two scale: value planes
