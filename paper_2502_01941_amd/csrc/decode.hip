@@ -21,7 +21,21 @@ constexpr int kFinMaxHeads = 64;
 
 // lower score first, then the newer token: the order in which decode tokens are evicted
 __device__ __forceinline__ bool evict_before(float sa, int pa, float sb, int pb) {
-  return sa < sb || (sa == sb && pa > pb);
+  return (sa < sb) | ((sa == sb) & (pa > pb));
+}
+
+// Of two eviction candidates the better one goes to (score, pos, slot); a slot of -1 is none.
+__device__ __forceinline__ void take_better(float& score, int& pos, int& slot, float s, int p, int l) {
+  const bool better = (l >= 0) & ((slot < 0) | evict_before(s, p, score, pos));
+  score = better ? s : score;
+  pos = better ? p : pos;
+  slot = better ? l : slot;
+}
+template <int MASK>
+__device__ __forceinline__ void take_better_of_lane(float& score, int& pos, int& slot) {
+  take_better(score, pos, slot, __uint_as_float(lane_xor<MASK>(__float_as_uint(score))),
+              static_cast<int>(lane_xor<MASK>(static_cast<uint32_t>(pos))),
+              static_cast<int>(lane_xor<MASK>(static_cast<uint32_t>(slot))));
 }
 
 // Second half of a decode step.  Per sequence, workgroup 0 turns the decode-slot logits into
@@ -30,8 +44,11 @@ __device__ __forceinline__ bool evict_before(float sa, int pa, float sb, int pb)
 // split partials of kFinHeadsPerGroup query heads into the attention output (Eq. 9).  Every workgroup
 // first derives the softmax statistics of the heads it needs from the split partials.  The kernel is bound by
 // its trips to memory, so what the second phase needs - the logits of the first round of slots, the first
-// partials - is requested ahead of the statistics and all of it is one trip: 7.8 us for one sequence of 3800 rows
-// and 32 heads (8.6 one after the other), 10.4 us for 16 sequences of 5121 (10.8).
+// partials - is requested along with the first splits' statistics and all of it is one trip.  Those come first:
+// loads return in order, and the statistics are worked out while 64 KB of logits follow.  Reductions stay off the
+// LDS pipe.  One sequence of 3790 rows and 32 heads, whole step: 18.6 us with the statistics last and exchanges
+// through LDS, 17.3 like this (kernel 7.8 and 6.5); 32 sequences of 2514 rows per KV head 41.0 and 39.5, 16 of
+// 5121 67.4 and 66.5.
 // kAhead: heads whose logits of a thread's first slot are requested that way.  32 cost 100 registers, one workgroup
 // per CU, which is dear where heads are few and sequences many (per-KV-head mode: 256 pairs of 4 heads 12.1 us),
 // so up to 8 heads take the small form.
@@ -45,8 +62,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     int32_t* __restrict__ evicted_pos, int32_t* __restrict__ status) {
   const int s = blockIdx.y, tid = threadIdx.x;
   const int lane = tid % kWave, wave = tid / kWave;
-  __shared__ float s_M[kFinMaxHeads];
-  __shared__ float s_invL[kFinMaxHeads];
+  __shared__ float2 s_stat[kFinMaxHeads];  // per head: maximum, 1 / sum
   __shared__ float s_w[kFinHeadsPerGroup][kDecodeMaxSplits];  // merge workgroups only
   __shared__ __attribute__((aligned(16))) float s_o[kFinThreads * 4];  // merge workgroups only
   __shared__ float s_best_score[kFinWaves];
@@ -68,6 +84,20 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   int n_extra = n_slots > kFinThreads ? n_slots % kFinThreads : 0;
   if (n_extra > kMaxExtra * kFinWaves) n_extra = 0;
   const int n_main = n_slots - n_extra;
+
+  // ---- the first splits' statistics of a wave's first two heads: loads return in order, so they come first ----
+  float m_first[2], l_first[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int h = h_lo + wave + i * kFinWaves;
+    m_first[i] = -INFINITY;
+    l_first[i] = 0.f;
+    if (h < h_hi && lane < n_splits) {
+      const float2 ml = part_ml[(head0 + h) * n_splits + lane];
+      m_first[i] = ml.x;
+      l_first[i] = ml.y;
+    }
+  }
 
   // ---- what the second phase reads first -------------------------------------------------------------
   float z_first[kAhead];  // (a slot of no token may hold anything)
@@ -114,9 +144,15 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     const float2* ml = part_ml + (head0 + h) * n_splits;
     const float2* ml2 = part_ml + (head0 + (two ? h2 : h)) * n_splits;
     // the first 64 splits stay in registers, any others are looked at twice (out of cache)
-    const float2 none = make_float2(-INFINITY, 0.f);
-    const float2 a = lane < n_splits ? ml[lane] : none, b = lane < n_splits ? ml2[lane] : none;
-    float M = a.x, M2 = b.x;
+    const bool ahead = h < h_lo + 2 * kFinWaves;
+    float m = m_first[0], l = l_first[0], m2 = m_first[1], l2 = l_first[1];
+    if (!ahead) {
+      m = m2 = -INFINITY;
+      l = l2 = 0.f;
+      if (lane < n_splits) { m = ml[lane].x; l = ml[lane].y; }
+      if (lane < n_splits && two) { m2 = ml2[lane].x; l2 = ml2[lane].y; }
+    }
+    float M = m, M2 = m2;
     for (int i = lane + kWave; i < n_splits; i += kWave) {
       M = fmaxf(M, ml[i].x);
       M2 = fmaxf(M2, ml2[i].x);
@@ -124,22 +160,23 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     M = wave_max(M);
     M2 = wave_max(M2);
     float L = 0.f, L2 = 0.f;
-    for (int i = lane; i < n_splits; i += kWave) {
-      const float2 x = i == lane ? a : ml[i], y = i == lane ? b : ml2[i];
-      const float wgt = x.y > 0.f ? __builtin_amdgcn_exp2f(x.x - M) : 0.f;
-      const float wgt2 = y.y > 0.f ? __builtin_amdgcn_exp2f(y.x - M2) : 0.f;
-      L += x.y * wgt;
-      L2 += y.y * wgt2;
+    auto add_split = [&](int i, float m, float l, float m2, float l2) {
+      const float wgt = l > 0.f ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+      const float wgt2 = l2 > 0.f ? __builtin_amdgcn_exp2f(m2 - M2) : 0.f;
+      L += l * wgt;
+      L2 += l2 * wgt2;
       if (!retain) {
         s_w[h - h_lo][i] = wgt;
         if (two) s_w[h2 - h_lo][i] = wgt2;
       }
-    }
+    };
+    if (lane < n_splits) add_split(lane, m, l, m2, l2);
+    for (int i = lane + kWave; i < n_splits; i += kWave) add_split(i, ml[i].x, ml[i].y, ml2[i].x, ml2[i].y);
     L = wave_sum(L);
     L2 = wave_sum(L2);
     if (lane == 0) {
-      s_M[h] = M; s_invL[h] = 1.f / L;
-      if (two) { s_M[h2] = M2; s_invL[h2] = 1.f / L2; }
+      s_stat[h] = make_float2(M, 1.f / L);
+      if (two) s_stat[h2] = make_float2(M2, 1.f / L2);
     }
   }
   if (new_slot < 0) {  // pool full: the step is void for this sequence
@@ -182,7 +219,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
       float sum = 0.f;
 #pragma unroll
       for (int t = 0; t < kTeams; ++t) sum += s_o[t * kFinHeadsPerGroup * D + tid];
-      out[head0 * D + idx] = sum * s_invL[idx / D];
+      out[head0 * D + idx] = sum * s_stat[idx / D].y;
     }
     return;
   }
@@ -190,6 +227,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   // retention scores and the eviction candidate
   float best_score = INFINITY;
   int best_pos = -1, best_slot = -1, count = 0;
+  auto share = [&](float z, int h) { return __builtin_amdgcn_exp2f(z - s_stat[h].x) * s_stat[h].y; };
   constexpr int kHeadBatch = 16;  // loads in flight
   for (int slot = tid; slot < n_main; slot += kFinThreads) {
     const bool first = slot == tid;
@@ -201,7 +239,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
       if (first) {
 #pragma unroll
         for (int h = 0; h < kAhead; ++h)
-          if (h < H) score += __builtin_amdgcn_exp2f(z_first[h] - s_M[h]) * s_invL[h];
+          if (h < H) score += share(z_first[h], h);
       }
       for (int h0 = first ? kAhead : 0; h0 < H; h0 += kHeadBatch) {
         float zz[kHeadBatch];
@@ -209,11 +247,9 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
         for (int j = 0; j < kHeadBatch; ++j) zz[j] = z[static_cast<size_t>(min(h0 + j, H - 1)) * n_slots];
 #pragma unroll
         for (int j = 0; j < kHeadBatch; ++j)
-          if (h0 + j < H) score += __builtin_amdgcn_exp2f(zz[j] - s_M[h0 + j]) * s_invL[h0 + j];
+          if (h0 + j < H) score += share(zz[j], h0 + j);
       }
-      if (slot != new_slot && (best_slot < 0 || evict_before(score, pos, best_score, best_pos))) {
-        best_score = score; best_pos = pos; best_slot = slot;
-      }
+      if (slot != new_slot) take_better(best_score, best_pos, best_slot, score, pos, slot);
     }
     if (token_scores) token_scores[static_cast<size_t>(s) * n_slots + slot] = score;
   }
@@ -223,51 +259,41 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     if (slot < n_slots) {  // wave-uniform
       const int pos = slot == new_slot ? step_index : epos[k];
       float part = 0.f;
-      if (pos >= 0 && lane < H) part = __builtin_amdgcn_exp2f(ez[k] - s_M[lane]) * s_invL[lane];
+      if (pos >= 0 && lane < H) part = share(ez[k], lane);
       // same order of the head sum as in the main loop would need a serial add; a tree sum over the
       // heads differs from it only in rounding, within the score tolerance
       const float score = wave_sum(part);
       if (lane == 0) {
         if (pos >= 0) {
           ++count;
-          if (slot != new_slot && (best_slot < 0 || evict_before(score, pos, best_score, best_pos))) {
-            best_score = score; best_pos = pos; best_slot = slot;
-          }
+          if (slot != new_slot) take_better(best_score, best_pos, best_slot, score, pos, slot);
         }
         if (token_scores) token_scores[static_cast<size_t>(s) * n_slots + slot] = score;
       }
     }
   }
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    const float os = __shfl_xor(best_score, o, kWave);
-    const int op = __shfl_xor(best_pos, o, kWave);
-    const int ol = __shfl_xor(best_slot, o, kWave);
-    count += __shfl_xor(count, o, kWave);
-    if (ol >= 0 && (best_slot < 0 || evict_before(os, op, best_score, best_pos))) {
-      best_score = os; best_pos = op; best_slot = ol;
-    }
-  }
+  take_better_of_lane<32>(best_score, best_pos, best_slot);
+  take_better_of_lane<16>(best_score, best_pos, best_slot);
+  take_better_of_lane<8>(best_score, best_pos, best_slot);
+  take_better_of_lane<4>(best_score, best_pos, best_slot);
+  take_better_of_lane<2>(best_score, best_pos, best_slot);
+  take_better_of_lane<1>(best_score, best_pos, best_slot);
+  count = wave_sum(count);
   if (lane == 0) {
-    s_best_score[wave] = best_score; s_best_pos[wave] = best_pos;
-    s_best_slot[wave] = best_slot; s_count[wave] = count;
+    s_best_score[wave] = best_score; s_best_pos[wave] = best_pos; s_best_slot[wave] = best_slot;
+    s_count[wave] = count;
   }
   __syncthreads();  // also: every thread has read its slot_pos entries before thread 0 rewrites two
   if (wave == 0) {
-    const bool has = lane < kFinWaves;
-    best_score = has ? s_best_score[lane] : INFINITY;
-    best_pos = has ? s_best_pos[lane] : -1;
-    best_slot = has ? s_best_slot[lane] : -1;
-    int total = has ? s_count[lane] : 0;
-#pragma unroll
-    for (int o = kFinWaves / 2; o > 0; o >>= 1) {
-      const float os = __shfl_xor(best_score, o, kWave);
-      const int op = __shfl_xor(best_pos, o, kWave);
-      const int ol = __shfl_xor(best_slot, o, kWave);
-      total += __shfl_xor(total, o, kWave);
-      if (ol >= 0 && (best_slot < 0 || evict_before(os, op, best_score, best_pos))) {
-        best_score = os; best_pos = op; best_slot = ol;
-      }
-    }
+    static_assert(kFinWaves == 16, "one row of lanes");
+    best_score = s_best_score[lane % kFinWaves];
+    best_pos = s_best_pos[lane % kFinWaves];
+    best_slot = s_best_slot[lane % kFinWaves];
+    const int total = wave_sum(lane < kFinWaves ? s_count[lane] : 0);
+    take_better_of_lane<8>(best_score, best_pos, best_slot);
+    take_better_of_lane<4>(best_score, best_pos, best_slot);
+    take_better_of_lane<2>(best_score, best_pos, best_slot);
+    take_better_of_lane<1>(best_score, best_pos, best_slot);
     if (lane == 0) {
       sp[new_slot] = step_index;
       int ev = -1;

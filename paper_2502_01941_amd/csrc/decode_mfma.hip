@@ -217,10 +217,8 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
         }
       }
     }
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-      best = min(best, __shfl_xor(best, o, kWave));
-      last_used = max(last_used, __shfl_xor(last_used, o, kWave));
-    }
+    best = wave_min(best);
+    last_used = wave_max(last_used);
     if (lane == 0) { s_red[0][wave] = best; s_red[1][wave] = last_used; }
     __syncthreads();
 #pragma unroll

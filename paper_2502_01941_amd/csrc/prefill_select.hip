@@ -72,32 +72,6 @@ __device__ __forceinline__ uint64_t rank_key(float score, int idx) {
 }
 __device__ __forceinline__ uint64_t padding_key(int idx) { return 0xFFFFFFFFu - static_cast<uint32_t>(idx); }
 
-// Value of lane (own lane ^ MASK), MASK a power of two below 64, without a trip through the LDS pipe:
-// data-parallel-primitive moves inside a row of 16 lanes (1, 2: quad permutations; 4: the mirror of 8
-// lanes followed by the mirror of 4; 8: a rotation of the row by 8), row swaps for 16 and half swaps for 32.
-template <int MASK>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
-  static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8 || MASK == 16 || MASK == 32, "one lane bit");
-  if constexpr (MASK == 1) {
-    return __builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
-  } else if constexpr (MASK == 2) {
-    return __builtin_amdgcn_update_dpp(0u, v, 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
-  } else if constexpr (MASK == 4) {
-    const uint32_t m = __builtin_amdgcn_update_dpp(0u, v, 0x141, 0xf, 0xf, false);  // row_half_mirror: lane ^ 7
-    return __builtin_amdgcn_update_dpp(0u, m, 0x1B, 0xf, 0xf, false);               // quad_perm [3,2,1,0]: ^ 3
-  } else if constexpr (MASK == 8) {
-    return __builtin_amdgcn_update_dpp(0u, v, 0x128, 0xf, 0xf, false);  // row_ror:8
-  } else if constexpr (MASK == 16) {
-    // first result: own even rows, the other operand's even rows in the odd rows; second: the odd rows
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    return (threadIdx.x & 16) ? r[0] : r[1];
-  } else {
-    // first result: the lower half in both halves; second: the upper half in both
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return (threadIdx.x & 32) ? r[0] : r[1];
-  }
-}
-
 template <int MASK>
 __device__ __forceinline__ uint64_t lane_xor64(uint64_t v) {
   const uint32_t lo = lane_xor<MASK>(static_cast<uint32_t>(v));
