@@ -3,17 +3,25 @@
 // shots in descending order while the budget holds).  One workgroup per problem does all of it:
 //
 //   scores    Score(s_i) = (sum of the masses of the shot's chunks) / k_i;
-//   ranking   bitonic sort on one 64-bit key per shot (score descending, shot index ascending): keys
-//             live in registers, partners less than 64 apart are exchanged between lanes without LDS
-//             (DPP moves inside a row of 16, row and half swaps beyond), and for the larger strides the keys pass through LDS into a transposed layout in which
-//             those strides are lane distances too - two LDS round trips per merge level instead of
-//             one per compare-exchange step;
-//   budget    prefix sum of shot lengths in rank order (or the sequential first-fit walk);
-//   plan      prefix sum of kept lengths in position order gives every retained row's output slot;
-//             the original position of each output row is written in ascending order.
+//   budget    prefix selection needs no ranking, only where in it the budget ends: up to 128 shots a group of lanes
+//             per shot adds the lengths of all that rank no lower; above, the key of the shot at which the budget ends
+//             is found a digit at a time from histograms of lengths (in LDS; integer sums, so their order is free);
+//   ranking   first fit walks all shots in order: bitonic sort on one 64-bit key per shot (score descending, shot index
+//             ascending): keys live in registers, partners less than 64 apart are exchanged between lanes without LDS
+//             (DPP moves inside a row of 16, row and half swaps beyond), and for the larger strides the keys pass
+//             through LDS into a transposed layout in which those strides are lane distances too - two LDS round trips
+//             per merge level instead of one per compare-exchange step;
+//   plan      sums of kept lengths in position order give every retained row's output slot; the segments that keep
+//             tokens are numbered by the same pass, so that the original positions, written in ascending order, take a
+//             group of lanes for each of these and none for the others.
 //
-// The two halves can also run alone: scores only, or selection from caller-supplied scores.  All sums
-// run in a fixed order (no atomics), so results are reproducible run to run.
+// Bound by a chain of barriers and trips to memory in one workgroup.  Inside the kernel, sorting and walking the sums
+// against this: 40 shots 2.1 + 1.8 us and 0.6, 80 shots 3.4 + 1.5 and 1, 600 units 7.8 + 1.7 and 3.3 (the sort of 400
+// shots for first fit is 7.5); writing the positions of 600 units 4.0 and 1.9.  Whole call: 8192 tokens in 40 shots
+// 29.5 -> 26.6 us, 16 x 16001 tokens of head_dim 64 in 80 shots 117.8 -> 113.5, 64 x 600 units 159.6 -> 150.8.
+//
+// The two halves can also run alone: scores only, or selection from caller-supplied scores.  All
+// sums of floats run in a fixed order, so results are reproducible run to run.
 #include "common.hpp"
 
 #include <type_traits>
@@ -25,36 +33,35 @@ namespace {
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 
-// block-wide exclusive scan over `n` ints stored in LDS array `a` (in place), returns the total.
-// `tmp` is kSelWaves + 1 ints of LDS.
-__device__ int block_exclusive_scan(int* a, int n, int* tmp) {
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int per = (n + kSelThreads - 1) / kSelThreads;
-  const int lo = min(tid * per, n), hi = min(lo + per, n);
-  int sum = 0;
-  for (int i = lo; i < hi; ++i) sum += a[i];
-  int incl = sum;  // inclusive scan of the per-thread sums inside the wave
+// Inclusive sum over the lanes up to the own one, without a trip through the LDS pipe: shifts inside a row of 16 lanes,
+// then the last lane of a row (of the lower half) to the rows behind it.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Exclusive sums over all threads of two values at once; total_a and total_b are the sums.  tmp: 2 * kSelWaves ints.
+__device__ __forceinline__ void block_exclusive_scan(int& a, int& b, int& total_a, int& total_b, int* tmp) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int incl_a = wave_inclusive_scan(a), incl_b = wave_inclusive_scan(b);
+  if (lane == kWave - 1) { tmp[wave] = incl_a; tmp[kSelWaves + wave] = incl_b; }
+  __syncthreads();
+  int before_a = 0, before_b = 0;
+  total_a = total_b = 0;
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int up = __shfl_up(incl, o, kWave);
-    if (lane >= o) incl += up;
-  }
-  if (lane == kWave - 1) tmp[wave] = incl;
-  __syncthreads();
-  int before = 0, total = 0;
   for (int w = 0; w < kSelWaves; ++w) {
-    const int t = tmp[w];
-    if (w < wave) before += t;
-    total += t;
+    const int ta = tmp[w], tb = tmp[kSelWaves + w];
+    if (w < wave) { before_a += ta; before_b += tb; }
+    total_a += ta;
+    total_b += tb;
   }
-  int run = before + incl - sum;
-  for (int i = lo; i < hi; ++i) {
-    const int v = a[i];
-    a[i] = run;
-    run += v;
-  }
-  __syncthreads();
-  return total;
+  a = before_a + incl_a - a;
+  b = before_b + incl_b - b;
 }
 
 constexpr int kMaxPad = SHOTKV_MAX_SHOTS;            // keys sorted at most (a power of two)
@@ -64,11 +71,13 @@ static_assert((kMaxPad & (kMaxPad - 1)) == 0 && kMaxPad <= 4 * kSelThreads, "up 
 // One key per shot whose descending order is the ranking: score descending, then index ascending.
 // The float's bits are mapped to an unsigned integer with the same order (-0 ranks with +0); entry i
 // of the padding (i >= n_shots) gets the smallest score word and therefore ranks after every shot.
-__device__ __forceinline__ uint64_t rank_key(float score, int idx) {
+__device__ __forceinline__ uint32_t score_word(float score) {
   uint32_t b = __float_as_uint(score);
   if ((b << 1) == 0u) b = 0u;
-  const uint32_t u = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-  return (static_cast<uint64_t>(u) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(idx));
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+__device__ __forceinline__ uint64_t rank_key(float score, int idx) {
+  return (static_cast<uint64_t>(score_word(score)) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(idx));
 }
 __device__ __forceinline__ uint64_t padding_key(int idx) { return 0xFFFFFFFFu - static_cast<uint32_t>(idx); }
 
@@ -159,12 +168,7 @@ __device__ void first_fit_walk(const int* len, const uint16_t* shot, int n, int 
     const int my_len = r < n ? len[r] : 0;
     bool open = r < n && my_len <= left, taken = false;
     while (__builtin_amdgcn_ballot_w64(open) != 0) {
-      int incl = open ? my_len : 0;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int up = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += up;
-      }
+      const int incl = wave_inclusive_scan(open ? my_len : 0);
       const uint64_t over = __builtin_amdgcn_ballot_w64(open && incl > left);
       const int first = over ? __builtin_ctzll(over) : kWave;  // the first candidate that does not fit
       if (open && lane < first) taken = true;
@@ -174,6 +178,90 @@ __device__ void first_fit_walk(const int* len, const uint16_t* shot, int n, int 
     }
     if (taken) keep[shot[r]] = 1;
   }
+}
+
+// Whether each of a thread's shots (threadIdx.x + 1024 * j) is among the first of the ranking that fit into `left` tokens
+// together.  No ranking is needed for that, only the shot at which the budget ends: its key - score descending, then
+// index ascending, 44 bits - is found a digit of eight bits at a time, from a histogram of the lengths over the digit of
+// the keys that share the digits before.  A digit that one key has ends the search: two or three rounds unless scores are
+// equal.  hist: kDigits * 256 words, cleared.  All threads call it, after a barrier behind the clearing.
+constexpr int kDigits = 6;
+__device__ __forceinline__ void keep_prefix(const float (&score)[kMaxPad / kSelThreads],
+                                            const int (&len)[kMaxPad / kSelThreads], int n, int left, uint64_t* hist,
+                                            bool (&keep)[kMaxPad / kSelThreads]) {
+  constexpr int kPer = kMaxPad / kSelThreads;
+  constexpr int kCount = 40;  // a word is count << 40 | tokens
+  static_assert(kMaxPad <= 1 << 12, "indexes of 12 bits");
+  const int tid = threadIdx.x, lane = tid % kWave;
+  uint64_t key[kPer];
+  bool open[kPer];  // shares the digits so far with the shot at which the budget ends
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int i = tid + kSelThreads * j;
+    key[j] = static_cast<uint64_t>(score_word(score[j])) << 12 | static_cast<uint32_t>(kMaxPad - 1 - i);
+    open[j] = i < n;
+    keep[j] = false;
+  }
+#pragma clang loop unroll(disable)
+  for (int digit = 0; digit < kDigits; ++digit, hist += 256) {
+    const int shift = max(36 - 8 * digit, 0);
+    int d[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      d[j] = static_cast<int>(key[j] >> shift) & (digit == kDigits - 1 ? 15 : 255);
+      if (open[j])
+        atomicAdd(reinterpret_cast<unsigned long long*>(&hist[d[j]]), 1ull << kCount | static_cast<unsigned>(len[j]));
+    }
+    __syncthreads();
+    // every wave looks through all digits, highest first, four to a lane
+    uint64_t word[4];
+    int tokens = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      word[q] = hist[255 - 4 * lane - q];
+      tokens += static_cast<int>(word[q]);
+    }
+    int before = wave_inclusive_scan(tokens) - tokens;
+    const uint64_t over = __builtin_amdgcn_ballot_w64(before + tokens > left);
+    int at = -1, count = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = static_cast<int>(word[q]);
+      if (at < 0 && before + t > left) {
+        at = 255 - 4 * lane - q;
+        count = static_cast<int>(word[q] >> kCount);
+      }
+      if (at < 0) before += t;
+    }
+    const int first = over ? __builtin_ctzll(over) : 0;
+    at = over ? __builtin_amdgcn_readlane(at, first) : -1;  // all fit: every digit is above
+    left -= over ? __builtin_amdgcn_readlane(before, first) : 0;
+    count = over ? __builtin_amdgcn_readlane(count, first) : 1;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      keep[j] |= open[j] && d[j] > at;
+      open[j] = open[j] && d[j] == at;
+    }
+    if (count == 1) break;  // the shot at which the budget ends, or none
+  }
+}
+
+// The same for few shots, without the rounds: a group of lanes per shot adds the lengths of all that rank no lower.
+// word_len: n words, score word << 32 | length, behind a barrier.  lanes: per shot, 8 or 16.  Returned to all of the group.
+__device__ __forceinline__ bool among_first(const uint64_t* word_len, int n, int i, int part, int lanes, int left) {
+  const uint32_t own = i < n ? static_cast<uint32_t>(word_len[i] >> 32) : 0u;
+  int sum = 0;
+#pragma unroll 4
+  for (int j = part; j < n; j += lanes) {
+    const uint64_t x = word_len[j];
+    const uint32_t word = static_cast<uint32_t>(x >> 32);
+    sum += (word > own) | ((word == own) & (j <= i)) ? static_cast<int>(x) : 0;
+  }
+  sum += static_cast<int>(lane_xor<1>(static_cast<uint32_t>(sum)));
+  sum += static_cast<int>(lane_xor<2>(static_cast<uint32_t>(sum)));
+  sum += static_cast<int>(lane_xor<4>(static_cast<uint32_t>(sum)));
+  if (lanes == 16) sum += static_cast<int>(lane_xor<8>(static_cast<uint32_t>(sum)));
+  return sum <= left;
 }
 
 // Sum of words[first], words[first + width], ... of n words: kBatch loads in flight, added up as a tree.
@@ -209,17 +297,21 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
   float* scores = shot_scores + static_cast<size_t>(p) * n_shots;
 
   __shared__ int s_off[SHOTKV_MAX_SHOTS + 1];
-  __shared__ uint64_t s_key[kKeySlots];       // the sort's exchange buffer, then (as ints) the scan array
-  __shared__ uint16_t s_idx[SHOTKV_MAX_SHOTS];
+  __shared__ uint64_t s_key[kKeySlots];       // histograms or the sort's exchange buffer, then (as ints) first rows
+  __shared__ uint16_t s_idx[SHOTKV_MAX_SHOTS + 2];  // the ranking, then the segments that keep tokens
   __shared__ uint8_t s_keep[SHOTKV_MAX_SHOTS];
-  __shared__ int s_tmp[kSelWaves + 1];
+  __shared__ int s_tmp[2 * kSelWaves];
   __shared__ int s_flag;
   __shared__ float s_sum[kSelThreads / 2];    // mass of every shot, where a shot has more than one lane
-  int* s_a = reinterpret_cast<int*>(s_key);   // SHOTKV_MAX_SHOTS + 2 ints
-  static_assert(sizeof(uint64_t) * kKeySlots >= sizeof(int) * (SHOTKV_MAX_SHOTS + 2), "scan array fits");
+  int* s_a = reinterpret_cast<int*>(s_key);   // SHOTKV_MAX_SHOTS + 3 ints
+  static_assert(sizeof(uint64_t) * kKeySlots >= sizeof(int) * (SHOTKV_MAX_SHOTS + 3), "first rows fit");
+  static_assert(kKeySlots >= kDigits * 256, "histograms fit");
 
   // ---- shot boundaries into LDS, validated: 0 <= off[0], strictly increasing, off[n] <= n_tokens --
   if (tid == 0) s_flag = 0;
+  if (SELECT)
+    for (int i = tid; i < kDigits * 256; i += kSelThreads) s_key[i] = 0;
+  const int budget = SELECT ? budget_tokens[p / share] : 0;  // (requested with the boundaries)
   __syncthreads();
   int local_bad = 0;
   for (int i = tid; i <= n_shots; i += kSelThreads) {
@@ -294,7 +386,7 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
   if (st == SHOTKV_ST_OK) {
     n_prefix = s_off[0];
     n_tail = n_tokens - s_off[n_shots];
-    shot_budget = min(budget_tokens[p / share], cap) - n_prefix - n_tail;
+    shot_budget = min(budget, cap) - n_prefix - n_tail;
     if (shot_budget < 0) st = SHOTKV_ST_BUDGET_TOO_SMALL;
   }
   if (st != SHOTKV_ST_OK) {
@@ -303,74 +395,103 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     return;
   }
 
-  // ---- rank: sort one key per shot, descending ----------------------------------------------------
-  int n_pad = kWave;
-  while (n_pad < n_shots) n_pad <<= 1;
-  {
-    uint64_t key[kMaxPerThread];
+  if (select_mode == SHOTKV_SELECT_PREFIX && n_shots <= kSelThreads / 8) {
+    // Rounds of the histogram cost 0.6 us each, this about as much in all: 40 shots 27.5 us a call with the histogram.
+    if (tid < n_shots)
+      s_key[tid] = static_cast<uint64_t>(score_word(my_score[0])) << 32 |
+                   static_cast<uint32_t>(s_off[tid + 1] - s_off[tid]);
+    __syncthreads();
+    const int lanes = n_shots <= kSelThreads / 16 ? 16 : 8, i = tid / lanes;
+    const bool keep = among_first(s_key, n_shots, i, tid % lanes, lanes, shot_budget);
+    if (tid % lanes == 0 && i < n_shots) s_keep[i] = keep;
+    __syncthreads();
+  } else if (select_mode == SHOTKV_SELECT_PREFIX) {
+    int len[kMaxPerThread];
+    bool keep[kMaxPerThread];
 #pragma unroll
     for (int j = 0; j < kMaxPerThread; ++j) {
       const int i = tid + kSelThreads * j;
-      key[j] = i < n_shots ? rank_key(my_score[j], i) : padding_key(i);
+      len[j] = i < n_shots ? s_off[i + 1] - s_off[i] : 0;
     }
-    if (n_pad <= kSelThreads) {
-      uint64_t k1[1] = {key[0]};
-      sort_keys_descending<1>(k1, n_pad, s_key);
-      key[0] = k1[0];
-    } else if (n_pad <= 2 * kSelThreads) {
-      uint64_t k2[2] = {key[0], key[1]};
-      sort_keys_descending<2>(k2, n_pad, s_key);
-      key[0] = k2[0];
-      key[1] = k2[1];
-    } else {
-      sort_keys_descending<kMaxPerThread>(key, n_pad, s_key);
-    }
+    keep_prefix(my_score, len, n_shots, shot_budget, s_key, keep);
 #pragma unroll
     for (int j = 0; j < kMaxPerThread; ++j) {
-      const int r = tid + kSelThreads * j;  // rank
-      if (r < n_shots) s_idx[r] = static_cast<uint16_t>(0xFFFFFFFFu - static_cast<uint32_t>(key[j]));
+      const int i = tid + kSelThreads * j;
+      if (i < n_shots) s_keep[i] = keep[j];
     }
-  }
-  __syncthreads();  // the ranking is complete, and the exchange buffer is free to become the scan array
+    __syncthreads();  // (also: the histograms' memory becomes the scan array)
+  } else {
+    // ---- rank: sort one key per shot, descending --------------------------------------------------
+    int n_pad = kWave;
+    while (n_pad < n_shots) n_pad <<= 1;
+    {
+      uint64_t key[kMaxPerThread];
+#pragma unroll
+      for (int j = 0; j < kMaxPerThread; ++j) {
+        const int i = tid + kSelThreads * j;
+        key[j] = i < n_shots ? rank_key(my_score[j], i) : padding_key(i);
+      }
+      if (n_pad <= kSelThreads) {
+        uint64_t k1[1] = {key[0]};
+        sort_keys_descending<1>(k1, n_pad, s_key);
+        key[0] = k1[0];
+      } else if (n_pad <= 2 * kSelThreads) {
+        uint64_t k2[2] = {key[0], key[1]};
+        sort_keys_descending<2>(k2, n_pad, s_key);
+        key[0] = k2[0];
+        key[1] = k2[1];
+      } else {
+        sort_keys_descending<kMaxPerThread>(key, n_pad, s_key);
+      }
+#pragma unroll
+      for (int j = 0; j < kMaxPerThread; ++j) {
+        const int r = tid + kSelThreads * j;  // rank
+        if (r < n_shots) s_idx[r] = static_cast<uint16_t>(0xFFFFFFFFu - static_cast<uint32_t>(key[j]));
+      }
+    }
+    __syncthreads();  // the ranking is complete, and the exchange buffer is free to hold the lengths
 
-  // ---- budget walk in rank order ---------------------------------------------------------------------
-  for (int i = tid; i < n_shots; i += kSelThreads) {
-    const int shot = s_idx[i];
-    s_a[i] = s_off[shot + 1] - s_off[shot];
-    s_keep[i] = 0;
-  }
-  __syncthreads();
-  if (select_mode == SHOTKV_SELECT_PREFIX) {
-    block_exclusive_scan(s_a, n_shots, s_tmp);
-    // s_a[r] = tokens used by the shots ranked above r; lengths are positive, so the inclusive sums
-    // are increasing and the kept ranks are exactly those whose inclusive sum fits
-    for (int r = tid; r < n_shots; r += kSelThreads) {
-      const int shot = s_idx[r];
-      const int inclusive = s_a[r] + (s_off[shot + 1] - s_off[shot]);
-      if (inclusive <= shot_budget) s_keep[shot] = 1;
+    // ---- budget walk in rank order -----------------------------------------------------------------
+    for (int i = tid; i < n_shots; i += kSelThreads) {
+      const int shot = s_idx[i];
+      s_a[i] = s_off[shot + 1] - s_off[shot];
+      s_keep[i] = 0;
     }
-  } else if (tid < kWave) {
-    first_fit_walk(s_a, s_idx, n_shots, shot_budget, s_keep);
+    __syncthreads();
+    if (tid < kWave) first_fit_walk(s_a, s_idx, n_shots, shot_budget, s_keep);
+    __syncthreads();
   }
-  __syncthreads();
 
   // ---- copy plan in position order: segment 0 = prefix, 1..n = shots, n+1 = tail ----------------
+  // A segment's first output row and, among the segments that keep tokens, its number.
   const int n_seg = n_shots + 2;
-  auto segment = [&](int s, int& src, int& len) {
-    if (s == 0) { src = 0; len = n_prefix; }
-    else if (s == n_seg - 1) { src = s_off[n_shots]; len = n_tail; }
-    else { src = s_off[s - 1]; len = s_keep[s - 1] ? (s_off[s] - s_off[s - 1]) : 0; }
+  auto segment_start = [&](int s) { return s == 0 ? 0 : s_off[s - 1]; };
+  auto segment_len = [&](int s) {
+    if (s > 0 && s <= n_shots && !s_keep[s - 1]) return 0;
+    return (s <= n_shots ? s_off[s] : n_tokens) - segment_start(s);
   };
-  for (int s = tid; s < n_seg; s += kSelThreads) {
-    int src, len;
-    segment(s, src, len);
-    s_a[s] = len;
+  const int per = (n_seg + kSelThreads - 1) / kSelThreads, seg0 = min(tid * per, n_seg), seg1 = min(seg0 + per, n_seg);
+  int row = 0, number = 0, total, n_kept;
+  for (int s = seg0; s < seg1; ++s) {
+    const int len = segment_len(s);
+    row += len;
+    number += len > 0;
   }
+  block_exclusive_scan(row, number, total, n_kept, s_tmp);
+  for (int s = seg0; s < seg1; ++s) {
+    const int len = segment_len(s);
+    if (len > 0) {
+      s_a[number] = row;
+      s_idx[number] = static_cast<uint16_t>(s);
+      row += len;
+      ++number;
+    }
+  }
+  if (tid == 0) s_a[n_kept] = total;
   __syncthreads();
-  const int total = block_exclusive_scan(s_a, n_seg, s_tmp);  // s_a[s] = first output row of segment s
-  // every retained row's original position: a group of lanes per segment, lanes along the rows; the
+  // Every retained row's original position: a group of lanes per segment that keeps tokens, lanes along the rows; the
   // group is as wide as an average shot is long (a wave for shots of hundreds of tokens, 8..32 lanes for
-  // sentence-sized units), so that most lanes have a row to write
+  // sentence-sized units), so that most lanes have a row to write.
   int group_w = 8;
   {
     const int avg = n_shots > 0 ? (s_off[n_shots] - s_off[0]) / n_shots : kWave;
@@ -378,16 +499,14 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
   }
   const int n_groups = kSelThreads / group_w, gid = tid / group_w, gl = tid % group_w;
   constexpr int kSegBatch = 4;  // segments whose LDS lookups are in flight together
-  for (int s0 = gid; s0 < n_seg; s0 += n_groups * kSegBatch) {
+  for (int k0 = gid; k0 < n_kept; k0 += n_groups * kSegBatch) {
     int src[kSegBatch], len[kSegBatch], dst[kSegBatch];
 #pragma unroll
     for (int b = 0; b < kSegBatch; ++b) {
-      const int s = s0 + b * n_groups;
-      src[b] = 0; len[b] = 0; dst[b] = 0;
-      if (s < n_seg) {
-        segment(s, src[b], len[b]);
-        dst[b] = s_a[s];
-      }
+      const int k = min(k0 + b * n_groups, n_kept - 1);
+      dst[b] = s_a[k];
+      len[b] = k0 + b * n_groups < n_kept ? s_a[k + 1] - dst[b] : 0;
+      src[b] = segment_start(s_idx[k]);
     }
 #pragma unroll
     for (int b = 0; b < kSegBatch; ++b)

@@ -263,6 +263,42 @@ def test_ranking_sizes_and_special_scores(kv, n):
             np.testing.assert_array_equal(helpers.bits(res.k_out[p, :, :kept]), helpers.bits(k[p][:, idx]))
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129, 255, 700, 1024, 1025, 2049, 4096])
+def test_where_the_budget_ends(kv, n):
+    """Prefix selection without a ranking: a group of lanes per shot up to 128 shots, a search for the last shot's key
+    digit by digit above.  Budgets that end exactly at, one before and one behind a shot's end, that keep nothing and
+    everything; scores that differ in the last bit only, that are equal in blocks and all of them."""
+    rng = np.random.default_rng(n)
+    P, H, Hkv, W, D = 15, 2, 1, 4, 64
+    lens = rng.integers(1, 6, size=(P, n))
+    N = int(lens.sum(axis=1).max()) + 9
+    off = np.zeros((P, n + 1), dtype=np.int32)
+    off[:, 0] = rng.integers(0, 4, size=P)
+    off[:, 1:] = off[:, :1] + np.cumsum(lens, axis=1)
+    kinds = [rng.random(n).astype(np.float32), 1 + np.float32(2.0 ** -23) * rng.permutation(n).astype(np.float32),
+             rng.integers(0, 3, size=n).astype(np.float32), np.zeros(n, dtype=np.float32),
+             np.exp(30 * rng.standard_normal(n)).astype(np.float32)]
+    scores = np.stack([kinds[p % 5] for p in range(P)])
+    budgets, wants = np.zeros(P, dtype=np.int32), []
+    for p in range(P):
+        order = np.asarray(orc.rank_shots(scores[p]))
+        ends = np.cumsum(lens[p][order])
+        room = [0, int(ends[-1]), int(ends[n // 2]), int(ends[n // 3]) - 1, int(ends[(2 * n) // 3]) + 1][(p + p // 5) % 5]
+        budgets[p] = off[p, 0] + (N - off[p, -1]) + room
+        keep = np.asarray(orc.select_shots(scores[p], lens[p], room, orc.SELECT_PREFIX))
+        assert np.array_equal(np.sort(order[ends <= room]), np.flatnonzero(keep))
+        wants.append((keep, orc.kept_positions_from_mask(keep, off[p], N)))
+    k, v = (torch.randn((P, Hkv, N, D), device="cuda") for _ in range(2))
+    res = kv.select_and_compact(torch.from_numpy(scores).cuda(), k, v, torch.from_numpy(off).cuda(),
+                                torch.from_numpy(budgets).cuda(), N, H, W)
+    torch.cuda.synchronize()
+    for p, (keep, pos) in enumerate(wants):
+        assert int(res.status[p]) == 0 and int(res.kept_count[p]) == len(pos)
+        assert np.array_equal(res.shot_selected[p].cpu().numpy().astype(bool), keep.astype(bool))
+        assert np.array_equal(res.kept_positions[p, :len(pos)].cpu().numpy(), pos)
+        assert torch.equal(res.k_out[p, :, :len(pos)], k[p][:, torch.from_numpy(pos).long().cuda()])
+
+
 def test_many_shots_selection(kv):
     """Sentence-sized units: thousands of short spans stress the sort, the scans and the copy plan."""
     P, H, Hkv, D, W, N, n = 2, 8, 2, 128, 32, 40000, 3000
