@@ -34,11 +34,15 @@
 //
 // fp32: the matrix unit's own fp32 form takes 16 times as long per product as bf16, so both operands are split
 // into three bf16 parts (split_f32) and six products of parts are summed in fp32, 0.37 of that time; the few values
-// that bf16 parts cannot hold take the fp32 form (logits_block).  Error of the scores against float64 over head
+// that bf16 parts cannot hold take the fp32 form (logits_block).  Splitting is as much vector work (350 instructions a
+// block) as the products are matrix work, so four and eight waves split a block between them and read each other's parts
+// from LDS, for a second barrier and 26 KB more LDS; two workgroups per CU instead of three is the price: 640 workgroups
+// (2 problems of 20000 tokens) 121 us a call, 120 if each wave splits all.  Error of the scores against float64 over head
 // layouts, windows and 1001 .. 65000 tokens: 0.3 - 0.8e-7 of the norm.  One query block per wave (96 operand
-// registers at head_dim 128), up to eight waves per workgroup, all reading the same block.  4 problems of 4001 tokens,
-// 8 KV heads, 128 query rows, head_dim 128: 37 us, with the fp32 form 48, with plain vector arithmetic 394; 16 of 8192
-// tokens (whole call) 351 us, with the fp32 form 420.
+// registers at head_dim 128), up to eight waves per workgroup.  4 problems of 4001 tokens, 8 KV heads, 128 query rows,
+// head_dim 128: 33 us, 37 if each wave splits for itself, with the fp32 form 48, with plain vector arithmetic 394.  Whole
+// calls, shared and each for itself: 16 of 8192 tokens 302 and 321 us, head_dim 64 4 of 9000 with 256 rows 103 and 112,
+// one of 100000 with 224 rows 247 and 277.
 //
 // The direct-to-LDS loads are written as inline assembly and their completion is tracked by hand with
 // s_waitcnt vmcnt: when they are visible to the compiler it makes every LDS read wait for all loads
@@ -58,6 +62,9 @@ typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) const char lds_cchar;  // keeps LDS reads as ds_read, not flat
 typedef __attribute__((address_space(3))) const int lds_cint;
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8_out;
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
@@ -106,6 +113,9 @@ template <typename T, int D> struct Element {
   static constexpr int kLoadsPerBlock = kBlockKeys * kRowBytes / 1024;  // 1 KB direct-to-LDS instructions
   static constexpr int kBufBytes = kLoadsPerBlock * KeyLayout<kRowBytes>::kLoadBytes;
   typedef KeyLayout<kRowBytes> Layout;
+  // fp32: the three bf16 parts of a block lie in LDS like three bf16 blocks
+  typedef KeyLayout<2 * D> PartLayout;
+  static constexpr int kPartBytes = kBlockKeys * 2 * D / 1024 * PartLayout::kLoadBytes;
 };
 __device__ __forceinline__ floatx16 multiply_step(bf16x8 a, bf16x8 b, floatx16 acc) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
@@ -245,8 +255,10 @@ template <typename T> struct Queries {
 // S^T of one 32-key block and this wave's NQW query blocks.  fp32: from the bf16 parts; an infinite key element, or one
 // that rounds up to infinity, makes its logits NaN, and the block is then taken again in the matrix unit's fp32 form,
 // as every block is for queries that are not plain.
+//
+// parts: where the workgroup's waves have put the block's bf16 parts (split_block), null if every wave splits for itself.
 template <typename T, int D, int NQW>
-__device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
+__device__ __forceinline__ void logits_block(lds_cchar* lds_buf, lds_cchar* parts, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
                                              const Queries<T>& src, int lane, floatx16 (&acc)[NQW]) {
   typedef typename Element<T, D>::Layout L;
   typedef typename Element<T, D>::Vec Vec;
@@ -268,11 +280,21 @@ __device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&
     }
   } else {
     if (src.plain) {
+      typedef typename Element<T, D>::PartLayout P;
+      const int part_base = P::operand_base(lane & 31, lane >> 5);
 #pragma unroll
       for (int kp = 0; kp < Element<T, D>::kSteps / 2; ++kp) {
-        const Vec a0 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp));
-        const Vec a1 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp + 1));
-        const Split a = split_f32(a0, a1);
+        Split a;
+        if (parts) {
+          lds_cchar* at = parts + P::operand(part_base, kp);
+          a.hi = *reinterpret_cast<lds_bf16x8*>(at);
+          a.mid = *reinterpret_cast<lds_bf16x8*>(at + Element<T, D>::kPartBytes);
+          a.lo = *reinterpret_cast<lds_bf16x8*>(at + 2 * Element<T, D>::kPartBytes);
+        } else {
+          const Vec a0 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp));
+          const Vec a1 = *reinterpret_cast<lds_vec*>(lds_buf + L::operand(base, 2 * kp + 1));
+          a = split_f32(a0, a1);
+        }
 #pragma unroll
         for (int q = 0; q < NQW; ++q)
           acc[q] = multiply_split(a, bq[q][3 * kp], bq[q][3 * kp + 1], bq[q][3 * kp + 2], acc[q]);
@@ -301,14 +323,36 @@ __device__ __forceinline__ void logits_block(lds_cchar* lds_buf, const bf16x8 (&
   }
 }
 
+// fp32: this wave's share of splitting a block for all waves of the workgroup: pairs of steps wave, wave + WAVES, ...
+// Every lane takes the elements that it needs as an operand, so the parts keep the operands' order.
+template <int D, int WAVES>
+__device__ __forceinline__ void split_block(lds_cchar* lds_buf, lds_char* parts, int wave, int lane) {
+  typedef Element<float, D> E;
+  typedef __attribute__((address_space(3))) const floatx4 lds_floatx4;
+  const int base = E::Layout::operand_base(lane & 31, lane >> 5);
+  const int part_base = E::PartLayout::operand_base(lane & 31, lane >> 5);
+  constexpr int kPairs = E::kSteps / 2;
+#pragma unroll
+  for (int i = 0; i < (kPairs + WAVES - 1) / WAVES; ++i) {
+    const int kp = wave + i * WAVES;
+    if (kPairs % WAVES != 0 && kp >= kPairs) break;
+    const Split a = split_f32(*reinterpret_cast<lds_floatx4*>(lds_buf + E::Layout::operand(base, 2 * kp)),
+                              *reinterpret_cast<lds_floatx4*>(lds_buf + E::Layout::operand(base, 2 * kp + 1)));
+    lds_char* at = parts + E::PartLayout::operand(part_base, kp);
+    *reinterpret_cast<lds_bf16x8_out*>(at) = a.hi;
+    *reinterpret_cast<lds_bf16x8_out*>(at + E::kPartBytes) = a.mid;
+    *reinterpret_cast<lds_bf16x8_out*>(at + 2 * E::kPartBytes) = a.lo;
+  }
+}
+
 // One 32-key block against this wave's NQW query blocks.
 template <typename T, int D, int NQW, bool MASKED, bool EXACT>
-__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
+__device__ __forceinline__ void compute_block(lds_cchar* lds_buf, lds_cchar* parts, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
                                               const Queries<T>& src, int lane, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
   floatx16 acc[NQW];
-  logits_block<T, D, NQW>(lds_buf, bq, src, lane, acc);
+  logits_block<T, D, NQW>(lds_buf, parts, bq, src, lane, acc);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int last_visible = causal_base + ((src.qb0 + q) * 32 + row) % W;
@@ -320,12 +364,12 @@ __device__ __forceinline__ void compute_block(lds_cchar* lds_buf, const bf16x8 (
 // 2^(z - reference) of every query stay in `e` so that the caller can credit them to the chunks on either
 // side of each boundary.  Nothing is added to l_run here.
 template <typename T, int D, int NQW, bool MASKED>
-__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
+__device__ __forceinline__ void weights_block(lds_cchar* lds_buf, lds_cchar* parts, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
                                               const Queries<T>& src, int lane, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW],
                                               floatx16 (&e)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
-  logits_block<T, D, NQW>(lds_buf, bq, src, lane, e);
+  logits_block<T, D, NQW>(lds_buf, parts, bq, src, lane, e);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     if (MASKED) {
@@ -449,7 +493,11 @@ struct GroupShape {
   static constexpr int kQueryRegs = kNQW * Element<T, D>::kQueryVecs * 4;
   static constexpr int kRegWaves =
       (kQueryRegs > 64 || kNQW > 2) ? 2 : kQueryRegs > 32 ? SHOTKV_SCORE_WAVES_PER_SIMD : SHOTKV_SCORE_WAVES_PER_SIMD + 1;
-  static constexpr int kLdsWaves = 160 * 1024 / (kRing * Element<T, D>::kBufBytes + 1024) * kWaves / 4;
+  // Whether the waves split fp32 blocks between them.  Two waves gain less from it than the second barrier costs: 8
+  // problems of 8000 tokens, 16 query / 8 KV heads, head_dim 128, 157 us a call, 150 if each splits for itself.
+  static constexpr bool kShared = sizeof(T) == 4 && WAVES >= 4;
+  static constexpr int kPartsBytes = kShared ? 3 * Element<T, D>::kPartBytes : 16;
+  static constexpr int kLdsWaves = 160 * 1024 / (kRing * Element<T, D>::kBufBytes + kPartsBytes + 1024) * kWaves / 4;
   static constexpr int kMinWavesPerSimd = kLdsWaves < 1 ? 1 : kLdsWaves < kRegWaves ? kLdsWaves : kRegWaves;
 };
 
@@ -464,6 +512,7 @@ score_partials_mfma_kernel(
   constexpr int NQW = S::kNQW;
   constexpr int R = NQB * 32;
   __shared__ __attribute__((aligned(64))) char lds[kRing][E::kBufBytes];
+  __shared__ __attribute__((aligned(64))) char lds_parts[S::kPartsBytes];
   __shared__ int s_end[kEndCache];
   __shared__ int s_count[S::kWaves][2];
 
@@ -667,7 +716,8 @@ score_partials_mfma_kernel(
     else if (n_q == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * S::kLoads) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * S::kLoads) : "memory");
     // ... and after the barrier so has the other waves'; all are also done reading the block before
-    if (S::kWaves > 1) asm volatile("s_barrier" ::: "memory");
+    if (S::kShared) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if (S::kWaves > 1) asm volatile("s_barrier" ::: "memory");
     if (n_stash == kStash) flush();
     if (next_key0 < k_end) {
       issue_block<E, S::kLoads>(k_plane, next_key0, k_end - next_key0,
@@ -681,19 +731,26 @@ score_partials_mfma_kernel(
     const int cur_rem = min(kBlockKeys, k_end - cur_key0);
     const bool masked = cur_rem < kBlockKeys || cur_key0 + kBlockKeys - 1 > causal_base;
     lds_cchar* blk = lds_base + cur_buf * E::kBufBytes;
+    lds_cchar* parts = nullptr;
+    if constexpr (S::kShared) {
+      // (the waves have read the parts of the block before: the barrier above)
+      split_block<D, S::kWaves>(blk, (lds_char*)&lds_parts[0], wave, lane);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      parts = (lds_cchar*)&lds_parts[0];
+    }
     if (cur_end >= cur_key0 + cur_rem) {  // no chunk ends inside the block
       if (first_block)
-        compute_block<T, D, NQW, true, true>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, true, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else if (masked)
-        compute_block<T, D, NQW, true, false>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, true, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else
-        compute_block<T, D, NQW, false, false>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, false, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
     } else {
       floatx16 e[NQW];
       if (masked)
-        weights_block<T, D, NQW, true>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       else
-        weights_block<T, D, NQW, false>(blk, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       uint32_t lo0 = 0u, lo1 = 0u;  // elements already credited (lower / upper lane half)
       do {
         const int hi = cur_end - cur_key0;  // wave-uniform, 1..31

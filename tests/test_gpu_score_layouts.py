@@ -149,6 +149,22 @@ def test_float32_values_over_the_whole_range(kv, D, G, W, case):
     np.testing.assert_allclose(got, want, rtol=SCORE_RTOL, atol=0)
 
 
+@pytest.mark.parametrize("G", [4, 8])
+@pytest.mark.parametrize("D", [64, 128])
+def test_float32_forms_side_by_side(kv, D, G):
+    """One query head that bf16 parts cannot hold: its wave takes the fp32 form while the others of the workgroup read the
+    block's parts that all of them have made."""
+    N, Hkv, W = 700, 2, 32
+    rng = np.random.default_rng(G + D)
+    q = rng.standard_normal((1, Hkv * G, W, D), dtype=np.float32)
+    k = rng.standard_normal((1, Hkv, N, D), dtype=np.float32)
+    q[:, 1, :, 5] = 2.0**120 * rng.standard_normal((1, W), dtype=np.float32)
+    k[..., 5] = 2.0**-120 * rng.standard_normal(k.shape[:3], dtype=np.float32)
+    off = np.array([0, 50, 97, 130, 131, 400, 401, 690], dtype=np.int32)
+    got, want = _scores_and_oracle(kv, q, k, off, 1.0 / math.sqrt(D))
+    np.testing.assert_allclose(got, want, rtol=SCORE_RTOL, atol=0)
+
+
 def test_a_unit_of_many_slices(kv):
     """One unit over 128 slices of the key axis and 8 KV heads: its first key takes nearly all of the mass, 8, and the
     other thousand (slice, head) parts 2.2e-7 each, just under half a unit in the last place below 8, 2.8e-5 of it
