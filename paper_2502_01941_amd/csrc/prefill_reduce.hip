@@ -16,6 +16,16 @@ namespace {
 constexpr int kMassThreads = 256;
 constexpr int kMaxRows = 256;
 
+// Sum over groups of LANES lanes, widest exchange first, off the LDS pipe.
+template <int LANES>
+__device__ __forceinline__ float sum_over_lanes(float x) {
+  if constexpr (LANES == 1) {
+    return x;
+  } else {
+    return sum_over_lanes<LANES / 2>(x + __uint_as_float(lane_xor<LANES / 2>(__float_as_uint(x))));
+  }
+}
+
 // LANES: lanes per chunk, R / 4 rounded up to a power of two
 template <int LANES>
 __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* __restrict__ partial,
@@ -94,8 +104,7 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
       m += row0 + 1 < n_valid ? exp2f(x[j].y - lse.y) : 0.f;
       m += row0 + 2 < n_valid ? exp2f(x[j].z - lse.z) : 0.f;
       m += row0 + 3 < n_valid ? exp2f(x[j].w - lse.w) : 0.f;
-#pragma unroll
-      for (int o = LANES / 2; o > 0; o >>= 1) m += __shfl_xor(m, o, kWave);
+      m = sum_over_lanes<LANES>(m);
       const int c = c0 + j * kTeams;
       if (row0 == 0 && c < c_end) chunk_mass[(static_cast<size_t>(p) * max_c + c) * H_kv + g] = m;
     }
