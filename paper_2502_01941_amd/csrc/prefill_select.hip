@@ -6,7 +6,8 @@
 //   budget    prefix selection needs no ranking, only where in it the budget ends: up to 128 shots a group of lanes
 //             per shot adds the lengths of all that rank no lower; above, the key of the shot at which the budget ends
 //             is found a digit at a time from histograms of lengths (in LDS; integer sums, so their order is free);
-//   ranking   first fit walks all shots in order: bitonic sort on one 64-bit key per shot (score descending, shot index
+//   ranking   first fit walks all shots in order: up to 128 shots a group of lanes per shot counts the ones above, more
+//             are sorted: bitonic sort on one 64-bit key per shot (score descending, shot index
 //             ascending): keys live in registers, partners less than 64 apart are exchanged between lanes without LDS
 //             (DPP moves inside a row of 16, row and half swaps beyond), and for the larger strides the keys pass
 //             through LDS into a transposed layout in which those strides are lane distances too - two LDS round trips
@@ -18,7 +19,8 @@
 // Bound by a chain of barriers and trips to memory in one workgroup.  Inside the kernel, sorting and walking the sums
 // against this: 40 shots 2.1 + 1.8 us and 0.6, 80 shots 3.4 + 1.5 and 1, 600 units 7.8 + 1.7 and 3.3 (the sort of 400
 // shots for first fit is 7.5); writing the positions of 600 units 4.0 and 1.9.  Whole call: 8192 tokens in 40 shots
-// 29.5 -> 26.6 us, 16 x 16001 tokens of head_dim 64 in 80 shots 117.8 -> 113.5, 64 x 600 units 159.6 -> 150.8.
+// 29.5 -> 26.6 us, 16 x 16001 tokens of head_dim 64 in 80 shots 117.8 -> 113.5, 64 x 600 units 159.6 -> 150.8.  First fit,
+// sorting against counting: 13 x 1424 tokens in 4 shots 36.6 -> 33.9, 60 problems of 109 shots 112.2 -> 109.7.
 //
 // The two halves can also run alone: scores only, or selection from caller-supplied scores.  All
 // sums of floats run in a fixed order, so results are reproducible run to run.
@@ -246,14 +248,15 @@ __device__ __forceinline__ void keep_prefix(const float (&score)[kMaxPad / kSelT
   }
 }
 
-// The same for few shots, without the rounds: a group of lanes per shot adds the lengths of all that rank no lower.
-// word_len: n words, score word << 32 | length, behind a barrier.  lanes: per shot, 8 or 16.  Returned to all of the group.
-__device__ __forceinline__ bool among_first(const uint64_t* word_len, int n, int i, int part, int lanes, int left) {
-  const uint32_t own = i < n ? static_cast<uint32_t>(word_len[i] >> 32) : 0u;
+// The same for few shots, without the rounds: a group of lanes per shot adds the lengths of all that rank no lower, or, for
+// first fit, counts them.  word_add: n words, score word << 32 | what the shot adds, behind a barrier.  lanes: per shot, 8
+// or 16.  Returned to all of the group.
+__device__ __forceinline__ int sum_of_no_lower(const uint64_t* word_add, int n, int i, int part, int lanes) {
+  const uint32_t own = i < n ? static_cast<uint32_t>(word_add[i] >> 32) : 0u;
   int sum = 0;
 #pragma unroll 4
   for (int j = part; j < n; j += lanes) {
-    const uint64_t x = word_len[j];
+    const uint64_t x = word_add[j];
     const uint32_t word = static_cast<uint32_t>(x >> 32);
     sum += (word > own) | ((word == own) & (j <= i)) ? static_cast<int>(x) : 0;
   }
@@ -261,7 +264,7 @@ __device__ __forceinline__ bool among_first(const uint64_t* word_len, int n, int
   sum += static_cast<int>(lane_xor<2>(static_cast<uint32_t>(sum)));
   sum += static_cast<int>(lane_xor<4>(static_cast<uint32_t>(sum)));
   if (lanes == 16) sum += static_cast<int>(lane_xor<8>(static_cast<uint32_t>(sum)));
-  return sum <= left;
+  return sum;
 }
 
 // Sum of words[first], words[first + width], ... of n words: kBatch loads in flight, added up as a tree.
@@ -354,7 +357,16 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
   if (MASS && !bad && width > 1) {  // (the choice is the same for the whole workgroup)
     const int i = tid / width;
     float sum = i < n_shots ? shot_sum(i, tid % width, width) : 0.f;
-    for (int o = width >> 1; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+    auto add = [&](auto mask_c) {
+      constexpr int MASK = decltype(mask_c)::value;
+      if (width > MASK) sum += __uint_as_float(lane_xor<MASK>(__float_as_uint(sum)));  // (width is uniform)
+    };
+    add(std::integral_constant<int, 32>{});
+    add(std::integral_constant<int, 16>{});
+    add(std::integral_constant<int, 8>{});
+    add(std::integral_constant<int, 4>{});
+    add(std::integral_constant<int, 2>{});
+    add(std::integral_constant<int, 1>{});
     if (i < n_shots && tid % width == 0) s_sum[i] = sum;
     __syncthreads();
   }
@@ -395,17 +407,21 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     return;
   }
 
-  if (select_mode == SHOTKV_SELECT_PREFIX && n_shots <= kSelThreads / 8) {
+  const bool prefix = select_mode == SHOTKV_SELECT_PREFIX;
+  if (n_shots <= kSelThreads / 8) {
     // Rounds of the histogram cost 0.6 us each, this about as much in all: 40 shots 27.5 us a call with the histogram.
     if (tid < n_shots)
       s_key[tid] = static_cast<uint64_t>(score_word(my_score[0])) << 32 |
-                   static_cast<uint32_t>(s_off[tid + 1] - s_off[tid]);
+                   (prefix ? static_cast<uint32_t>(s_off[tid + 1] - s_off[tid]) : 1u);
     __syncthreads();
     const int lanes = n_shots <= kSelThreads / 16 ? 16 : 8, i = tid / lanes;
-    const bool keep = among_first(s_key, n_shots, i, tid % lanes, lanes, shot_budget);
-    if (tid % lanes == 0 && i < n_shots) s_keep[i] = keep;
-    __syncthreads();
-  } else if (select_mode == SHOTKV_SELECT_PREFIX) {
+    const int sum = sum_of_no_lower(s_key, n_shots, i, tid % lanes, lanes);
+    if (tid % lanes == 0 && i < n_shots) {
+      if (prefix) s_keep[i] = sum <= shot_budget;
+      else s_idx[sum - 1] = static_cast<uint16_t>(i);
+    }
+    __syncthreads();  // (also: the words' memory is free)
+  } else if (prefix) {
     int len[kMaxPerThread];
     bool keep[kMaxPerThread];
 #pragma unroll
@@ -450,7 +466,8 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
       }
     }
     __syncthreads();  // the ranking is complete, and the exchange buffer is free to hold the lengths
-
+  }
+  if (!prefix) {
     // ---- budget walk in rank order -----------------------------------------------------------------
     for (int i = tid; i < n_shots; i += kSelThreads) {
       const int shot = s_idx[i];

@@ -277,7 +277,7 @@ def test_where_the_budget_ends(kv, n):
     off[:, 1:] = off[:, :1] + np.cumsum(lens, axis=1)
     kinds = [rng.random(n).astype(np.float32), 1 + np.float32(2.0 ** -23) * rng.permutation(n).astype(np.float32),
              rng.integers(0, 3, size=n).astype(np.float32), np.zeros(n, dtype=np.float32),
-             np.exp(30 * rng.standard_normal(n)).astype(np.float32)]
+             np.exp(20 * rng.standard_normal(n)).astype(np.float32)]
     scores = np.stack([kinds[p % 5] for p in range(P)])
     budgets, wants = np.zeros(P, dtype=np.int32), []
     for p in range(P):
