@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
     const char* __restrict__ k_prefill, const char* __restrict__ v_prefill,
     const int32_t* __restrict__ prefill_count, char* __restrict__ k_dec, char* __restrict__ v_dec,
     const int32_t* __restrict__ slot_pos, int cap, int n_slots, int H, int H_kv, int n_group,
-    int n_splits, int split_tokens, float scale_log2e, const char* __restrict__ q_new,
+    int n_splits, int split_tokens, bool ahead, float scale_log2e, const char* __restrict__ q_new,
     const char* __restrict__ k_new, const char* __restrict__ v_new, float2* __restrict__ part_ml,
     float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out) {
   constexpr int kRow = D * static_cast<int>(sizeof(T));  // bytes per row
@@ -193,20 +193,30 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
   // A wave's first block is requested before the count of live rows has arrived (dead rows may hold anything).
   const int early_rows = min(range_end, cap) - range_begin;
   if (wave * S::kBlock < early_rows) load_block(kp + static_cast<size_t>(range_begin) * kRow, wave * S::kBlock, early_rows);
-
   // Only a range that reaches into the decode slots needs the slot that takes the new token, the lowest free
   // one, and the slot map of its (first) piece with the last occupied slot of it (a pool that is still filling
   // up is empty behind that); all come out of one round of loads.
+  // Where a launch is one round of workgroups, a range of nothing but slots does not wait for the map with the wave's first
+  // K block: with one more trip to memory than the others it would end the launch (16 sequences of 5121 rows 65.7 us a
+  // step, 66.7 waiting; 32 of 2514, head_dim 64, per KV head, 38.2 and 39.6).  A free slot may hold anything: its logits
+  // are not used, and the new token's row replaces what its slot held.
+  const int early_slots = !PIECES && ahead && range_begin >= cap ? range_end - range_begin : 0;
   int new_slot = n_slots, last_used = -1;
   if (range_end > cap) {
     constexpr int kBatch = 8;  // loads in flight per thread
     const int d_lo = max(range_begin - cap, 0), d_hi = min(range_begin + kMaxRange, range_end) - cap;
     int best = INT32_MAX;
-#pragma clang loop unroll(disable)
-    for (int i0 = tid; i0 < n_slots && (best == INT32_MAX || i0 < d_hi); i0 += kBatch * kThreads) {
-      int pos[kBatch];
+    int pos[kBatch];
+    auto load_map = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) pos[j] = sp[min(i0 + j * kThreads, n_slots - 1)];
+    };
+    load_map(tid);
+    if (wave * S::kBlock < early_slots)  // behind the map, as loads return in order
+      load_block(kd + static_cast<size_t>(range_begin - cap) * kRow, wave * S::kBlock, early_slots);
+#pragma clang loop unroll(disable)
+    for (int i0 = tid; i0 < n_slots && (best == INT32_MAX || i0 < d_hi); i0 += kBatch * kThreads) {
+      if (i0 != tid) load_map(i0);
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
         const int i = min(i0 + j * kThreads, n_slots - 1);
@@ -277,6 +287,17 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
       float mx[kHeadSets];  // largest logit this lane has seen, of head col_head + kCols * m
 #pragma unroll
       for (int m = 0; m < kHeadSets; ++m) mx[m] = -INFINITY;
+      auto append = [&](int row0) __attribute__((always_inline)) {  // only this workgroup reads the slot this step
+        if (new_row >= row0 && new_row < row0 + S::kBlock) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (row0 + (i / S::kLoads) * S::kTokens + tau == new_row) {
+              kraw[i] = stream_load<Vec>(kn + (i % S::kLoads) * 256 + a_off);
+              *reinterpret_cast<Vec*>(kd0 + static_cast<size_t>(new_row) * kRow + (i % S::kLoads) * 256 + a_off) =
+                  kraw[i];
+            }
+        }
+      };
       auto fetch = [&](int blk) __attribute__((always_inline)) {
         if (blk < nb_p) {
           load_block(kp0, blk * S::kBlock, n_p);
@@ -294,15 +315,7 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
           const int off = used ? r * kRow + (i % S::kLoads) * 256 + a_off : kOutOfBounds;
           kraw[i] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, kNonTemporal));
         }
-        if (new_row >= row0 && new_row < row0 + S::kBlock) {  // append: only this workgroup reads the slot this step
-#pragma unroll
-          for (int i = 0; i < 8; ++i)
-            if (row0 + (i / S::kLoads) * S::kTokens + tau == new_row) {
-              kraw[i] = stream_load<Vec>(kn + (i % S::kLoads) * 256 + a_off);
-              *reinterpret_cast<Vec*>(kd0 + static_cast<size_t>(new_row) * kRow + (i % S::kLoads) * 256 + a_off) =
-                  kraw[i];
-            }
-        }
+        append(row0);
       };
       // Logits of the block in kraw to zbuf[z0..]; counts(row, z): what the row at z0 + row adds to the maximum.
       auto multiply_block = [&](int z0, auto counts) __attribute__((always_inline)) {
@@ -343,8 +356,12 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
         }
       };
       int blk = wave;
-      // the wave's first block: of the first piece it is there already if it lies among the live rows
-      if (blk < n_blk && !(first && blk < nb_p)) fetch(blk);
+      // the wave's first block: of the first piece it is there already if it lies among the live rows, or was requested
+      // ahead of the slot map
+      if (blk < n_blk) {
+        if (first && early_slots > 0) append(blk * S::kBlock);
+        else if (!(first && blk < nb_p)) fetch(blk);
+      }
 #pragma clang loop unroll(disable)
       for (; blk + kWaves < n_blk; blk += kWaves) {
         use_block(blk);
@@ -500,6 +517,7 @@ static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state&
                                  const void* k_new, const void* v_new, const DecodeWorkspace& w, hipStream_t s) {
   const dim3 grid(d.n_splits, d.H_kv, d.S), block(kThreads);
   const float c = d.sm_scale * kLog2e;
+  const bool ahead = static_cast<long>(d.n_splits) * d.H_kv * d.S <= 1024;  // one round: up to four workgroups per CU
   KernelTimer timer(d.timing, kKernelDecodePartial, s);
 #define SHOTKV_LAUNCH_DEC(GG)                                                                           \
   auto* kernel = d.split_tokens > kMaxRange ? decode_partial_kernel<T, D, GG, true>                     \
@@ -507,7 +525,7 @@ static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state&
   hipLaunchKernelGGL(kernel, grid, block, 0, s,                                                         \
                      static_cast<const char*>(st.k_prefill), static_cast<const char*>(st.v_prefill),    \
                      st.prefill_count, static_cast<char*>(st.k_dec), static_cast<char*>(st.v_dec),      \
-                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, d.n_splits, d.split_tokens, c,    \
+                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, d.n_splits, d.split_tokens, ahead, c, \
                      static_cast<const char*>(q_new), static_cast<const char*>(k_new),                  \
                      static_cast<const char*>(v_new), w.part_ml, w.part_o, w.z_dec, w.new_slot)
   switch (padded_group(d.G)) {  // the kernel is instantiated for power-of-two groups and skips the padding

@@ -107,6 +107,20 @@ def test_new_token_in_a_later_piece(kv, D, dtype, cap, n_slots, free):
     _check_steps(kv, rng, state, n_slots - 1, 2, scale)
 
 
+@pytest.mark.parametrize("S", [128, 129])
+def test_slots_requested_ahead_of_their_map_and_not(kv, S):
+    """Ranges of nothing but slots ask for their first rows before the slot map is known in launches of up to 1024
+    workgroups (128 sequences of 8 KV heads here) and after it in larger ones; free slots hold poison, and the new token's
+    slot lies at the start, inside and behind the occupied ones."""
+    rng = np.random.default_rng(S)
+    Hkv, D, n_slots, budget = 8, 64, 40, 39
+    used = [np.setdiff1d(np.arange(n_slots), [0, 7, 31] if s % 3 == 0 else [5, 6, 39] if s % 3 == 1 else np.arange(20, 40))
+            for s in range(S)]
+    scale = D ** -0.5
+    state = _state(kv, rng, S, Hkv, Hkv, D, torch.bfloat16, 0, [0] * S, n_slots, used, budget, scale)
+    _check_steps(kv, rng, state, budget, 2, scale)
+
+
 @pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
 def test_infinite_values_stay_in_their_column(kv, D, dtype):
     """The last live prefill row and the last occupied slot hold an infinite value each: it shows in its own output
