@@ -47,7 +47,7 @@ __device__ __forceinline__ void take_better_of_lane(float& score, int& pos, int&
 // partials - is requested along with the first splits' statistics and all of it is one trip.  Those come first:
 // loads return in order, and the statistics are worked out while 64 KB of logits follow.  Reductions stay off the
 // LDS pipe.  One sequence of 3790 rows and 32 heads, whole step: 18.6 us with the statistics last and exchanges
-// through LDS, 17.3 like this (kernel 7.8 and 6.5); 32 sequences of 2514 rows per KV head 41.0 and 39.5, 16 of
+// through LDS, 17.3 like this (kernel 7.8 and 7.1); 32 sequences of 2514 rows per KV head 41.0 and 39.5, 16 of
 // 5121 67.4 and 66.5.
 // kAhead: heads whose logits of a thread's first slot are requested that way.  32 cost 100 registers, one workgroup
 // per CU, which is dear where heads are few and sequences many (per-KV-head mode: 256 pairs of 4 heads 12.1 us),
