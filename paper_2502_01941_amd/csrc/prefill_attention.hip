@@ -22,12 +22,11 @@
 //                     instead of bf16's 8, which holds the output within 4.6e-4 of its row maximum with one
 //                     instruction per step (a bf16 weight is off by up to 2^-9; bf16 hi + lo would cost a
 //                     second instruction).  fp16's narrow range is dealt with by two exact power-of-two
-//                     scalings: the softmax reference sits 15 to 16 below the running maximum, so the largest
-//                     weight lies in [2^15, 2^16) and anything above 2^-39 of it survives; and the pre-pass
+//                     scalings: the softmax reference sits 15 below the running maximum, so weights lie
+//                     in (0, 2^15] and anything above 2^-39 of the largest survives; and the pre-pass
 //                     scales every KV-head plane of V so that its largest finite |v| lands in [2^14, 2^15).
-//                     Sums of weights are taken in fp32 and carry the same reference; in tiles without window rows
-//                     they add the weights as the product takes them (fp16), so that both sides of the quotient are
-//                     off the same way.
+//                     Sums of weights stay in fp32, add the weights before they are rounded, and carry the same
+//                     reference.
 // K and packed-V blocks are streamed global -> LDS with direct-to-LDS loads into a ring of three stages
 // shared by the four waves (one barrier per block); the LDS layouts are bank-conflict free for the
 // 128-bit operand reads (K as in the score kernel; V^T rows of 64 bytes with a two-bit XOR of the
@@ -55,12 +54,13 @@ constexpr int kRowBytes = kD * 2;
 constexpr int kGroupBytes = 4 * kRowBytes + 64;       // K: four rows + pad = one direct-to-LDS instruction
 constexpr int kKBytes = 8 * kGroupBytes;              // 8704
 constexpr int kVtBytes = kD * kBlockKeys * 2;         // 8192: [128 d][32 keys] fp16
-// The softmax reference moves to the running maximum - kWeightShift (log2 domain), and then stays until a weight passes
-// fp16's largest value, 2 above: weights keep their 11 bits down to 2^-29 of the largest, or below.  Nothing but the sum of
-// the weights has to be looked at in a block where it stays (an infinite one shows it), which saves the block's maximum.
-// A reference with more headroom (8 below the maximum, 2^7) moves less often yet, but its weights lose bits from 2^-22
-// on - one of 2^-26 is off by up to 0.8 %, one of 2^-30 by 11 % - and where the heaviest keys carry small values those
-// weights make the output.
+// Softmax reference = running maximum - kWeightShift (log2 domain), in every block: the largest weight is then a power
+// of two, which fp16 holds exactly, and weights keep their 11 bits down to 2^-29 of it.  A reference that stays where it
+// is for a while is faster, and loses precision.  One that stays until a weight passes fp16's range (8192 tokens 570 us,
+// 587 as it is, 32768 7900 and 8215, whole calls) has a largest weight that is rounded, and sums that need no maximum, of
+// the rounded weights, put the same error in the denominator: rows that two keys share are off by up to twice as much.  One
+// with more headroom (8 below the maximum, 2^7; 8192 tokens 550) loses bits from 2^-22 on - a weight of 2^-26 is off by up
+// to 0.8 %, one of 2^-30 by 11 % - and where the heaviest keys carry small values those weights make the output.
 constexpr int kWeightShift = 15;
 constexpr int kStageBytes = kKBytes + kVtBytes;
 constexpr int kRing = 3;
@@ -229,7 +229,7 @@ template <bool EMIT>
 __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, int p, int q0, lds_cchar* lds_base) {
   // Operands read from LDS ahead of the matrix instructions that take them, those of O^T ahead of the softmax: as many
   // as three waves per SIMD have registers for.  Read two at a time where they are taken, as the compiler does by itself,
-  // 8192 tokens take 575 us instead of 568.
+  // 8192 tokens take 572 us instead of 567, 1500 tokens 79 instead of 76.
   constexpr int kKAhead = 6, kVAhead = 4;
   const int n_tokens = x.n_tokens, W = x.W, R = x.R, max_c = x.max_c;
   const float c = x.c;
@@ -266,7 +266,6 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
     issue_vt(vt_plane + static_cast<size_t>(b) * kVtBytes, lds_addr + slot * kStageBytes + kKBytes, 2 * wave, piece);
   };
 
-  constexpr f16x2 kOnes = {static_cast<_Float16>(1.f), static_cast<_Float16>(1.f)};
   float m_run = -INFINITY, l_run = 0.f, l_chunk = 0.f;
   floatx16 ot[4];
 #pragma unroll
@@ -319,7 +318,6 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
     if (!has_work && !wave_emits) continue;
     floatx16 acc;
     f16x8 p16[2];
-    float block_sum = 0.f;  // of the weights in fp32, where they are kept
     f16x8 va[8];  // A operands of O^T: step i % 2 of head-dim rows 32 * (i / 2) ..
     uint32_t v_even = blk + kKBytes + v_read;
     asm("" : "+v"(v_even));
@@ -355,15 +353,13 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
 #pragma unroll
       for (int i = 0; i < kVAhead; ++i) va[i] = load_v(i);
       __builtin_amdgcn_sched_barrier(0);
-      // the reference goes to kWeightShift below the row's maximum, in all rows of a wave where one has a new maximum
-      auto follow = [&]() __attribute__((always_inline)) {
-        float bm = fmaxf(acc[0], acc[1]);
+      float bm = fmaxf(acc[0], acc[1]);
 #pragma unroll
-        for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, acc[v]), acc[v + 1]);
-        bm = max_across_halves(bm);
-        // finite from the first block on: key 0 is always visible
-        const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
-        if (__builtin_amdgcn_ballot_w64(m_new > m_run) == 0) return;
+      for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, acc[v]), acc[v + 1]);
+      bm = max_across_halves(bm);
+      // finite from the first block on: key 0 is always visible
+      const float m_new = fmaxf(m_run, fmaf(bm, c, -static_cast<float>(kWeightShift)));
+      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 from -inf
         l_run *= alpha;
         if (EMIT) l_chunk *= alpha;
@@ -372,46 +368,23 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
 #pragma unroll
           for (int v = 0; v < 16; ++v) ot[t][v] *= alpha;
         m_run = m_new;
-      };
-      auto weight = [&](int v) { return __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run)); };
-      auto pack = [&](int v, float w0, float w1) {
+      }
+      float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) {
+        const float w0 = __builtin_amdgcn_exp2f(fmaf(acc[v], c, -m_run));
+        const float w1 = __builtin_amdgcn_exp2f(fmaf(acc[v + 1], c, -m_run));
         const f16x2 w = to_f16x2(w0, w1);
         p16[v / 8][v % 8] = w[0];
         p16[v / 8][v % 8 + 1] = w[1];
-        return w;
-      };
-      // the weights against the reference as it stands, and their sum as the product will see them
-      auto weigh = [&]() __attribute__((always_inline)) {
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; v += 4) {
-          s0 = __builtin_amdgcn_fdot2(pack(v, weight(v), weight(v + 1)), kOnes, s0, false);
-          s1 = __builtin_amdgcn_fdot2(pack(v + 2, weight(v + 2), weight(v + 3)), kOnes, s1, false);
-        }
-        return s0 + s1;
-      };
-      float sum;
-      if (EMIT) {  // the statistics take the weights in fp32
-        follow();
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; v += 2) {
-          acc[v] = weight(v);
-          acc[v + 1] = weight(v + 1);
-          pack(v, acc[v], acc[v + 1]);
-          s0 += acc[v];
-          s1 += acc[v + 1];
-        }
-        sum = block_sum = s0 + s1;
-      } else {
-        sum = weigh();
-        // a weight past fp16's range is infinite and so is the sum
-        if (__builtin_amdgcn_ballot_w64(!(sum < 0x1p30f)) != 0) {
-          follow();
-          sum = weigh();
+        s0 += w0;
+        s1 += w1;
+        if (EMIT) {  // the statistics take the weights as well
+          acc[v] = w0;
+          acc[v + 1] = w1;
         }
       }
-      l_run += sum;
+      l_run += s0 + s1;
     } else {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -420,14 +393,16 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
     if (wave_emits) {
       while (cur_c < n_seg && cur_s < key0 + kBlockKeys) {
         const int lo = max(cur_s, key0) - key0 - 4 * half, hi = min(cur_e, key0 + kBlockKeys) - key0 - 4 * half;
-        float sum = block_sum;
+        float sum = 0.f;
         if (cur_s > key0 || cur_e < key0 + kBlockKeys) {
-          sum = 0.f;
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int r = 8 * (v >> 2) + (v & 3);
             sum += (r >= lo && r < hi) ? acc[v] : 0.f;
           }
+        } else {  // (in the same order)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) sum += acc[v];
         }
         l_chunk += sum;
         if (cur_e <= key0 + kBlockKeys) finish_chunk();
@@ -476,11 +451,12 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
 
 // n_plain tiles of queries that are not in the window, then the rest; the longest first.
 //
-// Bound by power: with the matrix pipe busy 66 % of the time the clock is 1.56 GHz at 32768 tokens (60 % and 1.65 GHz
-// before the reference stayed).  Whole call, 32 query / 8 KV heads, before and after the reference stays, operands are
-// read ahead and the segment ends sit in the lanes: 1500 tokens 88 and 80 us, 3000 tokens 161 and 145, 8192 603 and 573,
-// 32768 8385 and 7920.  Waves of 64 queries, which read LDS half as often, have registers for two per SIMD: 7400 - 7700
-// us at 32768 tokens, but 372 instead of 350 at 6000 and slower in most calls below, so there is one kernel.
+// Bound by matrix and vector issue, which add up, at a power-limited clock.  Operands read ahead of the softmax, segment
+// ends in the lanes, 168 registers and the heads of all problems in one order for the XCDs; whole call, 32 query / 8 KV
+// heads, without all of that and with it: 1500 tokens 87 and 76 us, 3000 158 and 142, 8192 606 and 587, 32768 8378 and
+// 8218; 8 problems of 5000 with 8 heads 504 and 480.  Outputs are the same bits.  Waves of 64 queries, which read LDS half
+// as often, have registers for two per SIMD: 3 - 5 % faster at 32768 tokens, but 6 % slower at 6000 and slower in most
+// calls below (measured with a reference that stays), so there is one kernel.
 __global__ __launch_bounds__(kThreadsQ, 3) void attention_scores_kernel(AttentionArgs x, int n_plain) {
   __shared__ __attribute__((aligned(64))) char lds[kRing][kStageBytes];
   lds_cchar* lds_base = (lds_cchar*)&lds[0][0];

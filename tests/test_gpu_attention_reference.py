@@ -72,3 +72,38 @@ def test_light_keys_keep_their_bits_behind_a_heavy_one(kv, heavy):
     ref = orc.causal_attention(to_np(q[0]), to_np(k[0]), to_np(v[0]), scale)
     got = attn[0].cpu().numpy()
     assert np.all(np.abs(got - ref) <= OUT_TOL * np.abs(ref).max(axis=2, keepdims=True))
+
+
+def test_rows_that_two_keys_share(kv):
+    """Two keys of nearly the same weight and opposite values, behind a first key whose weight is a little less and whose
+    value is zero.  Every fp16 weight but the row's largest, which is a power of two, is off by at most 2^-11 of itself, and
+    the sum of the weights is taken before they are rounded, so an output is off by at most 2^-11 of what the lighter of the
+    two adds to it (and 2^-18 for the fp32 sums).  Weights rounded in the sum too, or a largest weight that is not a power of
+    two, give up to twice that."""
+    H, Hkv, W, D, N, n = 4, 2, 32, 128, 700, 4
+    rng = np.random.default_rng(2)
+    heavy = [40, 75]
+    q = np.zeros((1, H, N, D), dtype=np.float32)
+    q[..., 0] = 1.0
+    q[..., 1:3] = 0.5 * rng.random((1, H, N, 2), dtype=np.float32)      # logits (log2 domain) of the two
+    k = np.zeros((1, Hkv, N, D), dtype=np.float32)
+    k[..., 1:, 0] = -100.0                                              # every key but the first: no weight
+    k[..., heavy, 0] = 0.0
+    k[..., heavy[0], 1] = k[..., heavy[1], 2] = 1.0
+    v = np.zeros((1, Hkv, N, D), dtype=np.float32)
+    v[..., heavy, :] = np.where(rng.random((1, Hkv, 2, D)) < 0.5, -1.0, 1.0)
+    scale = math.log(2.0)
+    q, k, v = (torch.from_numpy(x).to(torch.bfloat16).cuda() for x in (q, k, v))
+    off = torch.from_numpy(np.linspace(3, N - 40, n + 1).astype(np.int32)[None]).cuda()
+    bud = torch.tensor([N // 2], dtype=torch.int32, device="cuda")
+    attn, _ = kv.prefill_attention_compress(q, k, v, off, bud, N // 2, W, scale)
+    torch.cuda.synchronize()
+    got = attn[0].cpu().numpy().astype(np.float64)
+    qh, vh = to_np(q[0]).astype(np.float64), to_np(v[0]).astype(np.float64)
+    rows = slice(heavy[1], N)
+    logits = np.concatenate([np.zeros((H, N, 1)), qh[..., 1:3]], axis=2)[:, rows]
+    p = np.exp2(logits)
+    p /= p.sum(axis=2, keepdims=True)
+    lighter = np.minimum(p[..., 1], p[..., 2])
+    ref = np.stack([p[h, :, 1:] @ vh[h // (H // Hkv), heavy] for h in range(H)])
+    assert np.all(np.abs(got[:, rows] - ref) <= 2.0 ** -11 * lighter[..., None] + 2.0 ** -18)
