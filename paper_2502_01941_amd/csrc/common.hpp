@@ -262,6 +262,7 @@ constexpr int kDecodeMaxSplits = 1024;  // token ranges per (sequence, KV head) 
 // query heads per KV head rounded up to 1, 2, 4 or 8: what the decode kernels are instantiated for
 inline int padded_group(int G) { return G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : G <= 8 ? 8 : 0; }
 
+int decode_resident(int G, int row_bytes);  // workgroups of the decode kernel that the chip holds at once
 int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens);
 hipError_t launch_decode_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
                                  const void* k_new, const void* v_new, const DecodeWorkspace& w,

@@ -309,6 +309,8 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
 
 }  // namespace
 
+int decode_resident(int G, int row_bytes) { return G > 4 && row_bytes <= 256 ? 768 : 1024; }
+
 int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
   // Token ranges per (sequence, KV head).  The workgroups of a launch should all be resident at once, so a count is
   // rounded down: 1056 workgroups of which 1024 fit take nearly twice as long as 960.  With more than two query
@@ -321,9 +323,8 @@ int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
   // with 528 workgroups, 80.7 with 792; 50 of 900 rows 63.8 with 400, 75.0 with 800; 7 heads 51.3 and 57.9; 512-byte
   // rows 120 and 112.5.
   const int pairs = S * H_kv;
-  const int many = max(1, 1024 / pairs), few = max(1, 768 / pairs);
-  const bool three_fit = G > 4 && row_bytes <= 256;
-  int splits = three_fit || (G > 2 && few * pairs >= 640) ? few : many;
+  const int many = max(1, decode_resident(G, row_bytes) / pairs), few = max(1, 768 / pairs);
+  int splits = G > 2 && few * pairs >= 640 ? few : many;
   // no range shorter than 96 tokens (one sequence of 3800 rows: 20.5 us, 21.6 with 128, 25 with 32) ...
   splits = min(splits, max(1, total_tokens / 96));
   // ... none longer than one piece of logits per workgroup, and no more than the finish kernel takes

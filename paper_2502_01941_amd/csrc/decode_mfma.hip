@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
     const char* __restrict__ k_prefill, const char* __restrict__ v_prefill,
     const int32_t* __restrict__ prefill_count, char* __restrict__ k_dec, char* __restrict__ v_dec,
     const int32_t* __restrict__ slot_pos, int cap, int n_slots, int H, int H_kv, int n_group,
-    int n_splits, int split_tokens, bool ahead, float scale_log2e, const char* __restrict__ q_new,
+    int n_splits, int split_tokens, int ahead_slots, float scale_log2e, const char* __restrict__ q_new,
     const char* __restrict__ k_new, const char* __restrict__ v_new, float2* __restrict__ part_ml,
     float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out) {
   constexpr int kRow = D * static_cast<int>(sizeof(T));  // bytes per row
@@ -196,11 +196,12 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
   // Only a range that reaches into the decode slots needs the slot that takes the new token, the lowest free
   // one, and the slot map of its (first) piece with the last occupied slot of it (a pool that is still filling
   // up is empty behind that); all come out of one round of loads.
-  // Where a launch is one round of workgroups, a range of nothing but slots does not wait for the map with the wave's first
-  // K block: with one more trip to memory than the others it would end the launch (16 sequences of 5121 rows 65.7 us a
-  // step, 66.7 waiting; 32 of 2514, head_dim 64, per KV head, 38.2 and 39.6).  A free slot may hold anything: its logits
-  // are not used, and the new token's row replaces what its slot held.
-  const int early_slots = !PIECES && ahead && range_begin >= cap ? range_end - range_begin : 0;
+  // A range of nothing but slots does not wait for the map with a wave's first K block if that begins among the first
+  // ahead_slots slots (ahead_of_map); the whole block is requested, and a wave whose block was not requested asks for it
+  // when the map is there.  A free slot may hold anything: its logits are not used, and the new token's row replaces what
+  // its slot held.
+  const bool early = !PIECES && range_begin >= cap &&
+                     wave * S::kBlock < min(range_end - range_begin, ahead_slots - (range_begin - cap));
   int new_slot = n_slots, last_used = -1;
   if (range_end > cap) {
     constexpr int kBatch = 8;  // loads in flight per thread
@@ -212,8 +213,8 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
       for (int j = 0; j < kBatch; ++j) pos[j] = sp[min(i0 + j * kThreads, n_slots - 1)];
     };
     load_map(tid);
-    if (wave * S::kBlock < early_slots)  // behind the map, as loads return in order
-      load_block(kd + static_cast<size_t>(range_begin - cap) * kRow, wave * S::kBlock, early_slots);
+    if (early)  // behind the map, as loads return in order
+      load_block(kd + static_cast<size_t>(range_begin - cap) * kRow, wave * S::kBlock, range_end - range_begin);
 #pragma clang loop unroll(disable)
     for (int i0 = tid; i0 < n_slots && (best == INT32_MAX || i0 < d_hi); i0 += kBatch * kThreads) {
       if (i0 != tid) load_map(i0);
@@ -304,7 +305,8 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
           return;
         }
         // A slot without a token is given an offset out of bounds, so it is zeros and costs no traffic, as in the V pass
-        // (every other slot of 1025 free: 60.9 us a step for 16 caches of 4000 rows, 68.5 with all slots fetched).
+        // (every other slot of 1025 free: 58.7 us a step for 16 caches of 4000 rows, 60.8 with all slots fetched).  A
+        // block requested ahead of the map has its free slots fetched.
         const int row0 = (blk - nb_p) * S::kBlock;
         char* at = kd0 + static_cast<size_t>(row0) * kRow;
         const auto rows = __builtin_amdgcn_make_buffer_rsrc(at, 0, (n_d - row0) * kRow, kBufferFlags);
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
       // the wave's first block: of the first piece it is there already if it lies among the live rows, or was requested
       // ahead of the slot map
       if (blk < n_blk) {
-        if (first && early_slots > 0) append(blk * S::kBlock);
+        if (first && early) append(blk * S::kBlock);
         else if (!(first && blk < nb_p)) fetch(blk);
       }
 #pragma clang loop unroll(disable)
@@ -512,12 +514,28 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
 
 }  // namespace
 
+// Slots whose K rows the ranges of nothing but slots request ahead of the slot map, a trip to memory earlier: where a
+// launch is one round of workgroups they would end it (16 sequences of 4096 rows and 1025 slots 64.4 us a step waiting for
+// the map and 63.5 ahead of it, 8 sequences 40.6 and 39.3, 16 of 2561 and 2560 74.0 and 71.6; 5 of 3414 and 1707, half
+// full, 30.5 and 29.1).  Rows of free slots are fetched for nothing that way, so no more than can be in use are requested:
+// a new token takes the lowest free slot, so a pool that is used from step 0 on is empty behind slot `step`, and behind
+// slot `budget` (with all slots requested an empty pool of 4096 beside 256 rows took 26.8 us, 25.5 without; so it is 25.3).
+// Ranges that a workgroup's waves take in little more than one block each have all their rows in flight at once and gain
+// only while slots are few: 3 sequences in ranges of 160 rows 23.7 and 23.3 us with a tenth of slots, 28.5 and 28.4 with a
+// third, 35.2 and 35.7 with two thirds; 8 of head_dim 64 in ranges of 196 rows 25.0 and 25.6 with two thirds.
+static int ahead_of_map(const DecodeDims& d, int row_bytes) {
+  const long workgroups = static_cast<long>(d.n_splits) * d.H_kv * d.S;
+  if (workgroups > decode_resident(d.G, row_bytes)) return 0;
+  if (d.split_tokens < 256 && d.cap / 2 < d.n_slots) return 0;
+  return min(d.n_slots - 1, min(d.step, d.budget)) + 1;
+}
+
 template <typename T, int D>
 static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
                                  const void* k_new, const void* v_new, const DecodeWorkspace& w, hipStream_t s) {
   const dim3 grid(d.n_splits, d.H_kv, d.S), block(kThreads);
   const float c = d.sm_scale * kLog2e;
-  const bool ahead = static_cast<long>(d.n_splits) * d.H_kv * d.S <= 1024;  // one round: up to four workgroups per CU
+  const int ahead_slots = ahead_of_map(d, D * static_cast<int>(sizeof(T)));
   KernelTimer timer(d.timing, kKernelDecodePartial, s);
 #define SHOTKV_LAUNCH_DEC(GG)                                                                           \
   auto* kernel = d.split_tokens > kMaxRange ? decode_partial_kernel<T, D, GG, true>                     \
@@ -525,7 +543,7 @@ static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state&
   hipLaunchKernelGGL(kernel, grid, block, 0, s,                                                         \
                      static_cast<const char*>(st.k_prefill), static_cast<const char*>(st.v_prefill),    \
                      st.prefill_count, static_cast<char*>(st.k_dec), static_cast<char*>(st.v_dec),      \
-                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, d.n_splits, d.split_tokens, ahead, c, \
+                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, d.n_splits, d.split_tokens, ahead_slots, c, \
                      static_cast<const char*>(q_new), static_cast<const char*>(k_new),                  \
                      static_cast<const char*>(v_new), w.part_ml, w.part_o, w.z_dec, w.new_slot)
   switch (padded_group(d.G)) {  // the kernel is instantiated for power-of-two groups and skips the padding

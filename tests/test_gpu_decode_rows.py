@@ -42,14 +42,14 @@ def _state(kv, rng, S, H, Hkv, D, dtype, cap, counts, n_slots, used, budget, sca
     return kv.DecodeState(kp, vp, count, kd, vd, slot_pos, budget, H, scale)
 
 
-def _check_steps(kv, rng, state, budget, n_steps, scale):
+def _check_steps(kv, rng, state, budget, n_steps, scale, first_step=1000):
     S, H, Hkv, D, dtype = state.S, state.H, state.H_kv, state.D, state.dtype
     host = []
     for s in range(S):
         c = int(state.prefill_count[s].item())
         host.append([to_np(state.k_prefill[s, :, :c]), to_np(state.v_prefill[s, :, :c]), c, to_np(state.k_dec[s]).copy(),
                      to_np(state.v_dec[s]).copy(), state.slot_pos[s].cpu().numpy().copy()])
-    for step in range(1000, 1000 + n_steps):
+    for step in range(first_step, first_step + n_steps):
         new = [torch.from_numpy(rng.standard_normal((S, h, D), dtype=np.float32)).to(dtype).cuda() for h in (H, Hkv, Hkv)]
         kv.decode_step(state, step, *new)
         torch.cuda.synchronize()
@@ -108,10 +108,9 @@ def test_new_token_in_a_later_piece(kv, D, dtype, cap, n_slots, free):
 
 
 @pytest.mark.parametrize("S", [128, 129])
-def test_slots_requested_ahead_of_their_map_and_not(kv, S):
-    """Ranges of nothing but slots ask for their first rows before the slot map is known in launches of up to 1024
-    workgroups (128 sequences of 8 KV heads here) and after it in larger ones; free slots hold poison, and the new token's
-    slot lies at the start, inside and behind the occupied ones."""
+def test_ranges_of_nothing_but_slots(kv, S):
+    """Caches without prefill rows, in launches of up to 1024 workgroups (128 sequences of 8 KV heads here) and larger ones;
+    free slots hold poison, and the new token's slot lies at the start, inside and behind the occupied ones."""
     rng = np.random.default_rng(S)
     Hkv, D, n_slots, budget = 8, 64, 40, 39
     used = [np.setdiff1d(np.arange(n_slots), [0, 7, 31] if s % 3 == 0 else [5, 6, 39] if s % 3 == 1 else np.arange(20, 40))
@@ -119,6 +118,30 @@ def test_slots_requested_ahead_of_their_map_and_not(kv, S):
     scale = D ** -0.5
     state = _state(kv, rng, S, Hkv, Hkv, D, torch.bfloat16, 0, [0] * S, n_slots, used, budget, scale)
     _check_steps(kv, rng, state, budget, 2, scale)
+
+
+@pytest.mark.parametrize("S,Hkv,G,cap,n_slots,budget,first_step", [
+    (3, 2, 4, 410, 205, 204, 1000),     # short ranges, slots a third: rows requested ahead of the map
+    (3, 2, 4, 409, 205, 204, 1000),     # slots more than a third: after it
+    (3, 2, 8, 410, 205, 204, 1000),
+    (3, 2, 4, 410, 205, 40, 1000),      # a budget below, and a step before, what the pool holds: the blocks behind it are
+    (3, 2, 4, 410, 205, 204, 60),       # requested after the map
+    (64, 8, 1, 200, 400, 399, 1000),    # two ranges of 300 rows, the second of slots only: ahead
+    (64, 8, 1, 200, 400, 399, 110),
+    (103, 5, 1, 400, 700, 699, 1000),   # 1030 workgroups: after the map
+])
+@pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
+def test_slots_requested_ahead_of_their_map_and_not(kv, D, dtype, S, Hkv, G, cap, n_slots, budget, first_step):
+    """Ranges of nothing but slots behind ranges of prefill rows, where their first rows are requested before the slot map
+    is known and where they are not; free slots hold poison, and the new token's slot lies at the start of the pool, in the
+    first block of a later range, and behind the occupied slots."""
+    rng = np.random.default_rng(S + G + cap + first_step)
+    mid = n_slots // 2 + 3
+    free = [[0, mid, n_slots - 1], [mid, mid + 1, n_slots - 2], np.arange(n_slots // 4, n_slots)]
+    used = [np.setdiff1d(np.arange(n_slots), free[s % 3]) for s in range(S)]
+    scale = D ** -0.5
+    state = _state(kv, rng, S, Hkv * G, Hkv, D, dtype, cap, [cap - s % 7 for s in range(S)], n_slots, used, budget, scale)
+    _check_steps(kv, rng, state, budget, 2, scale, first_step)
 
 
 @pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (64, torch.float32), (128, torch.float32)])
