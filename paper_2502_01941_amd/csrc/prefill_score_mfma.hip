@@ -256,8 +256,9 @@ template <typename T> struct Queries {
 // that rounds up to infinity, makes its logits NaN, and the block is then taken again in the matrix unit's fp32 form,
 // as every block is for queries that are not plain.
 //
-// parts: where the workgroup's waves have put the block's bf16 parts (split_block), null if every wave splits for itself.
-template <typename T, int D, int NQW>
+// SHARED (fp32): the workgroup's waves have put the block's bf16 parts at `parts` (split_block); otherwise every wave splits
+// for itself.  (A null pointer would not tell: it is the address of the first LDS variable.)
+template <typename T, int D, int NQW, bool SHARED>
 __device__ __forceinline__ void logits_block(lds_cchar* lds_buf, lds_cchar* parts, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
                                              const Queries<T>& src, int lane, floatx16 (&acc)[NQW]) {
   typedef typename Element<T, D>::Layout L;
@@ -285,7 +286,7 @@ __device__ __forceinline__ void logits_block(lds_cchar* lds_buf, lds_cchar* part
 #pragma unroll
       for (int kp = 0; kp < Element<T, D>::kSteps / 2; ++kp) {
         Split a;
-        if (parts) {
+        if constexpr (SHARED) {
           lds_cchar* at = parts + P::operand(part_base, kp);
           a.hi = *reinterpret_cast<lds_bf16x8*>(at);
           a.mid = *reinterpret_cast<lds_bf16x8*>(at + Element<T, D>::kPartBytes);
@@ -346,13 +347,13 @@ __device__ __forceinline__ void split_block(lds_cchar* lds_buf, lds_char* parts,
 }
 
 // One 32-key block against this wave's NQW query blocks.
-template <typename T, int D, int NQW, bool MASKED, bool EXACT>
+template <typename T, int D, int NQW, bool SHARED, bool MASKED, bool EXACT>
 __device__ __forceinline__ void compute_block(lds_cchar* lds_buf, lds_cchar* parts, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
                                               const Queries<T>& src, int lane, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
   floatx16 acc[NQW];
-  logits_block<T, D, NQW>(lds_buf, parts, bq, src, lane, acc);
+  logits_block<T, D, NQW, SHARED>(lds_buf, parts, bq, src, lane, acc);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     const int last_visible = causal_base + ((src.qb0 + q) * 32 + row) % W;
@@ -363,13 +364,13 @@ __device__ __forceinline__ void compute_block(lds_cchar* lds_buf, lds_cchar* par
 // The same block when a chunk ends inside it: the exact online-softmax update, then the sixteen weights
 // 2^(z - reference) of every query stay in `e` so that the caller can credit them to the chunks on either
 // side of each boundary.  Nothing is added to l_run here.
-template <typename T, int D, int NQW, bool MASKED>
+template <typename T, int D, int NQW, bool SHARED, bool MASKED>
 __device__ __forceinline__ void weights_block(lds_cchar* lds_buf, lds_cchar* parts, const bf16x8 (&bq)[NQW][Element<T, D>::kQueryVecs],
                                               const Queries<T>& src, int lane, int key0, int rem, int causal_base, int W, float c,
                                               float (&m_run)[NQW], float (&l_run)[NQW], float (&l_grp)[NQW],
                                               floatx16 (&e)[NQW]) {
   const int row = lane & 31, half = lane >> 5;
-  logits_block<T, D, NQW>(lds_buf, parts, bq, src, lane, e);
+  logits_block<T, D, NQW, SHARED>(lds_buf, parts, bq, src, lane, e);
 #pragma unroll
   for (int q = 0; q < NQW; ++q) {
     if (MASKED) {
@@ -731,26 +732,25 @@ score_partials_mfma_kernel(
     const int cur_rem = min(kBlockKeys, k_end - cur_key0);
     const bool masked = cur_rem < kBlockKeys || cur_key0 + kBlockKeys - 1 > causal_base;
     lds_cchar* blk = lds_base + cur_buf * E::kBufBytes;
-    lds_cchar* parts = nullptr;
+    lds_cchar* parts = (lds_cchar*)&lds_parts[0];
     if constexpr (S::kShared) {
       // (the waves have read the parts of the block before: the barrier above)
       split_block<D, S::kWaves>(blk, (lds_char*)&lds_parts[0], wave, lane);
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      parts = (lds_cchar*)&lds_parts[0];
     }
     if (cur_end >= cur_key0 + cur_rem) {  // no chunk ends inside the block
       if (first_block)
-        compute_block<T, D, NQW, true, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, S::kShared, true, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else if (masked)
-        compute_block<T, D, NQW, true, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, S::kShared, true, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else
-        compute_block<T, D, NQW, false, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, S::kShared, false, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
     } else {
       floatx16 e[NQW];
       if (masked)
-        weights_block<T, D, NQW, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, S::kShared, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       else
-        weights_block<T, D, NQW, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, S::kShared, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       uint32_t lo0 = 0u, lo1 = 0u;  // elements already credited (lower / upper lane half)
       do {
         const int hi = cur_end - cur_key0;  // wave-uniform, 1..31

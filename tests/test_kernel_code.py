@@ -37,3 +37,17 @@ def test_no_generic_or_scratch_access(source):
     for name, code in _kernels(source).items():
         found = [i for i in code if i.startswith(("flat_load", "flat_store", "scratch_load", "scratch_store"))]
         assert not found, (name, found)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_shared_fp32_parts_are_made_once(D):
+    """fp32 scores: where the four or eight waves of a workgroup split a block of keys into bf16 parts between them, none
+    splits one for itself as well: such a kernel has a fraction of the conversions of the two-wave kernel, in which every
+    wave does (five times all of a block's, one for each form that a block can take)."""
+    count = {}
+    for name, code in _kernels("prefill_score_mfma.hip").items():
+        form = re.search(r"score_partials_mfma_kernelIfLi%dELi(\d)ELi(\d)E" % D, name)
+        if form:
+            count[form.groups()] = sum(i.startswith("v_cvt_pk_bf16_f32") for i in code)
+    own, shared = count.pop(("2", "2")), [count[f] for f in (("4", "4"), ("8", "8"))]
+    assert own > 0 and all(0 < n < own / 3 for n in shared), (own, shared)
