@@ -36,8 +36,7 @@
 // into three bf16 parts (split_f32) and six products of parts are summed in fp32, 0.37 of that time; the few values
 // that bf16 parts cannot hold take the fp32 form (logits_block).  Splitting is as much vector work (350 instructions a
 // block) as the products are matrix work, so four and eight waves split a block between them and read each other's parts
-// from LDS, for a second barrier and 26 KB more LDS; two workgroups per CU instead of three is the price: 640 workgroups
-// (2 problems of 20000 tokens) 121 us a call, 120 if each wave splits all.  Error of the scores against float64 over head
+// from LDS, for a second barrier and 26 KB more LDS, where that pays (share_parts).  Error of the scores against float64 over head
 // layouts, windows and 1001 .. 65000 tokens: 0.3 - 0.8e-7 of the norm.  One query block per wave (96 operand
 // registers at head_dim 128), up to eight waves per workgroup.  4 problems of 4001 tokens, 8 KV heads, 128 query rows,
 // head_dim 128: 33 us, 37 if each wave splits for itself, with the fp32 form 48, with plain vector arithmetic 394.  Whole
@@ -482,7 +481,7 @@ __device__ __forceinline__ void credit_elements(const floatx16 (&e)[NQW], uint32
 
 constexpr int kEndCache = 128;  // shot boundaries of a slice kept in LDS
 
-template <typename T, int D, int NQB, int WAVES>
+template <typename T, int D, int NQB, int WAVES, bool SHARED>
 struct GroupShape {
   static constexpr int kWaves = WAVES;                                      // waves per workgroup
   static constexpr int kNQW = NQB / kWaves;                                 // query blocks per wave
@@ -494,21 +493,19 @@ struct GroupShape {
   static constexpr int kQueryRegs = kNQW * Element<T, D>::kQueryVecs * 4;
   static constexpr int kRegWaves =
       (kQueryRegs > 64 || kNQW > 2) ? 2 : kQueryRegs > 32 ? SHOTKV_SCORE_WAVES_PER_SIMD : SHOTKV_SCORE_WAVES_PER_SIMD + 1;
-  // Whether the waves split fp32 blocks between them.  Two waves gain less from it than the second barrier costs: 8
-  // problems of 8000 tokens, 16 query / 8 KV heads, head_dim 128, 157 us a call, 150 if each splits for itself.
-  static constexpr bool kShared = sizeof(T) == 4 && WAVES >= 4;
-  static constexpr int kPartsBytes = kShared ? 3 * Element<T, D>::kPartBytes : 16;
+  static constexpr int kPartsBytes = SHARED ? 3 * Element<T, D>::kPartBytes : 16;
   static constexpr int kLdsWaves = 160 * 1024 / (kRing * Element<T, D>::kBufBytes + kPartsBytes + 1024) * kWaves / 4;
   static constexpr int kMinWavesPerSimd = kLdsWaves < 1 ? 1 : kLdsWaves < kRegWaves ? kLdsWaves : kRegWaves;
 };
 
-template <typename T, int D, int NQB, int WAVES>
-__global__ __launch_bounds__((GroupShape<T, D, NQB, WAVES>::kThreads), (GroupShape<T, D, NQB, WAVES>::kMinWavesPerSimd)) void
+template <typename T, int D, int NQB, int WAVES, bool SHARED>
+__global__ __launch_bounds__((GroupShape<T, D, NQB, WAVES, SHARED>::kThreads),
+                             (GroupShape<T, D, NQB, WAVES, SHARED>::kMinWavesPerSimd)) void
 score_partials_mfma_kernel(
     const T* __restrict__ q_obs, const T* __restrict__ k, int n_tokens, int H, int H_kv, int W,
     int n_rows, float c, const int32_t* __restrict__ shot_offsets, int share, int n_shots, int group_keys,
     int max_c, float* __restrict__ partial, float* __restrict__ group_stat) {
-  typedef GroupShape<T, D, NQB, WAVES> S;
+  typedef GroupShape<T, D, NQB, WAVES, SHARED> S;
   typedef Element<T, D> E;
   constexpr int NQW = S::kNQW;
   constexpr int R = NQB * 32;
@@ -717,7 +714,7 @@ score_partials_mfma_kernel(
     else if (n_q == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * S::kLoads) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * S::kLoads) : "memory");
     // ... and after the barrier so has the other waves'; all are also done reading the block before
-    if (S::kShared) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (SHARED) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     else if (S::kWaves > 1) asm volatile("s_barrier" ::: "memory");
     if (n_stash == kStash) flush();
     if (next_key0 < k_end) {
@@ -733,24 +730,24 @@ score_partials_mfma_kernel(
     const bool masked = cur_rem < kBlockKeys || cur_key0 + kBlockKeys - 1 > causal_base;
     lds_cchar* blk = lds_base + cur_buf * E::kBufBytes;
     lds_cchar* parts = (lds_cchar*)&lds_parts[0];
-    if constexpr (S::kShared) {
+    if constexpr (SHARED) {
       // (the waves have read the parts of the block before: the barrier above)
       split_block<D, S::kWaves>(blk, (lds_char*)&lds_parts[0], wave, lane);
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
     if (cur_end >= cur_key0 + cur_rem) {  // no chunk ends inside the block
       if (first_block)
-        compute_block<T, D, NQW, S::kShared, true, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, SHARED, true, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else if (masked)
-        compute_block<T, D, NQW, S::kShared, true, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, SHARED, true, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
       else
-        compute_block<T, D, NQW, S::kShared, false, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
+        compute_block<T, D, NQW, SHARED, false, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp);
     } else {
       floatx16 e[NQW];
       if (masked)
-        weights_block<T, D, NQW, S::kShared, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, SHARED, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       else
-        weights_block<T, D, NQW, S::kShared, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
+        weights_block<T, D, NQW, SHARED, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       uint32_t lo0 = 0u, lo1 = 0u;  // elements already credited (lower / upper lane half)
       do {
         const int hi = cur_end - cur_key0;  // wave-uniform, 1..31
@@ -812,11 +809,11 @@ int score_row_blocks(int dtype, int rows) {
   return need <= 2 ? need : need <= 4 ? 4 : (need <= 6 && dtype == SHOTKV_BF16) ? 6 : 8;
 }
 
-template <typename T, int D, int NQB, int WAVES>
+template <typename T, int D, int NQB, int WAVES, bool SHARED = false>
 static void launch_score(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
                          const PrefillWorkspace& w, hipStream_t s) {
-  hipLaunchKernelGGL((score_partials_mfma_kernel<T, D, NQB, WAVES>), dim3(w.n_groups, d.H_kv, d.P),
-                     dim3(GroupShape<T, D, NQB, WAVES>::kThreads), 0, s, static_cast<const T*>(q_obs),
+  hipLaunchKernelGGL((score_partials_mfma_kernel<T, D, NQB, WAVES, SHARED>), dim3(w.n_groups, d.H_kv, d.P),
+                     dim3(GroupShape<T, D, NQB, WAVES, SHARED>::kThreads), 0, s, static_cast<const T*>(q_obs),
                      static_cast<const T*>(k), d.n_tokens, d.H, d.H_kv, d.W, d.R_rows, d.sm_scale * kLog2e,
                      off, d.share, d.n_shots, w.group_keys, w.max_c, w.partial, w.group_stat);
 }
@@ -836,6 +833,19 @@ static bool four_waves(const PrefillDims& d) {
   return total_keys < (unit < 16 ? 1L << 19 : d.D == 64 ? 3L << 19 : unit < 64 ? 2L << 20 : 12L << 20);
 }
 
+// Whether the four or eight waves of a workgroup split fp32 blocks between them.  (Two waves gain less from it than the
+// second barrier costs: 8 problems of 8000 tokens, 16 query / 8 KV heads, head_dim 128, 157 us a call, 150 if each splits for
+// itself.)  Four waves at head_dim 128 that share leave room for two workgroups per CU, three where each wave splits for
+// itself: launches that are one round of three but not of two mostly lose.  Whole call, 128 rows, 8 KV heads, shared and
+// each for itself, by workgroups with a whole slice: 512 62.0 and 68.4 us, 528 69.5 and 67.8, 560 72.8 and 70.9, 640 120.2
+// and 119.0 (2 x 20000 tokens), 720 77.0 and 77.4, 744 83.1 and 79.6, 760 79.3 and 80.4, 768 80.2 and 81.5, 776 86.8 and
+// 92.6, 1000 92.4 and 96.6, 1250 197.6 and 203.  head_dim 64 (four per CU either way) 624 66.9 and 71.9, eight waves 624
+// 180 and 201.
+static bool share_parts(const PrefillDims& d, const PrefillWorkspace& w) {
+  const long workgroups = static_cast<long>(d.n_tokens / w.group_keys) * d.H_kv * d.P;
+  return d.D == 64 || workgroups <= 2 * 256 || workgroups >= 3 * 256;
+}
+
 template <typename T, int D>
 static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, const void* k, const int32_t* off,
                                     const PrefillWorkspace& w, hipStream_t s) {
@@ -846,13 +856,15 @@ static hipError_t launch_score_rows(const PrefillDims& d, const void* q_obs, con
     case 4:
       if constexpr (!kF32)
         if (!four_waves(d)) { launch_score<T, D, 4, 2>(d, q_obs, k, off, w, s); break; }
-      launch_score<T, D, 4, 4>(d, q_obs, k, off, w, s);
+      if constexpr (kF32)
+        if (share_parts(d, w)) { launch_score<T, D, 4, 4, true>(d, q_obs, k, off, w, s); break; }
+      if constexpr (!kF32 || D == 128) launch_score<T, D, 4, 4>(d, q_obs, k, off, w, s);
       break;
     case 6:
       if constexpr (!kF32) { launch_score<T, D, 6, 2>(d, q_obs, k, off, w, s); break; }
       return hipErrorInvalidValue;
     case 8:
-      launch_score<T, D, 8, kF32 ? 8 : 4>(d, q_obs, k, off, w, s);  // fp32 operands: one block per wave
+      launch_score<T, D, 8, kF32 ? 8 : 4, kF32>(d, q_obs, k, off, w, s);  // fp32 operands: one block per wave
       break;
     default: return hipErrorInvalidValue;
   }

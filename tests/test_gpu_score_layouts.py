@@ -165,6 +165,28 @@ def test_float32_forms_side_by_side(kv, D, G):
     np.testing.assert_allclose(got, want, rtol=SCORE_RTOL, atol=0)
 
 
+def test_float32_launches_that_share_their_parts_and_not(kv):
+    """Four waves at head_dim 128 split blocks between them, except in launches of 513 to 767 workgroups with a whole slice
+    of 256 keys: 32, 33, 47 and 48 problems of two such slices and 8 KV heads.  Same bits either way; one head of every
+    third problem has queries that bf16 parts cannot hold."""
+    P, Hkv, G, W, N, D = 48, 8, 4, 32, 600, 128
+    assert 48 << 10 <= 32 * Hkv * N and P * Hkv * N < 256 << 10     # slices of 256 keys
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q = torch.randn((P, Hkv * G, W, D), generator=gen, device="cuda")
+    k = torch.randn((P, Hkv, N, D), generator=gen, device="cuda")
+    q[::3, 1, :, 5] *= 2.0**120
+    k[::3, :, :, 5] *= 2.0**-120
+    off = torch.tensor([0, 50, 97, 130, 131, 400, 401, 590], dtype=torch.int32, device="cuda").expand(P, 8).contiguous()
+    scale = 1.0 / math.sqrt(D)
+    got = {n: kv.prefill_scores(q[:n], k[:n], off[:n], scale)[0] for n in (32, 33, 47, 48)}
+    torch.cuda.synchronize()
+    for n in (32, 33, 47):
+        assert torch.equal(got[n], got[48][:n])
+    for p in (0, 31, 46):
+        ref = oracle_prefill(q[p], k[p], k[p], off[p].cpu().numpy(), N, scale)
+        np.testing.assert_allclose(got[47][p].cpu().numpy(), ref["scores"], rtol=SCORE_RTOL, atol=0)
+
+
 def test_a_unit_of_many_slices(kv):
     """One unit over 128 slices of the key axis and 8 KV heads: its first key takes nearly all of the mass, 8, and the
     other thousand (slice, head) parts 2.2e-7 each, just under half a unit in the last place below 8, 2.8e-5 of it

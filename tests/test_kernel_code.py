@@ -46,8 +46,8 @@ def test_shared_fp32_parts_are_made_once(D):
     wave does (five times all of a block's, one for each form that a block can take)."""
     count = {}
     for name, code in _kernels("prefill_score_mfma.hip").items():
-        form = re.search(r"score_partials_mfma_kernelIfLi%dELi(\d)ELi(\d)E" % D, name)
+        form = re.search(r"score_partials_mfma_kernelIfLi%dELi\dELi(\d)ELb(\d)E" % D, name)
         if form:
             count[form.groups()] = sum(i.startswith("v_cvt_pk_bf16_f32") for i in code)
-    own, shared = count.pop(("2", "2")), [count[f] for f in (("4", "4"), ("8", "8"))]
+    own, shared = count[("2", "0")], [count[f] for f in (("4", "1"), ("8", "1"))]
     assert own > 0 and all(0 < n < own / 3 for n in shared), (own, shared)
