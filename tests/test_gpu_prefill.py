@@ -229,11 +229,13 @@ def test_select_and_compact_synthetic_scores(kv, mode):
         np.testing.assert_array_equal(helpers.bits(res.v_out[p, :, :kept]), helpers.bits(v[p][:, idx]))
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 129, 1000, 1023, 1024, 1025, 2047, 2049, 4095, 4096])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 256, 257, 400, 512, 513, 1000, 1023, 1024, 1025, 2047, 2049, 4095,
+                               4096])
 def test_ranking_sizes_and_special_scores(kv, n):
-    """The ranking at every size class of the sorting network (one, two and four keys per thread; with and
-    without the transposed passes; padding of 0..n_pad-1 entries), on scores with heavy ties, both zeros,
-    negative values, infinities and denormals: selection and positions bit-exact against the oracle."""
+    """Up to 128 shots are ranked by counting (sixteen lanes to a shot up to 64, eight above).  Above, first fit sorts:
+    every size class of the network (256, 512 and 1024 keys, two and four keys per thread, with and without padding);
+    prefix selection searches by digits.  Scores with heavy ties, both zeros, negative values, infinities and
+    denormals: selection and positions bit-exact against the oracle."""
     P, H, Hkv, D, W = 4, 2, 1, 128, 8
     N = 3 * n + 300
     _, k, v, off = _ragged_problem(P, H, Hkv, D, W, N, torch.bfloat16, 500 + n, n, 2, 40)
@@ -276,8 +278,9 @@ def test_where_the_budget_ends(kv, n):
     off[:, 0] = rng.integers(0, 4, size=P)
     off[:, 1:] = off[:, :1] + np.cumsum(lens, axis=1)
     kinds = [rng.random(n).astype(np.float32), 1 + np.float32(2.0 ** -23) * rng.permutation(n).astype(np.float32),
-             rng.integers(0, 3, size=n).astype(np.float32), np.zeros(n, dtype=np.float32),
-             np.exp(20 * rng.standard_normal(n)).astype(np.float32)]
+             rng.integers(0, 3, size=n).astype(np.float32), np.zeros(n, dtype=np.float32)]
+    with np.errstate(over="ignore"):
+        kinds.append(np.exp(30 * rng.standard_normal(n)).astype(np.float32))    # some are infinite, some are zero
     scores = np.stack([kinds[p % 5] for p in range(P)])
     budgets, wants = np.zeros(P, dtype=np.int32), []
     for p in range(P):
