@@ -107,3 +107,45 @@ def test_rows_that_two_keys_share(kv):
     lighter = np.minimum(p[..., 1], p[..., 2])
     ref = np.stack([p[h, :, 1:] @ vh[h // (H // Hkv), heavy] for h in range(H)])
     assert np.all(np.abs(got[:, rows] - ref) <= 2.0 ** -11 * lighter[..., None] + 2.0 ** -18)
+
+
+@pytest.mark.parametrize("what,value", [("q", math.nan), ("q", math.inf), ("k", math.nan), ("k", math.inf), ("k", -math.inf),
+                                        ("v", math.nan), ("v", math.inf)])
+def test_values_that_are_not_finite_stay_where_they_belong(kv, what, value):
+    """One infinite or NaN query, key or value element, in tiles with and without window rows.  Queries are positive in that
+    dimension.  A query shows in its own row, a key in the rows of its query heads from its position on (minus infinity: as
+    a key that is not there), a value in its column of the rows that can see its block of 32 keys.  Everything else is bit
+    for bit what it is without it: no other row of the wave, which shares the rescaling, is touched."""
+    H, Hkv, W, D, N, n, dim = 4, 2, 32, 128, 700, 4, 9
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((1, h, N, D), generator=gen, device="cuda") for h in (H, Hkv, Hkv))
+    q[..., dim] = q[..., dim].abs() + 0.5
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    off = torch.from_numpy(np.linspace(3, N - 40, n + 1).astype(np.int32)[None]).cuda()
+    bud = torch.tensor([N // 2], dtype=torch.int32, device="cuda")
+
+    def run(q, k, v):
+        attn, _ = kv.prefill_attention_compress(q, k, v, off, bud, N // 2, W, D ** -0.5)
+        torch.cuda.synchronize()
+        return attn[0]
+
+    clean = run(q, k, v)
+    for at in (0, 37, 300, 511, 660, 690):
+        t = {"q": q.clone(), "k": k.clone(), "v": v.clone()}
+        t[what][0, 1, at, dim] = value
+        got = run(t["q"], t["k"], t["v"])
+        touched = torch.zeros_like(clean, dtype=torch.bool)
+        if what == "q":
+            touched[1, at] = True
+        elif what == "k":
+            touched[2:, at:] = True         # query heads 2 and 3 read KV head 1
+        else:
+            touched[2:, at // 32 * 32:, dim] = True
+        assert torch.equal(got[~touched], clean[~touched]), at
+        if what == "k" and value < 0:       # no weight; row 0 has no other key
+            with np.errstate(invalid="ignore"):
+                ref = orc.causal_attention(to_np(q[0, 2:]), to_np(t["k"][0, 1:]), to_np(v[0, 1:]), D ** -0.5)[:, 1:]
+            assert np.all(np.abs(got[2:, 1:].cpu().numpy() - ref) <= OUT_TOL * np.abs(ref).max(axis=2, keepdims=True)), at
+        else:
+            shown = got[2:, at:, dim] if what == "v" else got[touched]
+            assert not torch.isfinite(shown).any(), at
