@@ -275,16 +275,18 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
 
   // Eq. 3 bookkeeping (emitting waves only): the segment whose sum is being collected, see max_chunks().  (Offsets
   // that are out of order give wrong statistics in range; the problem's scores are discarded.)
-  // The ends of 64 segments at a time sit in the lanes: a load at every end would wait for the stream as well.
+  // The ends of 64 segments at a time sit in the lanes, one load for all of them.
   const int32_t* off = x.shot_offsets + static_cast<size_t>(p / x.share) * (x.n_shots + 1);
   const int n_seg = wave_emits ? x.n_shots + 2 : 0;
   int ends = 0;
   auto segment_end = [&](int sg) {
-    if (sg % kWave == 0) {
+    const int at = sg & (kWave - 1);
+    if (at == 0) {
       const int i = sg + lane;
       ends = i <= x.n_shots ? off[i] : n_tokens;
+      asm volatile("" : "+v"(ends));  // waited for here: not at every end, with the store just issued and the stream
     }
-    return __builtin_amdgcn_readlane(ends, sg % kWave);
+    return __builtin_amdgcn_readlane(ends, at);
   };
   int cur_c = 0, cur_s = 0, cur_e = wave_emits ? segment_end(0) : 0;
   const int h_local = h - g * G;
@@ -390,19 +392,26 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
       for (int v = 0; v < 16; ++v) acc[v] = 0.f;
     }
     // ---- Eq. 3: this block's weights credited to the chunks it overlaps --------------------------
-    if (wave_emits) {
+    // The tiles with window rows are the longest and wait for the waves that do this, three instructions per weight and
+    // segment.  Whole call, with compares against both ends of a segment and a scalar load at each, and this: 8192 tokens in
+    // 2000 units 1276 and 963 us, in 320 640 and 621; 5000 tokens of 8 heads in 600 units 429 and 318, in 27 shots 204 and
+    // 169; with compares and all vector memory waited for at every end 469 and 176.
+    if (cur_c < n_seg && cur_s <= key0 && cur_e >= key0 + kBlockKeys) {  // one segment: the sum below without masks
+      float sum = 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum += acc[v];
+      l_chunk += sum;
+      if (cur_e == key0 + kBlockKeys) finish_chunk();
+    } else if (wave_emits) {
       while (cur_c < n_seg && cur_s < key0 + kBlockKeys) {
-        const int lo = max(cur_s, key0) - key0 - 4 * half, hi = min(cur_e, key0 + kBlockKeys) - key0 - 4 * half;
+        // the segment's rows of the block, a bit each; this lane holds rows 4 * half + 8 * (v / 4) + v % 4
+        auto below = [](int n) { return n > 0 ? ~0u >> (kBlockKeys - n) : 0u; };
+        const uint32_t rows = (below(min(cur_e - key0, kBlockKeys)) & ~below(cur_s - key0)) >> (4 * half);
         float sum = 0.f;
-        if (cur_s > key0 || cur_e < key0 + kBlockKeys) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + (v & 3);
-            sum += (r >= lo && r < hi) ? acc[v] : 0.f;
-          }
-        } else {  // (in the same order)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) sum += acc[v];
+        for (int v = 0; v < 16; ++v) {
+          const int in = __builtin_amdgcn_sbfe(static_cast<int>(rows), 8 * (v >> 2) + (v & 3), 1);  // all ones or zeros
+          sum += __int_as_float(__float_as_int(acc[v]) & in);
         }
         l_chunk += sum;
         if (cur_e <= key0 + kBlockKeys) finish_chunk();
@@ -453,8 +462,8 @@ __device__ __forceinline__ void attention_tile(const AttentionArgs& x, int h, in
 //
 // Bound by matrix and vector issue, which add up, at a power-limited clock.  Operands read ahead of the softmax, segment
 // ends in the lanes, 168 registers and the heads of all problems in one order for the XCDs; whole call, 32 query / 8 KV
-// heads, without all of that and with it: 1500 tokens 87 and 76 us, 3000 158 and 142, 8192 606 and 587, 32768 8378 and
-// 8218; 8 problems of 5000 with 8 heads 504 and 480.  Outputs are the same bits.  Waves of 64 queries, which read LDS half
+// heads, without all of that and with it: 1500 tokens 87 and 73 us, 3000 156 and 135, 8192 588 and 570, 32768 8080 and
+// 7930; 8 problems of 5000 with 8 heads 508 and 476.  Outputs are the same bits.  Waves of 64 queries, which read LDS half
 // as often, have registers for two per SIMD: 3 - 5 % faster at 32768 tokens, but 6 % slower at 6000 and slower in most
 // calls below (measured with a reference that stays), so there is one kernel.
 __global__ __launch_bounds__(kThreadsQ, 3) void attention_scores_kernel(AttentionArgs x, int n_plain) {

@@ -78,6 +78,7 @@ def test_attention_and_compression_match_the_oracle(kv, H, H_kv, W, N, n_shots, 
 
 @pytest.mark.parametrize("N,W,n_shots", [
     (480, 16, 61), (480, 16, 62), (480, 16, 63), (512, 32, 64), (600, 32, 127),  # 64 segments, the ends a wave holds
+    (480, 16, 470), (700, 64, 300),                 # units of one token, of one to a few
     (416, 32, 3), (417, 32, 3), (415, 32, 3),       # the window ends, or does not end, a tile of 128 queries (384 + 32)
     (64, 64, 2), (65, 64, 2), (191, 64, 2), (40, 32, 1),    # nothing but window rows in most or all tiles
 ])

@@ -51,3 +51,13 @@ def test_shared_fp32_parts_are_made_once(D):
             count[form.groups()] = sum(i.startswith("v_cvt_pk_bf16_f32") for i in code)
     own, shared = count[("2", "0")], [count[f] for f in (("4", "1"), ("8", "1"))]
     assert own > 0 and all(0 < n < own / 3 for n in shared), (own, shared)
+
+
+def test_segment_ends_do_not_wait_for_the_stream():
+    """Fused attention: the end of the next segment comes out of a register's lanes.  Where the load that fills the register
+    every 64 segments is not waited for in its own branch, every end waits for all vector memory: the blocks in flight and
+    the statistic just stored."""
+    for name, code in _kernels("prefill_attention.hip").items():
+        found = [(code[i - 1], line) for i, line in enumerate(code)
+                 if line.startswith("v_readlane_b32") and code[i - 1].startswith("s_waitcnt") and "vmcnt" in code[i - 1]]
+        assert not found, (name, found)
