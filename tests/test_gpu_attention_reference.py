@@ -1,6 +1,6 @@
 """GPU parity of the fused attention pass where its softmax reference has to move late: rows whose logits grow along
-the prompt, by a little in every block (the reference stays) or by far more than fp16 holds (it must follow), and
-rows whose first keys are the heaviest."""
+the prompt, by a little in every block or at once by far more than fp16 holds, and rows whose first keys are the
+heaviest; what its position does to the weights' precision, and values that are not finite."""
 import math
 
 import numpy as np
