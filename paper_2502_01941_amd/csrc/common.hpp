@@ -221,6 +221,7 @@ hipError_t launch_attention_scores(const PrefillDims& d, const void* q, const vo
 
 struct DecodeDims {
   int S, H, H_kv, G, D, dtype, cap, n_slots, budget, step, n_splits, split_tokens;
+  bool whole;  // one workgroup per sequence and KV head: n_splits and split_tokens only size the workspace
   float sm_scale;
   void* const* timing;  // the caller's timing events, or null
 };
@@ -228,7 +229,9 @@ struct DecodeDims {
 struct DecodeWorkspace {
   float2* part_ml;   // [S][H][n_splits] (max in log2 domain, sum)
   float*  part_o;    // [S][H][n_splits][D]
-  float*  z_dec;     // [S][H][n_slots] scaled logits (log2 domain) of decode slots, -inf when free
+  // [S][H][n_slots] scaled logits (log2 domain) of the occupied decode slots; where one workgroup takes all of a
+  // (sequence, KV head), [S][H_kv][n_slots] their weights summed over its query heads
+  float*  z_dec;
   int32_t* new_slot;  // [S] slot chosen for the new token this step, -1 if the pool is full
   size_t  bytes;
 };
@@ -264,8 +267,17 @@ inline int padded_group(int G) { return G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : G
 
 int decode_resident(int G, int row_bytes);  // workgroups of the decode kernel that the chip holds at once
 int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens);
+// Slots whose map, and tokens whose logits, a decode workgroup of four waves holds in LDS: the blocks of rows that a wave
+// takes at a time are dealt to the waves in turn.
+constexpr int kDecodeBlockBytes = 4096;
+constexpr int decode_map_rows(int row_bytes) {
+  const int block = kDecodeBlockBytes / row_bytes;
+  return (kDecodeMaxRange / block + 1 + 3) / 4 * 4 * block;
+}
+bool decode_whole(const DecodeDims& d, int row_bytes);
+int decode_launch_splits(const DecodeDims& d);  // token ranges of the launch
 hipError_t launch_decode_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
-                                 const void* k_new, const void* v_new, const DecodeWorkspace& w,
+                                 const void* k_new, const void* v_new, float* out, const DecodeWorkspace& w,
                                  hipStream_t s);
 hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& st, float* out,
                                 float* token_scores, int32_t* evicted_pos, int32_t* status,

@@ -53,7 +53,8 @@ __device__ __forceinline__ void take_better_of_lane(float& score, int& pos, int&
 // per CU, which is dear where heads are few and sequences many (per-KV-head mode: 256 pairs of 4 heads 12.1 us),
 // so up to 8 heads take the small form.
 constexpr int kFinHeadsPerGroup = 4;
-template <int D, int kAhead>
+// WHOLE: the outputs are written and z_dec holds H = H_kv partial scores per slot, to be added; only workgroup 0 is left.
+template <int D, int kAhead, bool WHOLE>
 __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     const float2* __restrict__ part_ml, const float* __restrict__ part_o,
     const float* __restrict__ z_dec, int32_t* __restrict__ slot_pos,
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   int32_t* sp = slot_pos + static_cast<size_t>(s) * n_slots;
   const int new_slot = new_slot_in[s];
   const size_t head0 = static_cast<size_t>(s) * H;
-  const bool retain = blockIdx.x == 0;
+  const bool retain = WHOLE || blockIdx.x == 0;
   // heads whose statistics this workgroup needs: all of them for the scores, its own for the merge
   const int h_lo = retain ? 0 : (static_cast<int>(blockIdx.x) - 1) * kFinHeadsPerGroup;
   const int h_hi = retain ? H : min(h_lo + kFinHeadsPerGroup, H);
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     const int h = h_lo + wave + i * kFinWaves;
     m_first[i] = -INFINITY;
     l_first[i] = 0.f;
-    if (h < h_hi && lane < n_splits) {
+    if (!WHOLE && h < h_hi && lane < n_splits) {
       const float2 ml = part_ml[(head0 + h) * n_splits + lane];
       m_first[i] = ml.x;
       l_first[i] = ml.y;
@@ -138,7 +139,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   // ---- global softmax statistics per head: one wave per head, lanes over the splits; each split's weight
   // 2^(m - M) is kept so that the merge below is a plain weighted sum
   // (a wave's heads are taken two at a time so that their first loads travel together)
-  for (int h = h_lo + wave; h < h_hi; h += 2 * kFinWaves) {
+  for (int h = h_lo + wave; !WHOLE && h < h_hi; h += 2 * kFinWaves) {
     const int h2 = h + kFinWaves;
     const bool two = h2 < h_hi;
     const float2* ml = part_ml + (head0 + h) * n_splits;
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
     return;
   }
 
-  __syncthreads();
+  if (!WHOLE) __syncthreads();
 
   if (!retain) {  // attention output of this workgroup's heads
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -227,7 +228,7 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
   // retention scores and the eviction candidate
   float best_score = INFINITY;
   int best_pos = -1, best_slot = -1, count = 0;
-  auto share = [&](float z, int h) { return __builtin_amdgcn_exp2f(z - s_stat[h].x) * s_stat[h].y; };
+  auto share = [&](float z, int h) { return WHOLE ? z : __builtin_amdgcn_exp2f(z - s_stat[h].x) * s_stat[h].y; };
   constexpr int kHeadBatch = 16;  // loads in flight
   for (int slot = tid; slot < n_main; slot += kFinThreads) {
     const bool first = slot == tid;
@@ -325,11 +326,44 @@ int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
   const int pairs = S * H_kv;
   const int many = max(1, decode_resident(G, row_bytes) / pairs), few = max(1, 768 / pairs);
   int splits = G > 2 && few * pairs >= 640 ? few : many;
-  // no range shorter than 96 tokens (one sequence of 3800 rows: 20.5 us, 21.6 with 128, 25 with 32) ...
-  splits = min(splits, max(1, total_tokens / 96));
+  // no range shorter than 96 tokens, or 64 where that makes no more than two workgroups per CU (one sequence of 3800 rows,
+  // 8 KV heads: 17.0 us with 96, 16.8 with 64, 18.4 with 128; of 1100 rows, 4 KV heads, 17.8, 15.4 and 17.8; 8 sequences
+  // of 600 fp32 rows 19.1, 19.5 and 20.9) ...
+  splits = min(splits, max(1, total_tokens / (pairs * (total_tokens / 64) <= 512 ? 64 : 96)));
   // ... none longer than one piece of logits per workgroup, and no more than the finish kernel takes
   splits = max(splits, ceil_div(total_tokens, kDecodeMaxRange));
   return max(1, min(splits, kDecodeMaxSplits));
+}
+
+// Whether one workgroup takes all tokens of a (sequence, KV head).  It knows the whole softmax, so it writes the output
+// and one partial score per slot instead of partial sums of every range and the logits of every head: those writes, a
+// hundredth of the bytes read, cost the row stream an eighth of its time (512 sequences of 5121 rows, 8 KV heads: step
+// 1840 us, 1760 without storing logits, 1600 without partial sums either, 1640 like this, where the finish kernel shrinks
+// from 51 to 12 as well).  It pays where the pairs alone fill the chip: three workgroups per CU are resident, two with
+// more than four query heads per KV head, and a second round of them has to be worth having.  Whole steps, ranges and
+// whole: 4 query heads, 5121 rows, 256 pairs 130 and 133 us, 352 171 and 157, 384 184 and 164, 512 242 and 207, 576 269
+// and 267, 768 355 and 306, 800 368 and 385, 832 389 and 399, 1024 477 and 430, 2048 950 and 838; 365 rows, 384 pairs
+// 25.2 and 27.1; 913 rows, 512 pairs 52.5 and 48.1; 8 query heads, 4401 rows, 320 pairs 166 and 186, 384 215 and 215, 448
+// 245 and 220, 512 240 and 206, 544 234 and 295, 640 276 and 300.  Where one range is all there is anyway nothing is won
+// (2048 pairs of 365 rows of one query head 41 and 57).
+bool decode_whole(const DecodeDims& d, int row_bytes) {
+  if (d.n_splits < 2 || d.n_slots > decode_map_rows(row_bytes)) return false;
+  const int pairs = d.S * d.H_kv;
+  const long bytes = static_cast<long>(d.cap + d.n_slots) * row_bytes;  // of a pair's K rows
+  if (d.G <= 4) return pairs >= (bytes < 1 << 20 ? 448 : 352) && (pairs <= 768 || pairs >= 896);
+  const int rounds = ceil_div(pairs, 512);
+  return 5 * pairs >= 4 * 512 * rounds;
+}
+
+// Token ranges that a launch takes, at most n_splits.  Where ranges of no more than one piece would be over a round of
+// workgroups, two or three longer ones that fill a round write less and start less often: 256 pairs of 5121 rows, 4 query
+// heads, six ranges 129.8 us and three 121.2; 352 pairs 171 and 164; 256 pairs of 4401 rows, 7 query heads, 130 and 122.5.
+// Four ranges gain nothing (192 pairs 96.7 and 97.4).
+int decode_launch_splits(const DecodeDims& d) {
+  if (d.whole) return 1;
+  const int resident = d.G > 4 ? 512 : 768, pairs = d.S * d.H_kv, splits = resident / pairs;
+  const bool few = d.n_splits * pairs > 1024 && splits >= 2 && splits <= 3 && splits * pairs >= resident - resident / 8;
+  return few ? min(splits, d.n_splits) : d.n_splits;
 }
 
 hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& st, float* out,
@@ -337,11 +371,13 @@ hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& 
                                 const DecodeWorkspace& w, hipStream_t s) {
   if (d.H > kFinMaxHeads || d.n_splits > kDecodeMaxSplits) return hipErrorInvalidValue;
   KernelTimer timer(d.timing, kKernelDecodeFinish, s);
-  const dim3 grid(1 + ceil_div(d.H, kFinHeadsPerGroup), d.S);
-  auto* kernel = d.D == 128 ? (d.H <= 8 ? decode_finish_kernel<128, 8> : decode_finish_kernel<128, 32>)
-                            : (d.H <= 8 ? decode_finish_kernel<64, 8> : decode_finish_kernel<64, 32>);
+  const int rows = d.whole ? d.H_kv : d.H;
+  const dim3 grid(d.whole ? 1 : 1 + ceil_div(d.H, kFinHeadsPerGroup), d.S);
+  auto* kernel = d.whole       ? (rows <= 8 ? decode_finish_kernel<128, 8, true> : decode_finish_kernel<128, 32, true>)
+                 : d.D == 128 ? (rows <= 8 ? decode_finish_kernel<128, 8, false> : decode_finish_kernel<128, 32, false>)
+                              : (rows <= 8 ? decode_finish_kernel<64, 8, false> : decode_finish_kernel<64, 32, false>);
   hipLaunchKernelGGL(kernel, grid, dim3(kFinThreads), 0, s, w.part_ml, w.part_o, w.z_dec, st.slot_pos, w.new_slot,
-                     d.n_slots, d.H, d.n_splits, d.budget, d.step, out, token_scores, evicted_pos, status);
+                     d.n_slots, rows, decode_launch_splits(d), d.budget, d.step, out, token_scores, evicted_pos, status);
   return hipGetLastError();
 }
 

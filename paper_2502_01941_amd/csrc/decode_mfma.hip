@@ -1,25 +1,25 @@
 // Split-KV decode attention with the logits on the matrix cores
 // (Section 5.1, Eq. 7 and 9: attention of the current query over prefill rows and decode slots).
 //
-// A workgroup owns one token range of one (sequence, KV head) and makes two passes over it, in pieces of at
-// most kMaxRange tokens:
+// A workgroup owns one token range of one (sequence, KV head).  The range is cut into blocks of 4 KB of rows, dealt to
+// its four waves in turn, and every wave makes two passes over its own blocks without waiting for the others, in pieces
+// of as many as the logit buffer holds (more than one piece only in the LONG form):
 //   1. K pass: the logits of 4 or 8 tokens per matrix step, with the head dimension cut into pieces that
 //      sit in different operand rows/columns, so that the A operands are whole K rows fetched straight
-//      from global memory with coalesced 16-byte loads (RowShape).  The scaled logits go to LDS, their
-//      maximum stays in registers.
-//   between: weights 2^(z - max) by all threads, tokens along the lanes; decode-slot logits are also written
-//      out for the retention score (Eq. 7).  The first V rows are already on their way: they are requested
-//      between the loads of a wave's last K block and its use.
+//      from global memory with coalesced 16-byte loads (RowShape), two blocks in flight or in use.  The scaled logits go
+//      to the wave's part of the LDS buffer, their maximum stays in registers.
+//   between: weights 2^(z - reference), the wave's own maximum rounded up, tokens along the lanes; decode-slot logits are also
+//      written out for the retention score (Eq. 7).  The first V rows are already on their way: they are requested ahead
+//      of the use of a wave's last K blocks.
 //   2. V pass: RowShape::kLanes lanes stream one V row each (16 bytes per lane) and accumulate weight * V with
-//      the weights read from LDS, the next batch of rows in flight while one is used.  No rescaling is
-//      needed because the maximum is already known.
-// Bound by the stream of K and V rows: 32 query / 8 KV heads, head_dim 128 bf16, 512 caches of ~5000 rows 1.79 ms
-// = 5.9 TB/s, 16 caches 58 us.  Before the rows of 64-dimensional heads and of fp32 caches took this form they
-// were scored and summed by one-pass vector arithmetic: 32 caches of 2001 + 512 rows, head_dim 64, 57 us then,
-// 33 us now; 8 caches of 2000 + 500 fp32 rows 57 -> 38 us a step.  Requesting the first V rows ahead of the
-// weights is worth 4 us of 74 at 16 caches.
-// Compared with a one-pass online softmax this moves the dot products off the vector ALU, removes the
-// cross-lane reductions per token and the per-token rescale of the output accumulators.
+//      the weights read from LDS, the next block in flight while one is used.  No rescaling is needed within a piece
+//      because the maximum is already known.
+// At the end the waves' sums are scaled to their common reference and added through LDS.
+// Bound by the stream of K and V rows.  32 query / 8 KV heads, head_dim 128 bf16, ~5100 rows, whole steps with waves that
+// wait for each other between the passes (8 KB blocks, one in flight) and with this: 16 sequences 66.1 and 64.3 us, 24
+// 101.2 and 96.7; 3 sequences of 5500 rows and 5 query heads per KV head 31.3 and 28.2; 2 of 1760 rows of head_dim 64 18.6
+// and 17.0 (short ranges: 8 KB blocks leave waves idle in the V pass, 19.4); one of 3790 rows 17.2 and 17.0.  512
+// sequences in one launch: see decode_whole.  A microbenchmark of the same reads reaches 7.0 TB/s, this 6.6 there.
 #include "common.hpp"
 
 #include <type_traits>
@@ -51,13 +51,39 @@ __device__ __forceinline__ float row_rotate(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 | N, 0xf, 0xf, false));
 }
 
+// Sums over the lanes that differ in bit 5 and, for rows of 16 lanes or fewer, 4 and 3 of the lane number, of N values per
+// lane, with half of the values left to each side of an exchange: an exchange adds two values at a time.  On return
+// x[0 .. kSumParts) are the sums of values kSumParts * part .. of the lane's `part`.
+template <int LANES, int N> constexpr int kSumParts = LANES == 32 ? N / 2 : N / 4;
+template <int LANES>
+__device__ __forceinline__ int sum_part(int lane) {
+  return LANES == 32 ? lane >> 5 : 2 * (lane >> 5) + ((lane >> 4) & 1);
+}
+template <int LANES, int N>
+__device__ __forceinline__ void sum_scatter(float (&x)[N]) {
+  auto add = [](const auto& r) { return __uint_as_float(r[0]) + __uint_as_float(r[1]); };
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i)
+    x[i] = add(__builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[i + N / 2]), false, false));
+  if constexpr (LANES <= 16)
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i)
+      x[i] = add(__builtin_amdgcn_permlane16_swap(__float_as_uint(x[i]), __float_as_uint(x[i + N / 4]), false, false));
+  if constexpr (LANES == 8)
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) x[i] += row_rotate<8>(x[i]);
+}
+
+// Lanes of a wave exchange values through LDS: a wave's LDS instructions run in order, so the compiler must keep theirs.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kMaxRange = kDecodeMaxRange;  // tokens whose logits the LDS buffer holds at a time
-#ifndef SHOTKV_DEC_V_UNROLL
-#define SHOTKV_DEC_V_UNROLL 4
-#endif
-constexpr int kVUnroll = SHOTKV_DEC_V_UNROLL;  // V rows a lane group has in flight
+constexpr int kBlockLoads = kDecodeBlockBytes / 1024;  // load instructions per block of rows
 
 // How a row lies across the lanes of the K pass.  A matrix step has 16 operand rows and 16 columns and four
 // k-slices of 16 bytes (lane / 16).  A's row holds piece `i % kPieces` of token `i / kPieces`, B's column
@@ -69,7 +95,7 @@ template <int ROW_BYTES> struct RowShape {
   static constexpr int kCols = 16 / kPieces;                        // query heads per matrix step
   static constexpr int kTokens = 16 / kPieces;                      // tokens per matrix step
   static constexpr int kLoads = ROW_BYTES * kTokens / (kWave * 16); // 1 KB loads per matrix step
-  static constexpr int kBlock = 8 * 1024 / ROW_BYTES;               // tokens a wave takes at a time (8 loads)
+  static constexpr int kBlock = kDecodeBlockBytes / ROW_BYTES;      // tokens a wave takes at a time
   static constexpr int kLanes = ROW_BYTES / 16;                     // lanes per row in the V pass
 };
 
@@ -116,14 +142,16 @@ template <> struct Widen<float> {
   }
 };
 
-template <typename T, int D, int G, bool PIECES>
-__global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_partial_kernel(
+// LONG: ranges of more than kMaxRange tokens, taken in pieces of about as many.  whole (LONG only): the range is all of a
+// sequence; the workgroup writes the attention output itself and, to z_dec, one partial score per slot and KV head.
+template <typename T, int D, int G, bool LONG>
+__global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_partial_kernel(
     const char* __restrict__ k_prefill, const char* __restrict__ v_prefill,
     const int32_t* __restrict__ prefill_count, char* __restrict__ k_dec, char* __restrict__ v_dec,
     const int32_t* __restrict__ slot_pos, int cap, int n_slots, int H, int H_kv, int n_group,
     int n_splits, int split_tokens, int ahead_slots, float scale_log2e, const char* __restrict__ q_new,
     const char* __restrict__ k_new, const char* __restrict__ v_new, float2* __restrict__ part_ml,
-    float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out) {
+    float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out, bool whole) {
   constexpr int kRow = D * static_cast<int>(sizeof(T));  // bytes per row
   typedef RowShape<kRow> S;
   constexpr int E = Widen<T>::kElems;
@@ -131,17 +159,18 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
-  constexpr int kGroups = kThreads / S::kLanes;  // V rows the workgroup takes at a time
-  constexpr int kBatchRows = kGroups * kVUnroll;
-  static_assert(kBatchRows % S::kBlock == 0, "row counts padded to V batches are whole K blocks");
-  // logits, then weights: the live prefill rows of a piece, then its slots, each padded to whole V batches
-  __shared__ __attribute__((aligned(16))) float zbuf[kMaxRange + 2 * kBatchRows][G];
+  constexpr int kRowsPerLoad = kWave / S::kLanes;  // V rows of one load instruction
+  static_assert(kRowsPerLoad * kBlockLoads == S::kBlock && kBlockLoads % S::kLoads == 0, "whole loads and steps");
+  // A wave's logits, then its weights, then its output sums: the blocks of a piece - its live prefill rows, then its
+  // slots, each padded to whole blocks - are dealt to the waves in turn.
+  constexpr int kMapRows = decode_map_rows(kRow), kOwnRows = kMapRows / kWaves;
+  static_assert(kWaves == 4 && kOwnRows % S::kBlock == 0, "whole blocks for four waves");
+  __shared__ __attribute__((aligned(16))) float zbuf[kWaves][kOwnRows][G];
   __shared__ float s_max[kWaves][G];
   __shared__ float s_sum[kWaves][G];
-  float (*s_o)[G][D] = reinterpret_cast<float (*)[G][D]>(&zbuf[0][0]);  // the waves' output sums, after the weights
-  static_assert(kWaves * D <= kMaxRange, "output sums fit");
+  static_assert(D <= kOwnRows, "output sums fit");
   __shared__ int s_red[2][kWaves];
-  __shared__ int s_sp[kMaxRange];  // slot map of the decode slots of the piece
+  __shared__ int s_sp[kMapRows + S::kBlock];  // slot map of the decode slots of the piece, and what nothing depends on
 
   // G is the group size rounded up to a power of two; heads past the real n_group are zero queries
   // whose results are never written
@@ -178,34 +207,41 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
   const char* kn = k_new + plane * kRow;
   const char* vn = v_new + plane * kRow;
 
-  // ---- K rows: block [row0, row0 + kBlock) of the `rows` rows that start at `base`.  Rows past the end re-read
-  // the last one, so every address stays inside the plane; their logits are not used. --------------------------
-  constexpr int kStepsPerBlock = 8 / S::kLoads;
-  Vec kraw[8];
-  auto load_block = [&](const char* base, int row0, int rows) __attribute__((always_inline)) {
-    const char* at = base + static_cast<size_t>(row0) * kRow;
+  // ---- K rows: block [row0, row0 + kBlock) of the `rows` rows that start at `base`.  For rows past the end the buffer's
+  // bounds check returns zeros; their logits are not used. ------------------------------------------------------------
+  constexpr int kStepsPerBlock = kBlockLoads / S::kLoads;
+  Vec kraw[2][kBlockLoads];  // the wave's next two blocks
+  auto load_block = [&](const char* base, int row0, int rows, Vec (&raw)[kBlockLoads]) __attribute__((always_inline)) {
+    char* at = const_cast<char*>(base) + static_cast<size_t>(row0) * kRow;
+    // (a block may lie behind the last row: never a negative size, which would be an unbounded one)
+    const auto block = __builtin_amdgcn_make_buffer_rsrc(at, 0, min(max(rows - row0, 0), S::kBlock) * kRow, kBufferFlags);
+    int off = tau * kRow + a_off;
+    asm("" : "+v"(off));
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t r = min((i / S::kLoads) * S::kTokens + tau, rows - 1 - row0);
-      kraw[i] = stream_load<Vec>(at + (r * kRow + (i % S::kLoads) * 256 + a_off));
-    }
+    for (int i = 0; i < kBlockLoads; ++i)
+      raw[i] = __builtin_bit_cast(
+          Vec, __builtin_amdgcn_raw_buffer_load_b128(
+                   block, off + (i / S::kLoads) * S::kTokens * kRow + (i % S::kLoads) * 256, 0, kNonTemporal));
   };
-  // A wave's first block is requested before the count of live rows has arrived (dead rows may hold anything).
+  // A wave's first blocks are requested before the count of live rows has arrived (dead rows may hold anything).
   const int early_rows = min(range_end, cap) - range_begin;
-  if (wave * S::kBlock < early_rows) load_block(kp + static_cast<size_t>(range_begin) * kRow, wave * S::kBlock, early_rows);
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    if ((wave + j * kWaves) * S::kBlock < early_rows)
+      load_block(kp + static_cast<size_t>(range_begin) * kRow, (wave + j * kWaves) * S::kBlock, early_rows, kraw[j]);
   // Only a range that reaches into the decode slots needs the slot that takes the new token, the lowest free
   // one, and the slot map of its (first) piece with the last occupied slot of it (a pool that is still filling
   // up is empty behind that); all come out of one round of loads.
-  // A range of nothing but slots does not wait for the map with a wave's first K block if that begins among the first
-  // ahead_slots slots (ahead_of_map); the whole block is requested, and a wave whose block was not requested asks for it
+  // A range of nothing but slots does not wait for the map with a wave's first K blocks if they begin among the first
+  // ahead_slots slots (ahead_of_map); whole blocks are requested, and a wave whose block was not requested asks for it
   // when the map is there.  A free slot may hold anything: its logits are not used, and the new token's row replaces what
   // its slot held.
-  const bool early = !PIECES && range_begin >= cap &&
-                     wave * S::kBlock < min(range_end - range_begin, ahead_slots - (range_begin - cap));
+  const int early_slots =
+      !LONG && range_begin >= cap ? min(range_end - range_begin, ahead_slots - (range_begin - cap)) : 0;
   int new_slot = n_slots, last_used = -1;
   if (range_end > cap) {
     constexpr int kBatch = 8;  // loads in flight per thread
-    const int d_lo = max(range_begin - cap, 0), d_hi = min(range_begin + kMaxRange, range_end) - cap;
+    const int d_lo = max(range_begin - cap, 0), d_hi = range_end - cap;
     int best = INT32_MAX;
     int pos[kBatch];
     auto load_map = [&](int i0) __attribute__((always_inline)) {
@@ -213,8 +249,11 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
       for (int j = 0; j < kBatch; ++j) pos[j] = sp[min(i0 + j * kThreads, n_slots - 1)];
     };
     load_map(tid);
-    if (early)  // behind the map, as loads return in order
-      load_block(kd + static_cast<size_t>(range_begin - cap) * kRow, wave * S::kBlock, range_end - range_begin);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if ((wave + j * kWaves) * S::kBlock < early_slots)  // behind the map, as loads return in order
+        load_block(kd + static_cast<size_t>(range_begin - cap) * kRow, (wave + j * kWaves) * S::kBlock,
+                   range_end - range_begin, kraw[j]);
 #pragma clang loop unroll(disable)
     for (int i0 = tid; i0 < n_slots && (best == INT32_MAX || i0 < d_hi); i0 += kBatch * kThreads) {
       if (i0 != tid) load_map(i0);
@@ -223,7 +262,7 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
         const int i = min(i0 + j * kThreads, n_slots - 1);
         if (pos[j] < 0) best = min(best, i);
         if (i >= d_lo && i < d_hi) {
-          s_sp[i - d_lo] = pos[j];
+          if (!LONG || i - d_lo < kMapRows) s_sp[i - d_lo] = pos[j];
           if (pos[j] >= 0) last_used = max(last_used, i);
         }
       }
@@ -243,65 +282,70 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
   }
   if (range_end == cap + n_slots && g == 0 && tid == 0) new_slot_out[s] = new_slot;
 
-  const int grp = tid / S::kLanes, v_off = 16 * (tid % S::kLanes);
-  float o[G][E], M[G], L[G];  // L: this thread's share of the sum of weights
+  float (*zown)[G] = zbuf[wave];
+  // Of this wave's tokens: the largest logits, this lane's share of the sums of weights, and its part of the output sums,
+  // elements kOwnSums * sum_part() .. of the [G][E] that lanes of the same columns hold together.
+  constexpr int kOwnSums = kSumParts<S::kLanes, G * E>;
+  float M[G], L[G], sums[kOwnSums];
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    M[h] = -INFINITY;
-    L[h] = 0.f;
+  for (int h = 0; h < G; ++h) { M[h] = -INFINITY; L[h] = 0.f; }
 #pragma unroll
-    for (int e = 0; e < E; ++e) o[h][e] = 0.f;
-  }
+  for (int j = 0; j < kOwnSums; ++j) sums[j] = 0.f;
 
-  // The range is taken in pieces that the logit buffer holds.  Only contexts of over a million tokens have more
-  // than one (PIECES); a loop around the body costs the others registers for what the compiler moves out of it, and
-  // this form has the register budget of two waves per SIMD for the same reason: 1.2 million rows, 32 query / 8 KV
-  // heads, 1288 us with four (spills), 879 with three, 809 with two; 28 / 4 heads 969, 969 and 490; 16 / 4 at
-  // head_dim 64 497, 282 and 240.
-  const int n_pieces = PIECES ? ceil_div(range_end - range_begin, kMaxRange) : range_end > range_begin;
-  if (new_slot >= 0)
+  const int n_p = max(min(range_end, pc) - range_begin, 0);  // live prefill rows of the range
+  const int d_lo = max(range_begin - cap, 0);                // its decode slots: [d_lo, d_lo + n_d)
+  const int n_d = max(min(range_end - cap, last_used + 1) - d_lo, 0);
+  const int new_row = new_slot >= d_lo && new_slot < d_lo + n_d ? new_slot - d_lo : -1;  // the new token's, if inside
+  const char* kp0 = kp + static_cast<size_t>(range_begin) * kRow;
+  const char* vp0 = vp + static_cast<size_t>(range_begin) * kRow;
+  char* kd0 = kd + static_cast<size_t>(d_lo) * kRow;
+  char* vd0 = vd + static_cast<size_t>(d_lo) * kRow;
+  // The blocks of the range: prefill rows, then slots; dealt to the waves in turn.  The slots of a whole sequence start a
+  // piece of their own, so that their weights are all still there when the sums are known.
+  int nb_p = ceil_div(n_p, S::kBlock);
+  if (LONG && whole) nb_p = ceil_div(nb_p, kWaves) * kWaves;
+  const int n_blk = new_slot >= 0 ? nb_p + ceil_div(n_d, S::kBlock) : 0;
+  int b0 = 0, b1 = 0, map0 = 0;  // the blocks of the piece, the first slot of the slot map
+  if (n_blk > 0)
 #pragma clang loop unroll(disable)
-    for (int piece = 0; piece < n_pieces; ++piece) {
-      const bool first = !PIECES || piece == 0;
-      const int t_begin = PIECES ? range_begin + piece * kMaxRange : range_begin;
-      const int t_end = PIECES ? min(range_end, t_begin + kMaxRange) : range_end;
-      const int n_p = max(min(t_end, pc) - t_begin, 0);         // live prefill rows of the piece
-      const int d_lo = max(t_begin - cap, 0);                   // its decode slots: [d_lo, d_lo + n_d)
-      const int n_d = max((first ? min(t_end - cap, last_used + 1) : t_end - cap) - d_lo, 0);
-      const int new_row = new_slot >= d_lo && new_slot < d_lo + n_d ? new_slot - d_lo : -1;  // the new token's, if inside
-      if (!first) {
-        __syncthreads();  // the previous piece's weights and slot map are done with
-        for (int i = tid; i < n_d; i += kThreads) s_sp[i] = sp[d_lo + i];
+    for (;; b0 = b1) {
+      const bool first = !LONG || b0 == 0;
+      // In a loop the compiler keeps what it can derive from the lane number in registers through it: made anew here.
+      int lane = threadIdx.x % kWave;
+      if (LONG) asm volatile("" : "+v"(lane));
+      const int i16 = lane & 15, ksl = lane >> 4, tau = i16 / S::kPieces;
+      const int col_piece = i16 / S::kCols, col_head = i16 % S::kCols, a_off = 64 * (i16 % S::kPieces) + 16 * ksl;
+      const int grp = lane / S::kLanes, v_off = 16 * (lane % S::kLanes);
+      b1 = n_blk;
+      if (LONG) b1 = min(b1, b0 < nb_p && whole ? min(b0 + kWaves * kOwnRows / S::kBlock, nb_p) : b0 + kWaves * kOwnRows / S::kBlock);
+      if (LONG && n_d > kMapRows) {
+        __syncthreads();  // the previous piece's slot map is done with
+        map0 = max(b0 - nb_p, 0) * S::kBlock;
+        for (int i = tid; i < kMapRows; i += kThreads)
+          if (map0 + i < n_d) s_sp[i] = sp[d_lo + map0 + i];
         __syncthreads();
       }
-      const char* kp0 = kp + static_cast<size_t>(t_begin) * kRow;
-      const char* vp0 = vp + static_cast<size_t>(t_begin) * kRow;
-      char* kd0 = kd + static_cast<size_t>(d_lo) * kRow;
-      char* vd0 = vd + static_cast<size_t>(d_lo) * kRow;
       auto slot_used = [&](int i) __attribute__((always_inline)) {
-        return (i == new_row || s_sp[min(i, kMaxRange - 1)] >= 0) && i < n_d;
+        return (i == new_row || s_sp[i - map0] >= 0) && i < n_d;
       };
 
       // ---- pass 1: logits --------------------------------------------------------------------------------
-      const int z_d = ceil_div(n_p, kBatchRows) * kBatchRows;  // first entry of the slots in zbuf
-      const int nb_p = ceil_div(n_p, S::kBlock), n_blk = nb_p + ceil_div(n_d, S::kBlock);
       float mx[kHeadSets];  // largest logit this lane has seen, of head col_head + kCols * m
 #pragma unroll
       for (int m = 0; m < kHeadSets; ++m) mx[m] = -INFINITY;
-      auto append = [&](int row0) __attribute__((always_inline)) {  // only this workgroup reads the slot this step
-        if (new_row >= row0 && new_row < row0 + S::kBlock) {
+      auto append = [&](int row0, Vec (&raw)[kBlockLoads]) __attribute__((always_inline)) {
+        if (new_row >= row0 && new_row < row0 + S::kBlock) {  // only this workgroup reads the slot this step
 #pragma unroll
-          for (int i = 0; i < 8; ++i)
+          for (int i = 0; i < kBlockLoads; ++i)
             if (row0 + (i / S::kLoads) * S::kTokens + tau == new_row) {
-              kraw[i] = stream_load<Vec>(kn + (i % S::kLoads) * 256 + a_off);
-              *reinterpret_cast<Vec*>(kd0 + static_cast<size_t>(new_row) * kRow + (i % S::kLoads) * 256 + a_off) =
-                  kraw[i];
+              raw[i] = stream_load<Vec>(kn + (i % S::kLoads) * 256 + a_off);
+              *reinterpret_cast<Vec*>(kd0 + static_cast<size_t>(new_row) * kRow + (i % S::kLoads) * 256 + a_off) = raw[i];
             }
         }
       };
-      auto fetch = [&](int blk) __attribute__((always_inline)) {
+      auto fetch = [&](int blk, Vec (&raw)[kBlockLoads]) __attribute__((always_inline)) {
         if (blk < nb_p) {
-          load_block(kp0, blk * S::kBlock, n_p);
+          load_block(kp0, blk * S::kBlock, n_p, raw);
           return;
         }
         // A slot without a token is given an offset out of bounds, so it is zeros and costs no traffic, as in the V pass
@@ -309,23 +353,27 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
         // block requested ahead of the map has its free slots fetched.
         const int row0 = (blk - nb_p) * S::kBlock;
         char* at = kd0 + static_cast<size_t>(row0) * kRow;
-        const auto rows = __builtin_amdgcn_make_buffer_rsrc(at, 0, (n_d - row0) * kRow, kBufferFlags);
+        const auto rows =
+            __builtin_amdgcn_make_buffer_rsrc(at, 0, min(max(n_d - row0, 0), S::kBlock) * kRow, kBufferFlags);
+        const int* map = s_sp + (row0 - map0) + tau;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int r = (i / S::kLoads) * S::kTokens + tau;
-          const bool used = s_sp[min(row0 + r, kMaxRange - 1)] >= 0;
-          const int off = used ? r * kRow + (i % S::kLoads) * 256 + a_off : kOutOfBounds;
-          kraw[i] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, kNonTemporal));
+        for (int i = 0; i < kBlockLoads; ++i) {
+          const bool used = map[(i / S::kLoads) * S::kTokens] >= 0;
+          int off = used ? tau * kRow + a_off : kOutOfBounds;
+          asm("" : "+v"(off));  // the constant goes into the instruction, not into both sides of the choice
+          raw[i] = __builtin_bit_cast(
+              Vec, __builtin_amdgcn_raw_buffer_load_b128(
+                       rows, off + (i / S::kLoads) * S::kTokens * kRow + (i % S::kLoads) * 256, 0, kNonTemporal));
         }
-        append(row0);
+        append(row0, raw);
       };
-      // Logits of the block in kraw to zbuf[z0..]; counts(row, z): what the row at z0 + row adds to the maximum.
-      auto multiply_block = [&](int z0, auto counts) __attribute__((always_inline)) {
+      // Logits of a block to zown[z0..]; counts(row, z): what the row at z0 + row adds to the maximum.
+      auto multiply_block = [&](int z0, const Vec (&raw)[kBlockLoads], auto counts) __attribute__((always_inline)) {
 #pragma unroll
         for (int st = 0; st < kStepsPerBlock; ++st) {
 #pragma unroll
           for (int m = 0; m < kHeadSets; ++m) {
-            const floatx4 acc = multiply_step<S::kLoads>(&kraw[st * S::kLoads], bq[m]);
+            const floatx4 acc = multiply_step<S::kLoads>(&raw[st * S::kLoads], bq[m]);
             const int hq = col_head + S::kCols * m;
             // this lane's column holds piece col_piece; rows 4*ksl + v are (token, piece) pairs
             constexpr int kOwn = 4 / S::kPieces;  // tokens among a lane's four rows
@@ -342,89 +390,106 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
               z *= scale_log2e;
               const int row = st * S::kTokens + kOwn * ksl + i;
               mx[m] = fmaxf(mx[m], counts(row, z));
-              if (i16 < S::kCols && hq < G) zbuf[z0 + row][hq] = z;
+              if (i16 < S::kCols && hq < G) zown[z0 + row][hq] = z;
             }
           }
         }
       };
-      auto use_block = [&](int blk) __attribute__((always_inline)) {
+      auto use_block = [&](int blk, const Vec (&raw)[kBlockLoads]) __attribute__((always_inline)) {
+        const int z0 = (blk - b0) / kWaves * S::kBlock;
         if (blk < nb_p) {
           // (a first block that was requested early holds dead rows behind the live ones)
           const int live = n_p - blk * S::kBlock;
-          multiply_block(blk * S::kBlock, [&](int row, float z) { return row < live ? z : -INFINITY; });
+          multiply_block(z0, raw, [&](int row, float z) { return row < live ? z : -INFINITY; });
         } else {
           const int row0 = (blk - nb_p) * S::kBlock;
-          multiply_block(z_d + row0, [&](int row, float z) { return slot_used(row0 + row) ? z : -INFINITY; });
+          multiply_block(z0, raw, [&](int row, float z) { return slot_used(row0 + row) ? z : -INFINITY; });
         }
       };
-      int blk = wave;
-      // the wave's first block: of the first piece it is there already if it lies among the live rows, or was requested
-      // ahead of the slot map
-      if (blk < n_blk) {
-        if (first && early) append(blk * S::kBlock);
-        else if (!(first && blk < nb_p)) fetch(blk);
+      // Two blocks are in flight or in use.  A wave's first two of the first piece are there already if they lie among the
+      // live rows, or were requested ahead of the slot map.
+      int blk = b0 + wave;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int b = blk + j * kWaves;
+        if (b >= b1) break;
+        if (first && b * S::kBlock < early_slots) append(b * S::kBlock, kraw[j]);
+        else if (!(first && b * S::kBlock < n_p)) fetch(b, kraw[j]);
       }
 #pragma clang loop unroll(disable)
-      for (; blk + kWaves < n_blk; blk += kWaves) {
-        use_block(blk);
-        fetch(blk + kWaves);
+      for (; blk + 2 * kWaves < b1; blk += 2 * kWaves) {
+        use_block(blk, kraw[0]);
+        fetch(blk + 2 * kWaves, kraw[0]);
+        use_block(blk + kWaves, kraw[1]);
+        if (blk + 3 * kWaves < b1) fetch(blk + 3 * kWaves, kraw[1]);
       }
 
-      // V rows b * kBatchRows + u * kGroups + grp of the piece's live prefill rows (b < nv_p) or slots; for rows past
-      // the end the buffer's bounds check returns zeros, at the price of a descriptor (a live row in their place, read
+      // V rows of block b, a live prefill row or slot each; for rows past the end the buffer's bounds
+      // check returns zeros, at the price of a descriptor (a live row in their place, read
       // again, could be infinite: zero times that; 16 caches of 5121 rows 68.8 us that way, 69.4 like this, 70.8 with
       // the rows cleared after the load)
-      const int nv_p = ceil_div(n_p, kBatchRows), n_v = nv_p + ceil_div(n_d, kBatchRows);
-      u32x4 vraw[2][kVUnroll];
-      auto load_rows = [&](int b, u32x4 (&raw)[kVUnroll]) __attribute__((always_inline)) {
-        const bool in_p = b < nv_p;
-        const int row0 = (in_p ? b : b - nv_p) * kBatchRows;
+      u32x4 vraw[2][kBlockLoads];
+      auto load_rows = [&](int b, u32x4 (&raw)[kBlockLoads]) __attribute__((always_inline)) {
+        const bool in_p = b < nb_p;
+        const int row0 = (in_p ? b : b - nb_p) * S::kBlock;
         char* at = const_cast<char*>(in_p ? vp0 : vd0) + static_cast<size_t>(row0) * kRow;
-        const auto rows = __builtin_amdgcn_make_buffer_rsrc(at, 0, ((in_p ? n_p : n_d) - row0) * kRow, kBufferFlags);
+        const int left = b < b1 ? min(max((in_p ? n_p : n_d) - row0, 0), S::kBlock) : 0;
+        const auto rows = __builtin_amdgcn_make_buffer_rsrc(at, 0, left * kRow, kBufferFlags);
+        const int* map = s_sp + (in_p ? 0 : min(row0 - map0, kMapRows)) + grp;
 #pragma unroll
-        for (int u = 0; u < kVUnroll; ++u) {
-          int off = (u * kGroups + grp) * kRow + v_off;
-          if (!in_p && s_sp[min(row0 + u * kGroups + grp, kMaxRange - 1)] < 0) off = kOutOfBounds;
-          raw[u] = __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, kNonTemporal);
+        for (int u = 0; u < kBlockLoads; ++u) {
+          const bool used = in_p | (map[u * kRowsPerLoad] >= 0);  // (no branch: the sums before would move behind it)
+          int off = used ? grp * kRow + v_off : kOutOfBounds;
+          asm("" : "+v"(off));
+          raw[u] = __builtin_amdgcn_raw_buffer_load_b128(rows, off + u * kRowsPerLoad * kRow, 0, kNonTemporal);
         }
       };
-      if (n_v > 0) load_rows(0, vraw[0]);  // in flight while the last logits and the weights are computed
-      if (blk < n_blk) use_block(blk);
+      const int new_blk = nb_p + new_row / S::kBlock;
+      const bool takes_new = new_row >= 0 && new_blk % kWaves == wave && (!LONG || (new_blk >= b0 && new_blk < b1));
+      u32x4 v_of_new = {0u, 0u, 0u, 0u};
+      if (takes_new) v_of_new = stream_load<u32x4>(vn + v_off);
+      // in flight while the last logits and the weights are computed
+      if (blk < b1) {
+        load_rows(b0 + wave, vraw[0]);
+        use_block(blk, kraw[0]);
+        if (blk + kWaves < b1) use_block(blk + kWaves, kraw[1]);
+      }
 
       // ---- between the passes: maximum, weights and their sum -----------------------------------------
-#pragma unroll
-      for (int m = 0; m < kHeadSets; ++m) {
-        // lanes 16, 32 and 48 away hold other tokens of the same head (and so do, redundantly, the other pieces)
-        const float w = max_across_halves(mx[m]);
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w), __float_as_uint(w), false, false);
-        const float wm = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-        const int hq = col_head + S::kCols * m;
-        if (lane < S::kCols && hq < G) s_max[wave][hq] = wm;
-      }
-      __syncthreads();
-      float ref[G];
+      // Every wave takes the values of the tokens whose logits it took, so no wave waits for another one here: the exchange
+      // through LDS is between lanes, in the order of a wave's instructions.
+      wave_lds_fence();
+      float ref[G], alpha[G];
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        float m_new = M[h];
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) m_new = fmaxf(m_new, s_max[w][h]);
-        if (!first) {  // a later piece: what the earlier ones gave moves to the new maximum
-          const float alpha = M[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M[h] - m_new);
-          L[h] *= alpha;
-#pragma unroll
-          for (int e = 0; e < E; ++e) o[h][e] *= alpha;
+        // lanes 16, 32 and 48 away hold other tokens of the same head (and so do, redundantly, the other pieces)
+        const int m = h / S::kCols;
+        if (h % S::kCols == 0) {
+          const float w = max_across_halves(mx[m]);
+          const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w), __float_as_uint(w), false, false);
+          mx[m] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        }
+        // (rounded up to a whole number: what moves sums from one reference to another is then a power of two, and exact)
+        const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx[m]), h % S::kCols));
+        const float m_new = fmaxf(M[h], ceilf(w));
+        alpha[h] = 0.f;
+        if (LONG && M[h] != -INFINITY) {  // what earlier pieces gave moves to the new maximum
+          alpha[h] = __builtin_amdgcn_exp2f(M[h] - m_new);
+          L[h] *= alpha[h];
         }
         M[h] = m_new;
         ref[h] = m_new == -INFINITY ? 0.f : m_new;
       }
+      const int own_rows = b0 + wave < b1 ? ((b1 - 1 - b0 - wave) / kWaves + 1) * S::kBlock : 0;
 #pragma clang loop unroll(disable)
-      for (int tt = tid; tt < n_v * kBatchRows; tt += kThreads) {
-        const int slot = tt - z_d;
-        const bool valid = slot < 0 ? tt < n_p : slot_used(slot);
+      for (int t = lane; t < own_rows; t += kWave) {
+        const int b = b0 + wave + t / S::kBlock * kWaves, row = b * S::kBlock + t % S::kBlock;
+        const int slot = row - nb_p * S::kBlock;
+        const bool valid = slot < 0 ? row < n_p : slot_used(slot);
         float z[G];
 #pragma unroll
-        for (int h = 0; h < G; ++h) z[h] = zbuf[tt][h];
-        if (slot >= 0 && valid) {
+        for (int h = 0; h < G; ++h) z[h] = zown[t][h];
+        if (slot >= 0 && valid && !(LONG && whole)) {
 #pragma unroll
           for (int h = 0; h < G; ++h)
             if (h < n_group) z_dec[(head0 + h) * n_slots + (d_lo + slot)] = z[h];
@@ -432,82 +497,127 @@ __global__ __launch_bounds__(kThreads, PIECES ? 2 : G == 8 ? 3 : 4) void decode_
 #pragma unroll
         for (int h = 0; h < G; ++h) {
           const float p = valid ? __builtin_amdgcn_exp2f(z[h] - ref[h]) : 0.f;
-          zbuf[tt][h] = p;
+          zown[t][h] = p;
           L[h] += p;
         }
       }
-      __syncthreads();
+      wave_lds_fence();
 
       // ---- pass 2: weighted values -----------------------------------------------------------------------
-      auto use_rows = [&](int b, u32x4 (&raw)[kVUnroll]) __attribute__((always_inline)) {
-        if (b >= nv_p) {
+      if (LONG) {
+        const int part = sum_part<S::kLanes>(lane);
 #pragma unroll
-          for (int u = 0; u < kVUnroll; ++u) {
-            const int row = (b - nv_p) * kBatchRows + u * kGroups + grp;
-            // the slot taking the new token: its value row is appended whatever weight the token got
-            if (row == new_row) {
-              raw[u] = stream_load<u32x4>(vn + v_off);
-              *reinterpret_cast<u32x4*>(vd0 + static_cast<size_t>(row) * kRow + v_off) = raw[u];
-            }
-          }
+        for (int j = 0; j < kOwnSums; ++j) {
+          float a = alpha[j / E];
+#pragma unroll
+          for (int q = 1; q * kOwnSums < G * E; ++q) a = part == q ? alpha[(q * kOwnSums + j) / E] : a;
+          sums[j] *= a;
         }
+      }
+      float o[G * E];
 #pragma unroll
-        for (int u = 0; u < kVUnroll; ++u) {
+      for (int i = 0; i < G * E; ++i) o[i] = 0.f;
+      auto use_rows = [&](int b, const u32x4 (&raw)[kBlockLoads]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kBlockLoads; ++u) {
           float vf[E];
           Widen<T>::get(raw[u], vf);
 #pragma unroll
           for (int h = 0; h < G; ++h) {
-            const float p = zbuf[b * kBatchRows + u * kGroups + grp][h];
+            const float p = zown[(b - b0) / kWaves * S::kBlock + u * kRowsPerLoad + grp][h];
 #pragma unroll
-            for (int e = 0; e < E; ++e) o[h][e] = fmaf(p, vf[e], o[h][e]);
+            for (int e = 0; e < E; ++e) o[h * E + e] = fmaf(p, vf[e], o[h * E + e]);
           }
         }
       };
 #pragma clang loop unroll(disable)
-      for (int b = 0; b < n_v; b += 2) {
-        if (b + 1 < n_v) load_rows(b + 1, vraw[1]);
-        use_rows(b, vraw[0]);
-        if (b + 1 >= n_v) break;
-        if (b + 2 < n_v) load_rows(b + 2, vraw[0]);
-        use_rows(b + 1, vraw[1]);
+      for (blk = b0 + wave; blk + kWaves < b1; blk += 2 * kWaves) {  // (a way out in its middle would copy the sums)
+        load_rows(blk + kWaves, vraw[1]);
+        use_rows(blk, vraw[0]);
+        load_rows(blk + 2 * kWaves, vraw[0]);
+        use_rows(blk + kWaves, vraw[1]);
       }
-      if (!PIECES) break;
+      if (blk < b1) use_rows(blk, vraw[0]);
+      // The slot taking the new token was free, so it came as zeros: its value row is appended, whatever weight the token
+      // got, and added here.
+      if (takes_new && grp == 0) {
+        *reinterpret_cast<u32x4*>(vd0 + static_cast<size_t>(new_row) * kRow + v_off) = v_of_new;
+        float vf[E];
+        Widen<T>::get(v_of_new, vf);
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          const float p = zown[(new_blk - b0) / kWaves * S::kBlock + new_row % S::kBlock][h];
+#pragma unroll
+          for (int e = 0; e < E; ++e) o[h * E + e] = fmaf(p, vf[e], o[h * E + e]);
+        }
+      }
+      sum_scatter<S::kLanes>(o);
+#pragma unroll
+      for (int j = 0; j < kOwnSums; ++j) sums[j] += o[j];
+      if (!LONG || b1 == n_blk) break;
     }
 
-  // sum over the row groups of a wave, then over the waves
+  // Sums over the waves, each with a maximum of its own.
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if constexpr (S::kLanes == 8) o[h][e] += row_rotate<8>(o[h][e]);
-      if constexpr (S::kLanes <= 16) o[h][e] = sum_across_row_pairs(o[h][e]);
-      o[h][e] = sum_across_halves(o[h][e]);
-    }
     const float l = wave_sum(L[h]);
-    if (lane == 0) s_sum[wave][h] = l;
+    if (lane == 0) { s_sum[wave][h] = l; s_max[wave][h] = M[h]; }
   }
-  __syncthreads();  // every wave is done with the weights
-  if (lane < S::kLanes) {
+  // of head h over all waves: maximum and sum of weights
+  auto merged = [&](int h, float& m, float& l) __attribute__((always_inline)) {
+    m = s_max[0][h];
 #pragma unroll
-    for (int h = 0; h < G; ++h)
+    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, s_max[w][h]);
+    l = 0.f;
 #pragma unroll
-      for (int e = 0; e < E; ++e) s_o[wave][h][lane * E + e] = o[h][e];
+    for (int w = 0; w < kWaves; ++w)
+      l = fmaf(s_sum[w][h], s_max[w][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_max[w][h] - m), l);
+  };
+  if (LONG && whole && n_d > 0) {
+    // the weights of the slots are those of the last piece: each wave's are scaled to the softmax and summed over the heads
+    __syncthreads();
+    float f[G];
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      float m, l;
+      merged(h, m, l);
+      f[h] = M[h] != -INFINITY ? __builtin_amdgcn_exp2f(M[h] - m) * (1.f / l) : 0.f;
+    }
+    for (int t = lane; t < kOwnRows; t += kWave) {
+      const int slot = (b0 - nb_p + wave + t / S::kBlock * kWaves) * S::kBlock + t % S::kBlock;
+      if (slot >= n_d) break;
+      float score = 0.f;
+#pragma unroll
+      for (int h = 0; h < G; ++h)
+        if (h < n_group) score = fmaf(zown[t][h], f[h], score);
+      z_dec[plane * n_slots + slot] = score;
+    }
+  }
+  wave_lds_fence();
+  float* s_o = &zown[0][0];  // [G][D], behind the weights
+  if (S::kLanes != 8 || (lane & 8) == 0) {
+#pragma unroll
+    for (int j = 0; j < kOwnSums; ++j) {
+      const int i = kOwnSums * sum_part<S::kLanes>(lane) + j;
+      s_o[i / E * D + lane % S::kLanes * E + i % E] = sums[j];
+    }
   }
   __syncthreads();
   for (int idx = tid; idx < G * D; idx += kThreads) {
     const int h = idx / D, dd = idx % D;
     if (h >= n_group) continue;
-    float acc = 0.f, l = 0.f;
+    float m, l;
+    merged(h, m, l);
+    float acc = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      acc += s_o[w][h][dd];
-      l += s_sum[w][h];
+    for (int w = 0; w < kWaves; ++w)
+      acc = fmaf((&zbuf[w][0][0])[idx], s_max[w][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_max[w][h] - m), acc);
+    if (LONG && whole) {
+      part_o[(head0 + h) * D + dd] = n_blk > 0 ? acc * (1.f / l) : 0.f;
+      continue;
     }
     const size_t r = (head0 + h) * n_splits + split;
     part_o[r * D + dd] = acc;
-    float m = M[0];
-#pragma unroll
-    for (int i = 1; i < G; ++i) m = i == h ? M[i] : m;
     if (dd == 0) part_ml[r] = make_float2(m, l);
   }
 }
@@ -532,20 +642,22 @@ static int ahead_of_map(const DecodeDims& d, int row_bytes) {
 
 template <typename T, int D>
 static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
-                                 const void* k_new, const void* v_new, const DecodeWorkspace& w, hipStream_t s) {
-  const dim3 grid(d.n_splits, d.H_kv, d.S), block(kThreads);
+                                 const void* k_new, const void* v_new, float* out, const DecodeWorkspace& w,
+                                 hipStream_t s) {
+  const int n_splits = decode_launch_splits(d), split_tokens = ceil_div(d.cap + d.n_slots, n_splits);
+  const dim3 grid(n_splits, d.H_kv, d.S), block(kThreads);
   const float c = d.sm_scale * kLog2e;
   const int ahead_slots = ahead_of_map(d, D * static_cast<int>(sizeof(T)));
   KernelTimer timer(d.timing, kKernelDecodePartial, s);
 #define SHOTKV_LAUNCH_DEC(GG)                                                                           \
-  auto* kernel = d.split_tokens > kMaxRange ? decode_partial_kernel<T, D, GG, true>                     \
-                                            : decode_partial_kernel<T, D, GG, false>;                   \
+  auto* kernel = split_tokens > kMaxRange || d.whole ? decode_partial_kernel<T, D, GG, true>            \
+                                                     : decode_partial_kernel<T, D, GG, false>;          \
   hipLaunchKernelGGL(kernel, grid, block, 0, s,                                                         \
                      static_cast<const char*>(st.k_prefill), static_cast<const char*>(st.v_prefill),    \
                      st.prefill_count, static_cast<char*>(st.k_dec), static_cast<char*>(st.v_dec),      \
-                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, d.n_splits, d.split_tokens, ahead_slots, c, \
+                     st.slot_pos, d.cap, d.n_slots, d.H, d.H_kv, d.G, n_splits, split_tokens, ahead_slots, c, \
                      static_cast<const char*>(q_new), static_cast<const char*>(k_new),                  \
-                     static_cast<const char*>(v_new), w.part_ml, w.part_o, w.z_dec, w.new_slot)
+                     static_cast<const char*>(v_new), w.part_ml, d.whole ? out : w.part_o, w.z_dec, w.new_slot, d.whole)
   switch (padded_group(d.G)) {  // the kernel is instantiated for power-of-two groups and skips the padding
     case 1: { SHOTKV_LAUNCH_DEC(1); break; }
     case 2: { SHOTKV_LAUNCH_DEC(2); break; }
@@ -558,14 +670,14 @@ static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state&
 }
 
 hipError_t launch_decode_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
-                                 const void* k_new, const void* v_new, const DecodeWorkspace& w,
+                                 const void* k_new, const void* v_new, float* out, const DecodeWorkspace& w,
                                  hipStream_t s) {
   if (d.dtype == SHOTKV_BF16) {
-    if (d.D == 128) return launch_partial<bf16_t, 128>(d, st, q_new, k_new, v_new, w, s);
-    if (d.D == 64) return launch_partial<bf16_t, 64>(d, st, q_new, k_new, v_new, w, s);
+    if (d.D == 128) return launch_partial<bf16_t, 128>(d, st, q_new, k_new, v_new, out, w, s);
+    if (d.D == 64) return launch_partial<bf16_t, 64>(d, st, q_new, k_new, v_new, out, w, s);
   } else {
-    if (d.D == 128) return launch_partial<float, 128>(d, st, q_new, k_new, v_new, w, s);
-    if (d.D == 64) return launch_partial<float, 64>(d, st, q_new, k_new, v_new, w, s);
+    if (d.D == 128) return launch_partial<float, 128>(d, st, q_new, k_new, v_new, out, w, s);
+    if (d.D == 64) return launch_partial<float, 64>(d, st, q_new, k_new, v_new, out, w, s);
   }
   return hipErrorInvalidValue;
 }

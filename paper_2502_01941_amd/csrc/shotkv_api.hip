@@ -265,6 +265,7 @@ static int make_decode_dims(const shotkv_config* cfg, int S, int cap, int n_slot
          carve_decode(nullptr, d->S, d->H, d->H_kv, d->D, n_slots, d->n_splits).bytes > SHOTKV_STATIC_SCRATCH_BYTES)
     --d->n_splits;
   d->split_tokens = ceil_div(total, d->n_splits);
+  d->whole = decode_whole(*d, row_bytes);
   return SHOTKV_OK;
 }
 
@@ -295,7 +296,7 @@ int shotkv_decode_step(const shotkv_config* cfg, int32_t S, const shotkv_decode_
   d.budget = st->decode_budget;
   d.step = step_index;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_decode_partial(d, *st, q_new, k_new, v_new, w, s);
+  hipError_t e = launch_decode_partial(d, *st, q_new, k_new, v_new, out, w, s);
   if (e == hipSuccess) e = launch_decode_finish(d, *st, out, token_scores, evicted_pos, status, w, s);
   return from_hip(e);
 }
