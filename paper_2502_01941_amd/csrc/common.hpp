@@ -206,6 +206,11 @@ hipError_t launch_reduce_select(const PrefillDims& d, bool with_mass, bool with_
                                 const int32_t* shot_offsets, const int32_t* budget_tokens, int cap,
                                 int32_t* kept_count, uint8_t* shot_selected, int32_t* status,
                                 int32_t* kept_positions, const PrefillWorkspace& w, hipStream_t s);
+// The selection and copy plan with the copies, in one launch or two.
+hipError_t launch_select_compact(const PrefillDims& d, bool with_mass, float* shot_scores, const int32_t* shot_offsets,
+                                 const int32_t* budget_tokens, const void* k, const void* v, void* k_out, void* v_out,
+                                 int cap, int32_t* kept_count, uint8_t* shot_selected, int32_t* status,
+                                 int32_t* kept_positions, const PrefillWorkspace& w, hipStream_t s);
 hipError_t launch_compact(const PrefillDims& d, const void* k, const void* v, void* k_out, void* v_out,
                           int cap, const int32_t* kept_positions, const int32_t* kept_count,
                           hipStream_t s);

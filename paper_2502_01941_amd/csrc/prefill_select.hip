@@ -14,7 +14,9 @@
 //             per merge level instead of one per compare-exchange step;
 //   plan      sums of kept lengths in position order give every retained row's output slot; the segments that keep
 //             tokens are numbered by the same pass, so that the original positions, written in ascending order, take a
-//             group of lanes for each of these and none for the others.
+//             group of lanes for each of these and none for the others;
+//   copies    where there are few, by as many workgroups as there are CUs, each of which does all of the above for itself
+//             (launch_select_compact); otherwise the positions go to the copying kernel.
 //
 // Bound by a chain of barriers and trips to memory in one workgroup.  Inside the kernel, sorting and walking the sums
 // against this: 40 shots 2.1 + 1.8 us and 0.6, 80 shots 3.4 + 1.5 and 1, 600 units 7.8 + 1.7 and 3.3 (the sort of 400
@@ -295,15 +297,28 @@ __device__ __forceinline__ float strided_sum(int n, int first, int width, Load w
   return sum;
 }
 
-template <bool MASS, bool SELECT>
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// The caches that a launch that copies as well reads and writes.
+struct CopyArgs {
+  const char* k;
+  const char* v;
+  char* k_out;
+  char* v_out;
+};
+
+// ROW_BYTES: bytes of a cache row where the workgroups of a problem (blockIdx.x) also copy a share of its rows each, 0
+// where they do not.  Each of them then makes the whole selection for itself; the first one writes it down.
+template <bool MASS, bool SELECT, int ROW_BYTES>
 __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     const float* __restrict__ chunk_mass, int max_c, int group_shift, int H_kv,
     float* __restrict__ shot_scores,
     const int32_t* __restrict__ shot_offsets, const int32_t* __restrict__ budget_tokens, int share,
     int n_shots, int n_tokens, int cap, int select_mode, int32_t* __restrict__ kept_count,
     uint8_t* __restrict__ shot_selected, int32_t* __restrict__ status,
-    int32_t* __restrict__ kept_positions) {
-  const int p = blockIdx.x, tid = threadIdx.x;
+    int32_t* __restrict__ kept_positions, CopyArgs copy) {
+  const int p = blockIdx.y, tid = threadIdx.x;
+  const bool writes = ROW_BYTES == 0 || blockIdx.x == 0;
   const int32_t* off_g = shot_offsets + static_cast<size_t>(p / share) * (n_shots + 1);
   float* scores = shot_scores + static_cast<size_t>(p) * n_shots;
 
@@ -389,7 +404,7 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     if (MASS) {
       if (!bad)
         my_score[j] = (width > 1 ? s_sum[i] : shot_sum(i, 0, 1)) / static_cast<float>(s_off[i + 1] - s_off[i]);
-      scores[i] = my_score[j];
+      if (writes) scores[i] = my_score[j];
     } else if (!bad) {
       my_score[j] = scores[i];
     }
@@ -410,6 +425,7 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     if (shot_budget < 0) st = SHOTKV_ST_BUDGET_TOO_SMALL;
   }
   if (st != SHOTKV_ST_OK) {
+    if (!writes) return;
     if (tid == 0) { status[p] = st; kept_count[p] = 0; }
     if (sel) for (int i = tid; i < n_shots; i += kSelThreads) sel[i] = 0;
     return;
@@ -524,7 +540,7 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
   }
   const int n_groups = kSelThreads / group_w, gid = tid / group_w, gl = tid % group_w;
   constexpr int kSegBatch = 4;  // segments whose LDS lookups are in flight together
-  for (int k0 = gid; k0 < n_kept; k0 += n_groups * kSegBatch) {
+  for (int k0 = gid; writes && k0 < n_kept; k0 += n_groups * kSegBatch) {
     int src[kSegBatch], len[kSegBatch], dst[kSegBatch];
 #pragma unroll
     for (int b = 0; b < kSegBatch; ++b) {
@@ -537,8 +553,47 @@ __global__ __launch_bounds__(kSelThreads) void reduce_select_kernel(
     for (int b = 0; b < kSegBatch; ++b)
       for (int i = gl; i < len[b]; i += group_w) kept_pos[dst[b] + i] = src[b] + i;
   }
-  if (sel) for (int i = tid; i < n_shots; i += kSelThreads) sel[i] = s_keep[i];
-  if (tid == 0) { status[p] = SHOTKV_ST_OK; kept_count[p] = total; }
+  if (sel && writes) for (int i = tid; i < n_shots; i += kSelThreads) sel[i] = s_keep[i];
+  if (tid == 0 && writes) { status[p] = SHOTKV_ST_OK; kept_count[p] = total; }
+
+  // ---- this workgroup's share of the retained rows, of all planes ---------------------------------
+  if constexpr (ROW_BYTES > 0) {
+    constexpr int kLanes = ROW_BYTES / 16, kTeams = kSelThreads / kLanes;
+    constexpr int kInFlight = 4;
+    int* s_src = s_a + SHOTKV_MAX_SHOTS + 8;  // tokens of the share's rows
+    static_assert(sizeof(uint64_t) * kKeySlots >= sizeof(int) * (SHOTKV_MAX_SHOTS + 8 + kSelThreads), "a share's rows fit");
+    const int share_rows = ceil_div(total, static_cast<int>(gridDim.x)), row0 = blockIdx.x * share_rows;
+    const int n_rows = min(share_rows, total - row0);  // at most one per thread
+    if (n_rows <= 0) return;
+    if (tid < n_rows) {
+      int lo = 0, hi = n_kept;  // the segment that the row lies in: s_a[lo] <= row < s_a[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (s_a[mid] <= row0 + tid) lo = mid;
+        else hi = mid;
+      }
+      s_src[tid] = segment_start(s_idx[lo]) + row0 + tid - s_a[lo];
+    }
+    __syncthreads();
+    const int lane16 = 16 * (tid % kLanes), n_items = n_rows * 2 * H_kv;  // an item is a row of a plane
+    const size_t plane0 = static_cast<size_t>(p) * H_kv;
+    for (int t0 = tid / kLanes; t0 < n_items; t0 += kTeams * kInFlight) {
+      u32x4 data[kInFlight];
+      char* dst[kInFlight];
+#pragma unroll
+      for (int j = 0; j < kInFlight; ++j) {
+        const int t = min(t0 + j * kTeams, n_items - 1), plane = t / n_rows, i = t - plane * n_rows;
+        const bool is_v = plane >= H_kv;
+        const size_t at = plane0 + (is_v ? plane - H_kv : plane);
+        const char* src = (is_v ? copy.v : copy.k) + (at * n_tokens + s_src[i]) * ROW_BYTES + lane16;
+        dst[j] = (is_v ? copy.v_out : copy.k_out) + (at * cap + row0 + i) * ROW_BYTES + lane16;
+        data[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src));
+      }
+#pragma unroll
+      for (int j = 0; j < kInFlight; ++j)
+        if (t0 + j * kTeams < n_items) __builtin_nontemporal_store(data[j], reinterpret_cast<u32x4*>(dst[j]));
+    }
+  }
 }
 
 }  // namespace
@@ -549,15 +604,53 @@ hipError_t launch_reduce_select(const PrefillDims& d, bool with_mass, bool with_
                                 int32_t* kept_positions, const PrefillWorkspace& w, hipStream_t s) {
   KernelTimer timer(d.timing, kKernelReduceSelect, s);
   const int group_shift = 31 - __builtin_clz(static_cast<unsigned>(w.group_keys));
-#define SHOTKV_LAUNCH_RS(M, S)                                                                          \
-  hipLaunchKernelGGL((reduce_select_kernel<M, S>), dim3(d.P), dim3(kSelThreads), 0, s, w.chunk_mass,    \
+#define SHOTKV_LAUNCH_RS(M, S, RB, WGS, COPY)                                                           \
+  hipLaunchKernelGGL((reduce_select_kernel<M, S, RB>), dim3(WGS, d.P), dim3(kSelThreads), 0, s, w.chunk_mass, \
                      w.max_c, group_shift, d.H_kv, shot_scores,                                         \
                      shot_offsets, budget_tokens, d.share, d.n_shots, d.n_tokens, cap, d.select_mode,   \
-                     kept_count, shot_selected, status, kept_positions)
-  if (with_mass && with_select) SHOTKV_LAUNCH_RS(true, true);
-  else if (with_mass) SHOTKV_LAUNCH_RS(true, false);
-  else if (with_select) SHOTKV_LAUNCH_RS(false, true);
+                     kept_count, shot_selected, status, kept_positions, COPY)
+  if (with_mass && with_select) SHOTKV_LAUNCH_RS(true, true, 0, 1, CopyArgs{});
+  else if (with_mass) SHOTKV_LAUNCH_RS(true, false, 0, 1, CopyArgs{});
+  else if (with_select) SHOTKV_LAUNCH_RS(false, true, 0, 1, CopyArgs{});
   else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_select_compact(const PrefillDims& d, bool with_mass, float* shot_scores, const int32_t* shot_offsets,
+                                 const int32_t* budget_tokens, const void* k, const void* v, void* k_out, void* v_out,
+                                 int cap, int32_t* kept_count, uint8_t* shot_selected, int32_t* status,
+                                 int32_t* kept_positions, const PrefillWorkspace& w, hipStream_t s) {
+  const int row_bytes = d.D * (d.dtype == SHOTKV_BF16 ? 2 : 4);
+  // Few rows: one launch, up to a workgroup per CU, each making the selection for itself and copying its share of the rows.
+  // It saves a launch and the way of the positions through memory, but copies of many rows want many small workgroups and
+  // the second workgroup of a CU slows the selections of both.  Whole calls, two launches and one, 8 KV heads, head_dim 128
+  // unless told otherwise, by bytes read and written: 7 MB (2000 tokens) 23 and 20.5 us, 10 MB 22 and 20.6, 27 MB (8192
+  // tokens, budget 3276) 25.6 and 23.7, with 128 workgroups 26.2, with 512 29; 54 MB 32.7 and 31.4; 33 MB as 64 problems
+  // 28.6 and 27.5; 2500 units 77 and 75; 64 MB 130 and 130.5 (600 units), 79 MB of fp32 54.6 and 54.5, 210 MB of head_dim 64
+  // 112 and 116, 322 MB 150 and 157.
+  constexpr int kMostWorkgroups = 256;
+  const int most_rows = min(cap, d.n_tokens), wgs = max(1, min(kMostWorkgroups / d.P, ceil_div(cap, 8)));
+  const long bytes = 4L * d.P * d.H_kv * most_rows * row_bytes;  // read and written
+  if (bytes > 48L << 20 || d.P > kMostWorkgroups || ceil_div(most_rows, wgs) > kSelThreads) {
+    const hipError_t e = launch_reduce_select(d, with_mass, true, shot_scores, shot_offsets, budget_tokens, cap, kept_count,
+                                              shot_selected, status, kept_positions, w, s);
+    return e != hipSuccess ? e : launch_compact(d, k, v, k_out, v_out, cap, kept_positions, kept_count, s);
+  }
+  { KernelTimer copy_timer(d.timing, kKernelCompact, s); }  // the copies are part of the same kernel
+  KernelTimer timer(d.timing, kKernelReduceSelect, s);
+  const int group_shift = 31 - __builtin_clz(static_cast<unsigned>(w.group_keys));
+  const CopyArgs copy = {static_cast<const char*>(k), static_cast<const char*>(v), static_cast<char*>(k_out),
+                         static_cast<char*>(v_out)};
+#define SHOTKV_LAUNCH_SC(RB)                                                 \
+  if (with_mass) SHOTKV_LAUNCH_RS(true, true, RB, wgs, copy);                \
+  else SHOTKV_LAUNCH_RS(false, true, RB, wgs, copy)
+  switch (row_bytes) {
+    case 128: SHOTKV_LAUNCH_SC(128); break;
+    case 256: SHOTKV_LAUNCH_SC(256); break;
+    case 512: SHOTKV_LAUNCH_SC(512); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef SHOTKV_LAUNCH_SC
 #undef SHOTKV_LAUNCH_RS
   return hipGetLastError();
 }

@@ -153,11 +153,8 @@ int shotkv_select_and_compact(const shotkv_config* cfg, int32_t P, int32_t n_tok
   const PrefillWorkspace w = carve(d, workspace);
   if (workspace_bytes < w.bytes) return SHOTKV_E_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_reduce_select(d, false, true, const_cast<float*>(shot_scores), shot_offsets,
-                                      budget_tokens, cap, kept_count, shot_selected, status, kept_positions,
-                                      w, s);
-  if (e == hipSuccess) e = launch_compact(d, k, v, k_out, v_out, cap, kept_positions, kept_count, s);
-  return from_hip(e);
+  return from_hip(launch_select_compact(d, false, const_cast<float*>(shot_scores), shot_offsets, budget_tokens, k, v, k_out,
+                                        v_out, cap, kept_count, shot_selected, status, kept_positions, w, s));
 }
 
 int shotkv_prefill_compress(const shotkv_config* cfg, int32_t P, int32_t n_tokens, int32_t n_shots,
@@ -183,9 +180,8 @@ int shotkv_prefill_compress(const shotkv_config* cfg, int32_t P, int32_t n_token
   hipError_t e = launch_score_partials(d, q_obs, k, shot_offsets, w, s);
   if (e == hipSuccess) e = launch_chunk_mass(d, d.R, w, s);
   if (e == hipSuccess)
-    e = launch_reduce_select(d, true, true, scores, shot_offsets, budget_tokens, cap, kept_count,
-                             shot_selected, status, kept_positions, w, s);
-  if (e == hipSuccess) e = launch_compact(d, k, v, k_out, v_out, cap, kept_positions, kept_count, s);
+    e = launch_select_compact(d, true, scores, shot_offsets, budget_tokens, k, v, k_out, v_out, cap, kept_count,
+                              shot_selected, status, kept_positions, w, s);
   return from_hip(e);
 }
 
@@ -236,9 +232,8 @@ int shotkv_prefill_attention_compress(const shotkv_config* cfg, int32_t P, int32
   if (e == hipSuccess) e = launch_attention_scores(d, q, k, w.vt, shot_offsets, attn_out, w, s);
   if (e == hipSuccess) e = launch_chunk_mass(d, d.R_rows, w, s);
   if (e == hipSuccess)
-    e = launch_reduce_select(d, true, true, scores, shot_offsets, budget_tokens, cap, kept_count,
-                             shot_selected, status, kept_positions, w, s);
-  if (e == hipSuccess) e = launch_compact(d, k, v, k_out, v_out, cap, kept_positions, kept_count, s);
+    e = launch_select_compact(d, true, scores, shot_offsets, budget_tokens, k, v, k_out, v_out, cap, kept_count,
+                              shot_selected, status, kept_positions, w, s);
   return from_hip(e);
 }
 
