@@ -395,88 +395,63 @@ __device__ __forceinline__ void weights_block(lds_cchar* lds_buf, lds_cchar* par
 }
 
 // Crediting the weights of a block to the chunks on either side of a boundary.  A lane holds key rows
-// 8*(v/4) + v%4 of the block (+4 in the upper lane half) in element v, in ascending order, and a boundary
-// is the same for the whole wave, so "element v lies in the interval" is one bit per lane half: the set
-// of a half's elements is a 16-bit scalar mask.  The adds then run under an execution mask made from bit
-// v of the two masks (s_bfe_i32 gives 0 or -1 for exec_lo / exec_hi): one vector add per weight and no
-// vector compares or selects.  Even and odd elements go to separate accumulators (two dependency chains).
-
-// elements of a lower-half lane whose row is below x, as a bit mask
-__device__ __forceinline__ uint32_t elements_below(int x) {
-  if (x <= 0) return 0u;
-  const int n = min(4 * (x >> 3) + min(x & 7, 4), 16);
-  return (1u << n) - 1u;
-}
-
-#define SHOTKV_MASKED_STEP2(V, ACC_A, ACC_B, XA, XB)                          \
-  "s_bfe_i32 exec_lo, %[s0], 0x1000" #V "\n\t"                                \
-  "s_bfe_i32 exec_hi, %[s1], 0x1000" #V "\n\t"                                \
+// 8*i + 4*half + v of the block in elements 4*i + v, so eight consecutive rows are four elements of both lane halves: a
+// group.  Groups without a boundary are added whole; in one with a boundary the elements of an interval are added under an
+// execution mask.  A boundary is the same for the whole wave, so "row r of the group lies in the interval" is bit r of a
+// scalar, rows 0..3 of it the lower lane half's and 4..7 the upper one's: s_bfe_i32 gives 0 or -1 for exec_lo / exec_hi,
+// and no vector compares or selects are needed.  The two scalar instructions per element are what masked adds cost: with
+// all sixteen elements masked for every interval a block with an end took 73 of them on average where units are 25 tokens,
+// and 20 so (and 26 vector adds instead of 36).  This kernel, 8 problems of 16384 tokens in 600 units, per KV head, 83.5
+// and 74.0 us; 16 x 16001 tokens of head_dim 64 in 80 units 75.1 and 71.4; whole calls, 16 x 8192 of head_dim 64 in units
+// of 6 tokens 177 and 150, 2 x 32768 in units of 15 108 and 101.  Weights of such a block against the carried reference,
+// without the block's maximum, are slower (sentences 142.9 and 145.5, head_dim 64 115 and 139).
+#define SHOTKV_MASKED_STEP2(V, U, ACC_A, ACC_B, XA, XB)                       \
+  "s_bfe_i32 exec_lo, %[m], 0x1000" #V "\n\t"                                \
+  "s_bfe_i32 exec_hi, %[m], 0x1000" #U "\n\t"                                \
   "v_add_f32 %[" #ACC_A "], %[" #ACC_A "], %[" #XA "]\n\t"                    \
   "v_add_f32 %[" #ACC_B "], %[" #ACC_B "], %[" #XB "]\n\t"
-#define SHOTKV_MASKED_STEP1(V, ACC_A, XA)                                     \
-  "s_bfe_i32 exec_lo, %[s0], 0x1000" #V "\n\t"                                \
-  "s_bfe_i32 exec_hi, %[s1], 0x1000" #V "\n\t"                                \
+#define SHOTKV_MASKED_STEP1(V, U, ACC_A, XA)                                  \
+  "s_bfe_i32 exec_lo, %[m], 0x1000" #V "\n\t"                                \
+  "s_bfe_i32 exec_hi, %[m], 0x1000" #U "\n\t"                                \
   "v_add_f32 %[" #ACC_A "], %[" #ACC_A "], %[" #XA "]\n\t"
 
-// elements 8*HALF .. 8*HALF+7 of two queries' weights; s0 / s1 already shifted so that bit i is element 8*HALF + i
-__device__ __forceinline__ void masked_add8(float& ae, float& ao, float& be, float& bo, float a0, float a1,
-                                            float a2, float a3, float a4, float a5, float a6, float a7,
-                                            float b0, float b1, float b2, float b3, float b4, float b5,
-                                            float b6, float b7, uint32_t s0, uint32_t s1) {
+// sums += the rows of a group that `rows` names
+__device__ __forceinline__ void masked_add4(float& a, float& b, float a0, float a1, float a2, float a3, float b0, float b1,
+                                            float b2, float b3, uint32_t rows) {
   uint64_t save;
   asm volatile("s_mov_b64 %[save], exec\n\t"
-               SHOTKV_MASKED_STEP2(0, ae, be, a0, b0) SHOTKV_MASKED_STEP2(1, ao, bo, a1, b1)
-               SHOTKV_MASKED_STEP2(2, ae, be, a2, b2) SHOTKV_MASKED_STEP2(3, ao, bo, a3, b3)
-               SHOTKV_MASKED_STEP2(4, ae, be, a4, b4) SHOTKV_MASKED_STEP2(5, ao, bo, a5, b5)
-               SHOTKV_MASKED_STEP2(6, ae, be, a6, b6) SHOTKV_MASKED_STEP2(7, ao, bo, a7, b7)
+               SHOTKV_MASKED_STEP2(0, 4, a, b, a0, b0) SHOTKV_MASKED_STEP2(1, 5, a, b, a1, b1)
+               SHOTKV_MASKED_STEP2(2, 6, a, b, a2, b2) SHOTKV_MASKED_STEP2(3, 7, a, b, a3, b3)
                "s_mov_b64 exec, %[save]"
-               : [ae] "+v"(ae), [ao] "+v"(ao), [be] "+v"(be), [bo] "+v"(bo), [save] "=&s"(save)
-               : [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3), [a4] "v"(a4), [a5] "v"(a5),
-                 [a6] "v"(a6), [a7] "v"(a7), [b0] "v"(b0), [b1] "v"(b1), [b2] "v"(b2), [b3] "v"(b3),
-                 [b4] "v"(b4), [b5] "v"(b5), [b6] "v"(b6), [b7] "v"(b7), [s0] "s"(s0), [s1] "s"(s1)
+               : [a] "+v"(a), [b] "+v"(b), [save] "=&s"(save)
+               : [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3), [b0] "v"(b0), [b1] "v"(b1), [b2] "v"(b2),
+                 [b3] "v"(b3), [m] "s"(rows)
                : "scc");
 }
-
-__device__ __forceinline__ void masked_add8(float& ae, float& ao, float a0, float a1, float a2, float a3,
-                                            float a4, float a5, float a6, float a7, uint32_t s0, uint32_t s1) {
+__device__ __forceinline__ void masked_add4(float& a, float a0, float a1, float a2, float a3, uint32_t rows) {
   uint64_t save;
   asm volatile("s_mov_b64 %[save], exec\n\t"
-               SHOTKV_MASKED_STEP1(0, ae, a0) SHOTKV_MASKED_STEP1(1, ao, a1) SHOTKV_MASKED_STEP1(2, ae, a2)
-               SHOTKV_MASKED_STEP1(3, ao, a3) SHOTKV_MASKED_STEP1(4, ae, a4) SHOTKV_MASKED_STEP1(5, ao, a5)
-               SHOTKV_MASKED_STEP1(6, ae, a6) SHOTKV_MASKED_STEP1(7, ao, a7)
+               SHOTKV_MASKED_STEP1(0, 4, a, a0) SHOTKV_MASKED_STEP1(1, 5, a, a1)
+               SHOTKV_MASKED_STEP1(2, 6, a, a2) SHOTKV_MASKED_STEP1(3, 7, a, a3)
                "s_mov_b64 exec, %[save]"
-               : [ae] "+v"(ae), [ao] "+v"(ao), [save] "=&s"(save)
-               : [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3), [a4] "v"(a4), [a5] "v"(a5),
-                 [a6] "v"(a6), [a7] "v"(a7), [s0] "s"(s0), [s1] "s"(s1)
+               : [a] "+v"(a), [save] "=&s"(save)
+               : [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3), [m] "s"(rows)
                : "scc");
 }
 #undef SHOTKV_MASKED_STEP2
 #undef SHOTKV_MASKED_STEP1
 
-// l_run[q] += sum of the elements of e[q] named by the masks (m0: lower lane half, m1: upper lane half)
+// sum[q] += the rows of group i of e[q] that `rows` names
 template <int NQW>
-__device__ __forceinline__ void credit_elements(const floatx16 (&e)[NQW], uint32_t m0, uint32_t m1,
-                                                float (&l_run)[NQW]) {
-  float se[NQW], so[NQW];
+__device__ __forceinline__ void credit_rows(const floatx16 (&e)[NQW], int i, uint32_t rows, float (&sum)[NQW]) {
 #pragma unroll
-  for (int q = 0; q < NQW; ++q) se[q] = so[q] = 0.f;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const uint32_t s0 = m0 >> (8 * h), s1 = m1 >> (8 * h);
-    const int b = 8 * h;
-#pragma unroll
-    for (int q = 0; q + 1 < NQW; q += 2)
-      masked_add8(se[q], so[q], se[q + 1], so[q + 1], e[q][b], e[q][b + 1], e[q][b + 2], e[q][b + 3], e[q][b + 4],
-                  e[q][b + 5], e[q][b + 6], e[q][b + 7], e[q + 1][b], e[q + 1][b + 1], e[q + 1][b + 2],
-                  e[q + 1][b + 3], e[q + 1][b + 4], e[q + 1][b + 5], e[q + 1][b + 6], e[q + 1][b + 7], s0, s1);
-    if (NQW & 1) {
-      constexpr int q = NQW - 1;
-      masked_add8(se[q], so[q], e[q][b], e[q][b + 1], e[q][b + 2], e[q][b + 3], e[q][b + 4], e[q][b + 5],
-                  e[q][b + 6], e[q][b + 7], s0, s1);
-    }
+  for (int q = 0; q + 1 < NQW; q += 2)
+    masked_add4(sum[q], sum[q + 1], e[q][4 * i], e[q][4 * i + 1], e[q][4 * i + 2], e[q][4 * i + 3], e[q + 1][4 * i],
+                e[q + 1][4 * i + 1], e[q + 1][4 * i + 2], e[q + 1][4 * i + 3], rows);
+  if (NQW & 1) {
+    constexpr int q = NQW - 1;
+    masked_add4(sum[q], e[q][4 * i], e[q][4 * i + 1], e[q][4 * i + 2], e[q][4 * i + 3], rows);
   }
-#pragma unroll
-  for (int q = 0; q < NQW; ++q) l_run[q] += se[q] + so[q];
 }
 
 constexpr int kEndCache = 128;  // shot boundaries of a slice kept in LDS
@@ -748,16 +723,33 @@ score_partials_mfma_kernel(
         weights_block<T, D, NQW, SHARED, true>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
       else
         weights_block<T, D, NQW, SHARED, false>(blk, parts, bq, src, lane, cur_key0, cur_rem, causal_base, W, c, m_run, l_run, l_grp, e);
-      uint32_t lo0 = 0u, lo1 = 0u;  // elements already credited (lower / upper lane half)
-      do {
-        const int hi = cur_end - cur_key0;  // wave-uniform, 1..31
-        const uint32_t hi0 = elements_below(hi), hi1 = elements_below(hi - 4);
-        credit_elements<NQW>(e, hi0 & ~lo0, hi1 & ~lo1, l_run);
-        finish_chunk();
-        lo0 = hi0;
-        lo1 = hi1;
-      } while (cur_end < cur_key0 + cur_rem);
-      credit_elements<NQW>(e, 0xffffu & ~lo0, 0xffffu & ~lo1, l_run);
+      float sum[NQW];  // of the current chunk's rows in this block
+      auto add_sum = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NQW; ++q) { l_run[q] += sum[q]; sum[q] = 0.f; }
+      };
+#pragma unroll
+      for (int q = 0; q < NQW; ++q) sum[q] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row0 = cur_key0 + 8 * i;
+        if (cur_end >= row0 + 8) {  // the group has no end inside
+#pragma unroll
+          for (int q = 0; q < NQW; ++q) sum[q] += (e[q][4 * i] + e[q][4 * i + 1]) + (e[q][4 * i + 2] + e[q][4 * i + 3]);
+        } else {
+          uint32_t open = 0xffu;  // rows not yet credited
+          do {
+            const uint32_t behind = 0xffu << max(cur_end - row0, 0);  // (offsets that are out of order may end before)
+            credit_rows<NQW>(e, i, open & ~behind, sum);
+            open = behind;
+            add_sum();
+            finish_chunk();
+          } while (cur_end < row0 + 8);
+          credit_rows<NQW>(e, i, open, sum);
+        }
+        if (i == 3) add_sum();
+        else if (cur_end == row0 + 8) { add_sum(); finish_chunk(); }
+      }
     }
     first_block = false;
     if (cur_end == cur_key0 + cur_rem) finish_chunk();  // the chunk ends with the block

@@ -253,6 +253,18 @@ def test_short_units_in_two_waves(kv):
     _check_scores(kv, rng, P, 4, Hkv, 32, 128, torch.bfloat16, N, _tiny_units(rng, P, N, n), (0, P - 1))
 
 
+@pytest.mark.parametrize("unit", [7, 8, 31, 33])
+@pytest.mark.parametrize("G,D,dtype", [(4, 128, torch.bfloat16), (8, 64, torch.bfloat16), (6, 64, torch.bfloat16),
+                                       (1, 128, torch.float32)])
+def test_ends_at_every_row_of_a_block(kv, G, D, dtype, unit):
+    """Units whose ends take every place in a block and in its groups of eight rows: one end a block or several, on the
+    edges of groups (8) and inside all of them, with one to three row blocks per wave."""
+    N, n = 2400, 2200 // unit
+    rng = np.random.default_rng(G * unit + D)
+    offs = (5 + unit * np.arange(n + 1, dtype=np.int32))[None]
+    _check_scores(kv, rng, 1, G, 2, 32, D, dtype, N, offs, (0,))
+
+
 @pytest.mark.parametrize("attention", [False, True])
 @pytest.mark.parametrize("N,n", [(4001, 24), (16384, 600)])
 def test_scores_have_no_bias(kv, N, n, attention):
