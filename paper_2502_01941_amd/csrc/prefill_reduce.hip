@@ -38,6 +38,23 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
   const int team = tid / LANES, row0 = 4 * (tid % LANES);
   const bool has_rows = row0 < R;
 
+  // The team's first chunks are requested ahead of the slices: both are one trip to memory (whole call, 8192 tokens in 40
+  // shots 24.1 and 23.5 us).
+  const float* rows = partial + head * max_c * R + row0;
+  const int c_end = min((static_cast<int>(blockIdx.x) + 1) * tile, max_c);
+  constexpr int kChunks = 4;  // chunks a team has in flight
+  float4 x[kChunks];
+  auto load_chunks = [&](int c0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kChunks; ++j) {
+      const int c = min(c0 + j * kTeams, c_end - 1);
+      x[j] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      if (has_rows) x[j] = *reinterpret_cast<const float4*>(rows + static_cast<size_t>(c) * R);
+    }
+  };
+  const int c_first = blockIdx.x * tile + team;
+  load_chunks(c_first);
+
   // ---- row denominators: every team combines its share of the slices, then the teams are combined ------
   __shared__ float s_max[kTeams][4 * LANES];
   __shared__ float s_sum[kTeams][4 * LANES];
@@ -49,22 +66,22 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
     const float* stat = group_stat + head * n_groups * R + row0;
     constexpr int kBatch = 4;  // loads in flight
     for (int s0 = team; s0 < n_groups; s0 += kTeams * kBatch) {
-      float4 x[kBatch];
+      float4 y[kBatch];
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
-        x[j] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        y[j] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
         const int sl = s0 + j * kTeams;
-        if (has_rows && sl < n_groups) x[j] = *reinterpret_cast<const float4*>(stat + static_cast<size_t>(sl) * R);
+        if (has_rows && sl < n_groups) y[j] = *reinterpret_cast<const float4*>(stat + static_cast<size_t>(sl) * R);
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         float m = M[e];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) m = fmaxf(m, reinterpret_cast<const float*>(&x[j])[e]);
+        for (int j = 0; j < kBatch; ++j) m = fmaxf(m, reinterpret_cast<const float*>(&y[j])[e]);
         if (m > -INFINITY) {
           L[e] *= exp2f(M[e] - m);
 #pragma unroll
-          for (int j = 0; j < kBatch; ++j) L[e] += exp2f(reinterpret_cast<const float*>(&x[j])[e] - m);  // 2^-inf = 0
+          for (int j = 0; j < kBatch; ++j) L[e] += exp2f(reinterpret_cast<const float*>(&y[j])[e] - m);  // 2^-inf = 0
           M[e] = m;
         }
       }
@@ -87,19 +104,10 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
 
   // ---- masses -------------------------------------------------------------------------------------------
   const float4 lse = *reinterpret_cast<const float4*>(&s_lse[row0]);
-  const float* rows = partial + head * max_c * R + row0;
-  const int c_end = min((static_cast<int>(blockIdx.x) + 1) * tile, max_c);
-  constexpr int kBatch = 4;  // chunks a team has in flight
-  for (int c0 = blockIdx.x * tile + team; c0 < c_end; c0 += kTeams * kBatch) {
-    float4 x[kBatch];
+  for (int c0 = c_first; c0 < c_end; c0 += kTeams * kChunks) {
+    if (c0 != c_first) load_chunks(c0);
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const int c = min(c0 + j * kTeams, c_end - 1);
-      x[j] = lse;  // (as one conditional expression it became a choice of pointers, and lse went through scratch)
-      if (has_rows) x[j] = *reinterpret_cast<const float4*>(rows + static_cast<size_t>(c) * R);
-    }
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
+    for (int j = 0; j < kChunks; ++j) {
       float m = row0 + 0 < n_valid ? exp2f(x[j].x - lse.x) : 0.f;  // 2^-inf = 0
       m += row0 + 1 < n_valid ? exp2f(x[j].y - lse.y) : 0.f;
       m += row0 + 2 < n_valid ? exp2f(x[j].z - lse.z) : 0.f;
