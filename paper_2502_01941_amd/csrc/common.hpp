@@ -81,6 +81,13 @@ __device__ __forceinline__ float max_across_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+// The larger of two numbers in one instruction: fmaxf first quiets every operand of unknown origin by an instruction of its
+// own.  (Of a NaN and a number the number; infinity of two NaNs, whose row is NaN anyway.)
+__device__ __forceinline__ float max_of_two(float a, float b) {
+  float top = INFINITY;
+  asm("" : "+s"(top));  // (a known constant would make it fmaxf again)
+  return __builtin_amdgcn_fmed3f(a, b, top);
+}
 __device__ __forceinline__ float sum_across_row_pairs(float x) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
