@@ -339,20 +339,29 @@ int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
 // and one partial score per slot instead of partial sums of every range and the logits of every head: those writes, a
 // hundredth of the bytes read, cost the row stream an eighth of its time (512 sequences of 5121 rows, 8 KV heads: step
 // 1840 us, 1760 without storing logits, 1600 without partial sums either, 1640 like this, where the finish kernel shrinks
-// from 51 to 12 as well).  It pays where the pairs alone fill the chip: three workgroups per CU are resident, two with
-// more than four query heads per KV head, and a second round of them has to be worth having.  Whole steps, ranges and
-// whole: 4 query heads, 5121 rows, 256 pairs 130 and 133 us, 352 171 and 157, 384 184 and 164, 512 242 and 207, 576 269
-// and 267, 768 355 and 306, 800 368 and 385, 832 389 and 399, 1024 477 and 430, 2048 950 and 838; 365 rows, 384 pairs
-// 25.2 and 27.1; 913 rows, 512 pairs 52.5 and 48.1; 8 query heads, 4401 rows, 320 pairs 166 and 186, 384 215 and 215, 448
-// 245 and 220, 512 240 and 206, 544 234 and 295, 640 276 and 300.  Where one range is all there is anyway nothing is won
-// (2048 pairs of 365 rows of one query head 41 and 57).
+// from 51 to 12 as well).  A workgroup takes as long as its sequence, so it pays where the pairs alone fill the chip, in whole
+// rounds of the workgroups that share it best: four per CU with one or two query heads per KV head, three with up to four,
+// two with more.  The share of its rounds that a launch must fill is read off whole steps (us, ranges and whole):
+//   4 query heads, bf16 x 128: 3163 + 64 rows, 384 pairs 105 and 121, 512 140 and 136, 576 157 and 160, 704 192 and 180, 768
+//     210 and 194, 800 220 and 269, 1024 281 and 287, 1152 315 and 296, 1536 425 and 390, 2048 570 and 531.  Fewer than 688
+//     pairs pay only by the logits that are not written: 1200 + 64 rows, 576 pairs, 71.3 and 74.6, + 512 rows 98.5 and 94.0;
+//     128-byte rows, + 64, 46.4 and 43.4; fp32 x 128, 3163 + 512, 354 and 363, x 64, + 300, 168 and 182.
+//   2 query heads, 3163 + 512 rows: 576 pairs 174 and 175, 768 231 and 215, 1024 310 and 286, 1152 351 and 361, 1536 472 and
+//     447; one query head: 768 221 and 214 (1200 + 64 rows 80.9 and 84.1), 1024 294 and 284, 1536 453 and 444.
+//   8 query heads, 1200 + 64 rows: 384 pairs 62 and 73, 448 81 and 73, 512 86 and 76, 576 92 and 121, 1024 146 and 144, 2048
+//     278 and 283; 128-byte rows 448 54 and 45, 896 84 and 82, 1024 91 and 83, 1152 101 and 104, 2048 170 and 158;
+//     fp32 x 64, 3163 + 512, 512 197 and 215, 768 288 and 281, 1536 565 and 561, x 128 more than ranges everywhere.
+// Where one range is all there is anyway nothing is won (2048 pairs of 365 rows of one query head 41 and 57).
 bool decode_whole(const DecodeDims& d, int row_bytes) {
   if (d.n_splits < 2 || d.n_slots > decode_map_rows(row_bytes)) return false;
   const int pairs = d.S * d.H_kv;
-  const long bytes = static_cast<long>(d.cap + d.n_slots) * row_bytes;  // of a pair's K rows
-  if (d.G <= 4) return pairs >= (bytes < 1 << 20 ? 448 : 352) && (pairs <= 768 || pairs >= 896);
-  const int rounds = ceil_div(pairs, 512);
-  return 5 * pairs >= 4 * 512 * rounds;
+  const int round = d.G > 4 ? 512 : d.G > 2 ? 768 : 1024, rounds = ceil_div(pairs, round);
+  const int filled = static_cast<int>(100L * pairs / (static_cast<long>(rounds) * round));  // per cent
+  const bool bf16 = row_bytes == 2 * d.D;
+  if (d.G > 4) return bf16 && filled >= 86 && (rounds == 1 || row_bytes <= 128);
+  if (d.G <= 2) return filled >= (d.G == 1 ? 94 : 75);
+  if (rounds > 1) return filled >= 70;
+  return filled >= 90 || (pairs >= 512 && bf16 && (d.D == 64 || d.n_slots >= 256));
 }
 
 // Token ranges that a launch takes, at most n_splits.  Where ranges of no more than one piece would be over a round of

@@ -23,25 +23,37 @@ def _run(kv, S, G, Hkv, D, dtype, cap, n_slots, seed):
     _check_steps(kv, rng, state, budget, 1, scale)
 
 
+def _round(G):
+    """(Sequence, KV head) pairs that fill a round of workgroups: two, three or four per CU."""
+    return 512 if G > 4 else 768 if G > 2 else 1024
+
+
 @pytest.mark.parametrize("D,dtype", [(64, BF16), (128, BF16), (64, F32), (128, F32)])
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 8])
 def test_one_workgroup_for_a_short_sequence(kv, G, D, dtype):  # noqa: F811
-    """448 and 512 (sequence, KV head) pairs."""
-    _run(kv, 224, G, 2, D, dtype, 230, 40, G)
-    _run(kv, 256, G, 2, D, dtype, 31, 163, G + 1)
+    """A round of (sequence, KV head) pairs, and a little less."""
+    S = _round(G) // 8
+    _run(kv, S, G, 8, D, dtype, 230, 840, G)
+    _run(kv, S - S // 16, G, 8, D, dtype, 1031, 43, G + 1)
 
 
 @pytest.mark.parametrize("G,D,dtype,over", [(1, 128, BF16, 0), (4, 128, BF16, 1), (2, 64, BF16, 1), (8, 64, BF16, 0),
-                                            (3, 128, F32, 1), (5, 64, F32, 17)])
+                                            (3, 128, F32, 1), (4, 64, F32, 17)])
 def test_one_workgroup_for_several_pieces(kv, G, D, dtype, over):  # noqa: F811
     """Prefill rows up to the end of a piece of four waves and past it, then the slots in a piece of their own."""
     piece = {128: 1152, 256: 1088, 512: 1056}[D * (2 if dtype == BF16 else 4)]
-    _run(kv, 64, G, 8, D, dtype, piece + over, 65, 10 * G + over)
+    _run(kv, _round(G) // 8, G, 8, D, dtype, piece + over, 65, 10 * G + over)
 
 
 def test_as_many_slots_as_the_map_holds(kv):  # noqa: F811
     for n_slots in (1088, 1089):  # the second takes more than one workgroup
-        _run(kv, 224, 1, 2, 128, BF16, 20, n_slots, n_slots)
+        _run(kv, 128, 1, 8, 128, BF16, 20, n_slots, n_slots)
+
+
+@pytest.mark.parametrize("G,D,S", [(4, 128, 65), (3, 128, 80), (4, 64, 64), (4, 128, 136), (8, 64, 112)])
+def test_rounds_that_are_not_full(kv, G, D, S):  # noqa: F811
+    """Shares of a round from which one workgroup takes a sequence: with many slots, short rows, in a second round."""
+    _run(kv, S, G, 8, D, BF16, 900, 257, S + G)
 
 
 @pytest.mark.parametrize("G,S,cap", [(4, 128, 4000), (2, 192, 3100), (8, 128, 4200)])
