@@ -26,8 +26,9 @@ __device__ __forceinline__ float sum_over_lanes(float x) {
   }
 }
 
-// LANES: lanes per chunk, R / 4 rounded up to a power of two
-template <int LANES>
+// LANES: lanes per chunk, R / 4 rounded up to a power of two.  AHEAD: the team's first chunks are requested ahead of the
+// slices' statistics.
+template <int LANES, bool AHEAD>
 __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* __restrict__ partial,
                                                                   const float* __restrict__ group_stat, int H_kv,
                                                                   int R, int n_valid, int n_groups, int max_c,
@@ -38,8 +39,6 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
   const int team = tid / LANES, row0 = 4 * (tid % LANES);
   const bool has_rows = row0 < R;
 
-  // The team's first chunks are requested ahead of the slices: both are one trip to memory (whole call, 8192 tokens in 40
-  // shots 24.1 and 23.5 us).
   const float* rows = partial + head * max_c * R + row0;
   const int c_end = min((static_cast<int>(blockIdx.x) + 1) * tile, max_c);
   constexpr int kChunks = 4;  // chunks a team has in flight
@@ -53,7 +52,7 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
     }
   };
   const int c_first = blockIdx.x * tile + team;
-  load_chunks(c_first);
+  if constexpr (AHEAD) load_chunks(c_first);
 
   // ---- row denominators: every team combines its share of the slices, then the teams are combined ------
   __shared__ float s_max[kTeams][4 * LANES];
@@ -105,7 +104,7 @@ __global__ __launch_bounds__(kMassThreads) void chunk_mass_kernel(const float* _
   // ---- masses -------------------------------------------------------------------------------------------
   const float4 lse = *reinterpret_cast<const float4*>(&s_lse[row0]);
   for (int c0 = c_first; c0 < c_end; c0 += kTeams * kChunks) {
-    if (c0 != c_first) load_chunks(c0);
+    if (!AHEAD || c0 != c_first) load_chunks(c0);
 #pragma unroll
     for (int j = 0; j < kChunks; ++j) {
       float m = row0 + 0 < n_valid ? exp2f(x[j].x - lse.x) : 0.f;  // 2^-inf = 0
@@ -130,9 +129,14 @@ hipError_t launch_chunk_mass(const PrefillDims& d, int n_valid, const PrefillWor
   const int tiles = max(1, min(ceil_div(w.max_c, 32), ceil_div(2048, heads)));
   const int tile = ceil_div(w.max_c, tiles);
   const dim3 grid(ceil_div(w.max_c, tile), d.H_kv, d.P);
-#define SHOTKV_LAUNCH_MASS(LL)                                                                               \
-  hipLaunchKernelGGL(chunk_mass_kernel<LL>, grid, dim3(kMassThreads), 0, s, w.partial, w.group_stat, d.H_kv, d.R, \
-                     n_valid, w.n_groups, w.max_c, tile, w.chunk_mass)
+  // Up to one workgroup per CU the kernel is two trips to memory, so the first chunks are asked for with the statistics
+  // (whole call, us, without and with: 8192 tokens in 40 shots 23.7 and 23.3, four of them 45.5 and 45.1, 32768 tokens 39.6
+  // and 39.3; 384 workgroups 129.8 and 129.5).  Many workgroups all asking before the first can go on to its sums lose
+  // (the kernel alone, 1216 workgroups 8.6 and 10.0, 2048 19.7 and 22.9).
+  const bool ahead = grid.x * static_cast<long>(heads) <= 256;
+#define SHOTKV_LAUNCH_MASS(LL)                                                                                          \
+  hipLaunchKernelGGL((ahead ? chunk_mass_kernel<LL, true> : chunk_mass_kernel<LL, false>), grid, dim3(kMassThreads), 0, \
+                     s, w.partial, w.group_stat, d.H_kv, d.R, n_valid, w.n_groups, w.max_c, tile, w.chunk_mass)
   if (d.R <= 32) SHOTKV_LAUNCH_MASS(8);
   else if (d.R <= 64) SHOTKV_LAUNCH_MASS(16);
   else if (d.R <= 128) SHOTKV_LAUNCH_MASS(32);
