@@ -573,7 +573,7 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
     for (int w = 0; w < kWaves; ++w)
       l = fmaf(s_sum[w][h], s_max[w][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_max[w][h] - m), l);
   };
-  if (LONG && whole && n_d > 0) {
+  if (LONG && whole && n_blk > 0 && n_d > 0) {  // (no piece was taken where the pool is full)
     // the weights of the slots are those of the last piece: each wave's are scaled to the softmax and summed over the heads
     __syncthreads();
     float f[G];

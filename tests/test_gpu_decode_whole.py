@@ -1,11 +1,14 @@
 """GPU parity of decode steps over many sequences, where one workgroup takes all of a (sequence, KV head) or a few take long
 ranges: prefill rows around the pieces that fit into LDS and around the blocks that are dealt to the waves, every row size
-and group size, pools full, with holes and still filling up, poison in dead rows and free slots."""
+and group size, pools with one slot left, with holes and still filling up, poison in dead rows and free slots; pools without
+a free slot among such pools."""
 import numpy as np
 import pytest
 import torch
 
-from test_gpu_decode_rows import _check_steps, _state, kv  # noqa: F401
+from helpers import to_np
+from oracle import shotkv_oracle as orc
+from test_gpu_decode_rows import RTOL, _check_steps, _state, kv  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +63,40 @@ def test_rounds_that_are_not_full(kv, G, D, S):  # noqa: F811
 def test_few_long_ranges(kv, G, S, cap):  # noqa: F811
     """Launches that would be over a round of workgroups in ranges of 1024 tokens take two or three longer ones."""
     _run(kv, S, G, 2, 64, BF16, cap, 150, S + G)
+
+
+@pytest.mark.parametrize("S,Hkv,G,D,cap,n_slots", [
+    (192, 8, 4, 64, 2000, 2),       # one workgroup for a sequence, two full rounds of them
+    (1536, 1, 4, 64, 2000, 2),      # the same as caches with a slot map for every KV head
+    (112, 8, 8, 64, 1500, 40),
+    (128, 2, 4, 64, 4000, 150)])    # three long ranges
+def test_full_pools_among_others(kv, S, Hkv, G, D, cap, n_slots):  # noqa: F811
+    """A sequence whose pool has no free slot reports that and changes nothing, neither its own caches nor the scores of
+    other sequences of the launch, finished long before or still running."""
+    rng = np.random.default_rng(S + Hkv)
+    full = [s >= S // 3 and s % 4 == 1 for s in range(S)]
+    counts = [cap if full[s] else int(rng.integers(1, cap // 8)) for s in range(S)]
+    used = [np.arange(n_slots) if full[s] else np.arange(n_slots - 1) for s in range(S)]
+    budget, scale = n_slots - 1, D ** -0.5
+    state = _state(kv, rng, S, Hkv * G, Hkv, D, BF16, cap, counts, n_slots, used, budget, scale)
+    before = [t.clone() for t in (state.k_dec, state.v_dec, state.slot_pos)]
+    new = [torch.from_numpy(rng.standard_normal((S, h, D), dtype=np.float32)).to(BF16).cuda() for h in (Hkv * G, Hkv, Hkv)]
+    state.out.fill_(7.0)
+    state.token_scores.fill_(7.0)
+    kv.decode_step(state, 1000, *new)
+    torch.cuda.synchronize()
+    is_full = torch.tensor(full, device="cuda")
+    assert torch.equal(state.status == orc.STATUS_NO_FREE_SLOT, is_full) and bool((state.status[~is_full] == orc.STATUS_OK).all())
+    assert not state.out[is_full].any() and not state.token_scores[is_full].any()
+    assert bool((state.evicted_pos[is_full] == -1).all())
+    for now, then in zip((state.k_dec, state.v_dec, state.slot_pos), before):
+        assert torch.equal(now[is_full].nan_to_num(1.25), then[is_full].nan_to_num(1.25))
+    for s in np.flatnonzero(~np.array(full)):
+        kd, vd, sp = (to_np(t[s]).copy() if t.is_floating_point() else t[s].cpu().numpy() for t in before)
+        kp, vp = to_np(state.k_prefill[s, :, :counts[s]]), to_np(state.v_prefill[s, :, :counts[s]])
+        with np.errstate(invalid="ignore", over="ignore"):
+            r = orc.decode_step(kp, vp, counts[s], kd, vd, sp, budget, 1000, *[to_np(t[s]) for t in new], scale)
+        np.testing.assert_allclose(state.token_scores[s].cpu().numpy(), r["token_scores"], rtol=RTOL, atol=1e-30)
+        got = state.out[s].cpu().numpy()
+        assert np.all(np.abs(got - r["out"]) <= RTOL * np.abs(r["out"]).max(axis=1, keepdims=True)), s
+        assert int(state.evicted_pos[s]) == r["evicted_pos"]
