@@ -80,6 +80,14 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// 2^(z - reference) of a whole reference, with a mantissa that z alone decides: z - reference is rounded at another place for
+// every reference, so equal logits of waves with different maxima would get weights that differ in the last bit.
+__device__ __forceinline__ float exp2_of_whole_reference(float z, float reference) {
+  const float top = fmaxf(ceilf(z), -0x1p30f);  // (minus infinity: no weight)
+  const float up = __builtin_amdgcn_fmed3f(top - reference, -1024.f, 1024.f);
+  return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(z - top), static_cast<int>(up));
+}
+
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kMaxRange = kDecodeMaxRange;  // tokens whose logits the LDS buffer holds at a time
@@ -496,7 +504,8 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
         }
 #pragma unroll
         for (int h = 0; h < G; ++h) {
-          const float p = valid ? __builtin_amdgcn_exp2f(z[h] - ref[h]) : 0.f;
+          // (LONG: the weights may become scores, where tokens of equal keys tie)
+          const float p = !valid ? 0.f : LONG ? exp2_of_whole_reference(z[h], ref[h]) : __builtin_amdgcn_exp2f(z[h] - ref[h]);
           zown[t][h] = p;
           L[h] += p;
         }

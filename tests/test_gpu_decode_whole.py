@@ -100,3 +100,30 @@ def test_full_pools_among_others(kv, S, Hkv, G, D, cap, n_slots):  # noqa: F811
         got = state.out[s].cpu().numpy()
         assert np.all(np.abs(got - r["out"]) <= RTOL * np.abs(r["out"]).max(axis=1, keepdims=True)), s
         assert int(state.evicted_pos[s]) == r["evicted_pos"]
+
+
+@pytest.mark.parametrize("S,Hkv,G,D,dtype,cap,n_slots", [
+    (96, 8, 4, 128, BF16, 700, 600), (128, 8, 1, 64, BF16, 1200, 800), (64, 8, 8, 64, BF16, 500, 700),
+    (96, 8, 3, 128, F32, 700, 600), (768, 1, 4, 64, F32, 700, 600)])
+def test_tokens_of_equal_keys_score_the_same_in_every_wave(kv, S, Hkv, G, D, dtype, cap, n_slots):  # noqa: F811
+    """Twelve slots, in blocks of every wave, hold one key that is opposed to the queries: their scores are the lowest and
+    equal to the last bit, whatever logits the waves that take them saw beside them, so the newest token goes."""
+    rng = np.random.default_rng(S + G)
+    scale = D ** -0.5
+    state = _state(kv, rng, S, Hkv * G, Hkv, D, dtype, cap, [cap - s % 100 for s in range(S)], n_slots,
+                   [np.arange(n_slots - 1)] * S, n_slots - 1, scale)
+    q, kn, vn = (torch.from_numpy(rng.standard_normal((S, h, D), dtype=np.float32)).to(dtype).cuda()
+                 for h in (Hkv * G, Hkv, Hkv))
+    block = 4096 // (D * (2 if dtype == BF16 else 4))
+    at = np.concatenate([np.arange(12)[:, None] * block + [3]])[:, 0]      # in twelve blocks that follow one another
+    assert at[-1] < n_slots - 1
+    toward = q.float().reshape(S, Hkv, G, D).mean(dim=2)
+    state.k_dec[:, :, at] = (-1.5 * toward).to(dtype)[:, :, None]
+    kv.decode_step(state, 5000, q, kn, vn)
+    torch.cuda.synchronize()
+    scores = state.token_scores[:, at]
+    assert torch.equal(scores, scores[:, :1].expand_as(scores))
+    others = torch.cat([state.token_scores[:, :n_slots - 1][:, np.setdiff1d(np.arange(n_slots - 1), at)]], dim=1)
+    lowest = scores[:, 0] < others.min(dim=1).values
+    assert int(lowest.sum()) > S // 2                                       # the case is really hit
+    assert bool((state.evicted_pos[lowest] == int(at[-1])).all())
