@@ -590,7 +590,8 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
     for (int h = 0; h < G; ++h) {
       float m, l;
       merged(h, m, l);
-      f[h] = M[h] != -INFINITY ? __builtin_amdgcn_exp2f(M[h] - m) * (1.f / l) : 0.f;
+      // (NaN where no wave has a finite logit, as in the finish kernel)
+      f[h] = (M[h] != -INFINITY ? __builtin_amdgcn_exp2f(M[h] - m) : 0.f) * (1.f / l);
     }
     for (int t = lane; t < kOwnRows; t += kWave) {
       const int slot = (b0 - nb_p + wave + t / S::kBlock * kWaves) * S::kBlock + t % S::kBlock;

@@ -127,3 +127,39 @@ def test_tokens_of_equal_keys_score_the_same_in_every_wave(kv, S, Hkv, G, D, dty
     lowest = scores[:, 0] < others.min(dim=1).values
     assert int(lowest.sum()) > S // 2                                       # the case is really hit
     assert bool((state.evicted_pos[lowest] == int(at[-1])).all())
+
+
+@pytest.mark.parametrize("S,Hkv,G,D,dtype,cap,n_slots", [
+    (96, 8, 4, 128, BF16, 1200, 300), (128, 8, 1, 64, F32, 1300, 300), (64, 8, 8, 64, BF16, 500, 700),   # one workgroup
+    (64, 4, 4, 64, BF16, 4000, 150),                                                                     # three long ranges
+    (3, 8, 4, 128, BF16, 700, 300)])                                                                     # short ranges
+def test_values_that_are_not_finite(kv, S, Hkv, G, D, dtype, cap, n_slots):  # noqa: F811
+    """Infinite values show in their column, keys that leave a head no finite logit make its outputs NaN and, as sums over the
+    heads, the scores; a NaN query likewise.  Other heads and other sequences are as the oracle has them."""
+    rng = np.random.default_rng(S + G)
+    budget, scale = n_slots - 1, D ** -0.5
+    counts = [cap - 3 * (s % 7) for s in range(S)]
+    state = _state(kv, rng, S, Hkv * G, Hkv, D, dtype, cap, counts, n_slots, [np.arange(n_slots - 1)] * S, budget, scale)
+    new = [torch.from_numpy(rng.standard_normal((S, h, D), dtype=np.float32)).to(dtype).cuda() for h in (Hkv * G, Hkv, Hkv)]
+    state.v_prefill[0, :, counts[0] - 1, 5], state.v_dec[0, :, n_slots - 2, 9] = float("inf"), float("-inf")
+    for t in (state.k_prefill[1, 0, :counts[1]], state.k_dec[1, 0, :n_slots - 1], new[1][1, 0]):
+        t[..., 0] = float("-inf")
+    new[0][1, :G, 0] = 1.0                  # sequence 1, KV head 0: every logit is minus infinity
+    new[0][2, G - 1, 7] = float("nan")      # sequence 2: one query head
+    before = [t.clone() for t in (state.k_dec, state.v_dec, state.slot_pos)]
+    kv.decode_step(state, 1000, *new)
+    torch.cuda.synchronize()
+    for s in [0, 1, 2, S // 2 + 1, S - 1]:
+        kd, vd, sp = (to_np(t[s]).copy() if t.is_floating_point() else t[s].cpu().numpy() for t in before)
+        kp, vp = to_np(state.k_prefill[s, :, :counts[s]]), to_np(state.v_prefill[s, :, :counts[s]])
+        with np.errstate(invalid="ignore", over="ignore"):
+            r = orc.decode_step(kp, vp, counts[s], kd, vd, sp, budget, 1000, *[to_np(t[s]) for t in new], scale)
+        assert int(state.status[s]) == orc.STATUS_OK
+        got, want = state.out[s].cpu().numpy(), r["out"]
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want)), s
+        assert np.array_equal(np.isneginf(got), np.isneginf(want)), s
+        assert np.isfinite(want).all() == (s > 2)
+        finite = np.isfinite(want)
+        top = np.abs(np.where(finite, want, 0)).max(axis=1, keepdims=True)
+        assert np.all(np.abs(got - want)[finite] <= np.broadcast_to(RTOL * top, got.shape)[finite]), s
+        np.testing.assert_allclose(state.token_scores[s].cpu().numpy(), r["token_scores"], rtol=RTOL, atol=1e-30)
