@@ -82,7 +82,8 @@ __device__ __forceinline__ float max_across_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 // The larger of two numbers in one instruction: fmaxf first quiets every operand of unknown origin by an instruction of its
-// own.  (Of a NaN and a number the number; infinity of two NaNs, whose row is NaN anyway.)
+// own.  Of a NaN and a number the number, of two NaNs infinity: only where a NaN makes everything that the maximum is used
+// for NaN (a softmax reference that is carried on to keys without one takes fmaxf).
 __device__ __forceinline__ float max_of_two(float a, float b) {
   float top = INFINITY;
   asm("" : "+s"(top));  // (a known constant would make it fmaxf again)

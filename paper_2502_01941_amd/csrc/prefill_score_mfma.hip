@@ -380,12 +380,11 @@ __device__ __forceinline__ void weights_block(lds_cchar* lds_buf, lds_cchar* par
       for (int v = 0; v < 16; ++v)
         if (8 * (v >> 2) + (v & 3) >= limit) e[q][v] = -INFINITY;
     }
-    float bm = max_of_two(e[q][0], e[q][1]);
+    float bm = fmaxf(e[q][0], e[q][1]);
 #pragma unroll
     for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, e[q][v]), e[q][v + 1]);
-    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
-    bm = max_of_two(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
-    const float m_new = max_of_two(m_run[q], bm * c);
+    bm = max_across_halves(bm);
+    const float m_new = fmaxf(m_run[q], bm * c);
     const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(m_run[q] - m_safe);
     l_run[q] *= alpha;

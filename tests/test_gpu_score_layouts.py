@@ -265,6 +265,30 @@ def test_ends_at_every_row_of_a_block(kv, G, D, dtype, unit):
     _check_scores(kv, rng, 1, G, 2, 32, D, dtype, N, offs, (0,))
 
 
+@pytest.mark.parametrize("D,dtype", [(128, torch.bfloat16), (64, torch.bfloat16), (128, torch.float32)])
+def test_poisoned_keys_stay_in_their_unit(kv, D, dtype):
+    """NaN keys take their slice out of the row denominators and their unit out of the slice; the other units keep finite
+    scores, the same whether one key is NaN or two next to each other in a block that holds a unit's end."""
+    P, Hkv, G, W, N = 1, 2, 4, 32, 600
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    q, k = (torch.randn((P, h, n, D), generator=gen, device="cuda").to(dtype) for h, n in ((Hkv * G, W), (Hkv, N)))
+    offs = torch.arange(0, 561, 20, dtype=torch.int32, device="cuda")[None]
+
+    def scores(*keys):
+        x = k.clone()
+        x[:, :, list(keys)] = float("nan")
+        s, status = kv.prefill_scores(q, x, offs, D ** -0.5)
+        torch.cuda.synchronize()
+        assert not status.any()
+        return s[0].cpu().numpy()
+
+    for key in (32, 36, 160, 288):      # rows 0 and 4 of a block, the first elements of a lane of either half
+        unit = key // 20
+        one, two = np.delete(scores(key + 1), unit), np.delete(scores(key, key + 1), unit)
+        assert np.isfinite(one).all() and (one > 0).all()
+        np.testing.assert_allclose(two, one, rtol=SCORE_RTOL, atol=0, err_msg=str(key))
+
+
 @pytest.mark.parametrize("attention", [False, True])
 @pytest.mark.parametrize("N,n", [(4001, 24), (16384, 600)])
 def test_scores_have_no_bias(kv, N, n, attention):
