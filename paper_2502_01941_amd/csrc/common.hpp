@@ -288,7 +288,6 @@ constexpr int decode_map_rows(int row_bytes) {
   return (kDecodeMaxRange / block + 1 + 3) / 4 * 4 * block;
 }
 bool decode_whole(const DecodeDims& d, int row_bytes);
-int decode_launch_splits(const DecodeDims& d);  // token ranges of the launch
 hipError_t launch_decode_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
                                  const void* k_new, const void* v_new, float* out, const DecodeWorkspace& w,
                                  hipStream_t s);

@@ -364,17 +364,6 @@ bool decode_whole(const DecodeDims& d, int row_bytes) {
   return filled >= 90 || (pairs >= 512 && bf16 && (d.D == 64 || d.n_slots >= 256));
 }
 
-// Token ranges that a launch takes, at most n_splits.  Where ranges of no more than one piece would be over a round of
-// workgroups, two or three longer ones that fill a round write less and start less often: 256 pairs of 5121 rows, 4 query
-// heads, six ranges 129.8 us and three 121.2; 352 pairs 171 and 164; 256 pairs of 4401 rows, 7 query heads, 130 and 122.5.
-// Four ranges gain nothing (192 pairs 96.7 and 97.4).
-int decode_launch_splits(const DecodeDims& d) {
-  if (d.whole) return 1;
-  const int resident = d.G > 4 ? 512 : 768, pairs = d.S * d.H_kv, splits = resident / pairs;
-  const bool few = d.n_splits * pairs > 1024 && splits >= 2 && splits <= 3 && splits * pairs >= resident - resident / 8;
-  return few ? min(splits, d.n_splits) : d.n_splits;
-}
-
 hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& st, float* out,
                                 float* token_scores, int32_t* evicted_pos, int32_t* status,
                                 const DecodeWorkspace& w, hipStream_t s) {
@@ -386,7 +375,7 @@ hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& 
                  : d.D == 128 ? (rows <= 8 ? decode_finish_kernel<128, 8, false> : decode_finish_kernel<128, 32, false>)
                               : (rows <= 8 ? decode_finish_kernel<64, 8, false> : decode_finish_kernel<64, 32, false>);
   hipLaunchKernelGGL(kernel, grid, dim3(kFinThreads), 0, s, w.part_ml, w.part_o, w.z_dec, st.slot_pos, w.new_slot,
-                     d.n_slots, rows, decode_launch_splits(d), d.budget, d.step, out, token_scores, evicted_pos, status);
+                     d.n_slots, rows, d.n_splits, d.budget, d.step, out, token_scores, evicted_pos, status);
   return hipGetLastError();
 }
 

@@ -654,7 +654,7 @@ template <typename T, int D>
 static hipError_t launch_partial(const DecodeDims& d, const shotkv_decode_state& st, const void* q_new,
                                  const void* k_new, const void* v_new, float* out, const DecodeWorkspace& w,
                                  hipStream_t s) {
-  const int n_splits = decode_launch_splits(d), split_tokens = ceil_div(d.cap + d.n_slots, n_splits);
+  const int n_splits = d.whole ? 1 : d.n_splits, split_tokens = d.whole ? d.cap + d.n_slots : d.split_tokens;
   const dim3 grid(n_splits, d.H_kv, d.S), block(kThreads);
   const float c = d.sm_scale * kLog2e;
   const int ahead_slots = ahead_of_map(d, D * static_cast<int>(sizeof(T)));

@@ -1,7 +1,7 @@
-"""GPU parity of decode steps over many sequences, where one workgroup takes all of a (sequence, KV head) or a few take long
-ranges: prefill rows around the pieces that fit into LDS and around the blocks that are dealt to the waves, every row size
-and group size, pools with one slot left, with holes and still filling up, poison in dead rows and free slots; pools without
-a free slot among such pools."""
+"""GPU parity of decode steps over many sequences, where one workgroup takes all of a (sequence, KV head), and of launches
+just too small for that: prefill rows around the pieces that fit into LDS and around the blocks that are dealt to the waves,
+every row size and group size, pools with one slot left, with holes and still filling up, poison in dead rows and free
+slots; pools without a free slot among such pools."""
 import numpy as np
 import pytest
 import torch
@@ -60,8 +60,8 @@ def test_rounds_that_are_not_full(kv, G, D, S):  # noqa: F811
 
 
 @pytest.mark.parametrize("G,S,cap", [(4, 128, 4000), (2, 192, 3100), (8, 128, 4200)])
-def test_few_long_ranges(kv, G, S, cap):  # noqa: F811
-    """Launches that would be over a round of workgroups in ranges of 1024 tokens take two or three longer ones."""
+def test_more_ranges_than_a_round(kv, G, S, cap):  # noqa: F811
+    """Launches of few sequences that are over a round of workgroups in ranges of 1024 tokens."""
     _run(kv, S, G, 2, 64, BF16, cap, 150, S + G)
 
 
@@ -69,7 +69,7 @@ def test_few_long_ranges(kv, G, S, cap):  # noqa: F811
     (192, 8, 4, 64, 2000, 2),       # one workgroup for a sequence, two full rounds of them
     (1536, 1, 4, 64, 2000, 2),      # the same as caches with a slot map for every KV head
     (112, 8, 8, 64, 1500, 40),
-    (128, 2, 4, 64, 4000, 150)])    # three long ranges
+    (128, 2, 4, 64, 4000, 150)])    # ranges
 def test_full_pools_among_others(kv, S, Hkv, G, D, cap, n_slots):  # noqa: F811
     """A sequence whose pool has no free slot reports that and changes nothing, neither its own caches nor the scores of
     other sequences of the launch, finished long before or still running."""
@@ -131,8 +131,7 @@ def test_tokens_of_equal_keys_score_the_same_in_every_wave(kv, S, Hkv, G, D, dty
 
 @pytest.mark.parametrize("S,Hkv,G,D,dtype,cap,n_slots", [
     (96, 8, 4, 128, BF16, 1200, 300), (128, 8, 1, 64, F32, 1300, 300), (64, 8, 8, 64, BF16, 500, 700),   # one workgroup
-    (64, 4, 4, 64, BF16, 4000, 150),                                                                     # three long ranges
-    (3, 8, 4, 128, BF16, 700, 300)])                                                                     # short ranges
+    (64, 4, 4, 64, BF16, 4000, 150), (3, 8, 4, 128, BF16, 700, 300)])                                    # ranges
 def test_values_that_are_not_finite(kv, S, Hkv, G, D, dtype, cap, n_slots):  # noqa: F811
     """Infinite values show in their column, keys that leave a head no finite logit make its outputs NaN and, as sums over the
     heads, the scores; a NaN query likewise.  Other heads and other sequences are as the oracle has them."""
