@@ -339,29 +339,30 @@ int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
 // and one partial score per slot instead of partial sums of every range and the logits of every head: those writes, a
 // hundredth of the bytes read, cost the row stream an eighth of its time (512 sequences of 5121 rows, 8 KV heads: step
 // 1840 us, 1760 without storing logits, 1600 without partial sums either, 1640 like this, where the finish kernel shrinks
-// from 51 to 12 as well).  A workgroup takes as long as its sequence, so it pays where the pairs alone fill the chip, in whole
-// rounds of the workgroups that share it best: four per CU with one or two query heads per KV head, three with up to four,
-// two with more.  The share of its rounds that a launch must fill is read off whole steps (us, ranges and whole):
-//   4 query heads, bf16 x 128: 3163 + 64 rows, 384 pairs 105 and 121, 512 140 and 136, 576 157 and 160, 704 192 and 180, 768
-//     210 and 194, 800 220 and 269, 1024 281 and 287, 1152 315 and 296, 1536 425 and 390, 2048 570 and 531.  Fewer than 688
-//     pairs pay only by the logits that are not written: 1200 + 64 rows, 576 pairs, 71.3 and 74.6, + 512 rows 98.5 and 94.0;
-//     128-byte rows, + 64, 46.4 and 43.4; fp32 x 128, 3163 + 512, 354 and 363, x 64, + 300, 168 and 182.
-//   2 query heads, 3163 + 512 rows: 576 pairs 174 and 175, 768 231 and 215, 1024 310 and 286, 1152 351 and 361, 1536 472 and
-//     447; one query head: 768 221 and 214 (1200 + 64 rows 80.9 and 84.1), 1024 294 and 284, 1536 453 and 444.
-//   8 query heads, 1200 + 64 rows: 384 pairs 62 and 73, 448 81 and 73, 512 86 and 76, 576 92 and 121, 1024 146 and 144, 2048
-//     278 and 283; 128-byte rows 448 54 and 45, 896 84 and 82, 1024 91 and 83, 1152 101 and 104, 2048 170 and 158;
-//     fp32 x 64, 3163 + 512, 512 197 and 215, 768 288 and 281, 1536 565 and 561, x 128 more than ranges everywhere.
-// Where one range is all there is anyway nothing is won (2048 pairs of 365 rows of one query head 41 and 57).
+// from 51 to 12 as well).  But a workgroup takes as long as its sequence, and a launch as long as its last workgroup, so it
+// from 51 to 12 as well).  But a workgroup takes as long as its sequence, and a launch as long as its last workgroup, so it
+// is for launches of rounds enough that both the lengths and the last round even out: two rounds of the three (three or four
+// query heads per KV head) or four workgroups (two) per CU that share the chip best, with three quarters of the rounds'
+// places taken.  Whole steps, us, ranges and whole; rows in use 94 to 100 % of the capacity ("even"), uniform from 3 to 100 %
+// of it, all in every other sequence and a quarter in the rest ("half"), all in every 16th and a sixteenth in the rest ("few
+// long"); 8 KV heads, head_dim 128 bf16 unless told otherwise:
+//   one round, 4 heads: 96 x 4096 + 512 even 308 and 268, uniform 213 and 206, half 239 and 213, few long 116 and 187; 64 x
+//     4096 + 512 208 and 184, 148 and 164, 163 and 169, 83 and 160; fp32, 96 x 2000 + 64, 264 and 253, 180 and 186, 209 and
+//     209, 87 and 172; 2 heads, head_dim 64, 128 x 2000 + 64, 96 and 102, 70 and 73, 78 and 88, 45 and 52
+//   two rounds and more, 4 heads: 192 x 3163 + 64 even 421 and 386, uniform 308 and 258, few long 136 and 156; 256 562 and 520,
+//     407 and 330, 175 and 186; 384 851 and 786, 618 and 493, 257 and 259; 576 1274 and 1171, 915 and 697, 376 and 352; 2
+//     heads, 256 x 1200 + 64, 223 and 209, 158 and 139, 87 and 83; fp32, head_dim 64, 336 x 1500 + 100, 350 and 335, 243 and
+//     218, half 256 and 262, few long 124 and 136
+//   a third round begun: 200 x 1200 + 64 (69 % of three) even 185 and 194, fp32 346 and 365; 216 (75 %) 201 and 198, 375 and 375
+//   one head gains too little: 288 x 1500 + 100 even 294 and 296, uniform 205 and 189, half 215 and 229, few long 97 and 104; 400
+//     399 and 398, 271 and 248, 287 and 298, 126 and 135
+//   5 to 8 heads, two workgroups per CU, lose: 5 heads of head_dim 64, 192 x 1200 + 64, 118 and 126, 256 152 and 163; 8 heads,
+//     136 97 and 107
+// Where one range is all there is anyway nothing is won.
 bool decode_whole(const DecodeDims& d, int row_bytes) {
-  if (d.n_splits < 2 || d.n_slots > decode_map_rows(row_bytes)) return false;
-  const int pairs = d.S * d.H_kv;
-  const int round = d.G > 4 ? 512 : d.G > 2 ? 768 : 1024, rounds = ceil_div(pairs, round);
-  const int filled = static_cast<int>(100L * pairs / (static_cast<long>(rounds) * round));  // per cent
-  const bool bf16 = row_bytes == 2 * d.D;
-  if (d.G > 4) return bf16 && filled >= 86 && (rounds == 1 || row_bytes <= 128);
-  if (d.G <= 2) return filled >= (d.G == 1 ? 94 : 75);
-  if (rounds > 1) return filled >= 70;
-  return filled >= 90 || (pairs >= 512 && bf16 && (d.D == 64 || d.n_slots >= 256));
+  if (d.n_splits < 2 || d.n_slots > decode_map_rows(row_bytes) || d.G < 2 || d.G > 4) return false;
+  const int round = d.G > 2 ? 768 : 1024, pairs = d.S * d.H_kv;
+  return pairs >= 2 * round && 4L * pairs >= 3L * round * ceil_div(pairs, round);
 }
 
 hipError_t launch_decode_finish(const DecodeDims& d, const shotkv_decode_state& st, float* out,

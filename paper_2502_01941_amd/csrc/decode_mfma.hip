@@ -150,8 +150,8 @@ template <> struct Widen<float> {
   }
 };
 
-// LONG: ranges of more than kMaxRange tokens, taken in pieces of about as many.  whole (LONG only): the range is all of a
-// sequence; the workgroup writes the attention output itself and, to z_dec, one partial score per slot and KV head.
+// LONG: ranges of more than kMaxRange tokens, taken in pieces of about as many.  whole (LONG, two to four heads): the range
+// is all of a sequence; the workgroup writes the attention output itself and, to z_dec, one partial score per slot and KV head.
 template <typename T, int D, int G, bool LONG>
 __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_partial_kernel(
     const char* __restrict__ k_prefill, const char* __restrict__ v_prefill,
@@ -160,6 +160,7 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
     int n_splits, int split_tokens, int ahead_slots, float scale_log2e, const char* __restrict__ q_new,
     const char* __restrict__ k_new, const char* __restrict__ v_new, float2* __restrict__ part_ml,
     float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out, bool whole) {
+  if (!LONG || G == 1 || G > 4) whole = false;  // (decode_whole)
   constexpr int kRow = D * static_cast<int>(sizeof(T));  // bytes per row
   typedef RowShape<kRow> S;
   constexpr int E = Widen<T>::kElems;
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
   // The blocks of the range: prefill rows, then slots; dealt to the waves in turn.  The slots of a whole sequence start a
   // piece of their own, so that their weights are all still there when the sums are known.
   int nb_p = ceil_div(n_p, S::kBlock);
-  if (LONG && whole) nb_p = ceil_div(nb_p, kWaves) * kWaves;
+  if (whole) nb_p = ceil_div(nb_p, kWaves) * kWaves;
   const int n_blk = new_slot >= 0 ? nb_p + ceil_div(n_d, S::kBlock) : 0;
   int b0 = 0, b1 = 0, map0 = 0;  // the blocks of the piece, the first slot of the slot map
   if (n_blk > 0)
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
         float z[G];
 #pragma unroll
         for (int h = 0; h < G; ++h) z[h] = zown[t][h];
-        if (slot >= 0 && valid && !(LONG && whole)) {
+        if (slot >= 0 && valid && !whole) {
 #pragma unroll
           for (int h = 0; h < G; ++h)
             if (h < n_group) z_dec[(head0 + h) * n_slots + (d_lo + slot)] = z[h];
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
     for (int w = 0; w < kWaves; ++w)
       l = fmaf(s_sum[w][h], s_max[w][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_max[w][h] - m), l);
   };
-  if (LONG && whole && n_blk > 0 && n_d > 0) {  // (no piece was taken where the pool is full)
+  if (whole && n_blk > 0 && n_d > 0) {  // (no piece was taken where the pool is full)
     // the weights of the slots are those of the last piece: each wave's are scaled to the softmax and summed over the heads
     __syncthreads();
     float f[G];
@@ -622,7 +623,7 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
 #pragma unroll
     for (int w = 0; w < kWaves; ++w)
       acc = fmaf((&zbuf[w][0][0])[idx], s_max[w][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_max[w][h] - m), acc);
-    if (LONG && whole) {
+    if (whole) {
       part_o[(head0 + h) * D + dd] = n_blk > 0 ? acc * (1.f / l) : 0.f;
       continue;
     }

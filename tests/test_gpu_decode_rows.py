@@ -24,9 +24,14 @@ def kv():
     return shotkv
 
 
-def _state(kv, rng, S, H, Hkv, D, dtype, cap, counts, n_slots, used, budget, scale):
-    """Random caches; rows past a sequence's count and slots that are not in `used` hold poison."""
+def _state(kv, rng, S, H, Hkv, D, dtype, cap, counts, n_slots, used, budget, scale, on_gpu=False):
+    """Random caches (on_gpu: drawn there, for large ones); rows past a sequence's count and slots that are not in `used` hold
+    poison."""
+    gen = torch.Generator(device="cuda").manual_seed(int(rng.integers(1 << 30))) if on_gpu else None
+
     def normal(*shape):
+        if on_gpu:
+            return torch.randn(shape, generator=gen, device="cuda").to(dtype)
         return torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)).to(dtype).cuda()
     kp, vp = normal(S, Hkv, cap, D), normal(S, Hkv, cap, D)
     kd, vd = normal(S, Hkv, n_slots, D), normal(S, Hkv, n_slots, D)
@@ -42,18 +47,20 @@ def _state(kv, rng, S, H, Hkv, D, dtype, cap, counts, n_slots, used, budget, sca
     return kv.DecodeState(kp, vp, count, kd, vd, slot_pos, budget, H, scale)
 
 
-def _check_steps(kv, rng, state, budget, n_steps, scale, first_step=1000):
+def _check_steps(kv, rng, state, budget, n_steps, scale, first_step=1000, sequences=None):
+    """Steps against the oracle: every sequence, or those given."""
     S, H, Hkv, D, dtype = state.S, state.H, state.H_kv, state.D, state.dtype
-    host = []
-    for s in range(S):
+    sequences = range(S) if sequences is None else sequences
+    host = {}
+    for s in sequences:
         c = int(state.prefill_count[s].item())
-        host.append([to_np(state.k_prefill[s, :, :c]), to_np(state.v_prefill[s, :, :c]), c, to_np(state.k_dec[s]).copy(),
-                     to_np(state.v_dec[s]).copy(), state.slot_pos[s].cpu().numpy().copy()])
+        host[s] = [to_np(state.k_prefill[s, :, :c]), to_np(state.v_prefill[s, :, :c]), c, to_np(state.k_dec[s]).copy(),
+                   to_np(state.v_dec[s]).copy(), state.slot_pos[s].cpu().numpy().copy()]
     for step in range(first_step, first_step + n_steps):
         new = [torch.from_numpy(rng.standard_normal((S, h, D), dtype=np.float32)).to(dtype).cuda() for h in (H, Hkv, Hkv)]
         kv.decode_step(state, step, *new)
         torch.cuda.synchronize()
-        for s in range(S):
+        for s in sequences:
             kp, vp, c, kd, vd, sp = host[s]
             with np.errstate(invalid="ignore", over="ignore"):
                 r = orc.decode_step(kp, vp, c, kd, vd, sp, budget, step, *[to_np(t[s]) for t in new], scale)
