@@ -313,16 +313,18 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(
 int decode_resident(int G, int row_bytes) { return G > 4 && row_bytes <= 256 ? 768 : 1024; }
 
 int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
-  // Token ranges per (sequence, KV head).  The workgroups of a launch should all be resident at once, so a count is
-  // rounded down: 1056 workgroups of which 1024 fit take nearly twice as long as 960.  With more than two query
-  // heads per KV head three workgroups per CU are better than four:
-  // 16 sequences of 4500 rows and 8 heads 73 us at 768 workgroups, 85 at 1024; 12 sequences of 5120 rows and 4
-  // heads 55 and 58 (62 at 1056); 16 of 5120 rows 69.8 and 70.8.  One or two heads: 54.1 and 52.8 us at 16
-  // sequences.  768 is passed over where it cannot be met within a sixth (64 sequences of 364 rows: 34.5 us with
-  // 512 workgroups, 33.8 with 1024) - but not where three per CU is all that fits (more than four heads and rows of up to
-  // 256 bytes, by registers and LDS; 512-byte rows fit four): 33 sequences of 1800 rows, 8 heads per KV head, 73.4 us
-  // with 528 workgroups, 80.7 with 792; 50 of 900 rows 63.8 with 400, 75.0 with 800; 7 heads 51.3 and 57.9; 512-byte
-  // rows 120 and 112.5.
+  // Token ranges per (sequence, KV head).  The workgroups of a launch should all be resident at once, so a count is rounded
+  // down.  Whole steps, us, 8 KV heads, rows + slots of a sequence, head_dim 128 bf16 unless told otherwise.
+  // With more than two query heads per KV head three workgroups per CU are better than four: 4 heads, 16 sequences of 4096 +
+  // 1025 rows 64.0 with 768 workgroups and 65.7 with 1024, 24 of 3000 + 301 57.3 and 59.4 (960), of head_dim 64 34.7 and 37.0;
+  // 12 of 4096 + 1025 51.8 and 51.0 (960).  One or two heads go either way: 2 heads, 24 of 3000 + 301 53.7 and 56.2, 33 of
+  // 1800 + 101 49.2 (528) and 48.5 (792), one of head_dim 64, 16 of 4096 + 1025 33.6 and 32.4, 50 of 900 + 65 26.1 (400) and
+  // 21.8 (800).  768 is passed over where it cannot be met within a sixth (4 heads, 33 of 1800 + 101 54.1 with 528 and 53.5 with
+  // 792, of head_dim 64 32.8 and 31.4; 64 of 300 + 65 29.8 and 29.4; 20 of 2000 + 301 38.9 with 640 and 39.7 with 960) - but not
+  // with more than four heads of up to 256 bytes: bf16 rows leave room for three per CU (137 registers), 8 heads, 33 of 1800 +
+  // 101, 67.0 with 528 and 73.6 with 792, 50 of 900 + 65 62.1 with 400 and 66.2 with 800, 5 heads 57.7 and 60.2.  fp32 rows
+  // leave room for four, and gain by it with 512 bytes (50 of 900 + 65: 102.7 and 94.6); with 256 bytes they would too (78.2
+  // and 72.6, 70.4 and 62.5), but steps that the static scratch memory holds would then outgrow it.
   const int pairs = S * H_kv;
   const int many = max(1, decode_resident(G, row_bytes) / pairs), few = max(1, 768 / pairs);
   int splits = G > 2 && few * pairs >= 640 ? few : many;

@@ -636,18 +636,17 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
 }  // namespace
 
 // Slots whose K rows the ranges of nothing but slots request ahead of the slot map, a trip to memory earlier: where a
-// launch is one round of workgroups they would end it (16 sequences of 4096 rows and 1025 slots 64.4 us a step waiting for
-// the map and 63.5 ahead of it, 8 sequences 40.6 and 39.3, 16 of 2561 and 2560 74.0 and 71.6; 5 of 3414 and 1707, half
-// full, 30.5 and 29.1).  Rows of free slots are fetched for nothing that way, so no more than can be in use are requested:
-// a new token takes the lowest free slot, so a pool that is used from step 0 on is empty behind slot `step`, and behind
-// slot `budget` (with all slots requested an empty pool of 4096 beside 256 rows took 26.8 us, 25.5 without; so it is 25.3).
-// Ranges that a workgroup's waves take in little more than one block each have all their rows in flight at once and gain
-// only while slots are few: 3 sequences in ranges of 160 rows 23.7 and 23.3 us with a tenth of slots, 28.5 and 28.4 with a
-// third, 35.2 and 35.7 with two thirds; 8 of head_dim 64 in ranges of 196 rows 25.0 and 25.6 with two thirds.
+// launch is one round of workgroups they would end it.  Whole steps, waiting for the map and ahead of it: 16 sequences of
+// 4096 rows and 1025 slots 65.0 and 63.9 us, 8 38.5 and 38.0, 5 of 3414 and 1707 33.3 and 32.5, half full 30.8 and 29.8; in
+// ranges of about a block per wave 4 of 700 and 501 17.7 and 17.1, 8 of 1000 and 2001, half full, 27.0 and 26.1, a tenth
+// full 26.4 and 25.7.  Rows of free slots are fetched for nothing that way, so no more than can be in use are requested: a new token
+// takes the lowest free slot, so a pool that is used from step 0 on is empty behind slot `step`, and behind slot `budget`
+// (with all slots requested, a tenth full: 16 of 2561 and 2560, head_dim 64, 31.4 and 30.6 like this, 5 of 3414 and 1707, fp32 of
+// head_dim 64, 25.5 and 24.1).  In more than one round other workgroups cover the trip (64 of 2000 and 1001, head_dim 64, half
+// full, 77.3 ahead of the map and 76.3 behind it).
 static int ahead_of_map(const DecodeDims& d, int row_bytes) {
   const long workgroups = static_cast<long>(d.n_splits) * d.H_kv * d.S;
   if (workgroups > decode_resident(d.G, row_bytes)) return 0;
-  if (d.split_tokens < 256 && d.cap / 2 < d.n_slots) return 0;
   return min(d.n_slots - 1, min(d.step, d.budget)) + 1;
 }
 

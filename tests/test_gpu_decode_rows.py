@@ -128,8 +128,8 @@ def test_ranges_of_nothing_but_slots(kv, S):
 
 
 @pytest.mark.parametrize("S,Hkv,G,cap,n_slots,budget,first_step", [
-    (3, 2, 4, 410, 205, 204, 1000),     # short ranges, slots a third: rows requested ahead of the map
-    (3, 2, 4, 409, 205, 204, 1000),     # slots more than a third: after it
+    (3, 2, 4, 410, 205, 204, 1000),     # short ranges: rows requested ahead of the map
+    (3, 2, 4, 409, 205, 204, 1000),
     (3, 2, 8, 410, 205, 204, 1000),
     (3, 2, 4, 410, 205, 40, 1000),      # a budget below, and a step before, what the pool holds: the blocks behind it are
     (3, 2, 4, 410, 205, 204, 60),       # requested after the map
