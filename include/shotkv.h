@@ -91,7 +91,9 @@ typedef struct {
    * state between calls.  Kinds, in order: chunk plan, score, row statistics, chunk mass, shot scores
    * and selection, compaction, decode partial, decode finish, V packing, fused attention.  Chunk plan and row
    * statistics have no kernels of their own (scoring and fused attention find their chunks themselves, chunk mass
-   * the row statistics): their events are recorded with nothing in between, so the kinds add up to the call. */
+   * the row statistics): their events are recorded with nothing in between, so the kinds add up to the call.  So are
+   * compaction's where few rows are copied (up to 48 MB read and written in a call): the kernel that selects makes the
+   * copies as well, and its kind has the time of both. */
   void* const* timing_events;
 } shotkv_config;
 
