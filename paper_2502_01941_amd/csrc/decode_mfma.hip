@@ -490,27 +490,31 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
         ref[h] = m_new == -INFINITY ? 0.f : m_new;
       }
       const int own_rows = b0 + wave < b1 ? ((b1 - 1 - b0 - wave) / kWaves + 1) * S::kBlock : 0;
+      auto take_weights = [&](auto scores_c) __attribute__((always_inline)) {
 #pragma clang loop unroll(disable)
-      for (int t = lane; t < own_rows; t += kWave) {
-        const int b = b0 + wave + t / S::kBlock * kWaves, row = b * S::kBlock + t % S::kBlock;
-        const int slot = row - nb_p * S::kBlock;
-        const bool valid = slot < 0 ? row < n_p : slot_used(slot);
-        float z[G];
+        for (int t = lane; t < own_rows; t += kWave) {
+          const int b = b0 + wave + t / S::kBlock * kWaves, row = b * S::kBlock + t % S::kBlock;
+          const int slot = row - nb_p * S::kBlock;
+          const bool valid = slot < 0 ? row < n_p : slot_used(slot);
+          float z[G];
 #pragma unroll
-        for (int h = 0; h < G; ++h) z[h] = zown[t][h];
-        if (slot >= 0 && valid && !whole) {
+          for (int h = 0; h < G; ++h) z[h] = zown[t][h];
+          if (slot >= 0 && valid && !whole) {
 #pragma unroll
-          for (int h = 0; h < G; ++h)
-            if (h < n_group) z_dec[(head0 + h) * n_slots + (d_lo + slot)] = z[h];
+            for (int h = 0; h < G; ++h)
+              if (h < n_group) z_dec[(head0 + h) * n_slots + (d_lo + slot)] = z[h];
+          }
+#pragma unroll
+          for (int h = 0; h < G; ++h) {
+            const float w = scores_c ? exp2_of_whole_reference(z[h], ref[h]) : __builtin_amdgcn_exp2f(z[h] - ref[h]);
+            const float p = valid ? w : 0.f;
+            zown[t][h] = p;
+            L[h] += p;
+          }
         }
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-          // (LONG: the weights may become scores, where tokens of equal keys tie)
-          const float p = !valid ? 0.f : LONG ? exp2_of_whole_reference(z[h], ref[h]) : __builtin_amdgcn_exp2f(z[h] - ref[h]);
-          zown[t][h] = p;
-          L[h] += p;
-        }
-      }
+      };
+      if (whole && b0 >= nb_p) take_weights(std::true_type{});  // these weights become scores, where tokens of equal keys tie
+      else take_weights(std::false_type{});
       wave_lds_fence();
 
       // ---- pass 2: weighted values -----------------------------------------------------------------------
