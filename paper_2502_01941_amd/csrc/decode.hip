@@ -342,12 +342,11 @@ int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
 // hundredth of the bytes read, cost the row stream an eighth of its time (512 sequences of 5121 rows, 8 KV heads: step
 // 1840 us, 1760 without storing logits, 1600 without partial sums either, 1640 like this, where the finish kernel shrinks
 // from 51 to 12 as well).  But a workgroup takes as long as its sequence, and a launch as long as its last workgroup, so it
-// from 51 to 12 as well).  But a workgroup takes as long as its sequence, and a launch as long as its last workgroup, so it
 // is for launches of rounds enough that both the lengths and the last round even out: two rounds of the three (three or four
-// query heads per KV head) or four workgroups (two) per CU that share the chip best, with three quarters of the rounds'
-// places taken.  Whole steps, us, ranges and whole; rows in use 94 to 100 % of the capacity ("even"), uniform from 3 to 100 %
-// of it, all in every other sequence and a quarter in the rest ("half"), all in every 16th and a sixteenth in the rest ("few
-// long"); 8 KV heads, head_dim 128 bf16 unless told otherwise:
+// query heads per KV head), four (two) or two workgroups (seven or eight, and rows of 128 bytes) per CU that share the chip
+// best, with three quarters of the rounds' places taken.  Whole steps, us, ranges and whole; rows in use 94 to 100 % of the
+// capacity ("even"), uniform from 3 to 100 % of it, all in every other sequence and a quarter in the rest ("half"), all in
+// every 16th and a sixteenth in the rest ("few long"); 8 KV heads, head_dim 128 bf16 unless told otherwise:
 //   one round, 4 heads: 96 x 4096 + 512 even 308 and 268, uniform 213 and 206, half 239 and 213, few long 116 and 187; 64 x
 //     4096 + 512 208 and 184, 148 and 164, 163 and 169, 83 and 160; fp32, 96 x 2000 + 64, 264 and 253, 180 and 186, 209 and
 //     209, 87 and 172; 2 heads, head_dim 64, 128 x 2000 + 64, 96 and 102, 70 and 73, 78 and 88, 45 and 52
@@ -358,12 +357,15 @@ int decode_splits(int S, int H_kv, int G, int row_bytes, int total_tokens) {
 //   a third round begun: 200 x 1200 + 64 (69 % of three) even 185 and 194, fp32 346 and 365; 216 (75 %) 201 and 198, 375 and 375
 //   one head gains too little: 288 x 1500 + 100 even 294 and 296, uniform 205 and 189, half 215 and 229, few long 97 and 104; 400
 //     399 and 398, 271 and 248, 287 and 298, 126 and 135
-//   5 to 8 heads, two workgroups per CU, lose: 5 heads of head_dim 64, 192 x 1200 + 64, 118 and 126, 256 152 and 163; 8 heads,
-//     136 97 and 107
+//   5 to 8 heads, two workgroups per CU, head_dim 64: 8 heads, 4 KV heads, 256 x 1784 + 407 even 136 and 123, uniform 113 and
+//     115, few long 93 and 108, 512 of them 256 and 241, 210 and 202, 167 and 185; 7 heads, 256 156 and 122, 133 and 114, 113
+//     and 108; 5 heads, 256 129 and 122, 108 and 114, 88 and 107, of 8 KV heads, 192 x 1200 + 64, 118 and 126; head_dim 128, 8
+//     heads, 2048 pairs of 1200 + 64, 278 and 283
 // Where one range is all there is anyway nothing is won.
 bool decode_whole(const DecodeDims& d, int row_bytes) {
-  if (d.n_splits < 2 || d.n_slots > decode_map_rows(row_bytes) || d.G < 2 || d.G > 4) return false;
-  const int round = d.G > 2 ? 768 : 1024, pairs = d.S * d.H_kv;
+  if (d.n_splits < 2 || d.n_slots > decode_map_rows(row_bytes)) return false;
+  if (d.G == 1 || (d.G > 4 && (d.G < 7 || row_bytes > 128))) return false;
+  const int round = d.G > 4 ? 512 : d.G > 2 ? 768 : 1024, pairs = d.S * d.H_kv;
   return pairs >= 2 * round && 4L * pairs >= 3L * round * ceil_div(pairs, round);
 }
 

@@ -150,8 +150,8 @@ template <> struct Widen<float> {
   }
 };
 
-// LONG: ranges of more than kMaxRange tokens, taken in pieces of about as many.  whole (LONG, two to four heads): the range
-// is all of a sequence; the workgroup writes the attention output itself and, to z_dec, one partial score per slot and KV head.
+// LONG: ranges of more than kMaxRange tokens, taken in pieces of about as many.  whole (LONG only): the range is all of a
+// sequence; the workgroup writes the attention output itself and, to z_dec, one partial score per slot and KV head.
 template <typename T, int D, int G, bool LONG>
 __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_partial_kernel(
     const char* __restrict__ k_prefill, const char* __restrict__ v_prefill,
@@ -160,8 +160,8 @@ __global__ __launch_bounds__(kThreads, (G == 8 ? 3 : 4) - LONG) void decode_part
     int n_splits, int split_tokens, int ahead_slots, float scale_log2e, const char* __restrict__ q_new,
     const char* __restrict__ k_new, const char* __restrict__ v_new, float2* __restrict__ part_ml,
     float* __restrict__ part_o, float* __restrict__ z_dec, int32_t* __restrict__ new_slot_out, bool whole) {
-  if (!LONG || G == 1 || G > 4) whole = false;  // (decode_whole)
   constexpr int kRow = D * static_cast<int>(sizeof(T));  // bytes per row
+  if (!LONG || G == 1 || (G == 8 && kRow > 128)) whole = false;  // (decode_whole)
   typedef RowShape<kRow> S;
   constexpr int E = Widen<T>::kElems;
   const int split = blockIdx.x, g = blockIdx.y, s = blockIdx.z;
