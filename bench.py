@@ -31,7 +31,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # `rocprofv3 --pmc` runs of this file, see profiles/score_partials_mfma_model32k_counters.md).  Valid only
 # for the kernel source it was measured on: reported as null once that file's hash differs.
 SCORE_KERNEL_SOURCE = os.path.join(ROOT, "paper_2502_01941_amd", "csrc", "prefill_score_mfma.hip")
-MEASURED_TRAFFIC = {"model32k": {"sha256": "1ee40a4943537b1dc561a440dcbcf016ca44bc53293114d7e8ffdbd744ba0aec",
+MEASURED_TRAFFIC = {"model32k": {"sha256": "9659e23c228aca2a3989d43466a4825fdf3e2d49e2b23165d2e0c65549ddc11e",
                                  "bytes": 8.96e9}}
 
 PREFILL_KINDS = ("score", "chunk_mass", "reduce_select", "compact")

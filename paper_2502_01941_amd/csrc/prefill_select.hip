@@ -627,7 +627,8 @@ hipError_t launch_select_compact(const PrefillDims& d, bool with_mass, float* sh
   // unless told otherwise, by bytes read and written: 7 MB (2000 tokens) 23 and 20.5 us, 10 MB 22 and 20.6, 27 MB (8192
   // tokens, budget 3276) 25.6 and 23.7, with 128 workgroups 26.2, with 512 29; 54 MB 32.7 and 31.4; 33 MB as 64 problems
   // 28.6 and 27.5; 2500 units 77 and 75; 64 MB 130 and 130.5 (600 units), 79 MB of fp32 54.6 and 54.5, 210 MB of head_dim 64
-  // 112 and 116, 322 MB 150 and 157.
+  // 112 and 116, 322 MB 150 and 157.  That every workgroup sorts for first fit costs nothing either: one problem of 4000 units
+  // 121.4 and 119.1, 2500 112.9 and 110.8, 8 of 1000 102.6 and 92.9, 64 of 600 102.2 and 100.5, 256 of 1000 198.6 and 198.8.
   constexpr int kMostWorkgroups = 256;
   const int most_rows = min(cap, d.n_tokens), wgs = max(1, min(kMostWorkgroups / d.P, ceil_div(cap, 8)));
   const long bytes = 4L * d.P * d.H_kv * most_rows * row_bytes;  // read and written
